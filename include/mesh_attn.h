@@ -157,7 +157,9 @@ ma_status_t mesh_attn_worklist_kv_major(const ma_problem_t* prob,
  * with the online-softmax reducer inside the kernel).
  * ------------------------------------------------------------------------- */
 
-/* Device workspace bytes mesh_attn_tile_fwd needs for this tile. */
+/* Device workspace bytes mesh_attn_tile_fwd uses for this tile: the work list
+ * and, for tiles of few work items, room for partial results of items that are
+ * split over several workgroups (at most 68 MB). */
 size_t mesh_attn_fwd_workspace_size(const ma_problem_t* prob, int32_t nq,
                                     int32_t nkv);
 
@@ -168,6 +170,9 @@ size_t mesh_attn_fwd_workspace_size(const ma_problem_t* prob, int32_t nq,
  *   lse     [Hq][nq*P] float32 device; -inf for a row that sees no key, whose
  *           O row is then 0.
  *   ws      device workspace of ws_bytes >= mesh_attn_fwd_workspace_size().
+ *           One sized for another tile that holds this one's work list but
+ *           not its partial results is accepted: no item is split then, which
+ *           is slower and rounds differently.
  * O = sum_j exp(x_j - LSE) v_j with x_j = s <q, k_j> over the visible keys;
  * LSE = ln sum_j exp(x_j).  bf16 MFMA products, float32 accumulation and
  * softmax. */
@@ -189,15 +194,16 @@ ma_status_t mesh_attn_tile_fwd(const ma_problem_t* prob, const int32_t* q_idx,
  * workspace: the work list is built on the device (from the index lists,
  * passed by value as kernel arguments) into a scratch array of
  * MA_NOALLOC_SCRATCH_BYTES that the library holds on every GPU it runs on
- * until the process ends.  The call allocates nothing (no hipMalloc, no
+ * until the process ends, beside one of 68 MB for the partial results of split
+ * items.  The call allocates nothing (no hipMalloc, no
  * pinned host memory, no host heap), copies nothing from the host and never
  * synchronizes.
  * Limits: nq, nkv <= MA_NOALLOC_MAX_LIST; nq * P / 256 <= MA_NOALLOC_MAX_QBLOCKS;
  * the tile's work list (mesh_attn_fwd_workspace_size bytes) must fit the
  * scratch array.  Larger tiles return MA_ERR_UNSUPPORTED with the sizes in
  * mesh_attn_last_error(), before anything is launched.
- * Every call on one GPU shares that GPU's scratch array (each call rewrites
- * it before reading it): calls on one stream are ordered, but calls that
+ * Every call on one GPU shares that GPU's scratch arrays (each call rewrites
+ * them before reading them): calls on one stream are ordered, but calls that
  * overlap on one GPU (different streams without ordering between them) race
  * and give undefined results. */
 ma_status_t mesh_attn_tile_fwd_noalloc(const ma_problem_t* prob,
@@ -225,7 +231,7 @@ typedef struct {
                             rows (see mesh_attn_block_shape, pass 0)         */
 } ma_chunk_t;
 
-/* Device workspace bytes mesh_attn_chunk_fwd needs (any chunk of the tile). */
+/* Device workspace bytes mesh_attn_chunk_fwd uses (any chunk of the tile). */
 size_t mesh_attn_chunk_fwd_workspace_size(const ma_problem_t* prob,
                                           int32_t nq, int32_t nkv);
 

@@ -18,10 +18,12 @@
 #include <memory>
 #include <mutex>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "host_error.h"
 #include "internal.h"
+#include "split.h"
 
 using namespace mesh_attn;
 
@@ -249,8 +251,10 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct Side {
   size_t off_ptr = 0, off_runs = 0, off_order = 0, off_queue = 0;
+  size_t off_pieces = 0, off_splits = 0;
   int32_t grid = 0;
-  int32_t n_items = 0;  // non-idle slots of the order
+  int32_t n_items = 0;   // non-idle slots of the order
+  int32_t n_splits = 0;  // split items; > 0: every slot has a piece
 };
 
 // An event recorded after a copy, with the device it belongs to (an event
@@ -352,7 +356,7 @@ std::string plan_key(int pass, const ma_problem_t* p, const int32_t* q_idx,
 void device_runs(const ma_problem_t* p, const int32_t* a_idx, int32_t na,
                  int32_t bm_a, Slice sa, const int32_t* b_idx, int32_t nb,
                  int32_t bm_b, Slice sb, bool a_is_q, std::vector<int32_t>* ptr,
-                 std::vector<DevRun>* out, std::vector<int64_t>* work) {
+                 std::vector<DevRun>* out, std::vector<int32_t>* work) {
   std::vector<Run> runs;
   build_runs(p, a_idx, na, bm_a, sa, b_idx, nb, bm_b, sb, a_is_q, ptr, &runs);
   const int32_t nab = static_cast<int32_t>(sa.len / bm_a);
@@ -377,7 +381,7 @@ void device_runs(const ma_problem_t* p, const int32_t* a_idx, int32_t na,
 // the items of one KV head land on one XCD when the KV head count allows it
 // (their workgroups then stream the same K/V through that XCD's L2).  Slot i
 // of the grid runs on XCD i % kNumXcd.
-std::vector<int2> workgroup_order(const std::vector<int64_t>& work,
+std::vector<int2> workgroup_order(const std::vector<int32_t>& work,
                                   int32_t heads, int32_t group_to_kv,
                                   int32_t num_kv_heads) {
   struct Item {
@@ -419,11 +423,79 @@ struct SideData {
   std::vector<int32_t> ptr;
   std::vector<DevRun> runs;
   std::vector<int2> order;
+  std::vector<DevPiece> pieces;  // per order slot; empty unless split
+  std::vector<DevSplit> splits;
 };
+
+// Workgroup order of one side from its runs and the blocks per item, with the
+// long items split over `slots` concurrent workgroups where that pays
+// (split.h; slots 0: never).
+void order_items(const std::vector<int32_t>& work, int32_t heads,
+                 int32_t group_to_kv, int32_t num_kv_heads, int32_t slots,
+                 SideData* s) {
+  const int32_t rows = static_cast<int32_t>(work.size());
+  const split::Cut cut = slots > 0
+                             ? split::choose(work.data(), rows, heads, slots)
+                             : split::Cut{0, 0};
+  if (cut.c == 0) {
+    s->order = workgroup_order(work, heads, group_to_kv, num_kv_heads);
+    return;
+  }
+  // The pieces of one head; all heads are cut alike.
+  struct Piece {
+    int32_t row, idx, len, run, off, part;
+  };
+  std::vector<Piece> pieces;
+  std::vector<std::pair<int32_t, int32_t>> split_rows;  // row, first part
+  int32_t parts = 0;
+  for (int32_t r = 0; r < rows; ++r) {
+    const int32_t n = split::num_pieces(cut, r, work[r]);
+    if (n > 1) split_rows.push_back({r, parts});
+    int32_t run = s->ptr[r], off = 0;
+    for (int32_t j = 0; j < n; ++j) {
+      const int32_t len = split::piece_begin(work[r], n, j + 1) -
+                          split::piece_begin(work[r], n, j);
+      while (len > 0 && off >= s->runs[run].nblk) off -= s->runs[run++].nblk;
+      pieces.push_back({r, j, len, run, off, n > 1 ? parts++ : -1});
+      off += len;
+    }
+  }
+  const int32_t m = static_cast<int32_t>(pieces.size());
+  const int32_t total = m * heads;
+  // Ranks: longest first over several rounds, by piece index in one.
+  auto key = [&](const Piece& pc) { return total > slots ? -pc.len : pc.idx; };
+  std::vector<int32_t> rank(m);
+  for (int32_t i = 0; i < m; ++i) rank[i] = i;
+  std::stable_sort(rank.begin(), rank.end(), [&](int32_t i, int32_t j) {
+    return key(pieces[i]) < key(pieces[j]);
+  });
+  s->order.assign(total, make_int2(-1, -1));
+  s->pieces.assign(total, DevPiece{0, 0, 0, -1});
+  for (int32_t a = 0, b; a < m; a = b) {
+    for (b = a + 1; b < m && key(pieces[rank[b]]) == key(pieces[rank[a]]);) ++b;
+    for (int32_t i = a; i < b; ++i) {
+      const Piece& pc = pieces[rank[i]];
+      for (int32_t h = 0; h < heads; ++h) {
+        const int32_t slot =
+            split_slot(total, m, heads, group_to_kv,
+                       num_kv_heads % kNumXcd == 0, h, a, b - a, i - a, slots);
+        s->order[slot] = make_int2(pc.row, h);
+        s->pieces[slot] = DevPiece{pc.run, pc.off, pc.len,
+                                   pc.part < 0 ? -1 : h * parts + pc.part};
+      }
+    }
+  }
+  for (int32_t h = 0; h < heads; ++h)
+    for (const auto& [row, part] : split_rows)
+      s->splits.push_back({row, h, h * parts + part,
+                           split::num_pieces(cut, row, work[row])});
+}
 
 size_t side_bytes(const SideData& s) {
   return align_up(s.ptr.size() * 4) + align_up(s.runs.size() * sizeof(DevRun)) +
-         align_up(s.order.size() * sizeof(int2)) + align_up(kNumXcd * 4);
+         align_up(s.order.size() * sizeof(int2)) + align_up(kNumXcd * 4) +
+         align_up(s.pieces.size() * sizeof(DevPiece)) +
+         align_up(s.splits.size() * sizeof(DevSplit));
 }
 
 void side_pack(const SideData& s, char* base, size_t off, Side* out) {
@@ -442,6 +514,15 @@ void side_pack(const SideData& s, char* base, size_t off, Side* out) {
   // queued_static_slots), uploaded as zeros with every call.
   out->off_queue = off;
   std::memset(base + off, 0, kNumXcd * 4);
+  out->n_splits = static_cast<int32_t>(s.splits.size());
+  off += align_up(kNumXcd * 4);
+  out->off_pieces = off;
+  if (!s.pieces.empty())
+    std::memcpy(base + off, s.pieces.data(), s.pieces.size() * sizeof(DevPiece));
+  off += align_up(s.pieces.size() * sizeof(DevPiece));
+  out->off_splits = off;
+  if (!s.splits.empty())
+    std::memcpy(base + off, s.splits.data(), s.splits.size() * sizeof(DevSplit));
   out->grid = static_cast<int32_t>(s.order.size());
   out->n_items = 0;
   for (const int2& it : s.order) out->n_items += it.x >= 0;
@@ -457,6 +538,18 @@ size_t side_bound(int64_t n_blocks, int64_t n_list, int64_t heads) {
          align_up(kNumXcd * 4);
 }
 
+// What splitting adds to one side: slots for the extra pieces, the piece of
+// every slot, the split items, and `parts` partial results of part_bytes.
+size_t split_bound(int64_t items, int32_t slots, int64_t parts,
+                   size_t part_bytes) {
+  if (parts == 0) return 0;
+  const int64_t most =
+      std::min<int64_t>(items, int64_t{split::kMaxRounds} * slots);
+  return align_up(parts * sizeof(int2)) +
+         align_up((most + parts) * sizeof(DevPiece)) +
+         align_up(parts / 2 * sizeof(DevSplit)) + align_up(parts * part_bytes);
+}
+
 constexpr ma_chunk_t kWholeTile{0, 1, 0, 1};
 
 // Builds (or finds) the plan of a tile, copies it to `ws` on `stream` and
@@ -464,9 +557,10 @@ constexpr ma_chunk_t kWholeTile{0, 1, 0, 1};
 // other thread can recycle the source buffer in between.
 ma_status_t upload_plan(int pass, const ma_problem_t* p, const int32_t* q_idx,
                         int32_t nq, const int32_t* kv_idx, int32_t nkv,
-                        const ma_chunk_t& ch, void* ws, hipStream_t stream,
-                        PlanView* view) {
-  const std::string key = plan_key(pass, p, q_idx, nq, kv_idx, nkv, ch);
+                        const ma_chunk_t& ch, bool may_split, void* ws,
+                        hipStream_t stream, PlanView* view) {
+  const std::string key =
+      plan_key(pass * 2 + may_split, p, q_idx, nq, kv_idx, nkv, ch);
   const int64_t P = p->partition_len;
   const Slice sq{P / ch.num_q_chunks, ch.q_chunk * (P / ch.num_q_chunks)};
   const Slice skv{P / ch.num_kv_chunks, ch.kv_chunk * (P / ch.num_kv_chunks)};
@@ -475,18 +569,19 @@ ma_status_t upload_plan(int pass, const ma_problem_t* p, const int32_t* q_idx,
   if (it == g_plans.end()) {
     const int32_t g = p->num_q_heads / p->num_kv_heads;
     SideData sa, sb;
-    std::vector<int64_t> work;
+    std::vector<int32_t> work;
     if (pass == 0) {
       device_runs(p, q_idx, nq, kFwdBM, sq, kv_idx, nkv, kFwdBN, skv, true,
                   &sa.ptr, &sa.runs, &work);
-      sa.order = workgroup_order(work, p->num_q_heads, g, p->num_kv_heads);
+      order_items(work, p->num_q_heads, g, p->num_kv_heads,
+                  may_split ? kFwdSlots : 0, &sa);
     } else {
       device_runs(p, q_idx, nq, kBwdBM, sq, kv_idx, nkv, kBwdBN, skv, true,
                   &sa.ptr, &sa.runs, &work);
-      sa.order = workgroup_order(work, p->num_q_heads, g, p->num_kv_heads);
+      order_items(work, p->num_q_heads, g, p->num_kv_heads, 0, &sa);
       device_runs(p, kv_idx, nkv, kBwdBN, skv, q_idx, nq, kBwdBM, sq, false,
                   &sb.ptr, &sb.runs, &work);
-      sb.order = workgroup_order(work, p->num_kv_heads, 1, p->num_kv_heads);
+      order_items(work, p->num_kv_heads, 1, p->num_kv_heads, 0, &sb);
     }
     if (g_plans.size() >= kMaxPlans) {
       auto lru = g_plans.begin();
@@ -539,6 +634,24 @@ size_t fwd_ws_bound(const ma_problem_t* p, int32_t nq, int32_t nkv) {
   return side_bound(nqb, nkv, p->num_q_heads);
 }
 
+size_t fwd_part_bytes(const ma_problem_t* p) {
+  return static_cast<size_t>(kFwdBM) * (p->head_dim + 1) * 4;
+}
+
+// What splitting the forward's items adds to fwd_ws_bound.  any_chunk: enough
+// for every chunk pair of the tile, which has fewer items of fewer blocks.
+size_t fwd_split_bytes(const ma_problem_t* p, int32_t nq, int32_t nkv,
+                       const ma_chunk_t& ch, bool any_chunk) {
+  const int64_t P = p->partition_len;
+  const int64_t items = nq * (P / ch.num_q_chunks / kFwdBM) * p->num_q_heads;
+  const int64_t blocks = nkv * (P / ch.num_kv_chunks / kFwdBN);
+  const int64_t counted =
+      any_chunk ? std::min<int64_t>(items, split::kMaxRounds * kFwdSlots)
+                : items;
+  const int64_t parts = split::parts_bound(counted, blocks, kFwdSlots);
+  return split_bound(items, kFwdSlots, parts, fwd_part_bytes(p));
+}
+
 size_t bwd_ws_bound(const ma_problem_t* p, int32_t nq, int32_t nkv) {
   const int64_t nqb = int64_t{nq} * p->partition_len / kBwdBM;
   const int64_t nkb = int64_t{nkv} * p->partition_len / kBwdBN;
@@ -577,6 +690,74 @@ ma_status_t check_chunk(const ma_problem_t* p, const ma_chunk_t& c, int32_t bm,
   return MA_OK;
 }
 
+// Partial slots of a split forward.
+int64_t parts_of(const ma_problem_t* p, int32_t nq, int32_t nkv,
+                 const ma_chunk_t& ch) {
+  const int64_t P = p->partition_len;
+  return split::parts_bound(
+      nq * (P / ch.num_q_chunks / kFwdBM) * p->num_q_heads,
+      nkv * (P / ch.num_kv_chunks / kFwdBN), kFwdSlots);
+}
+
+// The tile kernel over n_items slots and, if items were split, the fold of
+// their partial results.
+ma_status_t launch_fwd(const FwdParams& fp, int32_t head_dim, bool o_f32,
+                       int64_t n_items, const DevSplit* splits,
+                       int32_t n_splits, hipStream_t stream) {
+  hipError_t e =
+      launch_tile_fwd(fp, head_dim, o_f32,
+                      static_cast<int>(queued_launch_grid(n_items)), stream);
+  if (e != hipSuccess) return hip_fail(e, "tile_fwd launch");
+  if (n_splits > 0) {
+    const CombineParams cp{splits, fp.part_o, fp.part_lse, fp.o,
+                           fp.lse, fp.rows_q, fp.hq,       fp.accumulate};
+    e = launch_fwd_combine(cp, head_dim, o_f32, n_splits, stream);
+    if (e != hipSuccess) return hip_fail(e, "fwd_combine launch");
+  }
+  return ok();
+}
+
+// KV blocks that Q block `qb` of a whole tile sees (its work), without a run
+// list: along a partition the visible blocks are a prefix.
+int32_t visible_blocks(const ma_problem_t* p, const int32_t* q_idx,
+                       const int32_t* kv_idx, int32_t nkv, int64_t qb) {
+  const int64_t P = p->partition_len, qpb = P / kFwdBM, nbb = P / kFwdBN;
+  if (!p->causal) return static_cast<int32_t>(nkv * nbb);
+  const int64_t q_last =
+      token_pos(p, q_idx[qb / qpb], (qb % qpb) * kFwdBM + kFwdBM - 1);
+  const int64_t step = token_pos(p, 0, kFwdBN);  // positions per KV block
+  int64_t n = 0;
+  for (int32_t b = 0; b < nkv; ++b) {
+    const int64_t d = q_last - token_pos(p, kv_idx[b], 0);
+    if (d >= 0) n += std::min(nbb, d / step + 1);
+  }
+  return static_cast<int32_t>(n);
+}
+
+// The cut of a tile for the device-side list builder, the pieces and split
+// rows of one head.  Uses no heap.
+struct NoAllocSplit {
+  split::Cut cut;
+  int32_t row_pieces, split_rows;
+};
+
+NoAllocSplit noalloc_split(const ma_problem_t* p, const int32_t* q_idx,
+                           int32_t nq, const int32_t* kv_idx, int32_t nkv) {
+  int32_t work[kSplitMaxRows];
+  const int32_t nqb =
+      static_cast<int32_t>(int64_t{nq} * p->partition_len / kFwdBM);
+  for (int32_t qb = 0; qb < nqb; ++qb)
+    work[qb] = visible_blocks(p, q_idx, kv_idx, nkv, qb);
+  NoAllocSplit s{split::choose(work, nqb, p->num_q_heads, kFwdSlots), 0, 0};
+  if (s.cut.c == 0) return s;
+  for (int32_t qb = 0; qb < nqb; ++qb) {
+    const int32_t n = split::num_pieces(s.cut, qb, work[qb]);
+    s.row_pieces += n;
+    s.split_rows += n > 1;
+  }
+  return s;
+}
+
 // Forward of one chunk pair of a tile (the whole tile: one chunk each).
 ma_status_t fwd_impl(const ma_problem_t* prob, const int32_t* q_idx,
                      int32_t nq, const int32_t* kv_idx, int32_t nkv,
@@ -600,8 +781,13 @@ ma_status_t fwd_impl(const ma_problem_t* prob, const int32_t* q_idx,
   if (ws_bytes < need)
     return fail(MA_ERR_WORKSPACE_TOO_SMALL, "workspace %zu bytes < %zu",
                 ws_bytes, need);
+  // A workspace without room for partial results (one sized for another,
+  // larger tile) serves the call with whole items.
+  const bool may_split =
+      ws_bytes >= need + fwd_split_bytes(prob, nq, nkv, ch, false);
   PlanView plan;
-  st = upload_plan(0, prob, q_idx, nq, kv_idx, nkv, ch, ws, stream, &plan);
+  st = upload_plan(0, prob, q_idx, nq, kv_idx, nkv, ch, may_split, ws, stream,
+                   &plan);
   if (st != MA_OK) return st;
   char* wsb = static_cast<char*>(ws);
   FwdParams fp{};
@@ -622,11 +808,14 @@ ma_status_t fwd_impl(const ma_problem_t* prob, const int32_t* q_idx,
   fp.scale_log2 = prob->softmax_scale * kLog2e;
   fp.accumulate = accumulate;
   if (plan.a.grid == 0) return ok();  // cannot happen: every block is listed
-  hipError_t e = launch_tile_fwd(
-      fp, prob->head_dim, o_f32,
-      static_cast<int>(queued_launch_grid(plan.a.n_items)), stream);
-  if (e != hipSuccess) return hip_fail(e, "tile_fwd launch");
-  return ok();
+  if (plan.a.n_splits > 0) {
+    fp.pieces = reinterpret_cast<const DevPiece*>(wsb + plan.a.off_pieces);
+    fp.part_lse = reinterpret_cast<float*>(wsb + align_up(plan.bytes));
+    fp.part_o = fp.part_lse + parts_of(prob, nq, nkv, ch) * kFwdBM;
+  }
+  return launch_fwd(fp, prob->head_dim, o_f32, plan.a.n_items,
+                    reinterpret_cast<const DevSplit*>(wsb + plan.a.off_splits),
+                    plan.a.n_splits, stream);
 }
 
 // Backward of one chunk pair of a tile (the whole tile: one chunk each).
@@ -658,7 +847,8 @@ ma_status_t bwd_impl(const ma_problem_t* prob, const int32_t* q_idx,
     return fail(MA_ERR_WORKSPACE_TOO_SMALL, "workspace %zu bytes < %zu",
                 ws_bytes, need);
   PlanView plan;
-  st = upload_plan(1, prob, q_idx, nq, kv_idx, nkv, ch, ws, stream, &plan);
+  st = upload_plan(1, prob, q_idx, nq, kv_idx, nkv, ch, false, ws, stream,
+                   &plan);
   if (st != MA_OK) return st;
   char* wsb = static_cast<char*>(ws);
   BwdParams bp{};
@@ -787,7 +977,8 @@ ma_status_t mesh_attn_worklist_kv_major(const ma_problem_t* prob,
 size_t mesh_attn_fwd_workspace_size(const ma_problem_t* prob, int32_t nq,
                                     int32_t nkv) {
   if (check_problem(prob) != MA_OK || nq < 1 || nkv < 1) return 0;
-  return fwd_ws_bound(prob, nq, nkv);
+  return fwd_ws_bound(prob, nq, nkv) +
+         fwd_split_bytes(prob, nq, nkv, kWholeTile, false);
 }
 
 size_t mesh_attn_bwd_workspace_size(const ma_problem_t* prob, int32_t nq,
@@ -810,7 +1001,9 @@ ma_status_t mesh_attn_tile_fwd(const ma_problem_t* prob, const int32_t* q_idx,
 size_t mesh_attn_chunk_fwd_workspace_size(const ma_problem_t* prob,
                                           int32_t nq, int32_t nkv) {
   // A chunk's work list is never longer than the whole tile's.
-  return mesh_attn_fwd_workspace_size(prob, nq, nkv);
+  if (check_problem(prob) != MA_OK || nq < 1 || nkv < 1) return 0;
+  return fwd_ws_bound(prob, nq, nkv) +
+         fwd_split_bytes(prob, nq, nkv, kWholeTile, true);
 }
 
 ma_status_t mesh_attn_chunk_fwd(const ma_problem_t* prob, const int32_t* q_idx,
@@ -859,8 +1052,8 @@ ma_status_t mesh_attn_tile_fwd_noalloc(const ma_problem_t* prob,
                 "bytes) exceeds the scratch maximum (%d Q blocks, %zu bytes)",
                 static_cast<long long>(nqb), need, kNoAllocMaxQBlocks,
                 kNoAllocScratchBytes);
-  void* scratch = nullptr;
-  hipError_t e = noalloc_scratch(&scratch);
+  void *scratch = nullptr, *parts = nullptr;
+  hipError_t e = noalloc_scratch(&scratch, &parts);
   if (e != hipSuccess) return hip_fail(e, "hipGetSymbolAddress(scratch)");
   // Same regions as the uploaded plan: Q-block pointers, runs, order.
   char* base = static_cast<char*>(scratch);
@@ -869,10 +1062,21 @@ ma_status_t mesh_attn_tile_fwd_noalloc(const ma_problem_t* prob,
       off_runs + align_up(static_cast<size_t>(nqb) * nkv * 2 * sizeof(DevRun));
   const int64_t items = nqb * prob->num_q_heads;
   const bool by_kv = prob->num_kv_heads % kNumXcd == 0;
-  const int64_t grid = by_kv ? items : (items + kNumXcd - 1) / kNumXcd * kNumXcd;
+  int64_t grid = by_kv ? items : (items + kNumXcd - 1) / kNumXcd * kNumXcd;
   if (grid > INT32_MAX)
     return fail(MA_ERR_UNSUPPORTED, "noalloc forward: %lld workgroups",
                 static_cast<long long>(grid));
+  // The same split as the call with a workspace of full size, which has room
+  // for it beside the work list.
+  NoAllocSplit sp{{0, 0}, 0, 0};
+  const int64_t max_parts = parts_of(prob, nq, nkv, kWholeTile);
+  if (max_parts > 0 && need + split_bound(items, kFwdSlots, max_parts, 0) <=
+                           kNoAllocScratchBytes)
+    sp = noalloc_split(prob, q_idx, nq, kv_idx, nkv);
+  const bool split = sp.cut.c > 0;
+  const int64_t n_items =
+      split ? int64_t{sp.row_pieces} * prob->num_q_heads : items;
+  if (split) grid = n_items;
   PlanBuildParams bp{};
   bp.P = prob->partition_len;
   bp.n = prob->num_partitions;
@@ -891,8 +1095,14 @@ ma_status_t mesh_attn_tile_fwd_noalloc(const ma_problem_t* prob,
   bp.qblk_ptr = reinterpret_cast<int32_t*>(base);
   bp.runs = reinterpret_cast<DevRun*>(base + off_runs);
   bp.order = reinterpret_cast<int2*>(base + off_order);
-  bp.queue = reinterpret_cast<int32_t*>(
-      base + off_order + align_up(static_cast<size_t>(grid) * sizeof(int2)));
+  size_t off = off_order + align_up(static_cast<size_t>(grid) * sizeof(int2));
+  bp.queue = reinterpret_cast<int32_t*>(base + off);
+  off += align_up(kNumXcd * 4);
+  bp.cut = sp.cut;
+  bp.row_pieces = sp.row_pieces;
+  bp.pieces = reinterpret_cast<DevPiece*>(base + off);
+  off += split ? align_up(static_cast<size_t>(grid) * sizeof(DevPiece)) : 0;
+  bp.splits = reinterpret_cast<DevSplit*>(base + off);
   for (int32_t i = 0; i < nq; ++i) bp.q_idx[i] = q_idx[i];
   for (int32_t i = 0; i < nkv; ++i) bp.kv_idx[i] = kv_idx[i];
   e = launch_fwd_plan_build(bp, stream);
@@ -907,17 +1117,20 @@ ma_status_t mesh_attn_tile_fwd_noalloc(const ma_problem_t* prob,
   fp.runs = bp.runs;
   fp.order = bp.order;
   fp.queue = bp.queue;
-  fp.n_items = static_cast<int32_t>(items);
+  fp.n_items = static_cast<int32_t>(n_items);
   fp.rows_q = int64_t{nq} * prob->partition_len;
   fp.hq = prob->num_q_heads;
   fp.hkv = prob->num_kv_heads;
   fp.group = bp.group;
   fp.scale_log2 = prob->softmax_scale * kLog2e;
   fp.accumulate = 0;
-  e = launch_tile_fwd(fp, prob->head_dim, o_dtype == MA_FP32,
-                      static_cast<int>(queued_launch_grid(items)), stream);
-  if (e != hipSuccess) return hip_fail(e, "tile_fwd launch");
-  return ok();
+  if (split) {
+    fp.pieces = bp.pieces;
+    fp.part_lse = static_cast<float*>(parts);
+    fp.part_o = fp.part_lse + split::max_parts(kFwdSlots) * kFwdBM;
+  }
+  return launch_fwd(fp, prob->head_dim, o_dtype == MA_FP32, fp.n_items,
+                    bp.splits, sp.split_rows * prob->num_q_heads, stream);
 }
 
 ma_status_t mesh_attn_lse_merge(int32_t k_parts, int64_t rows, int32_t heads,

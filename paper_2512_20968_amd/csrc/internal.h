@@ -7,6 +7,8 @@
 
 #include <atomic>
 
+#include "split.h"
+
 namespace mesh_attn {
 
 // gfx950 (MI355X) has 8 XCDs; consecutive workgroup ids are dispatched to
@@ -31,6 +33,17 @@ struct DevRun {
   int32_t blk0, nblk, cls, delta;
 };
 
+// One workgroup's share of a split item: blocks [off, ..) of run `run`, nblk
+// blocks in all; part >= 0: write a partial result into that slot.
+struct DevPiece {
+  int32_t run, off, nblk, part;
+};
+
+// A split item: its partial results are slots [part0, part0 + nparts).
+struct DevSplit {
+  int32_t blk, head, part0, nparts;
+};
+
 struct FwdParams {
   const uint16_t* q;   // bf16 [rows_q][hq][d]
   const uint16_t* k;   // bf16 [rows_kv][hkv][d]
@@ -46,7 +59,32 @@ struct FwdParams {
   int32_t hq, hkv, group;
   float scale_log2;    // softmax scale * log2(e)
   int32_t accumulate;  // 1: fold into the float32 (O, LSE) already stored
+  // Split tiles only (null otherwise): the piece of each order slot and the
+  // partial results, [part][kFwdBM][d] and [part][kFwdBM] (log2 units).
+  const DevPiece* pieces;
+  float* part_o;
+  float* part_lse;
 };
+
+// Forward workgroups that run at once: one per compute unit (its eight waves
+// of 256 registers fill the SIMDs).
+constexpr int kFwdSlots = 256;
+
+// Folds the partial results of the split items into O and LSE.
+struct CombineParams {
+  const DevSplit* splits;
+  const float* part_o;
+  const float* part_lse;
+  void* o;
+  float* lse;
+  int64_t rows_q;
+  int32_t hq;
+  int32_t accumulate;
+};
+
+hipError_t launch_fwd_combine(const CombineParams& p, int head_dim,
+                              bool out_f32, int n_splits,
+                              hipStream_t stream);
 
 // Workgroup items of the forward and of both backward kernels.  The XCDs of
 // the part run at different speeds (a few per cent apart under load) while
@@ -129,6 +167,13 @@ constexpr size_t kNoAllocScratchBytes = size_t{8} << 20;  // per GPU
 constexpr int kNoAllocMaxList = 256;      // partitions per index list
 constexpr int kNoAllocMaxQBlocks = 4096;  // forward Q blocks of the tile
 
+// Partial results of a split tile: the most slots there are, d = 128.
+constexpr size_t kNoAllocPartBytes =
+    size_t{split::max_parts(kFwdSlots)} * kFwdBM * (128 + 1) * 4;
+// Block rows of a tile that is split at all, and pieces of one head.
+constexpr int kSplitMaxRows = split::kMaxRounds * kFwdSlots;
+constexpr int kSplitMaxPieces = kSplitMaxRows + split::max_parts(kFwdSlots);
+
 struct PlanBuildParams {
   int32_t P, n, layout, causal;   // problem (partition length, partitions)
   int32_t nq, nkv, hq, hkv, group;
@@ -139,13 +184,20 @@ struct PlanBuildParams {
   DevRun* runs;                   // [<= 2 nqb nkv]
   int2* order;                    // [grid]
   int32_t* queue;                 // [8] lane counters, zeroed by the build
+  // Split tiles (cut.c > 0): the pieces of a row of heads, the slots' pieces
+  // and the split items.
+  split::Cut cut;
+  int32_t row_pieces;             // pieces of all Q blocks of one head
+  DevPiece* pieces;               // [grid]
+  DevSplit* splits;
   int32_t q_idx[kNoAllocMaxList];
   int32_t kv_idx[kNoAllocMaxList];
 };
 
-// Device address of the scratch array on the current device (looked up with
-// hipGetSymbolAddress on the first call per device, then cached).
-hipError_t noalloc_scratch(void** ptr);
+// Device addresses of the scratch array and of the partial results' array
+// (kNoAllocPartBytes) on the current device, looked up with
+// hipGetSymbolAddress on the first call per device, then cached.
+hipError_t noalloc_scratch(void** ptr, void** parts);
 
 // Builds the forward work list and workgroup order of `p` (one workgroup).
 hipError_t launch_fwd_plan_build(const PlanBuildParams& p, hipStream_t stream);

@@ -29,6 +29,7 @@ namespace {
 // must never pass its name to a kernel (the name is a host-side stand-in):
 // noalloc_scratch() gives the device address.
 __device__ __align__(256) char scratch[kNoAllocScratchBytes];
+__device__ __align__(256) char part_scratch[kNoAllocPartBytes];
 
 constexpr int kBuildThreads = 1024;
 
@@ -91,6 +92,77 @@ __device__ int32_t run_delta(const PlanBuildParams& p, const PairRuns& r,
                               tok_pos(p, r.kp, k_row0));
 }
 
+// Positions of a split tile's pieces in its order.  All heads are cut alike,
+// so the pieces of one head (length, row, index) are ranked once and every
+// head's slots follow from the ranks.
+__device__ void split_order(const PlanBuildParams& p, const int* s_work) {
+  __shared__ int s_len[kSplitMaxPieces];
+  __shared__ uint16_t s_row[kSplitMaxPieces], s_idx[kSplitMaxPieces];
+  __shared__ int s_pre[kSplitMaxRows + 1], s_cut[kSplitMaxRows + 1];
+  const int t = threadIdx.x;
+  const int m = p.row_pieces;
+  // First piece, and first split row, of every row: a serial pass by one
+  // wave's lanes is short because a split tile has few rows per head.
+  if (t == 0) {
+    int at = 0, parts = 0, splits = 0;
+    for (int qb = 0; qb < p.nqb; ++qb) {
+      const int n = split::num_pieces(p.cut, qb, s_work[qb]);
+      s_pre[qb] = at;
+      s_cut[qb] = n > 1 ? parts : -1;
+      at += n;
+      if (n > 1) {
+        parts += n;
+        ++splits;
+      }
+    }
+    s_pre[p.nqb] = parts;
+    s_cut[p.nqb] = splits;
+  }
+  __syncthreads();
+  const int parts = s_pre[p.nqb], splits = s_cut[p.nqb];
+  for (int qb = t; qb < p.nqb; qb += kBuildThreads) {
+    const int w = s_work[qb], n = split::num_pieces(p.cut, qb, w);
+    for (int j = 0; j < n; ++j) {
+      const int i = s_pre[qb] + j;
+      s_len[i] = split::piece_begin(w, n, j + 1) - split::piece_begin(w, n, j);
+      s_row[i] = qb;
+      s_idx[i] = j;
+    }
+    if (n > 1) {
+      int before = 0;
+      for (int b2 = 0; b2 < qb; ++b2) before += s_cut[b2] >= 0;
+      for (int h = 0; h < p.hq; ++h)
+        p.splits[h * splits + before] =
+            DevSplit{qb, h, h * parts + s_cut[qb], n};
+    }
+  }
+  __syncthreads();
+  const int total = m * p.hq;
+  const bool by_kv = p.hkv % kNumXcd == 0;
+  for (int i = t; i < m; i += kBuildThreads) {
+    const int len = s_len[i], idx = s_idx[i], qb = s_row[i];
+    // Rank by length (several rounds) or by piece index (one round).
+    int gt = 0, eq = 0, eq_before = 0;
+    for (int i2 = 0; i2 < m; ++i2) {
+      const bool less = total > kFwdSlots ? s_len[i2] > len : s_idx[i2] < idx;
+      const bool same = total > kFwdSlots ? s_len[i2] == len : s_idx[i2] == idx;
+      gt += less;
+      eq += same;
+      eq_before += same & (i2 < i);
+    }
+    const int w = s_work[qb], n = split::num_pieces(p.cut, qb, w);
+    int run = p.qblk_ptr[qb], off = split::piece_begin(w, n, idx);
+    while (off > 0 && off >= p.runs[run].nblk) off -= p.runs[run++].nblk;
+    for (int h = 0; h < p.hq; ++h) {
+      const int slot = split_slot(total, m, p.hq, p.group, by_kv, h, gt, eq,
+                                  eq_before, kFwdSlots);
+      p.order[slot] = make_int2(qb, h);
+      p.pieces[slot] = DevPiece{
+          run, off, len, s_cut[qb] < 0 ? -1 : h * parts + s_cut[qb] + idx};
+    }
+  }
+}
+
 __global__ __launch_bounds__(kBuildThreads) void fwd_plan_build_kernel(
     PlanBuildParams p) {
   __shared__ int s_work[kNoAllocMaxQBlocks];
@@ -133,6 +205,12 @@ __global__ __launch_bounds__(kBuildThreads) void fwd_plan_build_kernel(
     }
   }
   if (t == kBuildThreads - 1) p.qblk_ptr[p.nqb] = s_scan[t];
+  if (p.cut.c > 0) {
+    __syncthreads();  // the runs, read back below
+    split_order(p, s_work);
+    if (t < kNumXcd) p.queue[t] = 0;
+    return;
+  }
 
   // Workgroup order.  Items (Q block, head) sorted by (work descending, head,
   // Q block); with the KV heads a multiple of the XCD count, the items of KV
@@ -171,10 +249,11 @@ __global__ __launch_bounds__(kBuildThreads) void fwd_plan_build_kernel(
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[kMaxDevices] = {};
+void* g_parts_ptr[kMaxDevices] = {};
 
 }  // namespace
 
-hipError_t noalloc_scratch(void** ptr) {
+hipError_t noalloc_scratch(void** ptr, void** parts) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
@@ -186,9 +265,15 @@ hipError_t noalloc_scratch(void** ptr) {
     e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
     if (e != hipSuccess) return e;
     if (p == nullptr) return hipErrorInvalidSymbol;
+    void* q = nullptr;
+    e = hipGetSymbolAddress(&q, HIP_SYMBOL(part_scratch));
+    if (e != hipSuccess) return e;
+    if (q == nullptr) return hipErrorInvalidSymbol;
     g_scratch_ptr[dev] = p;
+    g_parts_ptr[dev] = q;
   }
   *ptr = g_scratch_ptr[dev];
+  *parts = g_parts_ptr[dev];
   return hipSuccess;
 }
 

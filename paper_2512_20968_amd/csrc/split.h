@@ -1,0 +1,172 @@
+// Splitting of long work items over the blocks they walk, for launches with
+// too few items to fill the chip evenly.
+//
+// An item is one (block row, head) pair of a pass; every head has the same
+// work w[0..n) (blocks per row).  An item may be cut into equal pieces that
+// different workgroups compute as partial results and a second kernel folds.
+// The number of pieces of a row depends on its work alone, so all heads are
+// cut alike, the pieces of the rows of one KV head cover the same key ranges
+// (their workgroups share them in L2) and the XCD lanes stay even.  Integer
+// arithmetic on the work list only: the host and the device-side list builder
+// cut alike, and a tile gives the same bits from both.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace mesh_attn {
+namespace split {
+
+// A workgroup's start and end (work list, first tiles, fragments, epilogue)
+// take about as long as six blocks: forward items of 4 and 64 blocks measured
+// 14.3 and 100.8 us at d = 128 (1.44 us per block), 11.0 and 83.2 us at
+// d = 64 (1.20).
+constexpr int32_t kOverhead = 6;
+// Shortest piece worth a workgroup and a partial result; items of at most two
+// such pieces stay whole.
+constexpr int32_t kMinPiece = 4;
+// Tiles of more rounds of whole items than this are never split: the longest
+// first order leaves at most a fraction of a round idle.
+constexpr int32_t kMaxRounds = 8;
+
+// Rows [0, whole) of every head stay whole, the others are cut into pieces of
+// at most c blocks; c = 0: nothing is cut.
+struct Cut {
+  int32_t c, whole;
+};
+
+__host__ __device__ inline int32_t num_pieces(const Cut& s, int32_t row,
+                                              int32_t w) {
+  return s.c > 0 && row >= s.whole && w > s.c ? (w + s.c - 1) / s.c : 1;
+}
+
+// First block of piece j of n.
+__host__ __device__ inline int32_t piece_begin(int32_t w, int32_t n,
+                                               int32_t j) {
+  return static_cast<int32_t>(int64_t{w} * j / n);
+}
+
+// Most partial results a pass of `slots` concurrent workgroups holds.
+constexpr int32_t max_parts(int32_t slots) { return 2 * slots; }
+
+// Partial results a tile may need, from its sizes alone: `items` items of at
+// most `max_work` blocks.  Never less than what choose() gives.
+inline int64_t parts_bound(int64_t items, int64_t max_work, int32_t slots) {
+  if (items > int64_t{kMaxRounds} * slots || max_work <= 2 * kMinPiece)
+    return 0;
+  const int64_t by_work = items * ((max_work + kMinPiece - 1) / kMinPiece);
+  return by_work < max_parts(slots) ? by_work : max_parts(slots);
+}
+
+// Estimated time of a cut, in blocks of a workgroup: the pieces run longest
+// first on `slots` workgroups, so the launch takes its total divided by the
+// slots plus what the last round leaves idle (as long as the shortest
+// pieces), and never less than its longest piece; then the fold, about two
+// blocks plus one per 20 partials (a partial is written and read once).
+// parts < 0 if the cut needs more partials than there are.
+struct Estimate {
+  int64_t time, parts;
+};
+inline Estimate estimate(const int32_t* w, int32_t n, int32_t heads,
+                         const Cut& s, int32_t slots) {
+  int64_t pieces = 0, parts = 0, sum = 0;
+  int32_t longest = 0, shortest = INT32_MAX;
+  for (int32_t i = 0; i < n; ++i) {
+    const int32_t k = num_pieces(s, i, w[i]);
+    pieces += k;
+    if (k > 1) parts += k;
+    sum += w[i];
+    const int32_t hi = (w[i] + k - 1) / k, lo = w[i] / k;
+    if (hi > longest) longest = hi;
+    if (lo < shortest) shortest = lo;
+  }
+  pieces *= heads;
+  parts *= heads;
+  sum = sum * heads + pieces * kOverhead;
+  if (parts > max_parts(slots)) return {0, -1};
+  const int64_t idle = (slots - pieces % slots) % slots;
+  int64_t t = (sum + idle * (shortest + kOverhead) + slots - 1) / slots;
+  if (t < longest + kOverhead) t = longest + kOverhead;
+  return {t + (parts > 0 ? 2 + parts / 20 : 0), parts};
+}
+
+// The cut of a tile, {0, 0} to leave every item whole: the best estimate over
+// the pieces of the longest item, and for equal items also whole rounds with
+// only the rows of the last, partly filled round cut.  A cut has to be
+// estimated 5 % faster than whole items.
+inline Cut choose(const int32_t* w, int32_t n, int32_t heads, int32_t slots) {
+  const int64_t items = int64_t{n} * heads;
+  int32_t longest = 0, shortest = INT32_MAX;
+  for (int32_t i = 0; i < n; ++i) {
+    if (w[i] > longest) longest = w[i];
+    if (w[i] < shortest) shortest = w[i];
+  }
+  if (items > int64_t{kMaxRounds} * slots || longest <= 2 * kMinPiece)
+    return {0, 0};
+  const int64_t whole_time = estimate(w, n, heads, {0, 0}, slots).time;
+  Cut best{0, 0};
+  int64_t best_time = whole_time * 19 / 20;
+  auto consider = [&](const Cut& s) {
+    const Estimate e = estimate(w, n, heads, s, slots);
+    if (e.parts > 0 && e.time < best_time) {
+      best_time = e.time;
+      best = s;
+    }
+    return e.parts >= 0;
+  };
+  int32_t last = longest;
+  for (int32_t k = 2;; ++k) {
+    const int32_t c = (longest + k - 1) / k;
+    if (c < kMinPiece) break;
+    if (c == last) continue;
+    last = c;
+    if (!consider({c, 0})) break;
+  }
+  if (longest == shortest && items > slots) {
+    const int32_t rounds = static_cast<int32_t>(items / slots);
+    const int32_t whole = rounds * slots / heads;  // rows
+    if (whole > 0 && whole < n) {
+      const int64_t rest = items - int64_t{whole} * heads;
+      const int64_t k =
+          (int64_t{rounds + 1} * slots - int64_t{whole} * heads) / rest;
+      const int32_t c = static_cast<int32_t>((longest + k - 1) / k);
+      if (k > 1 && c >= kMinPiece) consider({c, whole});
+    }
+  }
+  return best;
+}
+
+}  // namespace split
+
+// Slot of a piece in the order of a split tile of `total` pieces, m per head.
+// `before`, `same` and `same_before` count the pieces of one head that rank
+// before it, equal to it, and equal to it with a lower index.  More pieces
+// than run at once: ranked longest first; lane x (slots j * 8 + x) holds the
+// pieces of KV heads x, x + 8, .. if the KV heads allow it, else pieces are
+// dealt round robin.  One round: ranked by piece index, and consecutive
+// pieces of a KV head share a lane, because they walk the same keys.
+constexpr int kXcdLanes = 8;
+__host__ __device__ inline int split_slot(int total, int m, int heads,
+                                          int group, bool by_kv, int h,
+                                          int before, int same,
+                                          int same_before, int slots) {
+  const int kvh = h / group, hg = h % group;
+  if (total <= slots) {
+    const int pos = kvh * group * m + before * group + hg * same + same_before;
+    const int len = total / kXcdLanes, more = total % kXcdLanes;
+    const int cut = more * (len + 1);  // pieces in the longer lanes
+    const int x = pos < cut ? pos / (len + 1) : more + (pos - cut) / len;
+    const int j = pos < cut ? pos % (len + 1) : (pos - cut) % len;
+    return j * kXcdLanes + x;
+  }
+  if (by_kv) {
+    const int lane_heads = heads / kXcdLanes;
+    const int heads_before = (kvh / kXcdLanes) * group + hg;
+    return (before * lane_heads + same * heads_before + same_before) *
+               kXcdLanes +
+           kvh % kXcdLanes;
+  }
+  return before * heads + h * same + same_before;
+}
+
+}  // namespace mesh_attn

@@ -18,7 +18,11 @@
 // the K/V loads, which makes both of its phases the longer ones of their
 // slots, so its waves run at raised issue priority.  On launches with many
 // items, the last items of each XCD's share are taken from per-XCD counters
-// (queued_slot), so that faster XCDs take more of them.
+// (queued_slot), so that faster XCDs take more of them.  On launches with few
+// items (split.h) a workgroup computes one piece of an item's KV blocks and
+// leaves a float32 partial result; fwd_combine_kernel folds them.  64 items of
+// 1024 blocks (d = 128): 1350 us whole, 477 us in 256 pieces of 256 blocks;
+// 64 causal items of 36 to 64 blocks: 107 us whole, 36 us split.
 //
 // Layout choices (64-wide wavefronts, v_mfma_f32_32x32x16_bf16):
 //  * Scores are computed transposed, S^T = K Q^T (A = K rows from LDS,
@@ -73,33 +77,33 @@ struct FwdLayout {
   }
 };
 
-// Position in the flattened list of KV blocks of one Q block's runs.
+// Position in the flattened list of KV blocks of one Q block's runs, with the
+// number of blocks left in this workgroup's piece of it.
 struct Cursor {
   DevRun run;
-  int r, off;
-  bool valid;
-  __device__ int64_t blk() const { return int64_t{run.blk0} + off; }
+  int r, off, left;
 };
 
-__device__ __forceinline__ Cursor first_block(const FwdParams& p, int r,
-                                              int run_e) {
-  Cursor c;
-  c.r = r;
-  c.off = 0;
-  c.valid = r < run_e;
-  if (c.valid) c.run = load_const(p.runs, r);
-  return c;
+// A KV block as the phases use it: its index in the tile's KV buffer (-1 past
+// the end of the piece), the class of its run and the mask limit of the
+// block's first query (key j is hidden from query i iff j - i > lim).
+struct Blk {
+  int idx, cls, lim;
+  __device__ bool valid() const { return idx >= 0; }
+};
+
+__device__ __forceinline__ Blk block_at(const Cursor& c) {
+  return Blk{c.left > 0 ? c.run.blk0 + c.off : -1, c.run.cls,
+             c.run.delta - c.off * BN};
 }
 
-__device__ __forceinline__ Cursor next_block(const FwdParams& p, Cursor c,
-                                             int run_e) {
-  if (!c.valid) return c;
+__device__ __forceinline__ Cursor next_block(const FwdParams& p, Cursor c) {
+  if (c.left <= 0) return c;
+  --c.left;
   if (++c.off == c.run.nblk) {
     c.off = 0;
-    if (++c.r < run_e)
-      c.run = load_const(p.runs, c.r);
-    else
-      c.valid = false;
+    ++c.r;
+    if (c.left > 0) c.run = load_const(p.runs, c.r);
   }
   return c;
 }
@@ -130,8 +134,23 @@ __global__ __launch_bounds__(NT, 1) void tile_fwd_kernel(FwdParams p) {
   const int qblk = item.x;
   const int h = item.y;
   const int hk = h / p.group;
-  const int run_b = load_const(p.qblk_ptr, qblk);
-  const int run_e = load_const(p.qblk_ptr, qblk + 1);
+  // The whole item, or on a split tile this workgroup's piece of it.
+  Cursor c0;
+  int part = -1;
+  if (p.pieces) {
+    const DevPiece pc = load_const(p.pieces, slot);
+    c0.r = pc.run;
+    c0.off = pc.off;
+    c0.left = pc.nblk;
+    part = pc.part;
+  } else {
+    c0.r = load_const(p.qblk_ptr, qblk);
+    c0.off = 0;
+    c0.left = 0;
+    const int run_e = load_const(p.qblk_ptr, qblk + 1);
+    for (int r = c0.r; r < run_e; ++r) c0.left += load_const(p.runs, r).nblk;
+  }
+  const int nblocks = c0.left;
 
   const int64_t q_row = int64_t{qblk} * BM + wave * 32 + li;
   const int q_in_blk = wave * 32 + li;
@@ -146,11 +165,8 @@ __global__ __launch_bounds__(NT, 1) void tile_fwd_kernel(FwdParams p) {
   float m = -INFINITY;  // reference max of scaled scores (log2 units)
   float l = 0.f;        // this lane's share of the row sum
 
-  // Number of KV blocks of this Q block.
-  int nblocks = 0;
-  for (int r = run_b; r < run_e; ++r) nblocks += load_const(p.runs, r).nblk;
-
   if (nblocks > 0) {
+    c0.run = load_const(p.runs, c0.r);
     // Direct global -> LDS staging, done by the four waves of group B.
     // Wave wg of the group fills rows wg*RPW .. +RPW of a tile with NLI
     // loads of 1 KB; lane i of load j takes row wg*RPW + j*RPI + i/CPR and
@@ -185,10 +201,10 @@ __global__ __launch_bounds__(NT, 1) void tile_fwd_kernel(FwdParams p) {
       char* kdst;
       char* vdst;
     };
-    auto make_round = [&](const Cursor& ck, const Cursor& cv, int n) {
+    auto make_round = [&](const Blk& bk, const Blk& bv, int n) {
       Round rd;
-      rd.rk = ck.valid ? rsrc_of(p.k, ck.blk()) : make_rsrc(p.k, 0);
-      rd.rv = cv.valid ? rsrc_of(p.v, cv.blk()) : make_rsrc(p.v, 0);
+      rd.rk = bk.valid() ? rsrc_of(p.k, bk.idx) : make_rsrc(p.k, 0);
+      rd.rv = bv.valid() ? rsrc_of(p.v, bv.idx) : make_rsrc(p.v, 0);
       rd.kdst = smem + (n & 1) * L::TILE;
       rd.vdst = smem + (2 + ((n + 1) & 1)) * L::TILE;
       return rd;
@@ -292,10 +308,10 @@ __global__ __launch_bounds__(NT, 1) void tile_fwd_kernel(FwdParams p) {
     // the run is hidden from query i of the Q block iff j - i > delta),
     // running max, rescale of O and l if some row of the wave has a new max,
     // then P = exp2(s S - m) into the bf16 B operand and the row sums.
-    auto softmax = [&](f32x16 (&sc)[2], const Cursor& cu, bf16x8 (&pb)[4],
+    auto softmax = [&](f32x16 (&sc)[2], const Blk& bl, bf16x8 (&pb)[4],
                        auto&& hook) {
-      if (cu.run.cls == 1) {
-        const int lim = cu.run.delta - cu.off * BN + q_in_blk;
+      if (bl.cls == 1) {
+        const int lim = bl.lim + q_in_blk;
 #pragma unroll
         for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
@@ -343,12 +359,13 @@ __global__ __launch_bounds__(NT, 1) void tile_fwd_kernel(FwdParams p) {
 
     // Prologue (all waves): K(0), V(0) and K(1) into LDS (group B loads),
     // then the scores and probabilities of block 0.
-    Cursor c0 = first_block(p, run_b, run_e);
-    Cursor c1 = next_block(p, c0, run_e);
+    const Blk b0 = block_at(c0);
+    Cursor cu = next_block(p, c0);  // the block furthest ahead
+    Blk bs = block_at(cu);          // block whose scores X(n) computes (n+1)
     if (grp == 1) {
-      load_k(c0.blk(), 0);
-      load_v(c0.blk(), 0);
-      if (c1.valid) load_k(c1.blk(), 1);
+      load_k(b0.idx, 0);
+      load_v(b0.idx, 0);
+      if (bs.valid()) load_k(bs.idx, 1);
     }
 #pragma unroll
     for (int kk = 0; kk < D / 16; ++kk) wait_for(qf[kk]);
@@ -358,7 +375,7 @@ __global__ __launch_bounds__(NT, 1) void tile_fwd_kernel(FwdParams p) {
     {
       f32x16 s0[2];
       scores(s0, 0);
-      softmax(s0, c0, pb, [](int) {});
+      softmax(s0, b0, pb, [](int) {});
     }
     // Every wave has read K(0) before group B refills K buffer 0.
     __syncthreads();
@@ -372,32 +389,34 @@ __global__ __launch_bounds__(NT, 1) void tile_fwd_kernel(FwdParams p) {
     // in LDS by slot 2n+2, when A's X(n+1) first reads them; the buffers they
     // overwrite were last read in slots 2n-2 and 2n-1.
     f32x16 snx[2];
-    Cursor cs = c1;  // block whose scores X(n) computes (block n+1)
     if (grp == 0) {
       for (int n = 0; n < nblocks; ++n) {
-        if (cs.valid) scores(snx, (n + 1) & 1);
+        if (bs.valid()) scores(snx, (n + 1) & 1);
         pv(pb, n & 1);
         lds_barrier();
-        if (cs.valid) {
-          softmax(snx, cs, pb, [](int) {});
-          cs = next_block(p, cs, run_e);
+        if (bs.valid()) {
+          softmax(snx, bs, pb, [](int) {});
+          cu = next_block(p, cu);
+          bs = block_at(cu);
         }
         lds_barrier();
       }
     } else {
-      Cursor ck = next_block(p, c1, run_e);  // K block to load next
-      Cursor cv = c1;                        // V block to load next
+      Blk bv = bs;  // V block to load next
+      cu = next_block(p, cu);
+      Blk bk = block_at(cu);  // K block to load next
       // Round n: K(n+2) and V(n+1), issued in slot 2n.  Issued as one burst
       // at the end of the softmax phase, the 2 NLI loads per wave held the
       // issuing waves up for several hundred cycles (measured: that phase
       // grew by about half); spread over the four exponential groups they
       // overlap the VALU work instead (about 5% faster overall).
       auto advance = [&]() {
-        ck = next_block(p, ck, run_e);
-        cv = next_block(p, cv, run_e);
+        bv = bk;
+        cu = next_block(p, cu);
+        bk = block_at(cu);
       };
       {
-        const Round rd = make_round(ck, cv, 0);
+        const Round rd = make_round(bk, bv, 0);
 #pragma unroll
         for (int t = 0; t < 2 * L::NLI; ++t) load_part(rd, t);
         advance();
@@ -412,19 +431,19 @@ __global__ __launch_bounds__(NT, 1) void tile_fwd_kernel(FwdParams p) {
       constexpr int PER = (2 * L::NLI) / 4;  // loads per exponential group
       static_assert(PER * 4 == 2 * L::NLI, "loads split evenly over 4 groups");
       for (int n = 0; n < nblocks; ++n) {
-        if (cs.valid) scores(snx, (n + 1) & 1);
+        if (bs.valid()) scores(snx, (n + 1) & 1);
         pv(pb, n & 1);
         wait_vmem();
         lds_barrier();
         // Block n+1 exists iff n + 1 < N; the last slot belongs to X(N-1)
         // and has no round after it.
-        if (cs.valid) {
+        if (bs.valid()) {
           // Cursor updates (scalar code with branches) go first, so that the
           // compiler does not sink the exponentials below them, away from
           // the loads they are meant to hide.
-          const Round rd = make_round(ck, cv, n + 1);
-          const Cursor cur = cs;
-          cs = next_block(p, cs, run_e);
+          const Round rd = make_round(bk, bv, n + 1);
+          const Blk cur = bs;
+          bs = bv;
           advance();
           softmax(snx, cur, pb, [&](int ss) {
             // Keep the compiler from hoisting all loads to the phase start.
@@ -443,6 +462,22 @@ __global__ __launch_bounds__(NT, 1) void tile_fwd_kernel(FwdParams p) {
   const float lt = l + __shfl_xor(l, 32);
   const float inv = lt > 0.f ? 1.f / lt : 0.f;
   const float lse2 = lt > 0.f ? m + __builtin_amdgcn_logf(lt) : -INFINITY;
+  if (part >= 0) {
+    // A partial result: O normalised, float32, and the LSE in log2 units.
+    const int64_t prow = int64_t{part} * BM + q_in_blk;
+    if (lh == 0) p.part_lse[prow] = lse2;
+#pragma unroll
+    for (int cc = 0; cc < D / 32; ++cc)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        f32x4 x;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) x[t] = oacc[cc][4 * g + t] * inv;
+        *reinterpret_cast<f32x4*>(p.part_o + prow * D + cc * 32 + g * 8 +
+                                  lh * 4) = x;
+      }
+    return;
+  }
   const int64_t lidx = int64_t{h} * p.rows_q + q_row;
   // Running accumulation (float32 partials only): fold (O, LSE) of this
   // call into the stored pair with the two-part online-softmax reducer,
@@ -515,6 +550,88 @@ __global__ __launch_bounds__(NT, 1) void tile_fwd_kernel(FwdParams p) {
     }
 }
 
+// ---------------------------------------------------------------------------
+// Fold of the partial results of split items (the online-softmax reducer, in
+// piece order): one workgroup per 256 / (D / 4) rows of an item, a lane per
+// four dims of a row, so that loads and stores are 16 bytes and contiguous.
+// Bound by memory: 256 partials of 256 x 128 (34 MB) in 7-9 us.
+// ---------------------------------------------------------------------------
+constexpr int NTC = 256;
+
+template <int D, bool OUT_F32>
+__global__ __launch_bounds__(NTC) void fwd_combine_kernel(CombineParams p) {
+  constexpr int LPR = D / 4;             // lanes per row
+  constexpr int RPB = NTC / LPR;         // rows per workgroup
+  constexpr int GPI = BM / RPB;          // workgroups per item
+  const DevSplit it = load_const(p.splits, blockIdx.x / GPI);
+  const int row = (blockIdx.x % GPI) * RPB + threadIdx.x / LPR;
+  const int sub = threadIdx.x % LPR;
+  const int64_t q_row = int64_t{it.blk} * BM + row;
+  const int64_t lidx = int64_t{it.head} * p.rows_q + q_row;
+  const int64_t oidx = (q_row * p.hq + it.head) * D + sub * 4;
+  float M = -INFINITY, S = 0.f;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  auto fold = [&](const f32x4& x, float lse) {
+    const float mn = fmaxf(M, lse);
+    const float mu = mn == -INFINITY ? 0.f : mn;
+    const float r = exp2_fast(M - mu), w = exp2_fast(lse - mu);
+    S = fmaf(S, r, w);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) acc[t] = fmaf(w, x[t], acc[t] * r);
+    M = mn;
+  };
+  constexpr int B = 4;  // partials in flight
+  for (int k0 = 0; k0 < it.nparts; k0 += B) {
+    f32x4 x[B];
+    float lv[B];
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      const int k = min(k0 + u, it.nparts - 1);
+      const int64_t prow = int64_t{it.part0 + k} * BM + row;
+      x[u] = *reinterpret_cast<const f32x4*>(p.part_o + prow * D + sub * 4);
+      lv[u] = p.part_lse[prow];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < B; ++u)
+      if (k0 + u < it.nparts) fold(x[u], lv[u]);
+  }
+  if constexpr (OUT_F32) {
+    if (p.accumulate) {
+      // Every lane of the row reads the stored LSE before lane 0 of the row
+      // rewrites it below (one wave, program order).
+      const float old2 = p.lse[lidx] * 1.4426950408889634f;
+      fold(*reinterpret_cast<const f32x4*>(static_cast<const float*>(p.o) +
+                                           oidx),
+           old2);
+    }
+  }
+  const float inv = S > 0.f ? 1.f / S : 0.f;
+  if (sub == 0)
+    p.lse[lidx] = M == -INFINITY
+                      ? -INFINITY
+                      : (M + __builtin_amdgcn_logf(S)) * 0.69314718055994531f;
+  if constexpr (OUT_F32) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) acc[t] *= inv;
+    *reinterpret_cast<f32x4*>(static_cast<float*>(p.o) + oidx) = acc;
+  } else {
+    bf16x4 val;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) val[t] = static_cast<__bf16>(acc[t] * inv);
+    *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(p.o) + oidx) = val;
+  }
+}
+
+template <int D, bool F32>
+hipError_t combine(const CombineParams& p, int n_splits,
+                   hipStream_t stream) {
+  constexpr int GPI = BM / (NTC / (D / 4));
+  hipLaunchKernelGGL((fwd_combine_kernel<D, F32>), dim3(n_splits * GPI),
+                     dim3(NTC), 0, stream, p);
+  return hipGetLastError();
+}
+
 template <int D, bool F32>
 hipError_t launch(const FwdParams& p, int grid, hipStream_t stream) {
   const size_t smem = FwdLayout<D>::SMEM + 16;  // + the item slot
@@ -526,6 +643,18 @@ hipError_t launch(const FwdParams& p, int grid, hipStream_t stream) {
 }
 
 }  // namespace
+
+hipError_t launch_fwd_combine(const CombineParams& p, int head_dim,
+                              bool out_f32, int n_splits,
+                              hipStream_t stream) {
+  if (head_dim == 128)
+    return out_f32 ? combine<128, true>(p, n_splits, stream)
+                   : combine<128, false>(p, n_splits, stream);
+  if (head_dim == 64)
+    return out_f32 ? combine<64, true>(p, n_splits, stream)
+                   : combine<64, false>(p, n_splits, stream);
+  return hipErrorInvalidValue;
+}
 
 hipError_t launch_tile_fwd(const FwdParams& p, int head_dim, bool out_f32,
                            int grid, hipStream_t stream) {

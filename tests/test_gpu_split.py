@@ -1,0 +1,116 @@
+"""Tiles whose long work items are split over several workgroups (few items,
+or a nearly empty last round), through the C ABI, against the float64 oracle:
+every row and head.  A call whose workspace has no room for partial results
+must give the whole-item result, and the allocation-free forward the bits of
+the call with a full workspace."""
+
+import dataclasses
+
+import pytest
+import torch
+
+import oracle
+import paper_2512_20968_amd as ma
+from mesh_inputs import WORKLOADS, make_qkv
+
+from helpers import check_fwd, log, to_np
+
+pytestmark = pytest.mark.gpu
+
+_T = dataclasses.replace(WORKLOADS["tiny-nc"], num_partitions=16, seed=71)
+# One round of equal pieces; causal with unequal rows, GQA and both layouts
+# (rows without a visible key among them); KV heads a multiple of the XCD
+# count; whole rounds with only the last rows cut; a piece count that leaves
+# uneven XCD lanes.
+FWD = [
+    dataclasses.replace(_T, name="one-round", q_idx=[2],
+                        kv_idx=list(range(9)), num_q_heads=3, num_kv_heads=1,
+                        head_dim=128),
+    dataclasses.replace(_T, name="causal-gqa", partition_len=512,
+                        q_idx=[5, 0, 4], kv_idx=[0, 3, 5, 1, 4], causal=True,
+                        num_q_heads=6, num_kv_heads=3),
+    dataclasses.replace(_T, name="striped-gqa8", partition_len=512,
+                        q_idx=[3, 0], kv_idx=[1, 3, 0, 2, 6], causal=True,
+                        layout=1, num_q_heads=16, num_kv_heads=8,
+                        head_dim=128, outliers=True),
+    dataclasses.replace(_T, name="tail-rows", q_idx=list(range(9)),
+                        kv_idx=list(range(4, 12)), num_q_heads=32,
+                        num_kv_heads=4),
+    dataclasses.replace(_T, name="uneven-lanes", q_idx=[1, 7, 3],
+                        kv_idx=[0, 2, 9], num_q_heads=7, num_kv_heads=7,
+                        head_dim=128),
+]
+
+
+@pytest.mark.parametrize("cfg", FWD, ids=[c.name for c in FWD])
+@pytest.mark.parametrize("out", [torch.bfloat16, torch.float32])
+def test_split_forward(gpu, cfg, out):
+    q, k, v, _ = make_qkv(cfg)
+    qd, kd, vd = (t.to(gpu) for t in (q, k, v))
+    prob = cfg.problem()
+    need = ma.mesh_attn_fwd_workspace_size(prob, cfg.nq, cfg.nkv)
+
+    def call(nbytes):
+        o = torch.full(qd.shape, float("nan"), dtype=out, device=gpu)
+        lse = torch.full((cfg.num_q_heads, qd.shape[0]), float("nan"),
+                         device=gpu)
+        if nbytes is None:
+            ma.mesh_attn_tile_fwd_noalloc(prob, cfg.q_idx, cfg.kv_idx, qd, kd,
+                                          vd, o, lse)
+        else:
+            ws = torch.empty(nbytes, dtype=torch.uint8, device=gpu)
+            ma.mesh_attn_tile_fwd(prob, cfg.q_idx, cfg.kv_idx, qd, kd, vd, o,
+                                  lse, ws=ws)
+        torch.cuda.synchronize()
+        return o, lse
+
+    log(f"{cfg.name}: split, whole, allocation-free")
+    o, lse = call(need)
+    o1, lse1 = call(need - 256)
+    o2, lse2 = call(None)
+    assert torch.equal(o, o2) and torch.equal(lse, lse2)
+    # The split took place: float32 sums in another order.
+    assert not torch.equal(lse, lse1)
+    ro, rl = oracle.tile_forward(prob, cfg.q_idx, cfg.kv_idx, to_np(q),
+                                 to_np(k), to_np(v))
+    check_fwd(f"{cfg.name} split", to_np(o), to_np(lse), ro, rl)
+    check_fwd(f"{cfg.name} whole", to_np(o1), to_np(lse1), ro, rl)
+
+
+def test_split_chunk_accumulation(gpu):
+    """Chunk tasks of a causal tile, each split: the running (O, LSE) is
+    folded with the partial results."""
+    cfg = dataclasses.replace(_T, partition_len=1536, num_partitions=6,
+                              q_idx=[4, 1], kv_idx=[1, 0, 4], causal=True,
+                              num_q_heads=2, num_kv_heads=1, head_dim=128)
+    kq, kkv = 2, 2
+    q, k, v, _ = make_qkv(cfg)
+    prob = cfg.problem()
+    P = cfg.partition_len
+
+    def chunk(x, n, parts, i):
+        c = P // n
+        return (x.view(parts, n, c, *x.shape[1:])[:, i]
+                .reshape(parts * c, *x.shape[1:]).contiguous())
+
+    ro, rl = oracle.tile_forward(prob, cfg.q_idx, cfg.kv_idx, to_np(q),
+                                 to_np(k), to_np(v))
+    ws = torch.empty(ma.mesh_attn_chunk_fwd_workspace_size(prob, cfg.nq,
+                                                           cfg.nkv),
+                     dtype=torch.uint8, device=gpu)
+    for i in range(kq):
+        qd = chunk(q, kq, cfg.nq, i).to(gpu)
+        o = torch.full(qd.shape, float("nan"), device=gpu)
+        lse = torch.full((cfg.num_q_heads, qd.shape[0]), float("nan"),
+                         device=gpu)
+        for j in range(kkv):
+            ma.mesh_attn_chunk_fwd(
+                prob, cfg.q_idx, cfg.kv_idx, (i, kq, j, kkv), qd,
+                chunk(k, kkv, cfg.nkv, j).to(gpu),
+                chunk(v, kkv, cfg.nkv, j).to(gpu), o, lse,
+                accumulate=int(j > 0), ws=ws)
+        torch.cuda.synchronize()
+        rows = [a * P + i * (P // kq) + r for a in range(cfg.nq)
+                for r in range(P // kq)]
+        check_fwd(f"chunk row {i}", to_np(o), to_np(lse), ro[rows],
+                  rl[:, rows])
