@@ -428,14 +428,15 @@ struct SideData {
 };
 
 // Workgroup order of one side from its runs and the blocks per item, with the
-// long items split over `slots` concurrent workgroups where that pays
-// (split.h; slots 0: never).
-void order_items(const std::vector<int32_t>& work, int32_t heads,
-                 int32_t group_to_kv, int32_t num_kv_heads, int32_t slots,
+// long items split over the concurrent workgroups of the pass where that pays
+// (split.h; pass null: never).  An item walks its runs `walks` times.
+void order_items(std::vector<int32_t> work, int32_t heads, int32_t group_to_kv,
+                 int32_t num_kv_heads, const split::Pass* pass, int32_t walks,
                  SideData* s) {
   const int32_t rows = static_cast<int32_t>(work.size());
-  const split::Cut cut = slots > 0
-                             ? split::choose(work.data(), rows, heads, slots)
+  for (int32_t& w : work) w *= walks;
+  const split::Cut cut = pass
+                             ? split::choose(work.data(), rows, heads, *pass)
                              : split::Cut{0, 0};
   if (cut.c == 0) {
     s->order = workgroup_order(work, heads, group_to_kv, num_kv_heads);
@@ -443,20 +444,27 @@ void order_items(const std::vector<int32_t>& work, int32_t heads,
   }
   // The pieces of one head; all heads are cut alike.
   struct Piece {
-    int32_t row, idx, len, run, off, part;
+    int32_t row, idx, len, run, off, walk, part;
   };
+  const int32_t slots = pass->slots;
   std::vector<Piece> pieces;
   std::vector<std::pair<int32_t, int32_t>> split_rows;  // row, first part
   int32_t parts = 0;
   for (int32_t r = 0; r < rows; ++r) {
     const int32_t n = split::num_pieces(cut, r, work[r]);
     if (n > 1) split_rows.push_back({r, parts});
-    int32_t run = s->ptr[r], off = 0;
+    int32_t run = s->ptr[r], off = 0, walk = 0;
     for (int32_t j = 0; j < n; ++j) {
       const int32_t len = split::piece_begin(work[r], n, j + 1) -
                           split::piece_begin(work[r], n, j);
-      while (len > 0 && off >= s->runs[run].nblk) off -= s->runs[run++].nblk;
-      pieces.push_back({r, j, len, run, off, n > 1 ? parts++ : -1});
+      while (len > 0 && off >= s->runs[run].nblk) {
+        off -= s->runs[run++].nblk;
+        if (run == s->ptr[r + 1]) {
+          run = s->ptr[r];
+          ++walk;
+        }
+      }
+      pieces.push_back({r, j, len, run, off, walk, n > 1 ? parts++ : -1});
       off += len;
     }
   }
@@ -470,7 +478,7 @@ void order_items(const std::vector<int32_t>& work, int32_t heads,
     return key(pieces[i]) < key(pieces[j]);
   });
   s->order.assign(total, make_int2(-1, -1));
-  s->pieces.assign(total, DevPiece{0, 0, 0, -1});
+  s->pieces.assign(total, DevPiece{0, 0, 0, -1, 0});
   for (int32_t a = 0, b; a < m; a = b) {
     for (b = a + 1; b < m && key(pieces[rank[b]]) == key(pieces[rank[a]]);) ++b;
     for (int32_t i = a; i < b; ++i) {
@@ -481,7 +489,8 @@ void order_items(const std::vector<int32_t>& work, int32_t heads,
                        num_kv_heads % kNumXcd == 0, h, a, b - a, i - a, slots);
         s->order[slot] = make_int2(pc.row, h);
         s->pieces[slot] = DevPiece{pc.run, pc.off, pc.len,
-                                   pc.part < 0 ? -1 : h * parts + pc.part};
+                                   pc.part < 0 ? -1 : h * parts + pc.part,
+                                   pc.walk};
       }
     }
   }
@@ -540,11 +549,11 @@ size_t side_bound(int64_t n_blocks, int64_t n_list, int64_t heads) {
 
 // What splitting adds to one side: slots for the extra pieces, the piece of
 // every slot, the split items, and `parts` partial results of part_bytes.
-size_t split_bound(int64_t items, int32_t slots, int64_t parts,
+size_t split_bound(int64_t items, const split::Pass& ps, int64_t parts,
                    size_t part_bytes) {
   if (parts == 0) return 0;
   const int64_t most =
-      std::min<int64_t>(items, int64_t{split::kMaxRounds} * slots);
+      std::min<int64_t>(items, int64_t{split::kMaxRounds} * ps.slots);
   return align_up(parts * sizeof(int2)) +
          align_up((most + parts) * sizeof(DevPiece)) +
          align_up(parts / 2 * sizeof(DevSplit)) + align_up(parts * part_bytes);
@@ -574,14 +583,16 @@ ma_status_t upload_plan(int pass, const ma_problem_t* p, const int32_t* q_idx,
       device_runs(p, q_idx, nq, kFwdBM, sq, kv_idx, nkv, kFwdBN, skv, true,
                   &sa.ptr, &sa.runs, &work);
       order_items(work, p->num_q_heads, g, p->num_kv_heads,
-                  may_split ? kFwdSlots : 0, &sa);
+                  may_split ? &kFwdPass : nullptr, 1, &sa);
     } else {
       device_runs(p, q_idx, nq, kBwdBM, sq, kv_idx, nkv, kBwdBN, skv, true,
                   &sa.ptr, &sa.runs, &work);
-      order_items(work, p->num_q_heads, g, p->num_kv_heads, 0, &sa);
+      order_items(work, p->num_q_heads, g, p->num_kv_heads,
+                  may_split ? &kDqPass : nullptr, 1, &sa);
       device_runs(p, kv_idx, nkv, kBwdBN, skv, q_idx, nq, kBwdBM, sq, false,
                   &sb.ptr, &sb.runs, &work);
-      order_items(work, p->num_kv_heads, 1, p->num_kv_heads, 0, &sb);
+      order_items(work, p->num_kv_heads, 1, p->num_kv_heads,
+                  may_split ? &kDkdvPass : nullptr, g, &sb);
     }
     if (g_plans.size() >= kMaxPlans) {
       auto lru = g_plans.begin();
@@ -646,10 +657,10 @@ size_t fwd_split_bytes(const ma_problem_t* p, int32_t nq, int32_t nkv,
   const int64_t items = nq * (P / ch.num_q_chunks / kFwdBM) * p->num_q_heads;
   const int64_t blocks = nkv * (P / ch.num_kv_chunks / kFwdBN);
   const int64_t counted =
-      any_chunk ? std::min<int64_t>(items, split::kMaxRounds * kFwdSlots)
+      any_chunk ? std::min<int64_t>(items, split::kMaxRounds * kFwdPass.slots)
                 : items;
-  const int64_t parts = split::parts_bound(counted, blocks, kFwdSlots);
-  return split_bound(items, kFwdSlots, parts, fwd_part_bytes(p));
+  const int64_t parts = split::parts_bound(counted, blocks, kFwdPass);
+  return split_bound(items, kFwdPass, parts, fwd_part_bytes(p));
 }
 
 size_t bwd_ws_bound(const ma_problem_t* p, int32_t nq, int32_t nkv) {
@@ -659,6 +670,38 @@ size_t bwd_ws_bound(const ma_problem_t* p, int32_t nq, int32_t nkv) {
   return side_bound(nqb, nkv, p->num_q_heads) +
          side_bound(nkb, nq, p->num_kv_heads) +
          2 * align_up(static_cast<size_t>(rows_q) * p->num_q_heads * 4);
+}
+
+// Partial slots of the split backward passes, and what splitting adds to
+// bwd_ws_bound (any_chunk as in fwd_split_bytes).
+struct BwdParts {
+  int64_t kv, q;
+  size_t kv_bytes, q_bytes;  // of the partial results
+  size_t bytes;
+};
+
+BwdParts bwd_parts(const ma_problem_t* p, int32_t nq, int32_t nkv,
+                   const ma_chunk_t& ch, bool any_chunk) {
+  const int64_t P = p->partition_len;
+  const int64_t nqb = nq * (P / ch.num_q_chunks / kBwdBM);
+  const int64_t nkb = nkv * (P / ch.num_kv_chunks / kBwdBN);
+  const int64_t kv_items = nkb * p->num_kv_heads;
+  const int64_t q_items = nqb * p->num_q_heads;
+  auto parts = [&](int64_t items, int64_t blocks, const split::Pass& ps) {
+    const int64_t most = int64_t{split::kMaxRounds} * ps.slots;
+    return split::parts_bound(any_chunk ? std::min(items, most) : items,
+                              blocks, ps);
+  };
+  const int32_t g = p->num_q_heads / p->num_kv_heads;
+  BwdParts b{parts(kv_items, nqb * g, kDkdvPass),
+             parts(q_items, nkb, kDqPass), 0, 0, 0};
+  const size_t tile = size_t{128} * p->head_dim * 4;
+  static_assert(kBwdBM == 128 && kBwdBN == 128, "rows of a partial result");
+  b.kv_bytes = align_up(b.kv * 2 * tile);
+  b.q_bytes = align_up(b.q * tile);
+  b.bytes = split_bound(kv_items, kDkdvPass, b.kv, 2 * tile) +
+            split_bound(q_items, kDqPass, b.q, tile);
+  return b;
 }
 
 ma_status_t check_head_dim(const ma_problem_t* p) {
@@ -696,7 +739,7 @@ int64_t parts_of(const ma_problem_t* p, int32_t nq, int32_t nkv,
   const int64_t P = p->partition_len;
   return split::parts_bound(
       nq * (P / ch.num_q_chunks / kFwdBM) * p->num_q_heads,
-      nkv * (P / ch.num_kv_chunks / kFwdBN), kFwdSlots);
+      nkv * (P / ch.num_kv_chunks / kFwdBN), kFwdPass);
 }
 
 // The tile kernel over n_items slots and, if items were split, the fold of
@@ -748,7 +791,7 @@ NoAllocSplit noalloc_split(const ma_problem_t* p, const int32_t* q_idx,
       static_cast<int32_t>(int64_t{nq} * p->partition_len / kFwdBM);
   for (int32_t qb = 0; qb < nqb; ++qb)
     work[qb] = visible_blocks(p, q_idx, kv_idx, nkv, qb);
-  NoAllocSplit s{split::choose(work, nqb, p->num_q_heads, kFwdSlots), 0, 0};
+  NoAllocSplit s{split::choose(work, nqb, p->num_q_heads, kFwdPass), 0, 0};
   if (s.cut.c == 0) return s;
   for (int32_t qb = 0; qb < nqb; ++qb) {
     const int32_t n = split::num_pieces(s.cut, qb, work[qb]);
@@ -846,9 +889,10 @@ ma_status_t bwd_impl(const ma_problem_t* prob, const int32_t* q_idx,
   if (ws_bytes < need)
     return fail(MA_ERR_WORKSPACE_TOO_SMALL, "workspace %zu bytes < %zu",
                 ws_bytes, need);
+  const BwdParts parts = bwd_parts(prob, nq, nkv, ch, false);
   PlanView plan;
-  st = upload_plan(1, prob, q_idx, nq, kv_idx, nkv, ch, false, ws, stream,
-                   &plan);
+  st = upload_plan(1, prob, q_idx, nq, kv_idx, nkv, ch,
+                   ws_bytes >= need + parts.bytes, ws, stream, &plan);
   if (st != MA_OK) return st;
   char* wsb = static_cast<char*>(ws);
   BwdParams bp{};
@@ -862,10 +906,23 @@ ma_status_t bwd_impl(const ma_problem_t* prob, const int32_t* q_idx,
   bp.dk = dk;
   bp.dv = dv;
   bp.delta = reinterpret_cast<float*>(wsb + align_up(plan.bytes));
-  bp.lse2 = reinterpret_cast<float*>(
-      wsb + align_up(plan.bytes) +
-      align_up(static_cast<size_t>(nq) * prob->partition_len *
-               prob->num_q_heads * 4));
+  const size_t row_bytes = align_up(static_cast<size_t>(nq) *
+                                    prob->partition_len * prob->num_q_heads * 4);
+  bp.lse2 =
+      reinterpret_cast<float*>(wsb + align_up(plan.bytes) + row_bytes);
+  char* part_base = wsb + align_up(plan.bytes) + 2 * row_bytes;
+  bp.n_kvsplits = plan.b.n_splits;
+  bp.n_qsplits = plan.a.n_splits;
+  if (plan.b.n_splits > 0) {
+    bp.kvpieces = reinterpret_cast<const DevPiece*>(wsb + plan.b.off_pieces);
+    bp.kvsplits = reinterpret_cast<const DevSplit*>(wsb + plan.b.off_splits);
+    bp.kvparts = reinterpret_cast<float*>(part_base);
+  }
+  if (plan.a.n_splits > 0) {
+    bp.qpieces = reinterpret_cast<const DevPiece*>(wsb + plan.a.off_pieces);
+    bp.qsplits = reinterpret_cast<const DevSplit*>(wsb + plan.a.off_splits);
+    bp.qparts = reinterpret_cast<float*>(part_base + parts.kv_bytes);
+  }
   bp.qblk_ptr = reinterpret_cast<const int32_t*>(wsb + plan.a.off_ptr);
   bp.qruns = reinterpret_cast<const DevRun*>(wsb + plan.a.off_runs);
   bp.qorder = reinterpret_cast<const int2*>(wsb + plan.a.off_order);
@@ -984,7 +1041,8 @@ size_t mesh_attn_fwd_workspace_size(const ma_problem_t* prob, int32_t nq,
 size_t mesh_attn_bwd_workspace_size(const ma_problem_t* prob, int32_t nq,
                                     int32_t nkv) {
   if (check_problem(prob) != MA_OK || nq < 1 || nkv < 1) return 0;
-  return bwd_ws_bound(prob, nq, nkv);
+  return bwd_ws_bound(prob, nq, nkv) +
+         bwd_parts(prob, nq, nkv, kWholeTile, false).bytes;
 }
 
 ma_status_t mesh_attn_tile_fwd(const ma_problem_t* prob, const int32_t* q_idx,
@@ -1070,7 +1128,7 @@ ma_status_t mesh_attn_tile_fwd_noalloc(const ma_problem_t* prob,
   // for it beside the work list.
   NoAllocSplit sp{{0, 0}, 0, 0};
   const int64_t max_parts = parts_of(prob, nq, nkv, kWholeTile);
-  if (max_parts > 0 && need + split_bound(items, kFwdSlots, max_parts, 0) <=
+  if (max_parts > 0 && need + split_bound(items, kFwdPass, max_parts, 0) <=
                            kNoAllocScratchBytes)
     sp = noalloc_split(prob, q_idx, nq, kv_idx, nkv);
   const bool split = sp.cut.c > 0;
@@ -1127,7 +1185,7 @@ ma_status_t mesh_attn_tile_fwd_noalloc(const ma_problem_t* prob,
   if (split) {
     fp.pieces = bp.pieces;
     fp.part_lse = static_cast<float*>(parts);
-    fp.part_o = fp.part_lse + split::max_parts(kFwdSlots) * kFwdBM;
+    fp.part_o = fp.part_lse + kFwdPass.max_parts() * kFwdBM;
   }
   return launch_fwd(fp, prob->head_dim, o_dtype == MA_FP32, fp.n_items,
                     bp.splits, sp.split_rows * prob->num_q_heads, stream);
@@ -1181,7 +1239,9 @@ ma_status_t mesh_attn_tile_bwd(const ma_problem_t* prob, const int32_t* q_idx,
 size_t mesh_attn_chunk_bwd_workspace_size(const ma_problem_t* prob,
                                           int32_t nq, int32_t nkv) {
   // A chunk's work lists and row buffers never exceed the whole tile's.
-  return mesh_attn_bwd_workspace_size(prob, nq, nkv);
+  if (check_problem(prob) != MA_OK || nq < 1 || nkv < 1) return 0;
+  return bwd_ws_bound(prob, nq, nkv) +
+         bwd_parts(prob, nq, nkv, kWholeTile, true).bytes;
 }
 
 ma_status_t mesh_attn_chunk_bwd(const ma_problem_t* prob, const int32_t* q_idx,

@@ -33,10 +33,12 @@ struct DevRun {
   int32_t blk0, nblk, cls, delta;
 };
 
-// One workgroup's share of a split item: blocks [off, ..) of run `run`, nblk
-// blocks in all; part >= 0: write a partial result into that slot.
-struct DevPiece {
-  int32_t run, off, nblk, part;
+// One workgroup's share of an item of a split tile: nblk blocks from block
+// `off` of run `run` on; part >= 0: write a partial result into that slot.
+// The dK/dV items walk their runs once per query head of the group; the share
+// starts in walk `walk`.
+struct alignas(32) DevPiece {
+  int32_t run, off, nblk, part, walk;
 };
 
 // A split item: its partial results are slots [part0, part0 + nparts).
@@ -66,9 +68,12 @@ struct FwdParams {
   float* part_lse;
 };
 
-// Forward workgroups that run at once: one per compute unit (its eight waves
-// of 256 registers fill the SIMDs).
-constexpr int kFwdSlots = 256;
+// The forward as the cut of long items sees it: one workgroup per compute unit
+// (its eight waves of 256 registers fill the SIMDs).  Items of 4 and 64 KV
+// blocks measured 14.3 and 100.8 us at d = 128 (1.44 us per block and six
+// blocks of overhead), 11.0 and 83.2 us at d = 64; folding 256 partials of
+// 256 x 128 takes 7-9 us, and writing them about as long.
+constexpr split::Pass kFwdPass{256, 6, 4, 2, 20};
 
 // Folds the partial results of the split items into O and LSE.
 struct CombineParams {
@@ -153,7 +158,23 @@ struct BwdParams {
   int32_t hq, hkv, group;
   float scale, scale_log2;
   int32_t accumulate;
+  // Split tiles (null otherwise): the piece of each slot of the two orders and
+  // the partial results, [part][dV, dK][kBwdBN][d] and [part][kBwdBM][d]; the
+  // split items of both sides, dK/dV first.
+  const DevPiece* kvpieces;
+  const DevPiece* qpieces;
+  float* kvparts;
+  float* qparts;
+  const DevSplit* kvsplits;
+  const DevSplit* qsplits;
+  int32_t n_kvsplits, n_qsplits;
 };
+
+// The backward passes as the cut of long items sees them; a block is 128 x 128.
+// dK/dV: one workgroup per compute unit, 3.8 us per block with the chip full;
+// dQ: two per compute unit, 5.5 us per block each.
+constexpr split::Pass kDkdvPass{256, 3, 2, 1, 40};
+constexpr split::Pass kDqPass{512, 2, 2, 1, 120};
 
 hipError_t launch_tile_bwd(const BwdParams& p, int head_dim, int grid_q,
                            int grid_kv, hipStream_t stream);
@@ -169,10 +190,10 @@ constexpr int kNoAllocMaxQBlocks = 4096;  // forward Q blocks of the tile
 
 // Partial results of a split tile: the most slots there are, d = 128.
 constexpr size_t kNoAllocPartBytes =
-    size_t{split::max_parts(kFwdSlots)} * kFwdBM * (128 + 1) * 4;
+    size_t{kFwdPass.max_parts()} * kFwdBM * (128 + 1) * 4;
 // Block rows of a tile that is split at all, and pieces of one head.
-constexpr int kSplitMaxRows = split::kMaxRounds * kFwdSlots;
-constexpr int kSplitMaxPieces = kSplitMaxRows + split::max_parts(kFwdSlots);
+constexpr int kSplitMaxRows = split::kMaxRounds * kFwdPass.slots;
+constexpr int kSplitMaxPieces = kSplitMaxRows + kFwdPass.max_parts();
 
 struct PlanBuildParams {
   int32_t P, n, layout, causal;   // problem (partition length, partitions)

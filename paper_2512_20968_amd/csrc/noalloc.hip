@@ -144,8 +144,8 @@ __device__ void split_order(const PlanBuildParams& p, const int* s_work) {
     // Rank by length (several rounds) or by piece index (one round).
     int gt = 0, eq = 0, eq_before = 0;
     for (int i2 = 0; i2 < m; ++i2) {
-      const bool less = total > kFwdSlots ? s_len[i2] > len : s_idx[i2] < idx;
-      const bool same = total > kFwdSlots ? s_len[i2] == len : s_idx[i2] == idx;
+      const bool less = total > kFwdPass.slots ? s_len[i2] > len : s_idx[i2] < idx;
+      const bool same = total > kFwdPass.slots ? s_len[i2] == len : s_idx[i2] == idx;
       gt += less;
       eq += same;
       eq_before += same & (i2 < i);
@@ -155,10 +155,10 @@ __device__ void split_order(const PlanBuildParams& p, const int* s_work) {
     while (off > 0 && off >= p.runs[run].nblk) off -= p.runs[run++].nblk;
     for (int h = 0; h < p.hq; ++h) {
       const int slot = split_slot(total, m, p.hq, p.group, by_kv, h, gt, eq,
-                                  eq_before, kFwdSlots);
+                                  eq_before, kFwdPass.slots);
       p.order[slot] = make_int2(qb, h);
       p.pieces[slot] = DevPiece{
-          run, off, len, s_cut[qb] < 0 ? -1 : h * parts + s_cut[qb] + idx};
+          run, off, len, s_cut[qb] < 0 ? -1 : h * parts + s_cut[qb] + idx, 0};
     }
   }
 }

@@ -17,14 +17,19 @@
 namespace mesh_attn {
 namespace split {
 
-// A workgroup's start and end (work list, first tiles, fragments, epilogue)
-// take about as long as six blocks: forward items of 4 and 64 blocks measured
-// 14.3 and 100.8 us at d = 128 (1.44 us per block), 11.0 and 83.2 us at
-// d = 64 (1.20).
-constexpr int32_t kOverhead = 6;
-// Shortest piece worth a workgroup and a partial result; items of at most two
-// such pieces stay whole.
-constexpr int32_t kMinPiece = 4;
+// A pass as the cut sees it; times in blocks of one of its workgroups.
+struct Pass {
+  int32_t slots;      // workgroups that run at once
+  int32_t overhead;   // a workgroup's start and end (work list, first tiles,
+                      // fragments, epilogue)
+  int32_t min_piece;  // shortest piece worth a workgroup and a partial result;
+                      // items of at most two such pieces stay whole
+  int32_t fold;       // launch of the kernel that folds the partials
+  int32_t fold_rate;  // partials written and read back per block
+  // Most partial results a pass holds.
+  __host__ __device__ constexpr int32_t max_parts() const { return 2 * slots; }
+};
+
 // Tiles of more rounds of whole items than this are never split: the longest
 // first order leaves at most a fraction of a round idle.
 constexpr int32_t kMaxRounds = 8;
@@ -46,29 +51,27 @@ __host__ __device__ inline int32_t piece_begin(int32_t w, int32_t n,
   return static_cast<int32_t>(int64_t{w} * j / n);
 }
 
-// Most partial results a pass of `slots` concurrent workgroups holds.
-constexpr int32_t max_parts(int32_t slots) { return 2 * slots; }
-
 // Partial results a tile may need, from its sizes alone: `items` items of at
 // most `max_work` blocks.  Never less than what choose() gives.
-inline int64_t parts_bound(int64_t items, int64_t max_work, int32_t slots) {
-  if (items > int64_t{kMaxRounds} * slots || max_work <= 2 * kMinPiece)
+inline int64_t parts_bound(int64_t items, int64_t max_work,
+                           const Pass& ps) {
+  if (items > int64_t{kMaxRounds} * ps.slots || max_work <= 2 * ps.min_piece)
     return 0;
-  const int64_t by_work = items * ((max_work + kMinPiece - 1) / kMinPiece);
-  return by_work < max_parts(slots) ? by_work : max_parts(slots);
+  const int64_t by_work =
+      items * ((max_work + ps.min_piece - 1) / ps.min_piece);
+  return by_work < ps.max_parts() ? by_work : ps.max_parts();
 }
 
 // Estimated time of a cut, in blocks of a workgroup: the pieces run longest
 // first on `slots` workgroups, so the launch takes its total divided by the
 // slots plus what the last round leaves idle (as long as the shortest
-// pieces), and never less than its longest piece; then the fold, about two
-// blocks plus one per 20 partials (a partial is written and read once).
+// pieces), and never less than its longest piece; then the fold.
 // parts < 0 if the cut needs more partials than there are.
 struct Estimate {
   int64_t time, parts;
 };
 inline Estimate estimate(const int32_t* w, int32_t n, int32_t heads,
-                         const Cut& s, int32_t slots) {
+                         const Cut& s, const Pass& ps) {
   int64_t pieces = 0, parts = 0, sum = 0;
   int32_t longest = 0, shortest = INT32_MAX;
   for (int32_t i = 0; i < n; ++i) {
@@ -82,32 +85,34 @@ inline Estimate estimate(const int32_t* w, int32_t n, int32_t heads,
   }
   pieces *= heads;
   parts *= heads;
-  sum = sum * heads + pieces * kOverhead;
-  if (parts > max_parts(slots)) return {0, -1};
-  const int64_t idle = (slots - pieces % slots) % slots;
-  int64_t t = (sum + idle * (shortest + kOverhead) + slots - 1) / slots;
-  if (t < longest + kOverhead) t = longest + kOverhead;
-  return {t + (parts > 0 ? 2 + parts / 20 : 0), parts};
+  sum = sum * heads + pieces * ps.overhead;
+  if (parts > ps.max_parts()) return {0, -1};
+  const int64_t idle = (ps.slots - pieces % ps.slots) % ps.slots;
+  int64_t t =
+      (sum + idle * (shortest + ps.overhead) + ps.slots - 1) / ps.slots;
+  if (t < longest + ps.overhead) t = longest + ps.overhead;
+  return {t + (parts > 0 ? ps.fold + parts / ps.fold_rate : 0), parts};
 }
 
 // The cut of a tile, {0, 0} to leave every item whole: the best estimate over
 // the pieces of the longest item, and for equal items also whole rounds with
 // only the rows of the last, partly filled round cut.  A cut has to be
 // estimated 5 % faster than whole items.
-inline Cut choose(const int32_t* w, int32_t n, int32_t heads, int32_t slots) {
+inline Cut choose(const int32_t* w, int32_t n, int32_t heads,
+                  const Pass& ps) {
   const int64_t items = int64_t{n} * heads;
   int32_t longest = 0, shortest = INT32_MAX;
   for (int32_t i = 0; i < n; ++i) {
     if (w[i] > longest) longest = w[i];
     if (w[i] < shortest) shortest = w[i];
   }
-  if (items > int64_t{kMaxRounds} * slots || longest <= 2 * kMinPiece)
+  if (items > int64_t{kMaxRounds} * ps.slots || longest <= 2 * ps.min_piece)
     return {0, 0};
-  const int64_t whole_time = estimate(w, n, heads, {0, 0}, slots).time;
+  const int64_t whole_time = estimate(w, n, heads, {0, 0}, ps).time;
   Cut best{0, 0};
   int64_t best_time = whole_time * 19 / 20;
   auto consider = [&](const Cut& s) {
-    const Estimate e = estimate(w, n, heads, s, slots);
+    const Estimate e = estimate(w, n, heads, s, ps);
     if (e.parts > 0 && e.time < best_time) {
       best_time = e.time;
       best = s;
@@ -117,20 +122,20 @@ inline Cut choose(const int32_t* w, int32_t n, int32_t heads, int32_t slots) {
   int32_t last = longest;
   for (int32_t k = 2;; ++k) {
     const int32_t c = (longest + k - 1) / k;
-    if (c < kMinPiece) break;
+    if (c < ps.min_piece) break;
     if (c == last) continue;
     last = c;
     if (!consider({c, 0})) break;
   }
-  if (longest == shortest && items > slots) {
-    const int32_t rounds = static_cast<int32_t>(items / slots);
-    const int32_t whole = rounds * slots / heads;  // rows
+  if (longest == shortest && items > ps.slots) {
+    const int32_t rounds = static_cast<int32_t>(items / ps.slots);
+    const int32_t whole = rounds * ps.slots / heads;  // rows
     if (whole > 0 && whole < n) {
       const int64_t rest = items - int64_t{whole} * heads;
       const int64_t k =
-          (int64_t{rounds + 1} * slots - int64_t{whole} * heads) / rest;
+          (int64_t{rounds + 1} * ps.slots - int64_t{whole} * heads) / rest;
       const int32_t c = static_cast<int32_t>((longest + k - 1) / k);
-      if (k > 1 && c >= kMinPiece) consider({c, whole});
+      if (k > 1 && c >= ps.min_piece) consider({c, whole});
     }
   }
   return best;

@@ -211,7 +211,8 @@ constexpr int NT_KV = 512;  // dK/dV: eight waves
 template <int D, int ROLE>
 __device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem,
                                           int kvblk, int hk, int run_b,
-                                          int run_e, int wave, int lane) {
+                                          int run_e, const DevPiece& pc,
+                                          int wave, int lane) {
   using L = DkdvLayout<D>;
   const int li = lane & 31;
   const int lh = lane >> 5;
@@ -227,18 +228,17 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem,
 #pragma unroll
   for (int cc = 0; cc < D / 32; ++cc) zero(acc[cc]);
 
-  if (run_b < run_e) {
+  if (pc.nblk > 0) {
     TileAddr<D> ta;
     ta.init(lane, wave, 0);
     bf16x8* pbuf = reinterpret_cast<bf16x8*>(smem + L::NSTAGE * L::STAGE);
-    // Stage cursor over (query head of the group, run, block in run, half).
+    // Stage cursor over (query head of the group, run, block in run, half);
+    // the callers count the stages.
     struct Cur {
       int g, r, off, s;
       DevRun run;
-      bool valid;
     };
     auto advance = [&](Cur c) {
-      if (!c.valid) return c;
       if (++c.s == 2) {
         c.s = 0;
         if (++c.off == c.run.nblk) {
@@ -250,7 +250,6 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem,
           c.run = load_const(p.kvruns, c.r);
         }
       }
-      c.valid = c.g < p.group;
       return c;
     };
     auto issue = [&](const Cur& c, int buf) {
@@ -273,16 +272,14 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem,
       }
     };
 
-    // Stages: every query head of the group x every block of the runs x 2.
-    int nstage = 0;
-    for (int r = run_b; r < run_e; ++r) nstage += load_const(p.kvruns, r).nblk;
-    nstage *= 2 * p.group;
+    const int nstage = 2 * pc.nblk;
     // Iterations t = 0 .. nstage: loads of stage t+1; the dV role computes
     // stage t (t < nstage), the dK role stage t-1 (t >= 1).  Every iteration
     // but the last ends with a barrier, the same count in both roles.  Stage
     // j lives in buffer j % 3 (its previous occupant, stage j-3, was last
     // read by the dK role in iteration j-2) and its P in P buffer j % 2.
-    Cur lc{0, run_b, 0, 0, load_const(p.kvruns, run_b), true};  // next load
+    Cur lc{pc.walk, pc.run, pc.off, 0,
+           load_const(p.kvruns, pc.run)};  // next load
     Cur cc_ = lc;  // stage this wave computes next
     issue(lc, 0);
     lc = advance(lc);
@@ -408,6 +405,16 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem,
   // loads are issued back to back instead of one read-modify-write at a time.
   float* out = ROLE == 0 ? p.dv : p.dk;
   const float sc_out = ROLE == 0 ? 1.f : p.scale;
+  if (pc.part >= 0) {
+    float* po = p.kvparts + (int64_t{pc.part} * 2 + ROLE) * BK * D;
+#pragma unroll
+    for (int c = 0; c < D / 32; ++c)
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        po[(kw * 32 + 8 * (i >> 2) + 4 * lh + (i & 3)) * D + c * 32 + li] =
+            acc[c][i] * sc_out;
+    return;
+  }
   auto index = [&](int c, int i) {
     const int64_t row =
         int64_t{kvblk} * BK + kw * 32 + 8 * (i >> 2) + 4 * lh + (i & 3);
@@ -443,10 +450,20 @@ __global__ __launch_bounds__(NT_KV, 1) void bwd_dkdv_kernel(BwdParams p) {
   const int hk = item.y;
   const int run_b = load_const(p.kvblk_ptr, kvblk);
   const int run_e = load_const(p.kvblk_ptr, kvblk + 1);
+  // The whole item (its runs once per query head of the group), or on a split
+  // tile this workgroup's piece of it.
+  DevPiece pc{run_b, 0, 0, -1, 0};
+  if (p.kvpieces) {
+    pc = load_const(p.kvpieces, slot);
+  } else {
+    for (int r = run_b; r < run_e; ++r)
+      pc.nblk += load_const(p.kvruns, r).nblk;
+    pc.nblk *= p.group;
+  }
   if (wave < 4)
-    dkdv_role<D, 0>(p, smem, kvblk, hk, run_b, run_e, wave, lane);
+    dkdv_role<D, 0>(p, smem, kvblk, hk, run_b, run_e, pc, wave, lane);
   else
-    dkdv_role<D, 1>(p, smem, kvblk, hk, run_b, run_e, wave, lane);
+    dkdv_role<D, 1>(p, smem, kvblk, hk, run_b, run_e, pc, wave, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -476,8 +493,14 @@ __global__ __launch_bounds__(NT, 1) void bwd_dq_kernel(BwdParams p) {
   const int qblk = item.x;
   const int h = item.y;
   const int hk = h / p.group;
-  const int run_b = load_const(p.qblk_ptr, qblk);
-  const int run_e = load_const(p.qblk_ptr, qblk + 1);
+  // The whole item, or on a split tile this workgroup's piece of it.
+  DevPiece pc{load_const(p.qblk_ptr, qblk), 0, 0, -1, 0};
+  if (p.qpieces) {
+    pc = load_const(p.qpieces, slot);
+  } else {
+    const int run_e = load_const(p.qblk_ptr, qblk + 1);
+    for (int r = pc.run; r < run_e; ++r) pc.nblk += load_const(p.qruns, r).nblk;
+  }
   const int q_in_blk = wave * 32 + li;
   const int64_t q_row = int64_t{qblk} * BQ + q_in_blk;
 
@@ -491,23 +514,21 @@ __global__ __launch_bounds__(NT, 1) void bwd_dq_kernel(BwdParams p) {
 #pragma unroll
   for (int cc = 0; cc < D / 32; ++cc) zero(acc[cc]);
 
-  if (run_b < run_e) {
+  if (pc.nblk > 0) {
     TileAddr<D> ta;
     ta.init(lane, wave, 0);
     struct Cur {
-      int r, off, s;
+      int r, off, s, left;  // left: stages from this one on
       DevRun run;
     };
     auto advance = [&](Cur c, bool* valid) {
-      *valid = true;
+      *valid = --c.left > 0;
       if (++c.s == 2) {
         c.s = 0;
         if (++c.off == c.run.nblk) {
           c.off = 0;
-          if (++c.r == run_e)
-            *valid = false;
-          else
-            c.run = load_const(p.qruns, c.r);
+          ++c.r;
+          if (*valid) c.run = load_const(p.qruns, c.r);
         }
       }
       return c;
@@ -519,7 +540,7 @@ __global__ __launch_bounds__(NT, 1) void bwd_dq_kernel(BwdParams p) {
       load_stage_tile<D>(p.v, row0, p.hkv, hk, base + L::TILE, wave, lane);
     };
 
-    Cur cur{run_b, 0, 0, load_const(p.qruns, run_b)};
+    Cur cur{pc.run, pc.off, 0, 2 * pc.nblk, load_const(p.qruns, pc.run)};
     issue(cur, 0);
 #pragma unroll
     for (int kk = 0; kk < D / 16; ++kk) {
@@ -606,6 +627,19 @@ __global__ __launch_bounds__(NT, 1) void bwd_dq_kernel(BwdParams p) {
 
   // Register 4g+t of chunk cc holds dim 32cc + 8g + 4lh + t of query q_row.
   // With accumulate, all old values are read before the first store.
+  if (pc.part >= 0) {
+    float* po = p.qparts + (int64_t{pc.part} * BQ + q_in_blk) * D;
+#pragma unroll
+    for (int cc = 0; cc < D / 32; ++cc)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        f32x4 val;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) val[t] = acc[cc][4 * g + t] * p.scale;
+        *reinterpret_cast<f32x4*>(po + cc * 32 + g * 8 + lh * 4) = val;
+      }
+    return;
+  }
   float* dst = p.dq + (q_row * p.hq + h) * D;
   f32x4 prev[D / 32][4];
 #pragma unroll
@@ -630,6 +664,54 @@ __global__ __launch_bounds__(NT, 1) void bwd_dq_kernel(BwdParams p) {
         val[t] = fmaf(acc[cc][4 * g + t], p.scale, prev[cc][g][t]);
       *reinterpret_cast<f32x4*>(dst + cc * 32 + g * 8 + lh * 4) = val;
     }
+}
+
+// ---------------------------------------------------------------------------
+// Sum of the partial gradients of split items, in piece order (a fixed order,
+// so the result stays deterministic).  A workgroup sums RPB rows of one
+// tensor of one item, four dims a lane: 16-byte contiguous loads and stores.
+// ---------------------------------------------------------------------------
+template <int D>
+struct SumLayout {
+  static constexpr int LPR = D / 4;       // lanes per row
+  static constexpr int RPB = NT / LPR;    // rows per workgroup
+  static constexpr int GPT = 128 / RPB;   // workgroups per 128-row tensor
+};
+
+template <int D>
+__global__ __launch_bounds__(NT) void bwd_sum_kernel(BwdParams p) {
+  using L = SumLayout<D>;
+  const int kv_wgs = p.n_kvsplits * 2 * L::GPT;
+  const bool kv = static_cast<int>(blockIdx.x) < kv_wgs;
+  const int wg = kv ? blockIdx.x : blockIdx.x - kv_wgs;
+  const int si = wg / (kv ? 2 * L::GPT : L::GPT);
+  const int role = kv ? wg / L::GPT % 2 : 0;  // 0: dV (or dQ), 1: dK
+  const DevSplit it = load_const(kv ? p.kvsplits : p.qsplits, si);
+  const int row = wg % L::GPT * L::RPB + threadIdx.x / L::LPR;
+  const int col = threadIdx.x % L::LPR * 4;
+  const int64_t stride = (kv ? 2 : 1) * 128 * D;  // floats per partial slot
+  const float* src = (kv ? p.kvparts : p.qparts) + it.part0 * stride +
+                     (role * 128 + row) * D + col;
+  const int heads = kv ? p.hkv : p.hq;
+  float* out = (kv ? (role ? p.dk : p.dv) : p.dq) +
+               ((int64_t{it.blk} * 128 + row) * heads + it.head) * D + col;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  if (p.accumulate) acc = *reinterpret_cast<const f32x4*>(out);
+  constexpr int B = 4;  // partials in flight
+  for (int k0 = 0; k0 < it.nparts; k0 += B) {
+    f32x4 x[B];
+#pragma unroll
+    for (int u = 0; u < B; ++u)
+      x[u] = *reinterpret_cast<const f32x4*>(
+          src + min(k0 + u, it.nparts - 1) * stride);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < B; ++u)
+      if (k0 + u < it.nparts)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[t] += x[u][t];
+  }
+  *reinterpret_cast<f32x4*>(out) = acc;
 }
 
 template <int D>
@@ -658,6 +740,13 @@ hipError_t launch(const BwdParams& p, int grid_q, int grid_kv,
   if (grid_q > 0) {
     hipLaunchKernelGGL(bwd_dq_kernel<D>, dim3(grid_q), dim3(NT), smem_q,
                        stream, p);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  const int sums =
+      (2 * p.n_kvsplits + p.n_qsplits) * SumLayout<D>::GPT;
+  if (sums > 0) {
+    hipLaunchKernelGGL(bwd_sum_kernel<D>, dim3(sums), dim3(NT), 0, stream, p);
     e = hipGetLastError();
   }
   return e;

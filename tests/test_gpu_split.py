@@ -11,9 +11,9 @@ import torch
 
 import oracle
 import paper_2512_20968_amd as ma
-from mesh_inputs import WORKLOADS, make_qkv
+from mesh_inputs import WORKLOADS, make_grad, make_qkv
 
-from helpers import check_fwd, log, to_np
+from helpers import check_fwd, check_grad, log, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -114,3 +114,59 @@ def test_split_chunk_accumulation(gpu):
                 for r in range(P // kq)]
         check_fwd(f"chunk row {i}", to_np(o), to_np(lse), ro[rows],
                   rl[:, rows])
+
+
+# Backward: both passes split in one round; GQA whose pieces cross the walks
+# over the group's heads; causal with rows and keys that see nothing; only the
+# dK/dV side split (many query heads on one KV head); KV heads a multiple of
+# the XCD count.
+BWD = [
+    dataclasses.replace(_T, name="both-sides", q_idx=[0, 2, 4],
+                        kv_idx=[1, 3, 0], num_q_heads=2, num_kv_heads=2,
+                        head_dim=128),
+    dataclasses.replace(_T, name="gqa-walks", partition_len=384,
+                        num_partitions=6, q_idx=[4, 1], kv_idx=[2, 0, 4],
+                        causal=True, num_q_heads=6, num_kv_heads=2),
+    dataclasses.replace(_T, name="one-kv-head", partition_len=512,
+                        num_partitions=4, q_idx=[3, 0], kv_idx=[1],
+                        causal=True, layout=1, num_q_heads=11,
+                        num_kv_heads=1, head_dim=128),
+    dataclasses.replace(_T, name="gqa8", q_idx=[3, 1, 5], kv_idx=[2, 3, 0, 1],
+                        causal=True, num_q_heads=16, num_kv_heads=8,
+                        outliers=True),
+]
+
+
+@pytest.mark.parametrize("accumulate", [0, 1])
+@pytest.mark.parametrize("cfg", BWD, ids=[c.name for c in BWD])
+def test_split_backward(gpu, cfg, accumulate):
+    cfg = dataclasses.replace(cfg, grad_seed=72)
+    q, k, v, _ = make_qkv(cfg)
+    do = make_grad(cfg)
+    prob = cfg.problem()
+    ro, rl = oracle.tile_forward(prob, cfg.q_idx, cfg.kv_idx, to_np(q),
+                                 to_np(k), to_np(v))
+    refs = oracle.tile_backward(prob, cfg.q_idx, cfg.kv_idx, to_np(q),
+                                to_np(k), to_np(v), to_np(do))[:3]
+    qd, kd, vd, dod = (t.to(gpu) for t in (q, k, v, do))
+    o = torch.from_numpy(ro).to(torch.bfloat16).to(gpu)
+    lse = torch.from_numpy(rl).float().to(gpu)
+    need = ma.mesh_attn_bwd_workspace_size(prob, cfg.nq, cfg.nkv)
+
+    def call(nbytes):
+        g = [torch.full(t.shape, 1.5 if accumulate else float("nan"),
+                        device=gpu) for t in (qd, kd, vd)]
+        ws = torch.empty(nbytes, dtype=torch.uint8, device=gpu)
+        ma.mesh_attn_tile_bwd(prob, cfg.q_idx, cfg.kv_idx, qd, kd, vd, o, dod,
+                              lse, *g, accumulate=accumulate, ws=ws)
+        torch.cuda.synchronize()
+        return [t - 1.5 if accumulate else t for t in g]
+
+    log(f"{cfg.name}: split, split again, whole")
+    split, again, whole = call(need), call(need), call(need - 256)
+    assert all(torch.equal(a, b) for a, b in zip(split, again))
+    # Split: float32 sums in another order.
+    assert not torch.equal(split[1], whole[1])
+    for name, s, w, r in zip(("dq", "dk", "dv"), split, whole, refs):
+        check_grad(f"{cfg.name} {name} split", to_np(s), r)
+        check_grad(f"{cfg.name} {name} whole", to_np(w), r)

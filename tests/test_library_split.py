@@ -14,12 +14,14 @@ _MAIN = r"""
 #include <cstdio>
 #include <cstdlib>
 #include <vector>
-#include "split.h"
+#include "internal.h"
 using namespace mesh_attn;
-// argv: slots heads group by_kv w...
+// argv: pass heads group by_kv w...
 int main(int argc, char** argv) {
-  const int slots = atoi(argv[1]), heads = atoi(argv[2]),
-            group = atoi(argv[3]), by_kv = atoi(argv[4]);
+  const split::Pass pass =
+      atoi(argv[1]) == 0 ? kFwdPass : atoi(argv[1]) == 1 ? kDkdvPass : kDqPass;
+  const int slots = pass.slots, heads = atoi(argv[2]), group = atoi(argv[3]),
+            by_kv = atoi(argv[4]);
   std::vector<int32_t> w;
   int32_t longest = 0;
   for (int i = 5; i < argc; ++i) {
@@ -27,10 +29,10 @@ int main(int argc, char** argv) {
     if (w.back() > longest) longest = w.back();
   }
   const int n = static_cast<int>(w.size());
-  const split::Cut c = split::choose(w.data(), n, heads, slots);
+  const split::Cut c = split::choose(w.data(), n, heads, pass);
   printf("cut %d %d\n", c.c, c.whole);
-  printf("bound %lld\n", static_cast<long long>(split::parts_bound(
-                             int64_t{n} * heads, longest, slots)));
+  printf("bound %d %lld\n", pass.max_parts(), static_cast<long long>(split::parts_bound(
+                             int64_t{n} * heads, longest, pass)));
   struct P { int row, idx, len, key; };
   std::vector<P> ps;
   for (int r = 0; r < n; ++r) {
@@ -75,28 +77,31 @@ def program(tmp_path_factory):
 
 
 CASES = [
-    # name, slots, heads, group, kv heads, work, split expected
-    ("one round, equal items", 256, 4, 4, 1, [1024] * 16, True),
-    ("one round, causal", 256, 8, 4, 2, list(range(36, 65, 4)), True),
-    ("one item", 256, 1, 1, 1, [64], True),
-    ("fewer pieces than lanes", 256, 1, 1, 1, [9], None),
-    ("rows without keys", 256, 4, 1, 4, [0, 0, 17, 40], True),
-    ("short items stay whole", 256, 4, 1, 4, [8, 8], False),
-    ("full rounds stay whole", 256, 32, 1, 32, [512] * 64, False),
-    ("past the last round that is split", 256, 32, 1, 32, [512] * 65, False),
-    ("nearly empty last round", 256, 32, 4, 8, [64] * 9, True),
-    ("nearly empty last round, odd heads", 256, 21, 3, 7, [200] * 25, True),
-    ("two workgroups per unit", 512, 12, 3, 4, list(range(4, 40, 3)), None),
-    ("longest work", 256, 1, 1, 1, [1 << 24] * 3, True),
+    # name, pass (0 forward, 1 dK/dV, 2 dQ), heads, group, kv heads, work,
+    # split expected
+    ("one round, equal items", 0, 4, 4, 1, [1024] * 16, True),
+    ("one round, causal", 0, 8, 4, 2, list(range(36, 65, 4)), True),
+    ("one item", 0, 1, 1, 1, [64], True),
+    ("fewer pieces than lanes", 0, 1, 1, 1, [9], None),
+    ("rows without keys", 0, 4, 1, 4, [0, 0, 17, 40], True),
+    ("short items stay whole", 0, 4, 1, 4, [8, 8], False),
+    ("full rounds stay whole", 0, 32, 1, 32, [512] * 64, False),
+    ("past the last round that is split", 0, 32, 1, 32, [512] * 65, False),
+    ("nearly empty last round", 0, 32, 4, 8, [64] * 9, True),
+    ("nearly empty last round, odd heads", 0, 21, 3, 7, [200] * 25, True),
+    ("two workgroups per unit", 2, 12, 3, 4, list(range(4, 40, 3)), None),
+    ("dK/dV, one round", 1, 4, 1, 4, [96] * 32, True),
+    ("dK/dV, two blocks", 1, 4, 1, 4, [4, 4], False),
+    ("longest work", 0, 1, 1, 1, [1 << 24] * 3, True),
 ]
 
 
-@pytest.mark.parametrize("name,slots,heads,group,hkv,work,want", CASES,
+@pytest.mark.parametrize("name,pass_,heads,group,hkv,work,want", CASES,
                          ids=[c[0] for c in CASES])
-def test_pieces_cover_items_and_slots(program, name, slots, heads, group, hkv,
+def test_pieces_cover_items_and_slots(program, name, pass_, heads, group, hkv,
                                       work, want):
     out = subprocess.run(
-        [program, *map(str, (slots, heads, group, int(hkv % 8 == 0), *work))],
+        [program, *map(str, (pass_, heads, group, int(hkv % 8 == 0), *work))],
         check=True, capture_output=True, text=True).stdout.split("\n")
     rows = [ln.split() for ln in out if ln]
     cut = tuple(int(x) for x in rows[0][1:])
@@ -116,9 +121,9 @@ def test_pieces_cover_items_and_slots(program, name, slots, heads, group, hkv,
         assert all(a[1] == b[0] for a, b in zip(ps, ps[1:]))
         if len(ps) > 1:
             parts += len(ps)
-            assert all(2 <= e - b <= cut[0] for b, e in ps)
+            assert all(1 <= e - b <= cut[0] for b, e in ps)
             assert row >= cut[1]
     # never more partial results than the workspace and the slots hold
-    assert parts * heads <= int(rows[1][1]) <= 2 * slots
+    assert parts * heads <= int(rows[1][2]) <= int(rows[1][1])
     # every piece of every head has a slot of its own, without gaps
     assert sorted(slots_seen) == list(range(len(slots_seen)))
