@@ -29,17 +29,17 @@
  *  - A call writes its device workspace on `stream` (the work list and the
  *    counters its workgroups take items from) and reads it back in its
  *    kernels, so a workspace serves one call at a time: calls that may
- *    overlap need workspaces of their own.  The work list is copied from a
+ *    overlap need workspaces of their own.  A long work list is copied from a
  *    cached pinned host buffer that the library may reuse for another tile
- *    after the copy has completed, so calls that take a workspace must not
- *    be recorded into a graph (stream capture) and replayed;
+ *    after the call's work has completed, so calls that take a workspace must
+ *    not be recorded into a graph (stream capture) and replayed;
  *    mesh_attn_tile_fwd_noalloc is the forward for that case.
  *  - The caller owns every buffer, host and device.  The library never
  *    allocates or frees device memory and never synchronizes a stream or the
  *    device; its only state is a bounded cache of pinned host copies of work
  *    lists (guarded by a mutex).  A cached copy is released only after the
- *    device has finished every upload from it (an event recorded after each
- *    upload, polled without waiting).
+ *    device has finished every call that read it (an event recorded behind
+ *    each call's work, polled without waiting).
  *  - Arguments are validated on the host before anything is enqueued.  On a
  *    non-OK status nothing was launched and mesh_attn_last_error() describes
  *    the problem.  Device work runs asynchronously on `stream`, which must
@@ -191,8 +191,9 @@ ma_status_t mesh_attn_tile_fwd(const ma_problem_t* prob, const int32_t* q_idx,
 /* mesh_attn_tile_fwd for callers that cannot allocate memory: code under
  * stream (graph) capture, tight serving loops, harnesses that forbid
  * allocation.  Same arguments and results as mesh_attn_tile_fwd without the
- * workspace: the work list is built on the device (from the index lists,
- * passed by value as kernel arguments) into a scratch array of
+ * workspace: a short work list is built on the host's stack and passed by
+ * value as a kernel argument; a longer one is built on the device (from the
+ * index lists, passed the same way) into a scratch array of
  * MA_NOALLOC_SCRATCH_BYTES that the library holds on every GPU it runs on
  * until the process ends, beside one of 68 MB for the partial results of split
  * items.  The call allocates nothing (no hipMalloc, no

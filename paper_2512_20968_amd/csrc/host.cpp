@@ -18,14 +18,15 @@
 #include <memory>
 #include <mutex>
 #include <string>
-#include <utility>
 #include <vector>
 
 #include "host_error.h"
 #include "internal.h"
-#include "split.h"
+#include "plan.h"
 
 using namespace mesh_attn;
+using mesh_attn::plan::Slice;
+using mesh_attn::plan::token_pos;
 
 static_assert(MA_NOALLOC_SCRATCH_BYTES == kNoAllocScratchBytes &&
                   MA_NOALLOC_MAX_LIST == kNoAllocMaxList &&
@@ -135,26 +136,6 @@ ma_status_t check_tile(const ma_problem_t* p, const int32_t* q_idx, int32_t nq,
   return check_list("kv_idx", kv_idx, nkv, p->num_partitions);
 }
 
-// Global position of token `row` of partition `part` (Section 3.7 layouts).
-// Within a partition positions grow with the row under both layouts, so a
-// block's first and last rows hold its extreme positions.
-inline int64_t token_pos(const ma_problem_t* p, int32_t part, int64_t row) {
-  return p->layout == MA_LAYOUT_STRIPED
-             ? row * p->num_partitions + part
-             : int64_t{part} * p->partition_len + row;
-}
-
-// Mask offset of a (query block, key run) pair in rows: key row k0 + j is
-// hidden from query row q0 + i iff j - i > offset.  Contiguous: the position
-// difference q0 - k0 across partitions.  Striped: position (row * n + part),
-// so key after query iff (j - i) * n > (q0 - k0) * n + (qp - kp), i.e. iff
-// j - i > (q0 - k0) + floor((qp - kp) / n), and |qp - kp| < n.
-inline int64_t mask_offset(const ma_problem_t* p, int32_t qp, int64_t q0,
-                           int32_t kp, int64_t k0) {
-  if (p->layout == MA_LAYOUT_STRIPED) return (q0 - k0) + (qp >= kp ? 0 : -1);
-  return token_pos(p, qp, q0) - token_pos(p, kp, k0);
-}
-
 // Class of one block pair from its extreme token positions.
 inline int block_class(int64_t q_first, int64_t q_last, int64_t k_first,
                        int64_t k_last, bool causal) {
@@ -166,12 +147,6 @@ inline int block_class(int64_t q_first, int64_t q_last, int64_t k_first,
 
 struct Run {
   int32_t row, list, begin, end, cls;
-};
-
-// The rows of each partition a buffer holds: `len` consecutive local rows
-// starting at local row `off` (the whole partition, or one GOO chunk of it).
-struct Slice {
-  int64_t len, off;
 };
 
 // Runs of one orientation.  "Rows" are the blocks of side A (bm_a rows each,
@@ -233,14 +208,16 @@ ma_status_t export_runs(const std::vector<int32_t>& ptr,
 }
 
 // ---------------------------------------------------------------------------
-// Device plans: the run list in the kernels' form plus the workgroup order,
-// packed into one pinned host buffer that is copied to the caller's
-// workspace on the caller's stream.
+// Device plans: the order table, runs and split rows of a call's passes
+// (plan.h).  A list of at most kInlinePlan bytes is built on the stack for
+// every call and travels in the kernel's arguments.  A longer one is packed
+// into one pinned host buffer that a kernel copies to the caller's workspace
+// on the caller's stream.
 //
-// Plans are cached per tile (at most kMaxPlans, least recently used evicted).
-// A pinned source must outlive every asynchronous copy from it, and freeing
-// pinned memory would wait for the device, so buffers are never freed while
-// the library is in use: every upload records an event on the caller's
+// The longer plans are cached per tile (at most kMaxPlans, least recently used
+// evicted).  A pinned source must outlive every asynchronous copy from it, and
+// freeing pinned memory would wait for the device, so buffers are never freed
+// while the library is in use: every upload records an event on the caller's
 // stream, an evicted plan's buffer joins a spare list, and a spare buffer is
 // reused for a new plan only once all events recorded after copies from it
 // have completed (hipEventQuery, which does not wait).  No call synchronizes.
@@ -249,12 +226,10 @@ ma_status_t export_runs(const std::vector<int32_t>& ptr,
 constexpr size_t kAlign = 256;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
-struct Side {
-  size_t off_ptr = 0, off_runs = 0, off_order = 0, off_queue = 0;
-  size_t off_pieces = 0, off_splits = 0;
-  int32_t grid = 0;
-  int32_t n_items = 0;   // non-idle slots of the order
-  int32_t n_splits = 0;  // split items; > 0: every slot has a piece
+// One pass's lists within a plan's bytes.
+struct PassView {
+  size_t off_rows = 0, off_runs = 0, off_splits = 0, off_queue = 0;
+  int32_t m = 0, n_items = 0, n_splits = 0, parts = 0, mode = 0;
 };
 
 // An event recorded after a copy, with the device it belongs to (an event
@@ -273,14 +248,16 @@ struct PinnedBuf {
 struct Plan {
   PinnedBuf* buf = nullptr;
   size_t bytes = 0;
-  Side a, b;             // fwd uses a; bwd uses a (Q-major) and b (KV-major)
+  PassView a, b;         // fwd uses a; bwd uses a (Q-major) and b (KV-major)
   uint64_t last_use = 0;
 };
 
-// What a kernel launch needs from a plan once it is uploaded.
+// What the launches need from a plan: the workspace bytes it takes and its
+// passes; src: the pinned copy, or null if the lists are in `blob`.
 struct PlanView {
   size_t bytes = 0;
-  Side a, b;
+  PassView a, b;
+  const void* src = nullptr;
 };
 
 std::mutex g_plan_mu;
@@ -350,249 +327,160 @@ std::string plan_key(int pass, const ma_problem_t* p, const int32_t* q_idx,
   return k;
 }
 
-// Kernel-side runs of one orientation.  Side A blocks (bm_a rows) own the
-// workgroups; side B blocks (bm_b rows) are iterated.  delta = mask offset of
-// the query block/run against the key block/run (mask_offset).
-void device_runs(const ma_problem_t* p, const int32_t* a_idx, int32_t na,
-                 int32_t bm_a, Slice sa, const int32_t* b_idx, int32_t nb,
-                 int32_t bm_b, Slice sb, bool a_is_q, std::vector<int32_t>* ptr,
-                 std::vector<DevRun>* out, std::vector<int32_t>* work) {
-  std::vector<Run> runs;
-  build_runs(p, a_idx, na, bm_a, sa, b_idx, nb, bm_b, sb, a_is_q, ptr, &runs);
-  const int32_t nab = static_cast<int32_t>(sa.len / bm_a);
-  const int32_t nbb = static_cast<int32_t>(sb.len / bm_b);
-  out->resize(runs.size());
-  work->assign(ptr->size() - 1, 0);
-  for (size_t i = 0; i < runs.size(); ++i) {
-    const Run& r = runs[i];
-    const int32_t a_part = a_idx[r.row / nab];
-    const int64_t a_row0 = sa.off + int64_t{r.row % nab} * bm_a;
-    const int32_t b_part = b_idx[r.list];
-    const int64_t b_row0 = sb.off + int64_t{r.begin} * bm_b;
-    const int64_t delta = a_is_q ? mask_offset(p, a_part, a_row0, b_part, b_row0)
-                                 : mask_offset(p, b_part, b_row0, a_part, a_row0);
-    (*out)[i] = DevRun{r.list * nbb + r.begin, r.end - r.begin, r.cls,
-                       static_cast<int32_t>(delta)};
-    (*work)[r.row] += r.end - r.begin;
-  }
+// Packs the lists of one built side behind `off`; returns the end.
+size_t pack_side(const plan::Built& b, const plan::Arrays& arr, int32_t heads,
+                 size_t align, char* base, size_t off, PassView* v) {
+  auto put = [&](const void* src, size_t bytes) {
+    const size_t at = off;
+    if (bytes > 0) std::memcpy(base + at, src, bytes);
+    off = (at + bytes + align - 1) / align * align;
+    return at;
+  };
+  v->off_rows = put(arr.rows, b.m * sizeof(DevRow));
+  v->off_runs = put(arr.runs, b.n_runs * sizeof(DevRun));
+  v->off_splits = put(arr.splits, b.n_splits * sizeof(DevSplit));
+  // The item counters, one per XCD lane (see queued_static_slots), zero.
+  const int32_t zeros[kNumXcd] = {};
+  v->off_queue = put(zeros, sizeof zeros);
+  v->m = b.m;
+  v->n_items = b.m * heads;
+  v->n_splits = b.n_splits;
+  v->parts = b.parts;
+  v->mode = b.mode;
+  return off;
 }
 
-// Workgroup order: items (block, head) sorted longest first, grouped so that
-// the items of one KV head land on one XCD when the KV head count allows it
-// (their workgroups then stream the same K/V through that XCD's L2).  Slot i
-// of the grid runs on XCD i % kNumXcd.
-std::vector<int2> workgroup_order(const std::vector<int32_t>& work,
-                                  int32_t heads, int32_t group_to_kv,
-                                  int32_t num_kv_heads) {
-  struct Item {
-    int64_t work;
-    int32_t blk, head, kvh;
-  };
-  std::vector<Item> items;
-  items.reserve(work.size() * heads);
-  // Blocks without runs are kept: their workgroup still writes the output
-  // (O = 0 and LSE = -inf, or zero gradients).
-  for (int32_t h = 0; h < heads; ++h)
-    for (size_t b = 0; b < work.size(); ++b)
-      items.push_back({work[b], static_cast<int32_t>(b), h, h / group_to_kv});
-  std::stable_sort(items.begin(), items.end(),
-                   [](const Item& x, const Item& y) {
-                     if (x.work != y.work) return x.work > y.work;
-                     if (x.kvh != y.kvh) return x.kvh < y.kvh;
-                     if (x.head != y.head) return x.head < y.head;
-                     return x.blk < y.blk;
-                   });
-  std::vector<std::vector<int2>> lanes(kNumXcd);
-  if (num_kv_heads % kNumXcd == 0) {
-    for (const Item& it : items)
-      lanes[it.kvh % kNumXcd].push_back(make_int2(it.blk, it.head));
+// The order of a pass for its kernels, its lists at `base` (device), or in the
+// PlanBlob if base is null.
+DevOrder order_at(const PassView& v, char* base) {
+  DevOrder o{};
+  if (base) {
+    o.rows = reinterpret_cast<const DevRow*>(base + v.off_rows);
+    o.runs = reinterpret_cast<const DevRun*>(base + v.off_runs);
+    o.splits = reinterpret_cast<const DevSplit*>(base + v.off_splits);
+    o.queue = reinterpret_cast<int32_t*>(base + v.off_queue);
   } else {
-    for (size_t i = 0; i < items.size(); ++i)
-      lanes[i % kNumXcd].push_back(make_int2(items[i].blk, items[i].head));
+    o.inline_list = 1;
+    o.off_runs = static_cast<int32_t>(v.off_runs);
+    o.off_splits = static_cast<int32_t>(v.off_splits);
   }
-  size_t depth = 0;
-  for (auto& l : lanes) depth = std::max(depth, l.size());
-  std::vector<int2> order(depth * kNumXcd, make_int2(-1, -1));
-  for (int x = 0; x < kNumXcd; ++x)
-    for (size_t j = 0; j < lanes[x].size(); ++j)
-      order[j * kNumXcd + x] = lanes[x][j];
-  return order;
+  o.m = v.m;
+  o.n_items = v.n_items;
+  o.mode = v.mode;
+  o.parts = v.parts;
+  o.n_splits = v.n_splits;
+  return o;
 }
 
-struct SideData {
-  std::vector<int32_t> ptr;
-  std::vector<DevRun> runs;
-  std::vector<int2> order;
-  std::vector<DevPiece> pieces;  // per order slot; empty unless split
-  std::vector<DevSplit> splits;
-};
-
-// Workgroup order of one side from its runs and the blocks per item, with the
-// long items split over the concurrent workgroups of the pass where that pays
-// (split.h; pass null: never).  An item walks its runs `walks` times.
-void order_items(std::vector<int32_t> work, int32_t heads, int32_t group_to_kv,
-                 int32_t num_kv_heads, const split::Pass* pass, int32_t walks,
-                 SideData* s) {
-  const int32_t rows = static_cast<int32_t>(work.size());
-  for (int32_t& w : work) w *= walks;
-  const split::Cut cut = pass
-                             ? split::choose(work.data(), rows, heads, *pass)
-                             : split::Cut{0, 0};
-  if (cut.c == 0) {
-    s->order = workgroup_order(work, heads, group_to_kv, num_kv_heads);
-    return;
+// Builds one or two sides into `blob` without heap memory; false if they do
+// not fit or take their last items from counters (which a PlanBlob, read in
+// place, does not hold).
+bool inline_plan(const plan::Side* sides, int n, PlanBlob* blob,
+                 PlanView* view) {
+  constexpr int kRows = kInlinePlan / sizeof(DevRow);
+  constexpr int kRuns = kInlinePlan / sizeof(DevRun);
+  constexpr int kSplits = kInlinePlan / sizeof(DevSplit);
+  DevRow rows[kRows];
+  DevRun runs[kRuns];
+  DevSplit splits[kSplits];
+  int32_t work[kRows];
+  const plan::Arrays arr{rows, kRows, runs, kRuns, splits, kSplits, work};
+  size_t off = 0;
+  for (int i = 0; i < n; ++i) {
+    plan::Built b;
+    if (!plan::build(sides[i], arr, &b)) return false;
+    if (int64_t{b.m} * sides[i].heads >= kQueuedMinItems) return false;
+    const size_t need = b.m * sizeof(DevRow) + b.n_runs * sizeof(DevRun) +
+                        b.n_splits * sizeof(DevSplit) + kNumXcd * 4 + 64;
+    if (off + need > kInlinePlan) return false;
+    off = pack_side(b, arr, sides[i].heads, 16, blob->bytes, off,
+                    i == 0 ? &view->a : &view->b);
   }
-  // The pieces of one head; all heads are cut alike.
-  struct Piece {
-    int32_t row, idx, len, run, off, walk, part;
-  };
-  const int32_t slots = pass->slots;
-  std::vector<Piece> pieces;
-  std::vector<std::pair<int32_t, int32_t>> split_rows;  // row, first part
-  int32_t parts = 0;
-  for (int32_t r = 0; r < rows; ++r) {
-    const int32_t n = split::num_pieces(cut, r, work[r]);
-    if (n > 1) split_rows.push_back({r, parts});
-    int32_t run = s->ptr[r], off = 0, walk = 0;
-    for (int32_t j = 0; j < n; ++j) {
-      const int32_t len = split::piece_begin(work[r], n, j + 1) -
-                          split::piece_begin(work[r], n, j);
-      while (len > 0 && off >= s->runs[run].nblk) {
-        off -= s->runs[run++].nblk;
-        if (run == s->ptr[r + 1]) {
-          run = s->ptr[r];
-          ++walk;
-        }
-      }
-      pieces.push_back({r, j, len, run, off, walk, n > 1 ? parts++ : -1});
-      off += len;
-    }
-  }
-  const int32_t m = static_cast<int32_t>(pieces.size());
-  const int32_t total = m * heads;
-  // Ranks: longest first over several rounds, by piece index in one.
-  auto key = [&](const Piece& pc) { return total > slots ? -pc.len : pc.idx; };
-  std::vector<int32_t> rank(m);
-  for (int32_t i = 0; i < m; ++i) rank[i] = i;
-  std::stable_sort(rank.begin(), rank.end(), [&](int32_t i, int32_t j) {
-    return key(pieces[i]) < key(pieces[j]);
-  });
-  s->order.assign(total, make_int2(-1, -1));
-  s->pieces.assign(total, DevPiece{0, 0, 0, -1, 0});
-  for (int32_t a = 0, b; a < m; a = b) {
-    for (b = a + 1; b < m && key(pieces[rank[b]]) == key(pieces[rank[a]]);) ++b;
-    for (int32_t i = a; i < b; ++i) {
-      const Piece& pc = pieces[rank[i]];
-      for (int32_t h = 0; h < heads; ++h) {
-        const int32_t slot =
-            split_slot(total, m, heads, group_to_kv,
-                       num_kv_heads % kNumXcd == 0, h, a, b - a, i - a, slots);
-        s->order[slot] = make_int2(pc.row, h);
-        s->pieces[slot] = DevPiece{pc.run, pc.off, pc.len,
-                                   pc.part < 0 ? -1 : h * parts + pc.part,
-                                   pc.walk};
-      }
-    }
-  }
-  for (int32_t h = 0; h < heads; ++h)
-    for (const auto& [row, part] : split_rows)
-      s->splits.push_back({row, h, h * parts + part,
-                           split::num_pieces(cut, row, work[row])});
-}
-
-size_t side_bytes(const SideData& s) {
-  return align_up(s.ptr.size() * 4) + align_up(s.runs.size() * sizeof(DevRun)) +
-         align_up(s.order.size() * sizeof(int2)) + align_up(kNumXcd * 4) +
-         align_up(s.pieces.size() * sizeof(DevPiece)) +
-         align_up(s.splits.size() * sizeof(DevSplit));
-}
-
-void side_pack(const SideData& s, char* base, size_t off, Side* out) {
-  out->off_ptr = off;
-  std::memcpy(base + off, s.ptr.data(), s.ptr.size() * 4);
-  off += align_up(s.ptr.size() * 4);
-  out->off_runs = off;
-  if (!s.runs.empty())
-    std::memcpy(base + off, s.runs.data(), s.runs.size() * sizeof(DevRun));
-  off += align_up(s.runs.size() * sizeof(DevRun));
-  out->off_order = off;
-  if (!s.order.empty())
-    std::memcpy(base + off, s.order.data(), s.order.size() * sizeof(int2));
-  off += align_up(s.order.size() * sizeof(int2));
-  // The item counters of this side's order, one per XCD lane (see
-  // queued_static_slots), uploaded as zeros with every call.
-  out->off_queue = off;
-  std::memset(base + off, 0, kNumXcd * 4);
-  out->n_splits = static_cast<int32_t>(s.splits.size());
-  off += align_up(kNumXcd * 4);
-  out->off_pieces = off;
-  if (!s.pieces.empty())
-    std::memcpy(base + off, s.pieces.data(), s.pieces.size() * sizeof(DevPiece));
-  off += align_up(s.pieces.size() * sizeof(DevPiece));
-  out->off_splits = off;
-  if (!s.splits.empty())
-    std::memcpy(base + off, s.splits.data(), s.splits.size() * sizeof(DevSplit));
-  out->grid = static_cast<int32_t>(s.order.size());
-  out->n_items = 0;
-  for (const int2& it : s.order) out->n_items += it.x >= 0;
+  view->bytes = off;
+  view->src = nullptr;
+  return true;
 }
 
 // Upper bound of one side's packed bytes from sizes alone (at most two
 // non-empty runs per (block, list entry): along a partition visibility only
 // drops, FULL blocks first, then PARTIAL, then EMPTY).
-size_t side_bound(int64_t n_blocks, int64_t n_list, int64_t heads) {
-  return align_up((n_blocks + 1) * 4) +
+size_t side_bound(int64_t n_blocks, int64_t n_list) {
+  return align_up(n_blocks * sizeof(DevRow)) +
          align_up(n_blocks * n_list * 2 * sizeof(DevRun)) +
-         align_up((n_blocks * heads + kNumXcd) * sizeof(int2)) +
          align_up(kNumXcd * 4);
 }
 
-// What splitting adds to one side: slots for the extra pieces, the piece of
-// every slot, the split items, and `parts` partial results of part_bytes.
-size_t split_bound(int64_t items, const split::Pass& ps, int64_t parts,
-                   size_t part_bytes) {
+// The list size that the allocation-free forward is limited by: 4 bytes per Q
+// block, 8 per item and two runs per Q block and KV partition.
+size_t noalloc_list_bytes(int64_t n_blocks, int64_t n_list, int64_t heads) {
+  return align_up((n_blocks + 1) * 4) +
+         align_up(n_blocks * n_list * 2 * sizeof(DevRun)) +
+         align_up((n_blocks * heads + kNumXcd) * 8) + align_up(kNumXcd * 4);
+}
+
+// What splitting adds to one side: table entries of the pieces, the split rows
+// (per head, so never more than the partials), and `parts` partial results of
+// part_bytes.
+size_t split_bound(int64_t parts, size_t part_bytes) {
   if (parts == 0) return 0;
-  const int64_t most =
-      std::min<int64_t>(items, int64_t{split::kMaxRounds} * ps.slots);
-  return align_up(parts * sizeof(int2)) +
-         align_up((most + parts) * sizeof(DevPiece)) +
-         align_up(parts / 2 * sizeof(DevSplit)) + align_up(parts * part_bytes);
+  return align_up(parts * sizeof(DevRow)) +
+         align_up(parts * sizeof(DevSplit)) + align_up(parts * part_bytes);
 }
 
 constexpr ma_chunk_t kWholeTile{0, 1, 0, 1};
 
-// Builds (or finds) the plan of a tile, copies it to `ws` on `stream` and
-// records the copy's completion event, all under the cache lock, so that no
-// other thread can recycle the source buffer in between.
-ma_status_t upload_plan(int pass, const ma_problem_t* p, const int32_t* q_idx,
-                        int32_t nq, const int32_t* kv_idx, int32_t nkv,
-                        const ma_chunk_t& ch, bool may_split, void* ws,
-                        hipStream_t stream, PlanView* view) {
-  const std::string key =
-      plan_key(pass * 2 + may_split, p, q_idx, nq, kv_idx, nkv, ch);
+// The sides of a call: the forward's Q-major one, or the backward's Q-major
+// (dQ) and KV-major (dK/dV) ones.  Returns their number.
+int sides_of(int pass, const ma_problem_t* p, const int32_t* q_idx, int32_t nq,
+             const int32_t* kv_idx, int32_t nkv, const ma_chunk_t& ch,
+             bool may_split, plan::Side out[2]) {
   const int64_t P = p->partition_len;
   const Slice sq{P / ch.num_q_chunks, ch.q_chunk * (P / ch.num_q_chunks)};
   const Slice skv{P / ch.num_kv_chunks, ch.kv_chunk * (P / ch.num_kv_chunks)};
-  std::lock_guard<std::mutex> lock(g_plan_mu);
+  const int32_t g = p->num_q_heads / p->num_kv_heads;
+  auto may = [&](const split::Pass& ps) { return may_split ? &ps : nullptr; };
+  if (pass == 0) {
+    out[0] = plan::Side{p,   q_idx, nq,   kFwdBM, sq, kv_idx, nkv, kFwdBN,
+                        skv, true,  p->num_q_heads, g, 1, may(kFwdPass)};
+    return 1;
+  }
+  out[0] = plan::Side{p,   q_idx, nq,   kBwdBM, sq, kv_idx, nkv, kBwdBN,
+                      skv, true,  p->num_q_heads, g, 1, may(kDqPass)};
+  out[1] = plan::Side{p,  kv_idx, nkv,  kBwdBN, skv, q_idx, nq, kBwdBM,
+                      sq, false,  p->num_kv_heads, 1, g, may(kDkdvPass)};
+  return 2;
+}
+
+// Builds the plan of a call: into `blob` if it is short, else (or from the
+// cache) into a pinned buffer, *buf.  Called with the cache locked for the
+// second part.
+ma_status_t cached_plan(const std::string& key, const plan::Side* sides, int n,
+                        Plan** out) {
   auto it = g_plans.find(key);
   if (it == g_plans.end()) {
-    const int32_t g = p->num_q_heads / p->num_kv_heads;
-    SideData sa, sb;
-    std::vector<int32_t> work;
-    if (pass == 0) {
-      device_runs(p, q_idx, nq, kFwdBM, sq, kv_idx, nkv, kFwdBN, skv, true,
-                  &sa.ptr, &sa.runs, &work);
-      order_items(work, p->num_q_heads, g, p->num_kv_heads,
-                  may_split ? &kFwdPass : nullptr, 1, &sa);
-    } else {
-      device_runs(p, q_idx, nq, kBwdBM, sq, kv_idx, nkv, kBwdBN, skv, true,
-                  &sa.ptr, &sa.runs, &work);
-      order_items(work, p->num_q_heads, g, p->num_kv_heads,
-                  may_split ? &kDqPass : nullptr, 1, &sa);
-      device_runs(p, kv_idx, nkv, kBwdBN, skv, q_idx, nq, kBwdBM, sq, false,
-                  &sb.ptr, &sb.runs, &work);
-      order_items(work, p->num_kv_heads, 1, p->num_kv_heads,
-                  may_split ? &kDkdvPass : nullptr, g, &sb);
+    std::vector<char> bytes;
+    Plan made;
+    for (int i = 0; i < n; ++i) {
+      const plan::Side& s = sides[i];
+      const int64_t rows = s.rows();
+      const int64_t extra = s.pass ? s.pass->max_parts() : 0;
+      std::vector<DevRow> table(rows + extra);
+      std::vector<DevRun> runs(rows * s.nb * 2);
+      std::vector<DevSplit> splits(extra);
+      std::vector<int32_t> work(rows);
+      const plan::Arrays arr{table.data(),  rows + extra,
+                             runs.data(),   static_cast<int64_t>(runs.size()),
+                             splits.data(), extra, work.data()};
+      plan::Built b;
+      if (!plan::build(s, arr, &b))
+        return fail(MA_ERR_CAPACITY, "work list of %lld rows",
+                    static_cast<long long>(rows));
+      bytes.resize(bytes.size() + align_up(b.m * sizeof(DevRow)) +
+                   align_up(b.n_runs * sizeof(DevRun)) +
+                   align_up(b.n_splits * sizeof(DevSplit)) +
+                   align_up(kNumXcd * 4));
+      made.bytes = pack_side(b, arr, s.heads, kAlign, bytes.data(), made.bytes,
+                             i == 0 ? &made.a : &made.b);
     }
     if (g_plans.size() >= kMaxPlans) {
       auto lru = g_plans.begin();
@@ -601,23 +489,39 @@ ma_status_t upload_plan(int pass, const ma_problem_t* p, const int32_t* q_idx,
       g_spare.push_back(lru->second.buf);
       g_plans.erase(lru);
     }
-    Plan plan;
-    plan.bytes = side_bytes(sa) + (pass == 0 ? 0 : side_bytes(sb));
-    ma_status_t st = take_buffer(plan.bytes, &plan.buf);
+    ma_status_t st = take_buffer(made.bytes, &made.buf);
     if (st != MA_OK) return st;
-    char* base = static_cast<char*>(plan.buf->host);
-    side_pack(sa, base, 0, &plan.a);
-    if (pass != 0) side_pack(sb, base, side_bytes(sa), &plan.b);
-    it = g_plans.emplace(key, plan).first;
+    std::memcpy(made.buf->host, bytes.data(), made.bytes);
+    it = g_plans.emplace(key, made).first;
   }
-  Plan& plan = it->second;
-  plan.last_use = ++g_plan_clock;
-  retire_completed(plan.buf);  // keeps the list as short as the copies in flight
-  hipError_t e = hipMemcpyAsync(ws, plan.buf->host, plan.bytes,
-                                hipMemcpyHostToDevice, stream);
-  if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(work list)");
+  it->second.last_use = ++g_plan_clock;
+  *out = &it->second;
+  return MA_OK;
+}
+
+// Runs `launch(view)`, which enqueues the work of a call on `stream`, with the
+// call's plan in `blob` or in a pinned buffer.  With a pinned one the cache
+// stays locked until the event behind that work is recorded, so that no other
+// thread can recycle the buffer in between.
+template <class F>
+ma_status_t with_plan(int pass, const ma_problem_t* p, const int32_t* q_idx,
+                      int32_t nq, const int32_t* kv_idx, int32_t nkv,
+                      const ma_chunk_t& ch, bool may_split, hipStream_t stream,
+                      PlanBlob* blob, F&& launch) {
+  plan::Side sides[2];
+  const int n =
+      sides_of(pass, p, q_idx, nq, kv_idx, nkv, ch, may_split, sides);
+  PlanView view;
+  if (inline_plan(sides, n, blob, &view)) return launch(view);
+  const std::string key =
+      plan_key(pass * 2 + may_split, p, q_idx, nq, kv_idx, nkv, ch);
+  std::lock_guard<std::mutex> lock(g_plan_mu);
+  Plan* plan = nullptr;
+  ma_status_t st = cached_plan(key, sides, n, &plan);
+  if (st != MA_OK) return st;
+  retire_completed(plan->buf);  // keeps the list as short as the copies in flight
   int dev = 0;
-  e = hipGetDevice(&dev);
+  hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
   std::vector<hipEvent_t>& pool = g_free_events[dev];
   hipEvent_t ev;
@@ -625,24 +529,28 @@ ma_status_t upload_plan(int pass, const ma_problem_t* p, const int32_t* q_idx,
     ev = pool.back();
     pool.pop_back();
   } else {
-    e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+    e = hipEventCreateWithFlags(&ev, hipEventDisableTiming |
+                                          hipEventDisableSystemFence);
     if (e != hipSuccess) return hip_fail(e, "hipEventCreateWithFlags");
   }
+  view.bytes = plan->bytes;
+  view.a = plan->a;
+  view.b = plan->b;
+  view.src = plan->buf->host;
+  st = launch(view);
+  // Also after a failed launch: the copy may have been enqueued before it.
   e = hipEventRecord(ev, stream);
   if (e != hipSuccess) {
     pool.push_back(ev);
-    return hip_fail(e, "hipEventRecord(work list)");
+    return st != MA_OK ? st : hip_fail(e, "hipEventRecord(work list)");
   }
-  plan.buf->pending.push_back(PendingEvent{ev, dev});
-  view->bytes = plan.bytes;
-  view->a = plan.a;
-  view->b = plan.b;
-  return MA_OK;
+  plan->buf->pending.push_back(PendingEvent{ev, dev});
+  return st;
 }
 
 size_t fwd_ws_bound(const ma_problem_t* p, int32_t nq, int32_t nkv) {
   const int64_t nqb = int64_t{nq} * p->partition_len / kFwdBM;
-  return side_bound(nqb, nkv, p->num_q_heads);
+  return side_bound(nqb, nkv);
 }
 
 size_t fwd_part_bytes(const ma_problem_t* p) {
@@ -660,15 +568,14 @@ size_t fwd_split_bytes(const ma_problem_t* p, int32_t nq, int32_t nkv,
       any_chunk ? std::min<int64_t>(items, split::kMaxRounds * kFwdPass.slots)
                 : items;
   const int64_t parts = split::parts_bound(counted, blocks, kFwdPass);
-  return split_bound(items, kFwdPass, parts, fwd_part_bytes(p));
+  return split_bound(parts, fwd_part_bytes(p));
 }
 
 size_t bwd_ws_bound(const ma_problem_t* p, int32_t nq, int32_t nkv) {
   const int64_t nqb = int64_t{nq} * p->partition_len / kBwdBM;
   const int64_t nkb = int64_t{nkv} * p->partition_len / kBwdBN;
   const int64_t rows_q = int64_t{nq} * p->partition_len;
-  return side_bound(nqb, nkv, p->num_q_heads) +
-         side_bound(nkb, nq, p->num_kv_heads) +
+  return side_bound(nqb, nkv) + side_bound(nkb, nq) +
          2 * align_up(static_cast<size_t>(rows_q) * p->num_q_heads * 4);
 }
 
@@ -699,8 +606,7 @@ BwdParts bwd_parts(const ma_problem_t* p, int32_t nq, int32_t nkv,
   static_assert(kBwdBM == 128 && kBwdBN == 128, "rows of a partial result");
   b.kv_bytes = align_up(b.kv * 2 * tile);
   b.q_bytes = align_up(b.q * tile);
-  b.bytes = split_bound(kv_items, kDkdvPass, b.kv, 2 * tile) +
-            split_bound(q_items, kDqPass, b.q, tile);
+  b.bytes = split_bound(b.kv, 2 * tile) + split_bound(b.q, tile);
   return b;
 }
 
@@ -742,24 +648,6 @@ int64_t parts_of(const ma_problem_t* p, int32_t nq, int32_t nkv,
       nkv * (P / ch.num_kv_chunks / kFwdBN), kFwdPass);
 }
 
-// The tile kernel over n_items slots and, if items were split, the fold of
-// their partial results.
-ma_status_t launch_fwd(const FwdParams& fp, int32_t head_dim, bool o_f32,
-                       int64_t n_items, const DevSplit* splits,
-                       int32_t n_splits, hipStream_t stream) {
-  hipError_t e =
-      launch_tile_fwd(fp, head_dim, o_f32,
-                      static_cast<int>(queued_launch_grid(n_items)), stream);
-  if (e != hipSuccess) return hip_fail(e, "tile_fwd launch");
-  if (n_splits > 0) {
-    const CombineParams cp{splits, fp.part_o, fp.part_lse, fp.o,
-                           fp.lse, fp.rows_q, fp.hq,       fp.accumulate};
-    e = launch_fwd_combine(cp, head_dim, o_f32, n_splits, stream);
-    if (e != hipSuccess) return hip_fail(e, "fwd_combine launch");
-  }
-  return ok();
-}
-
 // KV blocks that Q block `qb` of a whole tile sees (its work), without a run
 // list: along a partition the visible blocks are a prefix.
 int32_t visible_blocks(const ma_problem_t* p, const int32_t* q_idx,
@@ -770,10 +658,8 @@ int32_t visible_blocks(const ma_problem_t* p, const int32_t* q_idx,
       token_pos(p, q_idx[qb / qpb], (qb % qpb) * kFwdBM + kFwdBM - 1);
   const int64_t step = token_pos(p, 0, kFwdBN);  // positions per KV block
   int64_t n = 0;
-  for (int32_t b = 0; b < nkv; ++b) {
-    const int64_t d = q_last - token_pos(p, kv_idx[b], 0);
-    if (d >= 0) n += std::min(nbb, d / step + 1);
-  }
+  for (int32_t b = 0; b < nkv; ++b)
+    n += plan::count_le(token_pos(p, kv_idx[b], 0), step, q_last, nbb);
   return static_cast<int32_t>(n);
 }
 
@@ -781,7 +667,7 @@ int32_t visible_blocks(const ma_problem_t* p, const int32_t* q_idx,
 // rows of one head.  Uses no heap.
 struct NoAllocSplit {
   split::Cut cut;
-  int32_t row_pieces, split_rows;
+  int32_t row_pieces, split_rows, parts;
 };
 
 NoAllocSplit noalloc_split(const ma_problem_t* p, const int32_t* q_idx,
@@ -791,12 +677,14 @@ NoAllocSplit noalloc_split(const ma_problem_t* p, const int32_t* q_idx,
       static_cast<int32_t>(int64_t{nq} * p->partition_len / kFwdBM);
   for (int32_t qb = 0; qb < nqb; ++qb)
     work[qb] = visible_blocks(p, q_idx, kv_idx, nkv, qb);
-  NoAllocSplit s{split::choose(work, nqb, p->num_q_heads, kFwdPass), 0, 0};
+  NoAllocSplit s{split::choose(work, nqb, p->num_q_heads, kFwdPass), 0, 0, 0};
   if (s.cut.c == 0) return s;
   for (int32_t qb = 0; qb < nqb; ++qb) {
     const int32_t n = split::num_pieces(s.cut, qb, work[qb]);
     s.row_pieces += n;
-    s.split_rows += n > 1;
+    if (n == 1) continue;
+    ++s.split_rows;
+    s.parts += n;
   }
   return s;
 }
@@ -828,10 +716,6 @@ ma_status_t fwd_impl(const ma_problem_t* prob, const int32_t* q_idx,
   // larger tile) serves the call with whole items.
   const bool may_split =
       ws_bytes >= need + fwd_split_bytes(prob, nq, nkv, ch, false);
-  PlanView plan;
-  st = upload_plan(0, prob, q_idx, nq, kv_idx, nkv, ch, may_split, ws, stream,
-                   &plan);
-  if (st != MA_OK) return st;
   char* wsb = static_cast<char*>(ws);
   FwdParams fp{};
   fp.q = static_cast<const uint16_t*>(q);
@@ -839,26 +723,29 @@ ma_status_t fwd_impl(const ma_problem_t* prob, const int32_t* q_idx,
   fp.v = static_cast<const uint16_t*>(v);
   fp.o = o;
   fp.lse = lse;
-  fp.qblk_ptr = reinterpret_cast<const int32_t*>(wsb + plan.a.off_ptr);
-  fp.runs = reinterpret_cast<const DevRun*>(wsb + plan.a.off_runs);
-  fp.order = reinterpret_cast<const int2*>(wsb + plan.a.off_order);
-  fp.queue = reinterpret_cast<int32_t*>(wsb + plan.a.off_queue);
-  fp.n_items = plan.a.n_items;
   fp.rows_q = int64_t{nq} * (prob->partition_len / ch.num_q_chunks);
   fp.hq = prob->num_q_heads;
   fp.hkv = prob->num_kv_heads;
   fp.group = prob->num_q_heads / prob->num_kv_heads;
   fp.scale_log2 = prob->softmax_scale * kLog2e;
   fp.accumulate = accumulate;
-  if (plan.a.grid == 0) return ok();  // cannot happen: every block is listed
-  if (plan.a.n_splits > 0) {
-    fp.pieces = reinterpret_cast<const DevPiece*>(wsb + plan.a.off_pieces);
-    fp.part_lse = reinterpret_cast<float*>(wsb + align_up(plan.bytes));
-    fp.part_o = fp.part_lse + parts_of(prob, nq, nkv, ch) * kFwdBM;
-  }
-  return launch_fwd(fp, prob->head_dim, o_f32, plan.a.n_items,
-                    reinterpret_cast<const DevSplit*>(wsb + plan.a.off_splits),
-                    plan.a.n_splits, stream);
+  PlanBlob blob;
+  return with_plan(
+      0, prob, q_idx, nq, kv_idx, nkv, ch, may_split, stream, &blob,
+      [&](const PlanView& plan) {
+        hipError_t e = hipSuccess;
+        if (plan.src) {
+          e = launch_plan_copy(wsb, plan.src, plan.bytes, stream);
+          if (e != hipSuccess) return hip_fail(e, "work-list copy launch");
+        }
+        fp.order = order_at(plan.a, plan.src ? wsb : nullptr);
+        fp.part_lse = reinterpret_cast<float*>(
+            wsb + (plan.src ? align_up(plan.bytes) : 0));
+        fp.part_o = fp.part_lse + parts_of(prob, nq, nkv, ch) * kFwdBM;
+        e = launch_tile_fwd(fp, blob, prob->head_dim, o_f32, stream);
+        if (e != hipSuccess) return hip_fail(e, "tile_fwd launch");
+        return ok();
+      });
 }
 
 // Backward of one chunk pair of a tile (the whole tile: one chunk each).
@@ -890,10 +777,6 @@ ma_status_t bwd_impl(const ma_problem_t* prob, const int32_t* q_idx,
     return fail(MA_ERR_WORKSPACE_TOO_SMALL, "workspace %zu bytes < %zu",
                 ws_bytes, need);
   const BwdParts parts = bwd_parts(prob, nq, nkv, ch, false);
-  PlanView plan;
-  st = upload_plan(1, prob, q_idx, nq, kv_idx, nkv, ch,
-                   ws_bytes >= need + parts.bytes, ws, stream, &plan);
-  if (st != MA_OK) return st;
   char* wsb = static_cast<char*>(ws);
   BwdParams bp{};
   bp.q = static_cast<const uint16_t*>(q);
@@ -905,34 +788,6 @@ ma_status_t bwd_impl(const ma_problem_t* prob, const int32_t* q_idx,
   bp.dq = dq;
   bp.dk = dk;
   bp.dv = dv;
-  bp.delta = reinterpret_cast<float*>(wsb + align_up(plan.bytes));
-  const size_t row_bytes = align_up(static_cast<size_t>(nq) *
-                                    prob->partition_len * prob->num_q_heads * 4);
-  bp.lse2 =
-      reinterpret_cast<float*>(wsb + align_up(plan.bytes) + row_bytes);
-  char* part_base = wsb + align_up(plan.bytes) + 2 * row_bytes;
-  bp.n_kvsplits = plan.b.n_splits;
-  bp.n_qsplits = plan.a.n_splits;
-  if (plan.b.n_splits > 0) {
-    bp.kvpieces = reinterpret_cast<const DevPiece*>(wsb + plan.b.off_pieces);
-    bp.kvsplits = reinterpret_cast<const DevSplit*>(wsb + plan.b.off_splits);
-    bp.kvparts = reinterpret_cast<float*>(part_base);
-  }
-  if (plan.a.n_splits > 0) {
-    bp.qpieces = reinterpret_cast<const DevPiece*>(wsb + plan.a.off_pieces);
-    bp.qsplits = reinterpret_cast<const DevSplit*>(wsb + plan.a.off_splits);
-    bp.qparts = reinterpret_cast<float*>(part_base + parts.kv_bytes);
-  }
-  bp.qblk_ptr = reinterpret_cast<const int32_t*>(wsb + plan.a.off_ptr);
-  bp.qruns = reinterpret_cast<const DevRun*>(wsb + plan.a.off_runs);
-  bp.qorder = reinterpret_cast<const int2*>(wsb + plan.a.off_order);
-  bp.kvblk_ptr = reinterpret_cast<const int32_t*>(wsb + plan.b.off_ptr);
-  bp.kvruns = reinterpret_cast<const DevRun*>(wsb + plan.b.off_runs);
-  bp.kvorder = reinterpret_cast<const int2*>(wsb + plan.b.off_order);
-  bp.qqueue = reinterpret_cast<int32_t*>(wsb + plan.a.off_queue);
-  bp.kvqueue = reinterpret_cast<int32_t*>(wsb + plan.b.off_queue);
-  bp.q_items = plan.a.n_items;
-  bp.kv_items = plan.b.n_items;
   bp.rows_q = int64_t{nq} * (prob->partition_len / ch.num_q_chunks);
   bp.rows_kv = int64_t{nkv} * (prob->partition_len / ch.num_kv_chunks);
   bp.hq = prob->num_q_heads;
@@ -941,15 +796,29 @@ ma_status_t bwd_impl(const ma_problem_t* prob, const int32_t* q_idx,
   bp.scale = prob->softmax_scale;
   bp.scale_log2 = prob->softmax_scale * kLog2e;
   bp.accumulate = accumulate;
-  hipError_t e = launch_tile_bwd(
-      bp, prob->head_dim,
-      plan.a.n_items > 0 ? static_cast<int>(queued_launch_grid(plan.a.n_items)) : 0,
-      plan.b.n_items > 0 ? static_cast<int>(queued_launch_grid(plan.b.n_items)) : 0,
-      stream);
-  if (e != hipSuccess) return hip_fail(e, "tile_bwd launch");
-  return ok();
+  PlanBlob blob;
+  return with_plan(
+      1, prob, q_idx, nq, kv_idx, nkv, ch, ws_bytes >= need + parts.bytes,
+      stream, &blob, [&](const PlanView& plan) {
+        const size_t row_bytes =
+            align_up(static_cast<size_t>(nq) * prob->partition_len *
+                     prob->num_q_heads * 4);
+        char* at = wsb + align_up(plan.bytes);
+        bp.delta = reinterpret_cast<float*>(at);
+        bp.lse2 = reinterpret_cast<float*>(at + row_bytes);
+        bp.kvparts = reinterpret_cast<float*>(at + 2 * row_bytes);
+        bp.qparts =
+            reinterpret_cast<float*>(at + 2 * row_bytes + parts.kv_bytes);
+        bp.qorder = order_at(plan.a, wsb);
+        bp.kvorder = order_at(plan.b, wsb);
+        bp.plan_dst = wsb;
+        bp.plan_src = plan.src;
+        bp.plan_bytes = static_cast<int32_t>(plan.bytes);
+        const hipError_t e = launch_tile_bwd(bp, blob, prob->head_dim, stream);
+        if (e != hipSuccess) return hip_fail(e, "tile_bwd launch");
+        return ok();
+      });
 }
-
 
 }  // namespace
 
@@ -1103,92 +972,84 @@ ma_status_t mesh_attn_tile_fwd_noalloc(const ma_problem_t* prob,
                 "noalloc forward: index lists of %d and %d partitions exceed "
                 "the maximum of %d", nq, nkv, kNoAllocMaxList);
   const int64_t nqb = int64_t{nq} * prob->partition_len / kFwdBM;
-  const size_t need = fwd_ws_bound(prob, nq, nkv);
+  const size_t need = noalloc_list_bytes(nqb, nkv, prob->num_q_heads);
   if (nqb > kNoAllocMaxQBlocks || need > kNoAllocScratchBytes)
     return fail(MA_ERR_UNSUPPORTED,
                 "noalloc forward: the tile's work list (%lld Q blocks, %zu "
                 "bytes) exceeds the scratch maximum (%d Q blocks, %zu bytes)",
                 static_cast<long long>(nqb), need, kNoAllocMaxQBlocks,
                 kNoAllocScratchBytes);
+  const int64_t items = nqb * prob->num_q_heads;
+  if (items > INT32_MAX)
+    return fail(MA_ERR_UNSUPPORTED, "noalloc forward: %lld workgroups",
+                static_cast<long long>(items));
   void *scratch = nullptr, *parts = nullptr;
   hipError_t e = noalloc_scratch(&scratch, &parts);
   if (e != hipSuccess) return hip_fail(e, "hipGetSymbolAddress(scratch)");
-  // Same regions as the uploaded plan: Q-block pointers, runs, order.
-  char* base = static_cast<char*>(scratch);
-  const size_t off_runs = align_up(static_cast<size_t>(nqb + 1) * 4);
-  const size_t off_order =
-      off_runs + align_up(static_cast<size_t>(nqb) * nkv * 2 * sizeof(DevRun));
-  const int64_t items = nqb * prob->num_q_heads;
-  const bool by_kv = prob->num_kv_heads % kNumXcd == 0;
-  int64_t grid = by_kv ? items : (items + kNumXcd - 1) / kNumXcd * kNumXcd;
-  if (grid > INT32_MAX)
-    return fail(MA_ERR_UNSUPPORTED, "noalloc forward: %lld workgroups",
-                static_cast<long long>(grid));
-  // The same split as the call with a workspace of full size, which has room
-  // for it beside the work list.
-  NoAllocSplit sp{{0, 0}, 0, 0};
-  const int64_t max_parts = parts_of(prob, nq, nkv, kWholeTile);
-  if (max_parts > 0 && need + split_bound(items, kFwdPass, max_parts, 0) <=
-                           kNoAllocScratchBytes)
-    sp = noalloc_split(prob, q_idx, nq, kv_idx, nkv);
-  const bool split = sp.cut.c > 0;
-  const int64_t n_items =
-      split ? int64_t{sp.row_pieces} * prob->num_q_heads : items;
-  if (split) grid = n_items;
-  PlanBuildParams bp{};
-  bp.P = prob->partition_len;
-  bp.n = prob->num_partitions;
-  bp.layout = prob->layout;
-  bp.causal = prob->causal;
-  bp.nq = nq;
-  bp.nkv = nkv;
-  bp.hq = prob->num_q_heads;
-  bp.hkv = prob->num_kv_heads;
-  bp.group = prob->num_q_heads / prob->num_kv_heads;
-  bp.bm = kFwdBM;
-  bp.bn = kFwdBN;
-  bp.nqb = static_cast<int32_t>(nqb);
-  bp.nkbp = prob->partition_len / kFwdBN;
-  bp.grid = static_cast<int32_t>(grid);
-  bp.qblk_ptr = reinterpret_cast<int32_t*>(base);
-  bp.runs = reinterpret_cast<DevRun*>(base + off_runs);
-  bp.order = reinterpret_cast<int2*>(base + off_order);
-  size_t off = off_order + align_up(static_cast<size_t>(grid) * sizeof(int2));
-  bp.queue = reinterpret_cast<int32_t*>(base + off);
-  off += align_up(kNumXcd * 4);
-  bp.cut = sp.cut;
-  bp.row_pieces = sp.row_pieces;
-  bp.pieces = reinterpret_cast<DevPiece*>(base + off);
-  off += split ? align_up(static_cast<size_t>(grid) * sizeof(DevPiece)) : 0;
-  bp.splits = reinterpret_cast<DevSplit*>(base + off);
-  for (int32_t i = 0; i < nq; ++i) bp.q_idx[i] = q_idx[i];
-  for (int32_t i = 0; i < nkv; ++i) bp.kv_idx[i] = kv_idx[i];
-  e = launch_fwd_plan_build(bp, stream);
-  if (e != hipSuccess) return hip_fail(e, "noalloc work-list build launch");
   FwdParams fp{};
   fp.q = static_cast<const uint16_t*>(q);
   fp.k = static_cast<const uint16_t*>(k);
   fp.v = static_cast<const uint16_t*>(v);
   fp.o = o;
   fp.lse = lse;
-  fp.qblk_ptr = bp.qblk_ptr;
-  fp.runs = bp.runs;
-  fp.order = bp.order;
-  fp.queue = bp.queue;
-  fp.n_items = static_cast<int32_t>(n_items);
   fp.rows_q = int64_t{nq} * prob->partition_len;
   fp.hq = prob->num_q_heads;
   fp.hkv = prob->num_kv_heads;
-  fp.group = bp.group;
+  fp.group = prob->num_q_heads / prob->num_kv_heads;
   fp.scale_log2 = prob->softmax_scale * kLog2e;
-  fp.accumulate = 0;
-  if (split) {
-    fp.pieces = bp.pieces;
-    fp.part_lse = static_cast<float*>(parts);
-    fp.part_o = fp.part_lse + kFwdPass.max_parts() * kFwdBM;
+  fp.part_lse = static_cast<float*>(parts);
+  fp.part_o = fp.part_lse + kFwdPass.max_parts() * kFwdBM;
+  // A short list travels in the kernel's arguments, as with a workspace.
+  PlanBlob blob;
+  PlanView view;
+  plan::Side side[2];
+  sides_of(0, prob, q_idx, nq, kv_idx, nkv, kWholeTile, true, side);
+  if (inline_plan(side, 1, &blob, &view)) {
+    fp.order = order_at(view.a, nullptr);
+  } else {
+    // The same cut as the call with a workspace of full size.
+    NoAllocSplit sp{{0, 0}, 0, 0, 0};
+    if (parts_of(prob, nq, nkv, kWholeTile) > 0)
+      sp = noalloc_split(prob, q_idx, nq, kv_idx, nkv);
+    const bool split = sp.cut.c > 0;
+    PassView v;
+    v.m = split ? sp.row_pieces : static_cast<int32_t>(nqb);
+    v.n_items = v.m * prob->num_q_heads;
+    v.n_splits = sp.split_rows;
+    v.parts = sp.parts;
+    v.mode = split_mode(v.n_items, split, prob->num_kv_heads % kNumXcd == 0,
+                        kFwdPass.slots);
+    v.off_queue = align_up(static_cast<size_t>(v.m) * sizeof(DevRow));
+    v.off_splits = v.off_queue + kAlign;
+    v.off_runs = v.off_splits + align_up(sp.split_rows * sizeof(DevSplit));
+    char* base = static_cast<char*>(scratch);
+    fp.order = order_at(v, base);
+    PlanBuildParams bp{};
+    bp.P = prob->partition_len;
+    bp.n = prob->num_partitions;
+    bp.layout = prob->layout;
+    bp.causal = prob->causal;
+    bp.nq = nq;
+    bp.nkv = nkv;
+    bp.bm = kFwdBM;
+    bp.bn = kFwdBN;
+    bp.nqb = static_cast<int32_t>(nqb);
+    bp.nkbp = prob->partition_len / kFwdBN;
+    bp.cut = sp.cut;
+    bp.m = v.m;
+    bp.mode = v.mode;
+    bp.rows = reinterpret_cast<DevRow*>(base + v.off_rows);
+    bp.runs = reinterpret_cast<DevRun*>(base + v.off_runs);
+    bp.splits = reinterpret_cast<DevSplit*>(base + v.off_splits);
+    bp.queue = reinterpret_cast<int32_t*>(base + v.off_queue);
+    for (int32_t i = 0; i < nq; ++i) bp.q_idx[i] = q_idx[i];
+    for (int32_t i = 0; i < nkv; ++i) bp.kv_idx[i] = kv_idx[i];
+    e = launch_fwd_plan_build(bp, stream);
+    if (e != hipSuccess) return hip_fail(e, "noalloc work-list build launch");
   }
-  return launch_fwd(fp, prob->head_dim, o_dtype == MA_FP32, fp.n_items,
-                    bp.splits, sp.split_rows * prob->num_q_heads, stream);
+  e = launch_tile_fwd(fp, blob, prob->head_dim, o_dtype == MA_FP32, stream);
+  if (e != hipSuccess) return hip_fail(e, "tile_fwd launch");
+  return ok();
 }
 
 ma_status_t mesh_attn_lse_merge(int32_t k_parts, int64_t rows, int32_t heads,

@@ -11,10 +11,6 @@
 
 namespace mesh_attn {
 
-// gfx950 (MI355X) has 8 XCDs; consecutive workgroup ids are dispatched to
-// XCDs round robin, so id i runs on XCD i % 8.
-constexpr int kNumXcd = 8;
-
 // Forward block shape: 8 waves x 32 query rows, 64 keys per LDS stage.
 constexpr int kFwdBM = 256;
 constexpr int kFwdBN = 64;
@@ -33,17 +29,40 @@ struct DevRun {
   int32_t blk0, nblk, cls, delta;
 };
 
-// One workgroup's share of an item of a split tile: nblk blocks from block
-// `off` of run `run` on; part >= 0: write a partial result into that slot.
-// The dK/dV items walk their runs once per query head of the group; the share
-// starts in walk `walk`.
-struct alignas(32) DevPiece {
-  int32_t run, off, nblk, part, walk;
+// Entry of a pass's order table: the workgroup's share of an item, nblk blocks
+// of block row `row` from block `off` of run `run` on (the dK/dV items walk
+// their runs [run_b, run_e) once per query head of the group; the share
+// starts in walk `walk`).  part >= 0: it is a piece of a split item and leaves
+// its partial result in slot head * parts + part.  The entry's rank class is
+// [before, before + same) (split.h).
+struct DevRow {
+  int32_t row, run, off, nblk, part, walk, run_b, run_e, before, same;
 };
 
-// A split item: its partial results are slots [part0, part0 + nparts).
+// A row whose items are split: the partial results of head h are slots
+// [h * parts + part, .. + nparts).
 struct DevSplit {
-  int32_t blk, head, part0, nparts;
+  int32_t row, part, nparts;
+};
+
+// The order of a pass as its kernels get it.
+struct DevOrder {
+  const DevRow* rows;  // [m]
+  const DevRun* runs;
+  const DevSplit* splits;  // [n_splits]
+  int32_t* queue;      // [8] items taken from each XCD lane, 0 at launch; used
+                       // from kQueuedMinItems items on
+  int32_t m, n_items;  // table entries; times the heads: workgroup items
+  int32_t mode, parts, n_splits;
+  int32_t inline_list;  // the three lists are in the PlanBlob argument
+  int32_t off_runs, off_splits;  // at these offsets (rows first)
+};
+
+// A small work list travels in the kernel's arguments instead of the
+// workspace: no upload, and no pinned copy to keep until one is done.
+constexpr int kInlinePlan = 3072;
+struct PlanBlob {
+  alignas(16) char bytes[kInlinePlan];
 };
 
 struct FwdParams {
@@ -52,18 +71,13 @@ struct FwdParams {
   const uint16_t* v;
   void* o;             // bf16 or f32 [rows_q][hq][d]
   float* lse;          // [hq][rows_q]
-  const int32_t* qblk_ptr;   // [n_qblk + 1]
-  const DevRun* runs;
-  const int2* order;         // (qblk, q head); XCD lane x at slots j*8 + x
-  int32_t* queue;            // [8] items taken from each lane; 0 at launch
-  int32_t n_items;           // items (Q block, q head) in the order
+  DevOrder order;
   int64_t rows_q;
   int32_t hq, hkv, group;
   float scale_log2;    // softmax scale * log2(e)
   int32_t accumulate;  // 1: fold into the float32 (O, LSE) already stored
-  // Split tiles only (null otherwise): the piece of each order slot and the
-  // partial results, [part][kFwdBM][d] and [part][kFwdBM] (log2 units).
-  const DevPiece* pieces;
+  // Partial results of split items, [part][kFwdBM][d] and [part][kFwdBM] (log2
+  // units).
   float* part_o;
   float* part_lse;
 };
@@ -75,22 +89,6 @@ struct FwdParams {
 // 256 x 128 takes 7-9 us, and writing them about as long.
 constexpr split::Pass kFwdPass{256, 6, 4, 2, 20};
 
-// Folds the partial results of the split items into O and LSE.
-struct CombineParams {
-  const DevSplit* splits;
-  const float* part_o;
-  const float* part_lse;
-  void* o;
-  float* lse;
-  int64_t rows_q;
-  int32_t hq;
-  int32_t accumulate;
-};
-
-hipError_t launch_fwd_combine(const CombineParams& p, int head_dim,
-                              bool out_f32, int n_splits,
-                              hipStream_t stream);
-
 // Workgroup items of the forward and of both backward kernels.  The XCDs of
 // the part run at different speeds (a few per cent apart under load) while
 // the dispatcher gives each an eighth of the workgroups, so on launches with
@@ -100,21 +98,27 @@ hipError_t launch_fwd_combine(const CombineParams& p, int head_dim,
 // their XCD's lane or else of another lane, and about one in eight more of
 // them are launched than remaining items, so an XCD that runs faster takes
 // more of the last items.  Below kQueuedMinItems (16 items per compute unit
-// of the 256-CU part) every whole row of eight slots is static.
+// of the 256-CU part) every slot is static and no counter is read.
 constexpr int64_t kQueuedMinItems = 4096;
 __host__ __device__ inline int64_t queued_static_slots(int64_t n_items) {
-  return n_items >= kQueuedMinItems ? (n_items / 8) * 3 / 4 * 8
-                                    : (n_items / 8) * 8;
+  return n_items >= kQueuedMinItems ? (n_items / 8) * 3 / 4 * 8 : n_items;
 }
 __host__ __device__ inline int64_t queued_launch_grid(int64_t n_items) {
   const int64_t fixed = queued_static_slots(n_items);
   const int64_t dyn = n_items - fixed;
-  const int64_t extra = n_items >= kQueuedMinItems ? dyn / 8 + 8 : 0;
-  return fixed + (dyn + extra + 7) / 8 * 8;
+  return dyn > 0 ? fixed + (dyn + dyn / 8 + 8 + 7) / 8 * 8 : fixed;
 }
 
-hipError_t launch_tile_fwd(const FwdParams& p, int head_dim, bool out_f32,
-                           int grid, hipStream_t stream);
+// The tile kernel and, if items are split, the fold of their partial results.
+hipError_t launch_tile_fwd(const FwdParams& p, const PlanBlob& blob,
+                           int head_dim, bool out_f32, hipStream_t stream);
+
+// Copies `bytes` (a multiple of 16) of a work list from pinned host memory to
+// the device, by a kernel.  hipMemcpyAsync on the same stream held the next
+// kernel back by 18 to 26 us where it went through a copy engine (lists above
+// some 10 KB) and by 5 to 10 us below; this takes 3 to 5 us.
+hipError_t launch_plan_copy(void* dst, const void* src, size_t bytes,
+                            hipStream_t stream);
 
 struct MergeParams {
   const void* o_parts;
@@ -140,34 +144,23 @@ struct BwdParams {
   float* dv;
   float* delta;        // workspace [hq][rows_q]: rowsum(dO * O)
   float* lse2;         // workspace [hq][rows_q]: LSE * log2(e), -inf -> +inf
-  // Q-major runs (dQ kernel): Q blocks of kBwdBM rows, KV blocks of kBwdBN.
-  const int32_t* qblk_ptr;
-  const DevRun* qruns;
-  const int2* qorder;
-  // KV-major runs (dK/dV kernel): Q blocks of kBwdBM rows per KV block of
-  // kBwdBN; the delta field is q-first minus kv-first, as in the Q-major runs.
-  const int32_t* kvblk_ptr;
-  const DevRun* kvruns;
-  const int2* kvorder;   // (kvblk, kv head)
-  // Per-XCD-lane item counters of the two orders, 0 at launch, and their
-  // item counts (see queued_static_slots).
-  int32_t* qqueue;
-  int32_t* kvqueue;
-  int32_t q_items, kv_items;
+  // dQ: Q blocks of kBwdBM rows walk KV blocks of kBwdBN.  dK/dV: KV blocks
+  // walk Q blocks, once per query head of the group; a run's delta is q-first
+  // minus kv-first in both.  Both lists are in the workspace once the prep
+  // kernel has run, which copies them there: plan_bytes (a multiple of 16) from
+  // plan_src (pinned host memory; null: the PlanBlob argument) to plan_dst.
+  DevOrder qorder, kvorder;
+  void* plan_dst;
+  const void* plan_src;
+  int32_t plan_bytes;
   int64_t rows_q, rows_kv;
   int32_t hq, hkv, group;
   float scale, scale_log2;
   int32_t accumulate;
-  // Split tiles (null otherwise): the piece of each slot of the two orders and
-  // the partial results, [part][dV, dK][kBwdBN][d] and [part][kBwdBM][d]; the
-  // split items of both sides, dK/dV first.
-  const DevPiece* kvpieces;
-  const DevPiece* qpieces;
+  // Partial results of split items, [part][dV, dK][kBwdBN][d] and
+  // [part][kBwdBM][d].
   float* kvparts;
   float* qparts;
-  const DevSplit* kvsplits;
-  const DevSplit* qsplits;
-  int32_t n_kvsplits, n_qsplits;
 };
 
 // The backward passes as the cut of long items sees them; a block is 128 x 128.
@@ -176,8 +169,8 @@ struct BwdParams {
 constexpr split::Pass kDkdvPass{256, 3, 2, 1, 40};
 constexpr split::Pass kDqPass{512, 2, 2, 1, 120};
 
-hipError_t launch_tile_bwd(const BwdParams& p, int head_dim, int grid_q,
-                           int grid_kv, hipStream_t stream);
+hipError_t launch_tile_bwd(const BwdParams& p, const PlanBlob& blob,
+                           int head_dim, hipStream_t stream);
 
 // ---------------------------------------------------------------------------
 // Allocation-free forward (noalloc.hip): the work list is built on the device
@@ -195,22 +188,24 @@ constexpr size_t kNoAllocPartBytes =
 constexpr int kSplitMaxRows = split::kMaxRounds * kFwdPass.slots;
 constexpr int kSplitMaxPieces = kSplitMaxRows + kFwdPass.max_parts();
 
+// The runs of a tile within the limit fit kNoAllocScratchBytes; the order table
+// and the split rows lie beside them.
+constexpr size_t kNoAllocTableBytes =
+    (kNoAllocMaxQBlocks > kSplitMaxPieces ? kNoAllocMaxQBlocks
+                                          : kSplitMaxPieces) *
+        sizeof(DevRow) +
+    kFwdPass.max_parts() * sizeof(DevSplit) + 4096;
+
 struct PlanBuildParams {
   int32_t P, n, layout, causal;   // problem (partition length, partitions)
-  int32_t nq, nkv, hq, hkv, group;
-  int32_t bm, bn;                 // forward block shape
+  int32_t nq, nkv, bm, bn;        // lists and the forward block shape
   int32_t nqb, nkbp;              // Q blocks of the tile, KV blocks per part
-  int32_t grid;                   // workgroup slots of the order
-  int32_t* qblk_ptr;              // [nqb + 1] in the scratch array
-  DevRun* runs;                   // [<= 2 nqb nkv]
-  int2* order;                    // [grid]
-  int32_t* queue;                 // [8] lane counters, zeroed by the build
-  // Split tiles (cut.c > 0): the pieces of a row of heads, the slots' pieces
-  // and the split items.
   split::Cut cut;
-  int32_t row_pieces;             // pieces of all Q blocks of one head
-  DevPiece* pieces;               // [grid]
-  DevSplit* splits;
+  int32_t m, mode;                // table entries, slot mapping
+  DevRow* rows;                   // [m] in the scratch array
+  DevRun* runs;                   // [<= 2 nqb nkv]
+  DevSplit* splits;               // [split rows]
+  int32_t* queue;                 // [8] lane counters, zeroed by the build
   int32_t q_idx[kNoAllocMaxList];
   int32_t kv_idx[kNoAllocMaxList];
 };

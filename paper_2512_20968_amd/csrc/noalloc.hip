@@ -1,17 +1,16 @@
-// The allocation-free forward: the tile's work list is built on the device,
-// into a fixed scratch array that every call on a GPU shares, instead of
-// being built on the host and uploaded from pinned memory into a
-// caller-provided workspace.  Everything a launch needs travels in kernel
-// arguments (the index lists included), so the call allocates nothing, host
-// or device, and never waits.
+// The allocation-free forward of tiles whose work list does not fit a kernel
+// argument: the list is built on the device, into a fixed scratch array that
+// every call on a GPU shares, instead of being built on the host and copied
+// from pinned memory into a caller-provided workspace.  Everything a launch
+// needs travels in kernel arguments (the index lists included), so the call
+// allocates nothing, host or device, and never waits.
 //
-// The builder reproduces the host's canonical work list (Section 3.7 rule per
-// block pair; runs in KV-list order, FULL before PARTIAL, EMPTY dropped) and
-// its workgroup order (longest Q block first, the items of one KV head on one
-// XCD when the KV head count allows it) with one workgroup of 1024 threads.
-// Along one KV partition a Q block's classes only fall (positions grow with
-// the row under both layouts), so each (Q block, KV partition) pair has a
-// FULL prefix and a PARTIAL middle whose lengths are found by binary search.
+// The builder reproduces the host's list (plan.h): the Section 3.7 rule per
+// block pair, runs in KV-list order, and the order table, with one workgroup
+// of 1024 threads.  Along one KV partition a Q block's classes only fall
+// (positions grow with the row under both layouts), so each (Q block, KV
+// partition) pair has a FULL prefix and a PARTIAL middle whose lengths are
+// found by binary search.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -24,11 +23,12 @@
 namespace mesh_attn {
 namespace {
 
-// The scratch array of the allocation-free forward: kNoAllocScratchBytes on
-// every GPU the library runs on, held until the process ends.  Host code
+// The scratch arrays of the allocation-free forward, on every GPU the library
+// runs on, held until the process ends: the lists, and the partial results.  Host code
 // must never pass its name to a kernel (the name is a host-side stand-in):
 // noalloc_scratch() gives the device address.
-__device__ __align__(256) char scratch[kNoAllocScratchBytes];
+__device__ __align__(256) char scratch[kNoAllocScratchBytes +
+                                       kNoAllocTableBytes];
 __device__ __align__(256) char part_scratch[kNoAllocPartBytes];
 
 constexpr int kBuildThreads = 1024;
@@ -92,96 +92,56 @@ __device__ int32_t run_delta(const PlanBuildParams& p, const PairRuns& r,
                               tok_pos(p, r.kp, k_row0));
 }
 
-// Positions of a split tile's pieces in its order.  All heads are cut alike,
-// so the pieces of one head (length, row, index) are ranked once and every
-// head's slots follow from the ranks.
-__device__ void split_order(const PlanBuildParams& p, const int* s_work) {
-  __shared__ int s_len[kSplitMaxPieces];
-  __shared__ uint16_t s_row[kSplitMaxPieces], s_idx[kSplitMaxPieces];
-  __shared__ int s_pre[kSplitMaxRows + 1], s_cut[kSplitMaxRows + 1];
-  const int t = threadIdx.x;
-  const int m = p.row_pieces;
-  // First piece, and first split row, of every row: a serial pass by one
-  // wave's lanes is short because a split tile has few rows per head.
-  if (t == 0) {
-    int at = 0, parts = 0, splits = 0;
-    for (int qb = 0; qb < p.nqb; ++qb) {
-      const int n = split::num_pieces(p.cut, qb, s_work[qb]);
-      s_pre[qb] = at;
-      s_cut[qb] = n > 1 ? parts : -1;
-      at += n;
-      if (n > 1) {
-        parts += n;
-        ++splits;
+// The runs of Q block qb, FULL runs that continue each other in the KV buffer
+// as one; emit(run) for each.  Returns the blocks.
+template <class F>
+__device__ int row_runs(const PlanBuildParams& p, int qb, F emit) {
+  int work = 0;
+  DevRun full{0, 0, MA_CLS_FULL, 0};  // the FULL run being extended
+  for (int b = 0; b < p.nkv; ++b) {
+    const PairRuns r = pair_runs(p, qb, b);
+    work += r.nvis;
+    if (r.nfull > 0) {
+      const int blk0 = b * p.nkbp;
+      if (full.nblk > 0 && full.blk0 + full.nblk == blk0) {
+        full.nblk += r.nfull;
+      } else {
+        if (full.nblk > 0) emit(full);
+        full = DevRun{blk0, r.nfull, MA_CLS_FULL, run_delta(p, r, 0)};
       }
     }
-    s_pre[p.nqb] = parts;
-    s_cut[p.nqb] = splits;
-  }
-  __syncthreads();
-  const int parts = s_pre[p.nqb], splits = s_cut[p.nqb];
-  for (int qb = t; qb < p.nqb; qb += kBuildThreads) {
-    const int w = s_work[qb], n = split::num_pieces(p.cut, qb, w);
-    for (int j = 0; j < n; ++j) {
-      const int i = s_pre[qb] + j;
-      s_len[i] = split::piece_begin(w, n, j + 1) - split::piece_begin(w, n, j);
-      s_row[i] = qb;
-      s_idx[i] = j;
-    }
-    if (n > 1) {
-      int before = 0;
-      for (int b2 = 0; b2 < qb; ++b2) before += s_cut[b2] >= 0;
-      for (int h = 0; h < p.hq; ++h)
-        p.splits[h * splits + before] =
-            DevSplit{qb, h, h * parts + s_cut[qb], n};
+    if (r.nvis > r.nfull) {
+      if (full.nblk > 0) emit(full);
+      full.nblk = 0;
+      emit(DevRun{b * p.nkbp + r.nfull, r.nvis - r.nfull, MA_CLS_PARTIAL,
+                  run_delta(p, r, r.nfull)});
     }
   }
-  __syncthreads();
-  const int total = m * p.hq;
-  const bool by_kv = p.hkv % kNumXcd == 0;
-  for (int i = t; i < m; i += kBuildThreads) {
-    const int len = s_len[i], idx = s_idx[i], qb = s_row[i];
-    // Rank by length (several rounds) or by piece index (one round).
-    int gt = 0, eq = 0, eq_before = 0;
-    for (int i2 = 0; i2 < m; ++i2) {
-      const bool less = total > kFwdPass.slots ? s_len[i2] > len : s_idx[i2] < idx;
-      const bool same = total > kFwdPass.slots ? s_len[i2] == len : s_idx[i2] == idx;
-      gt += less;
-      eq += same;
-      eq_before += same & (i2 < i);
-    }
-    const int w = s_work[qb], n = split::num_pieces(p.cut, qb, w);
-    int run = p.qblk_ptr[qb], off = split::piece_begin(w, n, idx);
-    while (off > 0 && off >= p.runs[run].nblk) off -= p.runs[run++].nblk;
-    for (int h = 0; h < p.hq; ++h) {
-      const int slot = split_slot(total, m, p.hq, p.group, by_kv, h, gt, eq,
-                                  eq_before, kFwdPass.slots);
-      p.order[slot] = make_int2(qb, h);
-      p.pieces[slot] = DevPiece{
-          run, off, len, s_cut[qb] < 0 ? -1 : h * parts + s_cut[qb] + idx, 0};
-    }
-  }
+  if (full.nblk > 0) emit(full);
+  return work;
 }
 
 __global__ __launch_bounds__(kBuildThreads) void fwd_plan_build_kernel(
     PlanBuildParams p) {
   __shared__ int s_work[kNoAllocMaxQBlocks];
+  __shared__ int s_run[kNoAllocMaxQBlocks];     // first run of each Q block
+  // Split tiles: blocks and Q block of each piece (before ranking), first piece
+  // and first partial (or -1) of each Q block.  Whole items: piece i is Q
+  // block i.
+  __shared__ int s_len[kSplitMaxPieces];
+  __shared__ uint16_t s_row[kSplitMaxPieces];
+  __shared__ uint16_t s_pre[kSplitMaxRows];
+  __shared__ int16_t s_part[kSplitMaxRows];
   __shared__ int s_scan[kBuildThreads];
   const int t = threadIdx.x;
+  const bool cut = p.cut.c > 0;
   // Thread t owns a contiguous segment of Q blocks for the run list.
   const int seg = (p.nqb + kBuildThreads - 1) / kBuildThreads;
   const int lo = min(t * seg, p.nqb);
   const int hi = min(lo + seg, p.nqb);
   int cnt = 0;
-  for (int qb = lo; qb < hi; ++qb) {
-    int work = 0;
-    for (int b = 0; b < p.nkv; ++b) {
-      const PairRuns r = pair_runs(p, qb, b);
-      cnt += (r.nfull > 0) + (r.nvis > r.nfull);
-      work += r.nvis;
-    }
-    s_work[qb] = work;
-  }
+  for (int qb = lo; qb < hi; ++qb)
+    s_work[qb] = row_runs(p, qb, [&](const DevRun&) { ++cnt; });
   s_scan[t] = cnt;
   __syncthreads();
   // Inclusive scan of the segment counts (Hillis-Steele).
@@ -193,54 +153,61 @@ __global__ __launch_bounds__(kBuildThreads) void fwd_plan_build_kernel(
   }
   int at = s_scan[t] - cnt;
   for (int qb = lo; qb < hi; ++qb) {
-    p.qblk_ptr[qb] = at;
-    for (int b = 0; b < p.nkv; ++b) {
-      const PairRuns r = pair_runs(p, qb, b);
-      if (r.nfull > 0)
-        p.runs[at++] = DevRun{b * p.nkbp, r.nfull, MA_CLS_FULL,
-                              run_delta(p, r, 0)};
-      if (r.nvis > r.nfull)
-        p.runs[at++] = DevRun{b * p.nkbp + r.nfull, r.nvis - r.nfull,
-                              MA_CLS_PARTIAL, run_delta(p, r, r.nfull)};
-    }
+    s_run[qb] = at;
+    row_runs(p, qb, [&](const DevRun& r) { p.runs[at++] = r; });
   }
-  if (t == kBuildThreads - 1) p.qblk_ptr[p.nqb] = s_scan[t];
-  if (p.cut.c > 0) {
-    __syncthreads();  // the runs, read back below
-    split_order(p, s_work);
-    if (t < kNumXcd) p.queue[t] = 0;
-    return;
-  }
-
-  // Workgroup order.  Items (Q block, head) sorted by (work descending, head,
-  // Q block); with the KV heads a multiple of the XCD count, the items of KV
-  // head x go to XCD x % 8 (slot j * 8 + x), else item i takes slot i.
-  const bool by_kv = p.hkv % kNumXcd == 0;
-  for (int qb = t; qb < p.nqb; qb += kBuildThreads) {
-    const int w = s_work[qb];
-    int gt = 0, eq = 0, eq_before = 0;
-    for (int b2 = 0; b2 < p.nqb; ++b2) {
-      const int w2 = s_work[b2];
-      gt += w2 > w;
-      eq += w2 == w;
-      eq_before += (w2 == w) & (b2 < qb);
-    }
-    for (int h = 0; h < p.hq; ++h) {
-      int slot;
-      if (by_kv) {
-        const int kvh = h / p.group;
-        const int lane_heads = p.hq / kNumXcd;
-        const int heads_before = (kvh / kNumXcd) * p.group + h % p.group;
-        slot = (gt * lane_heads + eq * heads_before + eq_before) * kNumXcd +
-               kvh % kNumXcd;
-      } else {
-        slot = gt * p.hq + h * eq + eq_before;
+  const int n_runs = s_scan[kBuildThreads - 1];
+  if (cut) {
+    // A split tile has few Q blocks per head: one thread walks them.
+    if (t == 0) {
+      int pre = 0, parts = 0, splits = 0;
+      for (int qb = 0; qb < p.nqb; ++qb) {
+        const int n = split::num_pieces(p.cut, qb, s_work[qb]);
+        s_pre[qb] = static_cast<uint16_t>(pre);
+        s_part[qb] = static_cast<int16_t>(n > 1 ? parts : -1);
+        if (n > 1) {
+          p.splits[splits++] = DevSplit{qb, parts, n};
+          parts += n;
+        }
+        pre += n;
       }
-      p.order[slot] = make_int2(qb, h);
+    }
+    __syncthreads();
+    for (int qb = t; qb < p.nqb; qb += kBuildThreads) {
+      const int w = s_work[qb], n = split::num_pieces(p.cut, qb, w);
+      for (int j = 0; j < n; ++j) {
+        s_row[s_pre[qb] + j] = static_cast<uint16_t>(qb);
+        s_len[s_pre[qb] + j] =
+            split::piece_begin(w, n, j + 1) - split::piece_begin(w, n, j);
+      }
     }
   }
-  for (int slot = p.nqb * p.hq + t; slot < p.grid; slot += kBuildThreads)
-    p.order[slot] = make_int2(-1, -1);
+  __syncthreads();  // and the runs, read back below
+  // Ranks: longest first, or in one round by piece index; ties in table order.
+  const int* len_of = cut ? s_len : s_work;
+  const bool by_len = p.mode != kModeOneRound;
+  for (int i = t; i < p.m; i += kBuildThreads) {
+    const int qb = cut ? s_row[i] : i, idx = cut ? i - s_pre[qb] : 0;
+    const int len = len_of[i];
+    int before = 0, same = 0, same_before = 0;
+    for (int i2 = 0; i2 < p.m; ++i2) {
+      const int k2 = by_len ? -len_of[i2] : i2 - s_pre[s_row[i2]];
+      const int k = by_len ? -len : idx;
+      before += k2 < k;
+      same += k2 == k;
+      same_before += (k2 == k) & (i2 < i);
+    }
+    const int run_b = s_run[qb], run_e = qb + 1 < p.nqb ? s_run[qb + 1] : n_runs;
+    int run = run_b, off = 0;
+    if (idx > 0) {
+      const int w = s_work[qb];
+      off = split::piece_begin(w, split::num_pieces(p.cut, qb, w), idx);
+      while (off >= p.runs[run].nblk) off -= p.runs[run++].nblk;
+    }
+    const int part = cut && s_part[qb] >= 0 ? s_part[qb] + idx : -1;
+    p.rows[before + same_before] = DevRow{qb,   run, off,   len,   part,
+                                          0,    run_b, run_e, before, same};
+  }
   if (t < kNumXcd) p.queue[t] = 0;
 }
 

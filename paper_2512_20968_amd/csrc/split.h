@@ -143,35 +143,61 @@ inline Cut choose(const int32_t* w, int32_t n, int32_t heads,
 
 }  // namespace split
 
-// Slot of a piece in the order of a split tile of `total` pieces, m per head.
-// `before`, `same` and `same_before` count the pieces of one head that rank
-// before it, equal to it, and equal to it with a lower index.  More pieces
-// than run at once: ranked longest first; lane x (slots j * 8 + x) holds the
-// pieces of KV heads x, x + 8, .. if the KV heads allow it, else pieces are
-// dealt round robin.  One round: ranked by piece index, and consecutive
-// pieces of a KV head share a lane, because they walk the same keys.
-constexpr int kXcdLanes = 8;
-__host__ __device__ inline int split_slot(int total, int m, int heads,
-                                          int group, bool by_kv, int h,
-                                          int before, int same,
-                                          int same_before, int slots) {
-  const int kvh = h / group, hg = h % group;
-  if (total <= slots) {
-    const int pos = kvh * group * m + before * group + hg * same + same_before;
-    const int len = total / kXcdLanes, more = total % kXcdLanes;
-    const int cut = more * (len + 1);  // pieces in the longer lanes
-    const int x = pos < cut ? pos / (len + 1) : more + (pos - cut) / len;
-    const int j = pos < cut ? pos % (len + 1) : (pos - cut) % len;
-    return j * kXcdLanes + x;
-  }
-  if (by_kv) {
-    const int lane_heads = heads / kXcdLanes;
-    const int heads_before = (kvh / kXcdLanes) * group + hg;
-    return (before * lane_heads + same * heads_before + same_before) *
-               kXcdLanes +
-           kvh % kXcdLanes;
-  }
-  return before * heads + h * same + same_before;
+// gfx950 (MI355X) has 8 XCDs; consecutive workgroup ids are dispatched to
+// XCDs round robin, so id i runs on XCD i % 8.
+constexpr int kNumXcd = 8;
+
+// How the slots of a launch map to the pieces of one head, ranked, times the
+// heads.  Plain: rank by rank, the heads of equal ranks together.  By KV
+// head: XCD x (slots j * 8 + x) gets the pieces of KV heads x, x + 8, .., so
+// that they share K and V in its L2 (KV heads a multiple of 8).  One round
+// (a split tile of no more pieces than run at once, ranked by piece index):
+// consecutive pieces of a KV head, which walk the same keys, share an XCD.
+enum { kModePlain = 0, kModeByKv = 1, kModeOneRound = 2 };
+
+__host__ __device__ inline int split_mode(int64_t total, bool is_split,
+                                          bool by_kv, int32_t slots) {
+  if (is_split && total <= slots) return kModeOneRound;
+  return by_kv ? kModeByKv : kModePlain;
+}
+
+// Place of a slot: the KV-head and rank group it falls into.  A first look at
+// entry `probe` of the ranked table gives its class, the entries [before,
+// before + same) of equal rank; place_in_class then gives entry and head.
+struct SlotPlace {
+  int32_t probe;  // table entry whose class holds the slot
+  int32_t at;     // position within the heads that share the class's line
+  int32_t base;   // first KV head of that line
+};
+
+// m table entries, `heads` heads, `group` heads per KV head; slot < m * heads.
+__host__ __device__ inline SlotPlace place_slot(int mode, int slot, int m,
+                                                int heads, int group) {
+  if (mode == kModePlain) return {slot / heads, slot, 0};
+  const int x = slot % kNumXcd, j = slot / kNumXcd;
+  if (mode == kModeByKv) return {j / (heads / kNumXcd), j, x};
+  const int total = m * heads;
+  const int len = total / kNumXcd, more = total % kNumXcd;
+  const int pos = x < more ? x * (len + 1) + j : more + x * len + j;
+  const int kvh = pos / (group * m), at = pos - kvh * group * m;
+  return {at / group, at, kvh};
+}
+
+// Entry and head of the slot, given its class.
+__host__ __device__ inline void place_in_class(int mode, const SlotPlace& s,
+                                               int before, int same, int heads,
+                                               int group, int* entry,
+                                               int* head) {
+  const int line = mode == kModePlain  ? heads
+                   : mode == kModeByKv ? heads / kNumXcd
+                                       : group;
+  const int q = s.at - before * line;
+  const int hl = q / same;  // head within the line
+  *entry = before + q % same;
+  *head = mode == kModePlain ? hl
+          : mode == kModeByKv
+              ? (hl / group * kNumXcd + s.base) * group + hl % group
+              : s.base * group + hl;
 }
 
 }  // namespace mesh_attn

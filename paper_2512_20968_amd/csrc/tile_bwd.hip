@@ -52,10 +52,30 @@ static_assert(BQ == 2 * SUB && BK == 2 * SUB, "two stages per block");
 // ---------------------------------------------------------------------------
 // 1. prep: delta and the log2-domain LSE
 // ---------------------------------------------------------------------------
+// The first plan_wgs workgroups copy the work lists of the two passes to the
+// workspace, from pinned host memory or from the kernel's second argument.
+constexpr size_t kBlobOffset =
+    (sizeof(BwdParams) + alignof(PlanBlob) - 1) / alignof(PlanBlob) *
+    alignof(PlanBlob);
+
 template <int D>
-__global__ __launch_bounds__(NT) void bwd_prep_kernel(BwdParams p) {
+__global__ __launch_bounds__(NT) void bwd_prep_kernel(BwdParams p, PlanBlob) {
   constexpr int LPI = D / 8;  // lanes per (row, head)
-  const int64_t gid = int64_t{blockIdx.x} * NT + threadIdx.x;
+  const int plan_wgs = (p.plan_bytes / 16 + NT - 1) / NT;
+  if (static_cast<int>(blockIdx.x) < plan_wgs) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const char* src =
+        p.plan_src ? static_cast<const char*>(p.plan_src)
+                   : (const char*)__builtin_amdgcn_kernarg_segment_ptr() +
+                         kBlobOffset;
+    const int i = blockIdx.x * NT + threadIdx.x;
+    if (i < p.plan_bytes / 16)
+      static_cast<f32x4*>(p.plan_dst)[i] =
+          reinterpret_cast<const f32x4*>(src)[i];
+#endif
+    return;
+  }
+  const int64_t gid = int64_t{blockIdx.x - plan_wgs} * NT + threadIdx.x;
   const int64_t item = gid / LPI;  // row * hq + h
   const int sub = static_cast<int>(gid % LPI);
   const bool valid = item < p.rows_q * p.hq;
@@ -210,14 +230,15 @@ constexpr int NT_KV = 512;  // dK/dV: eight waves
 // reads stage t-1 while the dV role reads t and loads t+1).
 template <int D, int ROLE>
 __device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem,
-                                          int kvblk, int hk, int run_b,
-                                          int run_e, const DevPiece& pc,
-                                          int wave, int lane) {
+                                          const DevRow& pc, int hk, int wave,
+                                          int lane) {
   using L = DkdvLayout<D>;
   const int li = lane & 31;
   const int lh = lane >> 5;
   const int kw = wave & 3;
   const int k_in_blk = kw * 32 + li;
+  const int kvblk = pc.row;
+  const DevRun* runs = p.kvorder.runs;
   const int64_t kv_row = int64_t{kvblk} * BK + k_in_blk;
 
   // dV role: K fragments (B operand of S); dK role: V fragments (of dP).
@@ -243,11 +264,11 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem,
         c.s = 0;
         if (++c.off == c.run.nblk) {
           c.off = 0;
-          if (++c.r == run_e) {
-            c.r = run_b;
+          if (++c.r == pc.run_e) {
+            c.r = pc.run_b;
             ++c.g;
           }
-          c.run = load_const(p.kvruns, c.r);
+          c.run = load_const(runs, c.r);
         }
       }
       return c;
@@ -279,7 +300,7 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem,
     // j lives in buffer j % 3 (its previous occupant, stage j-3, was last
     // read by the dK role in iteration j-2) and its P in P buffer j % 2.
     Cur lc{pc.walk, pc.run, pc.off, 0,
-           load_const(p.kvruns, pc.run)};  // next load
+           load_const(runs, pc.run)};  // next load
     Cur cc_ = lc;  // stage this wave computes next
     issue(lc, 0);
     lc = advance(lc);
@@ -406,7 +427,8 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem,
   float* out = ROLE == 0 ? p.dv : p.dk;
   const float sc_out = ROLE == 0 ? 1.f : p.scale;
   if (pc.part >= 0) {
-    float* po = p.kvparts + (int64_t{pc.part} * 2 + ROLE) * BK * D;
+    const int64_t slot = int64_t{hk} * p.kvorder.parts + pc.part;
+    float* po = p.kvparts + (slot * 2 + ROLE) * BK * D;
 #pragma unroll
     for (int c = 0; c < D / 32; ++c)
 #pragma unroll
@@ -442,28 +464,17 @@ __global__ __launch_bounds__(NT_KV, 1) void bwd_dkdv_kernel(BwdParams p) {
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63;
-  const int slot = queued_slot(p.kv_items, p.kvqueue,
+  const DevOrder& order = p.kvorder;
+  const int slot = queued_slot(order.n_items, order.queue,
                                reinterpret_cast<int*>(smem + DkdvLayout<D>::SMEM));
   if (slot < 0) return;
-  const int2 item = load_const(p.kvorder, slot);
-  const int kvblk = item.x;
-  const int hk = item.y;
-  const int run_b = load_const(p.kvblk_ptr, kvblk);
-  const int run_e = load_const(p.kvblk_ptr, kvblk + 1);
-  // The whole item (its runs once per query head of the group), or on a split
-  // tile this workgroup's piece of it.
-  DevPiece pc{run_b, 0, 0, -1, 0};
-  if (p.kvpieces) {
-    pc = load_const(p.kvpieces, slot);
-  } else {
-    for (int r = run_b; r < run_e; ++r)
-      pc.nblk += load_const(p.kvruns, r).nblk;
-    pc.nblk *= p.group;
-  }
+  // The whole item (its runs once per query head of the group), or a piece.
+  int hk;
+  const DevRow pc = load_slot(order, slot, p.hkv, 1, &hk);
   if (wave < 4)
-    dkdv_role<D, 0>(p, smem, kvblk, hk, run_b, run_e, pc, wave, lane);
+    dkdv_role<D, 0>(p, smem, pc, hk, wave, lane);
   else
-    dkdv_role<D, 1>(p, smem, kvblk, hk, run_b, run_e, pc, wave, lane);
+    dkdv_role<D, 1>(p, smem, pc, hk, wave, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -486,21 +497,15 @@ __global__ __launch_bounds__(NT, 1) void bwd_dq_kernel(BwdParams p) {
   const int li = lane & 31;
   const int lh = lane >> 5;
 
-  const int slot = queued_slot(p.q_items, p.qqueue,
+  const DevOrder& order = p.qorder;
+  const int slot = queued_slot(order.n_items, order.queue,
                                reinterpret_cast<int*>(smem + L::SMEM));
   if (slot < 0) return;
-  const int2 item = load_const(p.qorder, slot);
-  const int qblk = item.x;
-  const int h = item.y;
+  // The whole item, or a piece of it.
+  int h;
+  const DevRow pc = load_slot(order, slot, p.hq, p.group, &h);
+  const int qblk = pc.row;
   const int hk = h / p.group;
-  // The whole item, or on a split tile this workgroup's piece of it.
-  DevPiece pc{load_const(p.qblk_ptr, qblk), 0, 0, -1, 0};
-  if (p.qpieces) {
-    pc = load_const(p.qpieces, slot);
-  } else {
-    const int run_e = load_const(p.qblk_ptr, qblk + 1);
-    for (int r = pc.run; r < run_e; ++r) pc.nblk += load_const(p.qruns, r).nblk;
-  }
   const int q_in_blk = wave * 32 + li;
   const int64_t q_row = int64_t{qblk} * BQ + q_in_blk;
 
@@ -528,7 +533,7 @@ __global__ __launch_bounds__(NT, 1) void bwd_dq_kernel(BwdParams p) {
         if (++c.off == c.run.nblk) {
           c.off = 0;
           ++c.r;
-          if (*valid) c.run = load_const(p.qruns, c.r);
+          if (*valid) c.run = load_const(order.runs, c.r);
         }
       }
       return c;
@@ -540,7 +545,7 @@ __global__ __launch_bounds__(NT, 1) void bwd_dq_kernel(BwdParams p) {
       load_stage_tile<D>(p.v, row0, p.hkv, hk, base + L::TILE, wave, lane);
     };
 
-    Cur cur{pc.run, pc.off, 0, 2 * pc.nblk, load_const(p.qruns, pc.run)};
+    Cur cur{pc.run, pc.off, 0, 2 * pc.nblk, load_const(order.runs, pc.run)};
     issue(cur, 0);
 #pragma unroll
     for (int kk = 0; kk < D / 16; ++kk) {
@@ -628,7 +633,8 @@ __global__ __launch_bounds__(NT, 1) void bwd_dq_kernel(BwdParams p) {
   // Register 4g+t of chunk cc holds dim 32cc + 8g + 4lh + t of query q_row.
   // With accumulate, all old values are read before the first store.
   if (pc.part >= 0) {
-    float* po = p.qparts + (int64_t{pc.part} * BQ + q_in_blk) * D;
+    const int64_t slot_p = int64_t{h} * order.parts + pc.part;
+    float* po = p.qparts + (slot_p * BQ + q_in_blk) * D;
 #pragma unroll
     for (int cc = 0; cc < D / 32; ++cc)
 #pragma unroll
@@ -681,20 +687,23 @@ struct SumLayout {
 template <int D>
 __global__ __launch_bounds__(NT) void bwd_sum_kernel(BwdParams p) {
   using L = SumLayout<D>;
-  const int kv_wgs = p.n_kvsplits * 2 * L::GPT;
+  const int kv_wgs = p.kvorder.n_splits * p.hkv * 2 * L::GPT;
   const bool kv = static_cast<int>(blockIdx.x) < kv_wgs;
   const int wg = kv ? blockIdx.x : blockIdx.x - kv_wgs;
   const int si = wg / (kv ? 2 * L::GPT : L::GPT);
   const int role = kv ? wg / L::GPT % 2 : 0;  // 0: dV (or dQ), 1: dK
-  const DevSplit it = load_const(kv ? p.kvsplits : p.qsplits, si);
+  const DevOrder& order = kv ? p.kvorder : p.qorder;
+  const int head = si / order.n_splits;
+  const DevSplit it = load_const(order.splits, si - head * order.n_splits);
+  const int64_t part0 = int64_t{head} * order.parts + it.part;
   const int row = wg % L::GPT * L::RPB + threadIdx.x / L::LPR;
   const int col = threadIdx.x % L::LPR * 4;
   const int64_t stride = (kv ? 2 : 1) * 128 * D;  // floats per partial slot
-  const float* src = (kv ? p.kvparts : p.qparts) + it.part0 * stride +
+  const float* src = (kv ? p.kvparts : p.qparts) + part0 * stride +
                      (role * 128 + row) * D + col;
   const int heads = kv ? p.hkv : p.hq;
   float* out = (kv ? (role ? p.dk : p.dv) : p.dq) +
-               ((int64_t{it.blk} * 128 + row) * heads + it.head) * D + col;
+               ((int64_t{it.row} * 128 + row) * heads + head) * D + col;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
   if (p.accumulate) acc = *reinterpret_cast<const f32x4*>(out);
   constexpr int B = 4;  // partials in flight
@@ -715,7 +724,7 @@ __global__ __launch_bounds__(NT) void bwd_sum_kernel(BwdParams p) {
 }
 
 template <int D>
-hipError_t launch(const BwdParams& p, int grid_q, int grid_kv,
+hipError_t launch(const BwdParams& p, const PlanBlob& blob,
                   hipStream_t stream) {
   // + one int for the item slot of a queued workgroup
   const size_t smem_kv = DkdvLayout<D>::SMEM + 16;
@@ -726,25 +735,27 @@ hipError_t launch(const BwdParams& p, int grid_q, int grid_kv,
     if (e != hipSuccess) return e;
   }
   const int64_t prep_threads = p.rows_q * p.hq * (D / 8);
-  const int prep_grid = static_cast<int>((prep_threads + NT - 1) / NT);
+  const int plan_wgs = (p.plan_bytes / 16 + NT - 1) / NT;
+  const int prep_grid =
+      plan_wgs + static_cast<int>((prep_threads + NT - 1) / NT);
   hipLaunchKernelGGL(bwd_prep_kernel<D>, dim3(prep_grid), dim3(NT), 0, stream,
-                     p);
+                     p, blob);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (grid_kv > 0) {
-    hipLaunchKernelGGL(bwd_dkdv_kernel<D>, dim3(grid_kv), dim3(NT_KV), smem_kv,
-                       stream, p);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  if (grid_q > 0) {
-    hipLaunchKernelGGL(bwd_dq_kernel<D>, dim3(grid_q), dim3(NT), smem_q,
-                       stream, p);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  const int sums =
-      (2 * p.n_kvsplits + p.n_qsplits) * SumLayout<D>::GPT;
+  hipLaunchKernelGGL(
+      bwd_dkdv_kernel<D>,
+      dim3(static_cast<int>(queued_launch_grid(p.kvorder.n_items))),
+      dim3(NT_KV), smem_kv, stream, p);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(
+      bwd_dq_kernel<D>,
+      dim3(static_cast<int>(queued_launch_grid(p.qorder.n_items))), dim3(NT),
+      smem_q, stream, p);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const int sums = (2 * p.kvorder.n_splits * p.hkv +
+                    p.qorder.n_splits * p.hq) * SumLayout<D>::GPT;
   if (sums > 0) {
     hipLaunchKernelGGL(bwd_sum_kernel<D>, dim3(sums), dim3(NT), 0, stream, p);
     e = hipGetLastError();
@@ -754,10 +765,10 @@ hipError_t launch(const BwdParams& p, int grid_q, int grid_kv,
 
 }  // namespace
 
-hipError_t launch_tile_bwd(const BwdParams& p, int head_dim, int grid_q,
-                           int grid_kv, hipStream_t stream) {
-  if (head_dim == 128) return launch<128>(p, grid_q, grid_kv, stream);
-  if (head_dim == 64) return launch<64>(p, grid_q, grid_kv, stream);
+hipError_t launch_tile_bwd(const BwdParams& p, const PlanBlob& blob,
+                           int head_dim, hipStream_t stream) {
+  if (head_dim == 128) return launch<128>(p, blob, stream);
+  if (head_dim == 64) return launch<64>(p, blob, stream);
   return hipErrorInvalidValue;
 }
 

@@ -59,15 +59,6 @@ __device__ __forceinline__ int queued_slot(int n_items, int32_t* queue,
   return __builtin_amdgcn_readfirstlane(*s_slot);
 }
 
-__device__ __forceinline__ f32x16 mfma32(const bf16x8& a, const bf16x8& b,
-                                         const f32x16& c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-}
-
-__device__ __forceinline__ float exp2_fast(float x) {
-  return __builtin_amdgcn_exp2f(x);
-}
-
 // Read-only kernel data (work lists) through the constant address space: the
 // compiler may then always use scalar loads for uniform addresses, whatever
 // else the kernel does.
@@ -81,6 +72,26 @@ __device__ __forceinline__ T load_const(const T* p, int64_t i) {
 #else
   return p[i];
 #endif
+}
+
+// Table entry and head of an order slot.
+__device__ __forceinline__ DevRow load_slot(const DevOrder& o, int slot,
+                                            int heads, int group, int* head) {
+  const SlotPlace at = place_slot(o.mode, slot, o.m, heads, group);
+  DevRow e = load_const(o.rows, at.probe);
+  int entry;
+  place_in_class(o.mode, at, e.before, e.same, heads, group, &entry, head);
+  if (entry != at.probe) e = load_const(o.rows, entry);
+  return e;
+}
+
+__device__ __forceinline__ f32x16 mfma32(const bf16x8& a, const bf16x8& b,
+                                         const f32x16& c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ float exp2_fast(float x) {
+  return __builtin_amdgcn_exp2f(x);
 }
 
 // Workgroup barrier for LDS-only hand-offs: waits for this wave's own LDS

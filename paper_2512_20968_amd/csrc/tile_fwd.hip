@@ -80,6 +80,7 @@ struct FwdLayout {
 // Position in the flattened list of KV blocks of one Q block's runs, with the
 // number of blocks left in this workgroup's piece of it.
 struct Cursor {
+  const DevRun* runs;
   DevRun run;
   int r, off, left;
 };
@@ -97,13 +98,13 @@ __device__ __forceinline__ Blk block_at(const Cursor& c) {
              c.run.delta - c.off * BN};
 }
 
-__device__ __forceinline__ Cursor next_block(const FwdParams& p, Cursor c) {
+__device__ __forceinline__ Cursor next_block(Cursor c) {
   if (c.left <= 0) return c;
   --c.left;
   if (++c.off == c.run.nblk) {
     c.off = 0;
     ++c.r;
-    if (c.left > 0) c.run = load_const(p.runs, c.r);
+    if (c.left > 0) c.run = load_const(c.runs, c.r);
   }
   return c;
 }
@@ -111,8 +112,29 @@ __device__ __forceinline__ Cursor next_block(const FwdParams& p, Cursor c) {
 // Row order of a 32-key tile as fed to the MFMA: swap bits 2 and 3.
 __device__ __forceinline__ int key_perm(int r) { return mfma_row_perm(r); }
 
+// The order of the launch; a list that travels in the kernel's arguments is
+// read there (the PlanBlob is the second argument).
+constexpr size_t kBlobOffset =
+    (sizeof(FwdParams) + alignof(PlanBlob) - 1) / alignof(PlanBlob) *
+    alignof(PlanBlob);
+
+__device__ __forceinline__ DevOrder order_of(const FwdParams& p) {
+  DevOrder o = p.order;
+#if defined(__HIP_DEVICE_COMPILE__)
+  if (o.inline_list) {
+    const char* blob =
+        (const char*)__builtin_amdgcn_kernarg_segment_ptr() + kBlobOffset;
+    o.rows = reinterpret_cast<const DevRow*>(blob);
+    o.runs = reinterpret_cast<const DevRun*>(blob + o.off_runs);
+    o.splits = reinterpret_cast<const DevSplit*>(blob + o.off_splits);
+  }
+#endif
+  return o;
+}
+
 template <int D, bool OUT_F32>
-__global__ __launch_bounds__(NT, 1) void tile_fwd_kernel(FwdParams p) {
+__global__ __launch_bounds__(NT, 1) void tile_fwd_kernel(FwdParams p,
+                                                             PlanBlob) {
   using L = FwdLayout<D>;
   extern __shared__ __align__(16) char smem[];
 
@@ -126,30 +148,20 @@ __global__ __launch_bounds__(NT, 1) void tile_fwd_kernel(FwdParams p) {
   const int li = lane & 31;
   const int lh = lane >> 5;
 
-  // Item (order slot; see queued_static_slots).
-  const int slot = queued_slot(p.n_items, p.queue,
+  // Item, or piece of one (order slot; see queued_static_slots).
+  const DevOrder order = order_of(p);
+  const int slot = queued_slot(order.n_items, order.queue,
                                reinterpret_cast<int*>(smem + L::SMEM));
   if (slot < 0) return;
-  const int2 item = load_const(p.order, slot);
-  const int qblk = item.x;
-  const int h = item.y;
+  int h;
+  const DevRow item = load_slot(order, slot, p.hq, p.group, &h);
+  const int qblk = item.row;
   const int hk = h / p.group;
-  // The whole item, or on a split tile this workgroup's piece of it.
   Cursor c0;
-  int part = -1;
-  if (p.pieces) {
-    const DevPiece pc = load_const(p.pieces, slot);
-    c0.r = pc.run;
-    c0.off = pc.off;
-    c0.left = pc.nblk;
-    part = pc.part;
-  } else {
-    c0.r = load_const(p.qblk_ptr, qblk);
-    c0.off = 0;
-    c0.left = 0;
-    const int run_e = load_const(p.qblk_ptr, qblk + 1);
-    for (int r = c0.r; r < run_e; ++r) c0.left += load_const(p.runs, r).nblk;
-  }
+  c0.runs = order.runs;
+  c0.r = item.run;
+  c0.off = item.off;
+  c0.left = item.nblk;
   const int nblocks = c0.left;
 
   const int64_t q_row = int64_t{qblk} * BM + wave * 32 + li;
@@ -166,7 +178,7 @@ __global__ __launch_bounds__(NT, 1) void tile_fwd_kernel(FwdParams p) {
   float l = 0.f;        // this lane's share of the row sum
 
   if (nblocks > 0) {
-    c0.run = load_const(p.runs, c0.r);
+    c0.run = load_const(c0.runs, c0.r);
     // Direct global -> LDS staging, done by the four waves of group B.
     // Wave wg of the group fills rows wg*RPW .. +RPW of a tile with NLI
     // loads of 1 KB; lane i of load j takes row wg*RPW + j*RPI + i/CPR and
@@ -360,7 +372,7 @@ __global__ __launch_bounds__(NT, 1) void tile_fwd_kernel(FwdParams p) {
     // Prologue (all waves): K(0), V(0) and K(1) into LDS (group B loads),
     // then the scores and probabilities of block 0.
     const Blk b0 = block_at(c0);
-    Cursor cu = next_block(p, c0);  // the block furthest ahead
+    Cursor cu = next_block(c0);  // the block furthest ahead
     Blk bs = block_at(cu);          // block whose scores X(n) computes (n+1)
     if (grp == 1) {
       load_k(b0.idx, 0);
@@ -396,14 +408,14 @@ __global__ __launch_bounds__(NT, 1) void tile_fwd_kernel(FwdParams p) {
         lds_barrier();
         if (bs.valid()) {
           softmax(snx, bs, pb, [](int) {});
-          cu = next_block(p, cu);
+          cu = next_block(cu);
           bs = block_at(cu);
         }
         lds_barrier();
       }
     } else {
       Blk bv = bs;  // V block to load next
-      cu = next_block(p, cu);
+      cu = next_block(cu);
       Blk bk = block_at(cu);  // K block to load next
       // Round n: K(n+2) and V(n+1), issued in slot 2n.  Issued as one burst
       // at the end of the softmax phase, the 2 NLI loads per wave held the
@@ -412,7 +424,7 @@ __global__ __launch_bounds__(NT, 1) void tile_fwd_kernel(FwdParams p) {
       // overlap the VALU work instead (about 5% faster overall).
       auto advance = [&]() {
         bv = bk;
-        cu = next_block(p, cu);
+        cu = next_block(cu);
         bk = block_at(cu);
       };
       {
@@ -462,9 +474,10 @@ __global__ __launch_bounds__(NT, 1) void tile_fwd_kernel(FwdParams p) {
   const float lt = l + __shfl_xor(l, 32);
   const float inv = lt > 0.f ? 1.f / lt : 0.f;
   const float lse2 = lt > 0.f ? m + __builtin_amdgcn_logf(lt) : -INFINITY;
-  if (part >= 0) {
+  if (item.part >= 0) {
     // A partial result: O normalised, float32, and the LSE in log2 units.
-    const int64_t prow = int64_t{part} * BM + q_in_blk;
+    const int64_t prow =
+        int64_t{h * order.parts + item.part} * BM + q_in_blk;
     if (lh == 0) p.part_lse[prow] = lse2;
 #pragma unroll
     for (int cc = 0; cc < D / 32; ++cc)
@@ -559,16 +572,20 @@ __global__ __launch_bounds__(NT, 1) void tile_fwd_kernel(FwdParams p) {
 constexpr int NTC = 256;
 
 template <int D, bool OUT_F32>
-__global__ __launch_bounds__(NTC) void fwd_combine_kernel(CombineParams p) {
+__global__ __launch_bounds__(NTC) void fwd_combine_kernel(FwdParams p,
+                                                          PlanBlob) {
   constexpr int LPR = D / 4;             // lanes per row
   constexpr int RPB = NTC / LPR;         // rows per workgroup
   constexpr int GPI = BM / RPB;          // workgroups per item
-  const DevSplit it = load_const(p.splits, blockIdx.x / GPI);
+  const DevOrder order = order_of(p);
+  const int si = blockIdx.x / GPI, h = si / order.n_splits;
+  const DevSplit it = load_const(order.splits, si - h * order.n_splits);
+  const int64_t part0 = int64_t{h} * order.parts + it.part;
   const int row = (blockIdx.x % GPI) * RPB + threadIdx.x / LPR;
   const int sub = threadIdx.x % LPR;
-  const int64_t q_row = int64_t{it.blk} * BM + row;
-  const int64_t lidx = int64_t{it.head} * p.rows_q + q_row;
-  const int64_t oidx = (q_row * p.hq + it.head) * D + sub * 4;
+  const int64_t q_row = int64_t{it.row} * BM + row;
+  const int64_t lidx = int64_t{h} * p.rows_q + q_row;
+  const int64_t oidx = (q_row * p.hq + h) * D + sub * 4;
   float M = -INFINITY, S = 0.f;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
   auto fold = [&](const f32x4& x, float lse) {
@@ -587,7 +604,7 @@ __global__ __launch_bounds__(NTC) void fwd_combine_kernel(CombineParams p) {
 #pragma unroll
     for (int u = 0; u < B; ++u) {
       const int k = min(k0 + u, it.nparts - 1);
-      const int64_t prow = int64_t{it.part0 + k} * BM + row;
+      const int64_t prow = (part0 + k) * BM + row;
       x[u] = *reinterpret_cast<const f32x4*>(p.part_o + prow * D + sub * 4);
       lv[u] = p.part_lse[prow];
     }
@@ -624,46 +641,50 @@ __global__ __launch_bounds__(NTC) void fwd_combine_kernel(CombineParams p) {
 }
 
 template <int D, bool F32>
-hipError_t combine(const CombineParams& p, int n_splits,
-                   hipStream_t stream) {
+hipError_t launch(const FwdParams& p, const PlanBlob& blob,
+                  hipStream_t stream) {
+  const size_t smem = FwdLayout<D>::SMEM + 16;  // + the item slot
+  hipError_t e = ensure_dynamic_lds<tile_fwd_kernel<D, F32>>(smem);
+  if (e != hipSuccess) return e;
+  const int grid = static_cast<int>(queued_launch_grid(p.order.n_items));
+  hipLaunchKernelGGL((tile_fwd_kernel<D, F32>), dim3(grid), dim3(NT), smem,
+                     stream, p, blob);
+  e = hipGetLastError();
+  if (e != hipSuccess || p.order.n_splits == 0) return e;
   constexpr int GPI = BM / (NTC / (D / 4));
-  hipLaunchKernelGGL((fwd_combine_kernel<D, F32>), dim3(n_splits * GPI),
-                     dim3(NTC), 0, stream, p);
+  hipLaunchKernelGGL((fwd_combine_kernel<D, F32>),
+                     dim3(p.order.n_splits * p.hq * GPI), dim3(NTC), 0, stream,
+                     p, blob);
   return hipGetLastError();
 }
 
-template <int D, bool F32>
-hipError_t launch(const FwdParams& p, int grid, hipStream_t stream) {
-  const size_t smem = FwdLayout<D>::SMEM + 16;  // + the item slot
-  const hipError_t e = ensure_dynamic_lds<tile_fwd_kernel<D, F32>>(smem);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((tile_fwd_kernel<D, F32>), dim3(grid), dim3(NT), smem,
-                     stream, p);
-  return hipGetLastError();
+// 16 bytes a lane.
+__global__ __launch_bounds__(NTC) void plan_copy_kernel(f32x4* dst,
+                                                        const f32x4* src,
+                                                        int n) {
+  const int i = blockIdx.x * NTC + threadIdx.x;
+  if (i < n) dst[i] = src[i];
 }
 
 }  // namespace
 
-hipError_t launch_fwd_combine(const CombineParams& p, int head_dim,
-                              bool out_f32, int n_splits,
-                              hipStream_t stream) {
-  if (head_dim == 128)
-    return out_f32 ? combine<128, true>(p, n_splits, stream)
-                   : combine<128, false>(p, n_splits, stream);
-  if (head_dim == 64)
-    return out_f32 ? combine<64, true>(p, n_splits, stream)
-                   : combine<64, false>(p, n_splits, stream);
-  return hipErrorInvalidValue;
+hipError_t launch_plan_copy(void* dst, const void* src, size_t bytes,
+                            hipStream_t stream) {
+  const int n = static_cast<int>(bytes / 16);
+  hipLaunchKernelGGL(plan_copy_kernel, dim3((n + NTC - 1) / NTC), dim3(NTC), 0,
+                     stream, static_cast<f32x4*>(dst),
+                     static_cast<const f32x4*>(src), n);
+  return hipGetLastError();
 }
 
-hipError_t launch_tile_fwd(const FwdParams& p, int head_dim, bool out_f32,
-                           int grid, hipStream_t stream) {
+hipError_t launch_tile_fwd(const FwdParams& p, const PlanBlob& blob,
+                           int head_dim, bool out_f32, hipStream_t stream) {
   if (head_dim == 128)
-    return out_f32 ? launch<128, true>(p, grid, stream)
-                   : launch<128, false>(p, grid, stream);
+    return out_f32 ? launch<128, true>(p, blob, stream)
+                   : launch<128, false>(p, blob, stream);
   if (head_dim == 64)
-    return out_f32 ? launch<64, true>(p, grid, stream)
-                   : launch<64, false>(p, grid, stream);
+    return out_f32 ? launch<64, true>(p, blob, stream)
+                   : launch<64, false>(p, blob, stream);
   return hipErrorInvalidValue;
 }
 
