@@ -441,7 +441,7 @@ int sides_of(int pass, const ma_problem_t* p, const int32_t* q_idx, int32_t nq,
   auto may = [&](const split::Pass& ps) { return may_split ? &ps : nullptr; };
   if (pass == 0) {
     out[0] = plan::Side{p,   q_idx, nq,   kFwdBM, sq, kv_idx, nkv, kFwdBN,
-                        skv, true,  p->num_q_heads, g, 1, may(kFwdPass)};
+                        skv, true,  p->num_q_heads, g, 1, may(fwd_pass(p->head_dim))};
     return 1;
   }
   out[0] = plan::Side{p,   q_idx, nq,   kBwdBM, sq, kv_idx, nkv, kBwdBN,
@@ -564,10 +564,10 @@ size_t fwd_split_bytes(const ma_problem_t* p, int32_t nq, int32_t nkv,
   const int64_t P = p->partition_len;
   const int64_t items = nq * (P / ch.num_q_chunks / kFwdBM) * p->num_q_heads;
   const int64_t blocks = nkv * (P / ch.num_kv_chunks / kFwdBN);
+  const split::Pass& ps = fwd_pass(p->head_dim);
   const int64_t counted =
-      any_chunk ? std::min<int64_t>(items, split::kMaxRounds * kFwdPass.slots)
-                : items;
-  const int64_t parts = split::parts_bound(counted, blocks, kFwdPass);
+      any_chunk ? std::min<int64_t>(items, ps.max_items) : items;
+  const int64_t parts = split::parts_bound(counted, blocks, ps);
   return split_bound(parts, fwd_part_bytes(p));
 }
 
@@ -595,9 +595,8 @@ BwdParts bwd_parts(const ma_problem_t* p, int32_t nq, int32_t nkv,
   const int64_t kv_items = nkb * p->num_kv_heads;
   const int64_t q_items = nqb * p->num_q_heads;
   auto parts = [&](int64_t items, int64_t blocks, const split::Pass& ps) {
-    const int64_t most = int64_t{split::kMaxRounds} * ps.slots;
-    return split::parts_bound(any_chunk ? std::min(items, most) : items,
-                              blocks, ps);
+    return split::parts_bound(
+        any_chunk ? std::min<int64_t>(items, ps.max_items) : items, blocks, ps);
   };
   const int32_t g = p->num_q_heads / p->num_kv_heads;
   BwdParts b{parts(kv_items, nqb * g, kDkdvPass),
@@ -645,7 +644,7 @@ int64_t parts_of(const ma_problem_t* p, int32_t nq, int32_t nkv,
   const int64_t P = p->partition_len;
   return split::parts_bound(
       nq * (P / ch.num_q_chunks / kFwdBM) * p->num_q_heads,
-      nkv * (P / ch.num_kv_chunks / kFwdBN), kFwdPass);
+      nkv * (P / ch.num_kv_chunks / kFwdBN), fwd_pass(p->head_dim));
 }
 
 // KV blocks that Q block `qb` of a whole tile sees (its work), without a run
@@ -677,7 +676,8 @@ NoAllocSplit noalloc_split(const ma_problem_t* p, const int32_t* q_idx,
       static_cast<int32_t>(int64_t{nq} * p->partition_len / kFwdBM);
   for (int32_t qb = 0; qb < nqb; ++qb)
     work[qb] = visible_blocks(p, q_idx, kv_idx, nkv, qb);
-  NoAllocSplit s{split::choose(work, nqb, p->num_q_heads, kFwdPass), 0, 0, 0};
+  NoAllocSplit s{split::choose(work, nqb, p->num_q_heads,
+                               fwd_pass(p->head_dim)), 0, 0, 0};
   if (s.cut.c == 0) return s;
   for (int32_t qb = 0; qb < nqb; ++qb) {
     const int32_t n = split::num_pieces(s.cut, qb, work[qb]);
@@ -998,7 +998,8 @@ ma_status_t mesh_attn_tile_fwd_noalloc(const ma_problem_t* prob,
   fp.group = prob->num_q_heads / prob->num_kv_heads;
   fp.scale_log2 = prob->softmax_scale * kLog2e;
   fp.part_lse = static_cast<float*>(parts);
-  fp.part_o = fp.part_lse + kFwdPass.max_parts() * kFwdBM;
+  fp.part_o =
+      fp.part_lse + fwd_pass(prob->head_dim).max_parts() * kFwdBM;
   // A short list travels in the kernel's arguments, as with a workspace.
   PlanBlob blob;
   PlanView view;
@@ -1018,7 +1019,7 @@ ma_status_t mesh_attn_tile_fwd_noalloc(const ma_problem_t* prob,
     v.n_splits = sp.split_rows;
     v.parts = sp.parts;
     v.mode = split_mode(v.n_items, split, prob->num_kv_heads % kNumXcd == 0,
-                        kFwdPass.slots);
+                        fwd_pass(prob->head_dim).slots);
     v.off_queue = align_up(static_cast<size_t>(v.m) * sizeof(DevRow));
     v.off_splits = v.off_queue + kAlign;
     v.off_runs = v.off_splits + align_up(sp.split_rows * sizeof(DevSplit));

@@ -82,12 +82,16 @@ struct FwdParams {
   float* part_lse;
 };
 
-// The forward as the cut of long items sees it: one workgroup per compute unit
-// (its eight waves of 256 registers fill the SIMDs).  Items of 4 and 64 KV
-// blocks measured 14.3 and 100.8 us at d = 128 (1.44 us per block and six
-// blocks of overhead), 11.0 and 83.2 us at d = 64; folding 256 partials of
-// 256 x 128 takes 7-9 us, and writing them about as long.
-constexpr split::Pass kFwdPass{256, 6, 4, 2, 20};
+// The forward as the cut of long items sees it.  d = 128: one workgroup per
+// compute unit (its eight waves of 256 registers fill the SIMDs); items of 4
+// and 64 KV blocks measured 14.3 and 100.8 us (1.44 us per block and six
+// blocks of overhead); folding 256 partials of 256 x 128 takes 7-9 us, and
+// writing them about as long.  d = 64: two workgroups per compute unit.
+constexpr split::Pass kFwdPass128{256, 2048, 6, 4, 2, 20};
+constexpr split::Pass kFwdPass64{512, 2048, 4, 4, 2, 60};
+constexpr const split::Pass& fwd_pass(int head_dim) {
+  return head_dim == 128 ? kFwdPass128 : kFwdPass64;
+}
 
 // Workgroup items of the forward and of both backward kernels.  The XCDs of
 // the part run at different speeds (a few per cent apart under load) while
@@ -166,8 +170,8 @@ struct BwdParams {
 // The backward passes as the cut of long items sees them; a block is 128 x 128.
 // dK/dV: one workgroup per compute unit, 3.8 us per block with the chip full;
 // dQ: two per compute unit, 5.5 us per block each.
-constexpr split::Pass kDkdvPass{256, 3, 2, 1, 40};
-constexpr split::Pass kDqPass{512, 2, 2, 1, 120};
+constexpr split::Pass kDkdvPass{256, 2048, 3, 2, 1, 40};
+constexpr split::Pass kDqPass{512, 4096, 2, 2, 1, 120};
 
 hipError_t launch_tile_bwd(const BwdParams& p, const PlanBlob& blob,
                            int head_dim, hipStream_t stream);
@@ -181,12 +185,20 @@ constexpr size_t kNoAllocScratchBytes = size_t{8} << 20;  // per GPU
 constexpr int kNoAllocMaxList = 256;      // partitions per index list
 constexpr int kNoAllocMaxQBlocks = 4096;  // forward Q blocks of the tile
 
-// Partial results of a split tile: the most slots there are, d = 128.
+// Partial results of a split tile: the most slots there are.
+constexpr size_t part_bytes(const split::Pass& ps, int head_dim) {
+  return size_t{1} * ps.max_parts() * kFwdBM * (head_dim + 1) * 4;
+}
 constexpr size_t kNoAllocPartBytes =
-    size_t{kFwdPass.max_parts()} * kFwdBM * (128 + 1) * 4;
+    part_bytes(kFwdPass128, 128) > part_bytes(kFwdPass64, 64)
+        ? part_bytes(kFwdPass128, 128)
+        : part_bytes(kFwdPass64, 64);
 // Block rows of a tile that is split at all, and pieces of one head.
-constexpr int kSplitMaxRows = split::kMaxRounds * kFwdPass.slots;
-constexpr int kSplitMaxPieces = kSplitMaxRows + kFwdPass.max_parts();
+constexpr int kSplitMaxRows = kFwdPass128.max_items;
+constexpr int kSplitMaxPieces = kSplitMaxRows + kFwdPass64.max_parts();
+static_assert(kFwdPass64.max_items == kSplitMaxRows &&
+                  kFwdPass64.max_parts() >= kFwdPass128.max_parts(),
+              "bounds of both head dims");
 
 // The runs of a tile within the limit fit kNoAllocScratchBytes; the order table
 // and the split rows lie beside them.
@@ -194,7 +206,7 @@ constexpr size_t kNoAllocTableBytes =
     (kNoAllocMaxQBlocks > kSplitMaxPieces ? kNoAllocMaxQBlocks
                                           : kSplitMaxPieces) *
         sizeof(DevRow) +
-    kFwdPass.max_parts() * sizeof(DevSplit) + 4096;
+    kFwdPass64.max_parts() * sizeof(DevSplit) + 4096;
 
 struct PlanBuildParams {
   int32_t P, n, layout, causal;   // problem (partition length, partitions)

@@ -20,6 +20,9 @@ namespace split {
 // A pass as the cut sees it; times in blocks of one of its workgroups.
 struct Pass {
   int32_t slots;      // workgroups that run at once
+  int32_t max_items;  // tiles of more items than this are never split: the
+                      // longest first order leaves at most a fraction of a
+                      // round of many idle
   int32_t overhead;   // a workgroup's start and end (work list, first tiles,
                       // fragments, epilogue)
   int32_t min_piece;  // shortest piece worth a workgroup and a partial result;
@@ -29,10 +32,6 @@ struct Pass {
   // Most partial results a pass holds.
   __host__ __device__ constexpr int32_t max_parts() const { return 2 * slots; }
 };
-
-// Tiles of more rounds of whole items than this are never split: the longest
-// first order leaves at most a fraction of a round idle.
-constexpr int32_t kMaxRounds = 8;
 
 // Rows [0, whole) of every head stay whole, the others are cut into pieces of
 // at most c blocks; c = 0: nothing is cut.
@@ -55,7 +54,7 @@ __host__ __device__ inline int32_t piece_begin(int32_t w, int32_t n,
 // most `max_work` blocks.  Never less than what choose() gives.
 inline int64_t parts_bound(int64_t items, int64_t max_work,
                            const Pass& ps) {
-  if (items > int64_t{kMaxRounds} * ps.slots || max_work <= 2 * ps.min_piece)
+  if (items > ps.max_items || max_work <= 2 * ps.min_piece)
     return 0;
   const int64_t by_work =
       items * ((max_work + ps.min_piece - 1) / ps.min_piece);
@@ -106,7 +105,7 @@ inline Cut choose(const int32_t* w, int32_t n, int32_t heads,
     if (w[i] > longest) longest = w[i];
     if (w[i] < shortest) shortest = w[i];
   }
-  if (items > int64_t{kMaxRounds} * ps.slots || longest <= 2 * ps.min_piece)
+  if (items > ps.max_items || longest <= 2 * ps.min_piece)
     return {0, 0};
   const int64_t whole_time = estimate(w, n, heads, {0, 0}, ps).time;
   Cut best{0, 0};

@@ -132,6 +132,108 @@ __device__ __forceinline__ DevOrder order_of(const FwdParams& p) {
   return o;
 }
 
+// Epilogue of one query row per lane pair (halves lh): O = acc / l, LSE =
+// (m + log2 l) * ln 2, or a partial result.
+template <int D, bool OUT_F32>
+__device__ __forceinline__ void write_rows(const FwdParams& p,
+                                           const DevOrder& order,
+                                           const DevRow& item, int h,
+                                           int64_t q_row, int q_in_blk, int lh,
+                                           const f32x16 (&oacc)[D / 32],
+                                           float m, float l) {
+  const float lt = l + __shfl_xor(l, 32);
+  const float inv = lt > 0.f ? 1.f / lt : 0.f;
+  const float lse2 = lt > 0.f ? m + __builtin_amdgcn_logf(lt) : -INFINITY;
+  if (item.part >= 0) {
+    // A partial result: O normalised, float32, and the LSE in log2 units.
+    const int64_t prow =
+        int64_t{h * order.parts + item.part} * BM + q_in_blk;
+    if (lh == 0) p.part_lse[prow] = lse2;
+#pragma unroll
+    for (int cc = 0; cc < D / 32; ++cc)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        f32x4 x;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) x[t] = oacc[cc][4 * g + t] * inv;
+        *reinterpret_cast<f32x4*>(p.part_o + prow * D + cc * 32 + g * 8 +
+                                  lh * 4) = x;
+      }
+    return;
+  }
+  const int64_t lidx = int64_t{h} * p.rows_q + q_row;
+  // Running accumulation (float32 partials only): fold (O, LSE) of this
+  // call into the stored pair with the two-part online-softmax reducer,
+  // lse = M + ln(e^(lse_old - M) + e^(lse_new - M)) with M the larger, and
+  // O = w_old O_old + w_new O_new with w = e^(lse_part - lse).  Both lane
+  // halves of a row read the stored LSE before the first half rewrites it
+  // (same wave, program order).
+  float w_old = 0.f, w_new = 1.f, lse_out = lse2;  // log2 units
+  if constexpr (OUT_F32) {
+    if (p.accumulate) {
+      const float old2 = p.lse[lidx] * 1.4426950408889634f;
+      const float mx = fmaxf(old2, lse2);
+      if (mx == -INFINITY) {
+        w_old = 1.f;  // neither part sees a key: keep the stored O = 0
+        w_new = 0.f;
+      } else {
+        const float a = exp2_fast(old2 - mx), b = exp2_fast(lse2 - mx);
+        const float sum = a + b;
+        lse_out = mx + __builtin_amdgcn_logf(sum);
+        w_old = a / sum;
+        w_new = b / sum;
+      }
+    }
+  }
+  if (lh == 0)
+    p.lse[lidx] =
+        lse_out == -INFINITY ? -INFINITY : lse_out * 0.69314718055994531f;
+  // O^T accumulator: register 4g+t of chunk cc holds dim 32cc + 8g + 4lh + t.
+  const int64_t obase = (q_row * p.hq + h) * D;
+  const float sc_new = inv * w_new;
+  // Accumulating: every stored value is read before the first store, so the
+  // loads are issued back to back.
+  f32x4 prev[OUT_F32 ? D / 32 : 1][4];
+  if constexpr (OUT_F32) {
+#pragma unroll
+    for (int cc = 0; cc < D / 32; ++cc)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) prev[cc][g] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (p.accumulate) {
+#pragma unroll
+      for (int cc = 0; cc < D / 32; ++cc)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          prev[cc][g] = *reinterpret_cast<const f32x4*>(
+              static_cast<const float*>(p.o) + obase + cc * 32 + g * 8 +
+              lh * 4);
+    }
+  }
+#pragma unroll
+  for (int cc = 0; cc < D / 32; ++cc)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int dim = cc * 32 + g * 8 + lh * 4;
+      f32x4 x;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) x[t] = oacc[cc][4 * g + t] * sc_new;
+      if constexpr (OUT_F32) {
+        f32x4* dst = reinterpret_cast<f32x4*>(static_cast<float*>(p.o) + obase +
+                                              dim);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) x[t] = fmaf(w_old, prev[cc][g][t], x[t]);
+        *dst = x;
+      } else {
+        bf16x4 val;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) val[t] = static_cast<__bf16>(x[t]);
+        *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(p.o) + obase + dim) =
+            val;
+      }
+    }
+}
+
+// Head dim 128 (head dim 64 below).
 template <int D, bool OUT_F32>
 __global__ __launch_bounds__(NT, 1) void tile_fwd_kernel(FwdParams p,
                                                              PlanBlob) {
@@ -470,97 +572,180 @@ __global__ __launch_bounds__(NT, 1) void tile_fwd_kernel(FwdParams p,
     }
   }
 
-  // Epilogue: O = acc / l, LSE = (m + log2 l) * ln 2.
-  const float lt = l + __shfl_xor(l, 32);
-  const float inv = lt > 0.f ? 1.f / lt : 0.f;
-  const float lse2 = lt > 0.f ? m + __builtin_amdgcn_logf(lt) : -INFINITY;
-  if (item.part >= 0) {
-    // A partial result: O normalised, float32, and the LSE in log2 units.
-    const int64_t prow =
-        int64_t{h * order.parts + item.part} * BM + q_in_blk;
-    if (lh == 0) p.part_lse[prow] = lse2;
+  write_rows<D, OUT_F32>(p, order, item, h, q_row, q_in_blk, lh, oacc, m, l);
+}
+
+// ---------------------------------------------------------------------------
+// Head dim 64.  A 64-key block has half the MFMAs of d = 128 (16 per wave, 512
+// cycles) and the same softmax (about 155 vector instructions per wave, 32 of
+// them exponentials), so the vector unit bounds it.  The two ping-pong groups
+// of d = 128 leave it idle whenever a wave waits on its own dependent
+// instructions; four waves per SIMD do so less, and a wave of 32 rows fits 128
+// registers at d = 64.  So two workgroups of eight waves share a compute unit,
+// every wave loading its eighth of the K and V tiles of the next two blocks
+// (64 KB per workgroup) before it computes two, one barrier per two blocks.
+// 16384 rows x 32768 keys x 32 heads: 5141 us (856 TFLOP/s) with the ping-pong
+// schedule, 4681 with one block per barrier here (vector unit busy in 75 % of
+// the cycles, MFMA in 47 %, 1.91 GHz), 4508 (976 TFLOP/s) with two.
+// ---------------------------------------------------------------------------
+template <bool OUT_F32>
+__global__ __launch_bounds__(NT, 4) void tile_fwd64_kernel(FwdParams p,
+                                                           PlanBlob) {
+  constexpr int D = 64;
+  using L = FwdLayout<D>;
+  extern __shared__ __align__(16) char smem[];
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63;
+  const int li = lane & 31;
+  const int lh = lane >> 5;
+
+  const DevOrder order = order_of(p);
+  const int slot = queued_slot(order.n_items, order.queue,
+                               reinterpret_cast<int*>(smem + 2 * L::SMEM));
+  if (slot < 0) return;
+  int h;
+  const DevRow item = load_slot(order, slot, p.hq, p.group, &h);
+  const int hk = h / p.group;
+  Cursor cu;
+  cu.runs = order.runs;
+  cu.r = item.run;
+  cu.off = item.off;
+  cu.left = item.nblk;
+
+  const int q_in_blk = wave * 32 + li;
+  const int64_t q_row = int64_t{item.row} * BM + q_in_blk;
+  bf16x8 qf[D / 16];
+  load_frags<D>(qf, p.q, q_row, p.hq, h, lh);
+  f32x16 oacc[D / 32];
 #pragma unroll
-    for (int cc = 0; cc < D / 32; ++cc)
+  for (int cc = 0; cc < D / 32; ++cc) zero(oacc[cc]);
+  float m = -INFINITY, l = 0.f;
+
+  if (cu.left > 0) {
+    cu.run = load_const(cu.runs, cu.r);
+    const int64_t row_elems = int64_t{p.hkv} * D;
+    const uint32_t row_bytes_g = static_cast<uint32_t>(row_elems * 2);
+    const uint32_t blk_bytes = static_cast<uint32_t>(BN * row_elems * 2);
+    // Loads: wave w fills rows 8w .. 8w + 7 of a tile, lane i row 8w + i/8,
+    // physical chunk i%8.
+    constexpr int RPW64 = BN / NW;  // 8 rows, one 1 KB load
+    static_assert(RPW64 == L::RPI, "one load per wave and tile");
+    const int lrow = wave * RPW64 + lane / L::CPR;
+    const uint32_t kvo =
+        lrow * row_bytes_g + (((lane % L::CPR) ^ L::kswz(lrow)) * 16);
+    const uint32_t vvo =
+        lrow * row_bytes_g + (((lane % L::CPR) ^ L::vswz(lrow)) * 16);
+    auto load = [&](const Blk& b, int buf) {
+      const int64_t at = (int64_t{b.idx} * BN * p.hkv + hk) * D;
+      char* dst = smem + buf * 2 * L::TILE + wave * RPW64 * L::ROWB;
+      buffer_load16_lds(make_rsrc(p.k + at, blk_bytes), dst, kvo, 0);
+      buffer_load16_lds(make_rsrc(p.v + at, blk_bytes), dst + L::TILE, vvo, 0);
+    };
+    // Operand addresses as in the d = 128 kernel.
+    int kra0, vra0;
+    {
+      const int prow = key_perm(li);
+      kra0 = prow * L::ROWB + ((lh ^ L::kswz(prow)) * 16);
+      const int g16 = lane >> 4, s16 = lane & 15;
+      const int vrow = 8 * (g16 >> 1) + (s16 >> 2);
+      const int c16 = 2 * (g16 & 1) + ((s16 & 3) >> 1);
+      vra0 = vrow * L::ROWB + ((c16 ^ L::vswz(vrow)) * 16) + 8 * (s16 & 1);
+    }
+
+    // One block: scores, online softmax, O += P V (as the d = 128 phases).
+    auto compute = [&](const Blk& cur, const char* kb) {
+      const char* vb = kb + L::TILE;
+      f32x16 sc[2];
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        f32x4 x;
+      for (int kt = 0; kt < 2; ++kt) {
+        zero(sc[kt]);
 #pragma unroll
-        for (int t = 0; t < 4; ++t) x[t] = oacc[cc][4 * g + t] * inv;
-        *reinterpret_cast<f32x4*>(p.part_o + prow * D + cc * 32 + g * 8 +
-                                  lh * 4) = x;
+        for (int kk = 0; kk < D / 16; ++kk)
+          sc[kt] = mfma32(*reinterpret_cast<const bf16x8*>(
+                              kb + (kra0 ^ (32 * kk)) + kt * 32 * L::ROWB),
+                          qf[kk], sc[kt]);
       }
-    return;
-  }
-  const int64_t lidx = int64_t{h} * p.rows_q + q_row;
-  // Running accumulation (float32 partials only): fold (O, LSE) of this
-  // call into the stored pair with the two-part online-softmax reducer,
-  // lse = M + ln(e^(lse_old - M) + e^(lse_new - M)) with M the larger, and
-  // O = w_old O_old + w_new O_new with w = e^(lse_part - lse).  Both lane
-  // halves of a row read the stored LSE before the first half rewrites it
-  // (same wave, program order).
-  float w_old = 0.f, w_new = 1.f, lse_out = lse2;  // log2 units
-  if constexpr (OUT_F32) {
-    if (p.accumulate) {
-      const float old2 = p.lse[lidx] * 1.4426950408889634f;
-      const float mx = fmaxf(old2, lse2);
-      if (mx == -INFINITY) {
-        w_old = 1.f;  // neither part sees a key: keep the stored O = 0
-        w_new = 0.f;
-      } else {
-        const float a = exp2_fast(old2 - mx), b = exp2_fast(lse2 - mx);
-        const float sum = a + b;
-        lse_out = mx + __builtin_amdgcn_logf(sum);
-        w_old = a / sum;
-        w_new = b / sum;
+      if (cur.cls == 1) {
+        const int lim = cur.lim + q_in_blk;
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+          for (int i = 0; i < 16; ++i)
+            if (kt * 32 + acc_row(i, lh) > lim) sc[kt][i] = -INFINITY;
       }
+      float mx = -INFINITY;
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sc[kt][i]);
+      mx = max_with_other_half(mx) * p.scale_log2;
+      const float m_new = fmaxf(m, mx);
+      const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
+      if (__builtin_amdgcn_ballot_w64(m_new != m)) {
+        const float alpha = exp2_fast(m - m_use);
+        l *= alpha;
+#pragma unroll
+        for (int cc = 0; cc < D / 32; ++cc)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) oacc[cc][i] *= alpha;
+        m = m_new;
+      }
+      float rs[4];
+      bf16x8 pb[4];
+#pragma unroll
+      for (int ss = 0; ss < 4; ++ss) {
+        float e8[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          e8[e] = exp2_fast(
+              fmaf(sc[ss >> 1][(ss & 1) * 8 + e], p.scale_log2, -m_use));
+          pb[ss][e] = static_cast<__bf16>(e8[e]);
+        }
+        rs[ss] = ((e8[0] + e8[1]) + (e8[2] + e8[3])) +
+                 ((e8[4] + e8[5]) + (e8[6] + e8[7]));
+      }
+      l += (rs[0] + rs[1]) + (rs[2] + rs[3]);
+#pragma unroll
+      for (int cc = 0; cc < D / 32; ++cc) {
+#pragma unroll
+        for (int ss = 0; ss < 4; ++ss) {
+          const char* a0 = vb + (vra0 ^ (64 * cc)) + ss * 16 * L::ROWB;
+          const bf16x8 a =
+              join_bf16(lds_read_tr16(a0), lds_read_tr16(a0 + 4 * L::ROWB));
+          oacc[cc] = mfma32(a, pb[ss], oacc[cc]);
+        }
+      }
+    };
+
+    // Two blocks per barrier: the loads of the next two are in flight while
+    // these two are computed.  Buffer pairs 0, 1 and 2, 3.
+    Blk b0 = block_at(cu);
+    cu = next_block(cu);
+    Blk b1 = block_at(cu);
+    load(b0, 0);
+    if (b1.valid()) load(b1, 1);
+#pragma unroll
+    for (int kk = 0; kk < D / 16; ++kk) wait_for(qf[kk]);
+    for (int pair = 0; b0.valid(); pair ^= 2) {
+      // This wave's loads of the two blocks have landed; behind the barrier so
+      // have all waves', and none still reads the other pair's buffers.
+      wait_vmem();
+      lds_barrier();
+      cu = next_block(cu);
+      const Blk n0 = block_at(cu);
+      cu = next_block(cu);
+      const Blk n1 = block_at(cu);
+      if (n0.valid()) load(n0, pair ^ 2);
+      if (n1.valid()) load(n1, (pair ^ 2) + 1);
+      const char* kb = smem + pair * 2 * L::TILE;
+      compute(b0, kb);
+      if (b1.valid()) compute(b1, kb + 2 * L::TILE);
+      b0 = n0;
+      b1 = n1;
     }
   }
-  if (lh == 0)
-    p.lse[lidx] =
-        lse_out == -INFINITY ? -INFINITY : lse_out * 0.69314718055994531f;
-  // O^T accumulator: register 4g+t of chunk cc holds dim 32cc + 8g + 4lh + t.
-  const int64_t obase = (q_row * p.hq + h) * D;
-  const float sc_new = inv * w_new;
-  // Accumulating: every stored value is read before the first store, so the
-  // loads are issued back to back.
-  f32x4 prev[OUT_F32 ? D / 32 : 1][4];
-  if constexpr (OUT_F32) {
-#pragma unroll
-    for (int cc = 0; cc < D / 32; ++cc)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) prev[cc][g] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (p.accumulate) {
-#pragma unroll
-      for (int cc = 0; cc < D / 32; ++cc)
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-          prev[cc][g] = *reinterpret_cast<const f32x4*>(
-              static_cast<const float*>(p.o) + obase + cc * 32 + g * 8 +
-              lh * 4);
-    }
-  }
-#pragma unroll
-  for (int cc = 0; cc < D / 32; ++cc)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int dim = cc * 32 + g * 8 + lh * 4;
-      f32x4 x;
-#pragma unroll
-      for (int t = 0; t < 4; ++t) x[t] = oacc[cc][4 * g + t] * sc_new;
-      if constexpr (OUT_F32) {
-        f32x4* dst = reinterpret_cast<f32x4*>(static_cast<float*>(p.o) + obase +
-                                              dim);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) x[t] = fmaf(w_old, prev[cc][g][t], x[t]);
-        *dst = x;
-      } else {
-        bf16x4 val;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) val[t] = static_cast<__bf16>(x[t]);
-        *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(p.o) + obase + dim) =
-            val;
-      }
-    }
+  write_rows<D, OUT_F32>(p, order, item, h, q_row, q_in_blk, lh, oacc, m, l);
 }
 
 // ---------------------------------------------------------------------------
@@ -644,11 +829,20 @@ template <int D, bool F32>
 hipError_t launch(const FwdParams& p, const PlanBlob& blob,
                   hipStream_t stream) {
   const size_t smem = FwdLayout<D>::SMEM + 16;  // + the item slot
-  hipError_t e = ensure_dynamic_lds<tile_fwd_kernel<D, F32>>(smem);
-  if (e != hipSuccess) return e;
   const int grid = static_cast<int>(queued_launch_grid(p.order.n_items));
-  hipLaunchKernelGGL((tile_fwd_kernel<D, F32>), dim3(grid), dim3(NT), smem,
-                     stream, p, blob);
+  hipError_t e = hipSuccess;
+  if constexpr (D == 64) {
+    const size_t smem64 = 2 * FwdLayout<D>::SMEM + 16;  // four block buffers
+    e = ensure_dynamic_lds<tile_fwd64_kernel<F32>>(smem64);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(tile_fwd64_kernel<F32>, dim3(grid), dim3(NT), smem64,
+                       stream, p, blob);
+  } else {
+    e = ensure_dynamic_lds<tile_fwd_kernel<D, F32>>(smem);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((tile_fwd_kernel<D, F32>), dim3(grid), dim3(NT), smem,
+                       stream, p, blob);
+  }
   e = hipGetLastError();
   if (e != hipSuccess || p.order.n_splits == 0) return e;
   constexpr int GPI = BM / (NTC / (D / 4));

@@ -35,7 +35,7 @@ FWD = [
                         head_dim=128, outliers=True),
     dataclasses.replace(_T, name="tail-rows", q_idx=list(range(9)),
                         kv_idx=list(range(4, 12)), num_q_heads=32,
-                        num_kv_heads=4),
+                        num_kv_heads=4, head_dim=128),
     dataclasses.replace(_T, name="uneven-lanes", q_idx=[1, 7, 3],
                         kv_idx=[0, 2, 9], num_q_heads=7, num_kv_heads=7,
                         head_dim=128),
