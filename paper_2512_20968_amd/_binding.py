@@ -3,6 +3,7 @@
 torch is used for device memory and the current stream only.
 """
 
+import array
 import ctypes
 import os
 import threading
@@ -141,6 +142,8 @@ def load_library():
     """Load libmesh_attn.so from the package directory (built by
     ``__graft_entry__.build()``).  Raises if it is missing."""
     global _lib
+    if _lib is not None:
+        return _lib
     with _lock:
         if _lib is None:
             path = library_path()
@@ -170,7 +173,14 @@ def _check(fn, status):
 
 
 def _idx(lst):
-    arr = np.ascontiguousarray(np.asarray(list(lst), dtype=np.int32))
+    lst = list(lst)
+    try:
+        ints = array.array("i", lst)  # refuses what does not fit 32 bits
+        if lst:
+            return ints, (ctypes.c_int32 * len(lst)).from_buffer(ints), len(lst)
+    except TypeError:  # not integers: NumPy's conversion rules
+        pass
+    arr = np.ascontiguousarray(np.asarray(lst, dtype=np.int32))
     return arr, arr.ctypes.data_as(_I32P), int(arr.size)
 
 
@@ -251,31 +261,38 @@ def mesh_attn_bwd_workspace_size(prob, nq, nkv):
 # Device calls (torch tensors)
 # ---------------------------------------------------------------------------
 
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 def _stream_ptr(stream):
+    # torch's current stream by its raw handle: building a Stream object
+    # costs more than the rest of a small call's checks.
     torch = _torch()
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 def _dev(t, name, shape, dtypes):
-    torch = _torch()
-    if not isinstance(t, torch.Tensor):
+    if not isinstance(t, _torch().Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
-    if t.device.type != "cuda":
+    if not t.is_cuda:
         raise ValueError(f"{name} must be on a GPU, got {t.device}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
     if t.dtype not in dtypes:
         raise ValueError(f"{name} dtype {t.dtype} not in {dtypes}")
-    if tuple(t.shape) != tuple(shape):
+    if t.shape != shape:
         raise ValueError(f"{name} shape {tuple(t.shape)} != {tuple(shape)}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _dtype_code(t):
@@ -283,13 +300,14 @@ def _dtype_code(t):
     return MA_FP32 if t.dtype == torch.float32 else MA_BF16
 
 
-def _workspace(nbytes, device, ws, stream=None):
+def _workspace(size_fn, pr, nq, nkv, device, ws, stream=None):
     torch = _torch()
     if ws is None:
+        nbytes = size_fn(pr, nq, nkv)
         ws = torch.empty(max(int(nbytes), 16), dtype=torch.uint8, device=device)
         if stream is not None:
             ws.record_stream(stream)
-    if ws.device.type != "cuda" or not ws.is_contiguous():
+    if not ws.is_cuda or not ws.is_contiguous():
         raise ValueError("workspace must be a contiguous GPU tensor")
     return ws, ws.numel() * ws.element_size()
 
@@ -310,11 +328,11 @@ def mesh_attn_tile_fwd(prob, q_idx, kv_idx, q, k, v, o, lse, ws=None,
         _dev(o, "o", (nq * P, hq, d), (torch.bfloat16, torch.float32)),
     ]
     lp = _dev(lse, "lse", (hq, nq * P), (torch.float32,))
-    need = mesh_attn_fwd_workspace_size(pr, nq, nkv)
-    ws, wsb = _workspace(need, q.device, ws, stream)
+    ws, wsb = _workspace(mesh_attn_fwd_workspace_size, pr, nq, nkv,
+                         q.device, ws, stream)
     st = load_library().mesh_attn_tile_fwd(
         ctypes.byref(pr), qp, nq, kp, nkv, *args[:3], args[3], _dtype_code(o),
-        lp, ctypes.c_void_p(ws.data_ptr()), wsb, _stream_ptr(stream))
+        lp, ws.data_ptr(), wsb, _stream_ptr(stream))
     _check("mesh_attn_tile_fwd", st)
     return o, lse
 
@@ -383,11 +401,11 @@ def mesh_attn_tile_bwd(prob, q_idx, kv_idx, q, k, v, o, d_o, lse, dq, dk, dv,
         _dev(dk, "dk", (nkv * P, hkv, d), f32),
         _dev(dv, "dv", (nkv * P, hkv, d), f32),
     ]
-    need = mesh_attn_bwd_workspace_size(pr, nq, nkv)
-    ws, wsb = _workspace(need, q.device, ws, stream)
+    ws, wsb = _workspace(mesh_attn_bwd_workspace_size, pr, nq, nkv,
+                         q.device, ws, stream)
     st = load_library().mesh_attn_tile_bwd(
         ctypes.byref(pr), qp, nq, kp, nkv, *args, int(accumulate),
-        ctypes.c_void_p(ws.data_ptr()), wsb, _stream_ptr(stream))
+        ws.data_ptr(), wsb, _stream_ptr(stream))
     _check("mesh_attn_tile_bwd", st)
     return dq, dk, dv
 
@@ -425,11 +443,11 @@ def mesh_attn_chunk_fwd(prob, q_idx, kv_idx, chunk, q, k, v, o, lse,
         _dev(o, "o", (rq, hq, d), f32),
         _dev(lse, "lse", (hq, rq), f32),
     ]
-    need = mesh_attn_chunk_fwd_workspace_size(pr, nq, nkv)
-    ws, wsb = _workspace(need, q.device, ws, stream)
+    ws, wsb = _workspace(mesh_attn_chunk_fwd_workspace_size, pr, nq, nkv,
+                         q.device, ws, stream)
     st = load_library().mesh_attn_chunk_fwd(
         ctypes.byref(pr), qp, nq, kp, nkv, ctypes.byref(ch), *args,
-        int(accumulate), ctypes.c_void_p(ws.data_ptr()), wsb,
+        int(accumulate), ws.data_ptr(), wsb,
         _stream_ptr(stream))
     _check("mesh_attn_chunk_fwd", st)
     return o, lse
@@ -467,11 +485,11 @@ def mesh_attn_chunk_bwd(prob, q_idx, kv_idx, chunk, q, k, v, o, d_o, lse, dq,
         _dev(dk, "dk", (rk, hkv, d), f32),
         _dev(dv, "dv", (rk, hkv, d), f32),
     ]
-    need = mesh_attn_chunk_bwd_workspace_size(pr, nq, nkv)
-    ws, wsb = _workspace(need, q.device, ws, stream)
+    ws, wsb = _workspace(mesh_attn_chunk_bwd_workspace_size, pr, nq, nkv,
+                         q.device, ws, stream)
     st = load_library().mesh_attn_chunk_bwd(
         ctypes.byref(pr), qp, nq, kp, nkv, ctypes.byref(ch), *args,
-        int(accumulate), ctypes.c_void_p(ws.data_ptr()), wsb,
+        int(accumulate), ws.data_ptr(), wsb,
         _stream_ptr(stream))
     _check("mesh_attn_chunk_bwd", st)
     return dq, dk, dv
