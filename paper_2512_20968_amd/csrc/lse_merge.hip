@@ -54,25 +54,32 @@ struct Slice<true> {
 // B partials per batch: the slices and LSE values of a batch are loaded
 // together (all loads issued before any is used), so a lane waits for one
 // round trip to memory per batch.  The host picks the smallest B that covers
-// k_parts (at most 16 for bf16 partials, 8 for float32).
-template <bool IN_F32, bool OUT_F32, int B>
+// k_parts (at most 16 for bf16 partials, 8 for float32); slots past k_parts
+// load the last partial again.
+//
+// LPI lanes per (row, head) item and items indexed in 32 bits, where head_dim
+// and the sizes allow it (else LPI 0, head_dim / 8 at run time, in 64 bits):
+// with 64-bit divisions by run-time values and a batch of 4, a fold of 3 float32 partials of 1535 x 21 x 64 (33 MB) spent as long on
+// addresses as on its one round trip to memory (8.8 us a kernel, 7.3 now).
+template <bool IN_F32, bool OUT_F32, int B, int LPI, typename Index>
 __global__ __launch_bounds__(NT) void lse_merge_kernel(MergeParams p) {
   constexpr float kLog2e = 1.4426950408889634f;
   constexpr float kLn2 = 0.69314718055994531f;
-  const int lpi = p.head_dim / 8;  // lanes per (row, head) item
-  const int64_t n_items = p.rows * p.heads;
-  const int64_t stride = int64_t{gridDim.x} * NT;
+  const int lpi = LPI ? LPI : p.head_dim / 8;  // lanes per (row, head) item
+  const Index n_lanes =
+      static_cast<Index>(p.rows) * static_cast<Index>(p.heads) * lpi;
+  const Index stride = static_cast<Index>(gridDim.x) * NT;
   const int64_t lstride = int64_t{p.heads} * p.rows;
   const int64_t ostride = p.rows * p.heads * p.head_dim;
-  for (int64_t gid = int64_t{blockIdx.x} * NT + threadIdx.x;
-       gid < n_items * lpi; gid += stride) {
-    const int64_t item = gid / lpi;
+  for (Index gid = static_cast<Index>(blockIdx.x) * NT + threadIdx.x;
+       gid < n_lanes; gid += stride) {
+    const Index item = gid / static_cast<Index>(lpi);
     const int sub = static_cast<int>(gid - item * lpi);
-    const int64_t row = item / p.heads;
+    const Index row = item / static_cast<Index>(p.heads);
     const int h = static_cast<int>(item - row * p.heads);
     // lse_parts[kp][h][row], o_parts[kp][row][h][d]
     const float* lp = p.lse_parts + int64_t{h} * p.rows + row;
-    const int64_t off0 = item * p.head_dim + sub * 8;
+    const int64_t off0 = static_cast<int64_t>(item) * p.head_dim + sub * 8;
 
     // Running reducer over the batches: M the largest LSE so far, S the sum
     // of exp(lse_k - M), acc the sum of exp(lse_k - M) O_k; at the end
@@ -118,7 +125,7 @@ __global__ __launch_bounds__(NT) void lse_merge_kernel(MergeParams p) {
     const float lse =
         M == -INFINITY ? -INFINITY : M + __builtin_amdgcn_logf(S) * kLn2;
     const float inv = S > 0.f ? 1.f / S : 0.f;
-    const int64_t oo = item * p.head_dim + sub * 8;
+    const int64_t oo = off0;
     if constexpr (OUT_F32) {
       f32x4* dst = reinterpret_cast<f32x4*>(static_cast<float*>(p.o_out) + oo);
       f32x4 a, b;
@@ -147,17 +154,32 @@ hipError_t launch_b(const MergeParams& p, hipStream_t stream) {
   // Enough workgroups to fill 256 CUs several times over; the kernel loops.
   const int64_t cap = 256 * 64;
   if (blocks > cap) blocks = cap;
-  hipLaunchKernelGGL((lse_merge_kernel<IF, OF, B>),
-                     dim3(static_cast<int>(blocks)), dim3(NT), 0, stream, p);
+  const dim3 grid(static_cast<int>(blocks));
+  // A lane's index passes n_lanes by at most one stride.
+  const bool small = threads + cap * NT < (int64_t{1} << 32);
+  if (small && p.head_dim == 128)
+    hipLaunchKernelGGL((lse_merge_kernel<IF, OF, B, 16, uint32_t>), grid,
+                       dim3(NT), 0, stream, p);
+  else if (small && p.head_dim == 64)
+    hipLaunchKernelGGL((lse_merge_kernel<IF, OF, B, 8, uint32_t>), grid,
+                       dim3(NT), 0, stream, p);
+  else
+    hipLaunchKernelGGL((lse_merge_kernel<IF, OF, B, 0, int64_t>), grid,
+                       dim3(NT), 0, stream, p);
   return hipGetLastError();
 }
 
 template <bool IF, bool OF>
 hipError_t launch(const MergeParams& p, hipStream_t stream) {
   if (p.k_parts <= 2) return launch_b<IF, OF, 2>(p, stream);
+  if (p.k_parts <= 3) return launch_b<IF, OF, 3>(p, stream);
   if (p.k_parts <= 4) return launch_b<IF, OF, 4>(p, stream);
-  if (IF || p.k_parts <= 8) return launch_b<IF, OF, 8>(p, stream);
-  return launch_b<IF, OF, 16>(p, stream);
+  if (p.k_parts <= 6) return launch_b<IF, OF, 6>(p, stream);
+  if constexpr (!IF) {
+    if (p.k_parts > 12) return launch_b<IF, OF, 16>(p, stream);
+    if (p.k_parts > 8) return launch_b<IF, OF, 12>(p, stream);
+  }
+  return launch_b<IF, OF, 8>(p, stream);
 }
 
 }  // namespace

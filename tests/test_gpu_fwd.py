@@ -257,3 +257,13 @@ def test_merge_zero_rows_is_noop(gpu):
     ml = torch.empty((2, 0), dtype=torch.float32, device=gpu)
     ma.mesh_attn_lse_merge(o, lse, mo, ml)
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("kparts", [3, 5, 6, 7, 9, 12, 13])
+@pytest.mark.parametrize("d", [8, 64, 72, 128, 256])
+def test_merge_batch_sizes_and_head_dims(gpu, kparts, d):
+    """Every batch size of the kernel with and without repeated partials, head
+    dims with and without a fixed lane count, both input types; rows x heads
+    is odd, so workgroups end inside an item."""
+    for in_dt in (torch.bfloat16, torch.float32):
+        test_merge_parity(gpu, kparts, 37, 3, d, in_dt, torch.float32, 0.2)
