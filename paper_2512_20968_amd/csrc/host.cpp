@@ -230,6 +230,7 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 struct PassView {
   size_t off_rows = 0, off_runs = 0, off_splits = 0, off_queue = 0;
   int32_t m = 0, n_items = 0, n_splits = 0, parts = 0, mode = 0;
+  bool is_short = false;
 };
 
 // An event recorded after a copy, with the device it belongs to (an event
@@ -347,6 +348,7 @@ size_t pack_side(const plan::Built& b, const plan::Arrays& arr, int32_t heads,
   v->n_splits = b.n_splits;
   v->parts = b.parts;
   v->mode = b.mode;
+  v->is_short = b.is_short;
   return off;
 }
 
@@ -369,6 +371,7 @@ DevOrder order_at(const PassView& v, char* base) {
   o.mode = v.mode;
   o.parts = v.parts;
   o.n_splits = v.n_splits;
+  o.is_short = v.is_short;
   return o;
 }
 
@@ -441,13 +444,13 @@ int sides_of(int pass, const ma_problem_t* p, const int32_t* q_idx, int32_t nq,
   auto may = [&](const split::Pass& ps) { return may_split ? &ps : nullptr; };
   if (pass == 0) {
     out[0] = plan::Side{p,   q_idx, nq,   kFwdBM, sq, kv_idx, nkv, kFwdBN,
-                        skv, true,  p->num_q_heads, g, 1, may(fwd_pass(p->head_dim))};
+                        skv, true,  p->num_q_heads, g, 1, may(fwd_pass(p->head_dim)), true};
     return 1;
   }
   out[0] = plan::Side{p,   q_idx, nq,   kBwdBM, sq, kv_idx, nkv, kBwdBN,
-                      skv, true,  p->num_q_heads, g, 1, may(kDqPass)};
+                      skv, true,  p->num_q_heads, g, 1, may(kDqPass), false};
   out[1] = plan::Side{p,  kv_idx, nkv,  kBwdBN, skv, q_idx, nq, kBwdBM,
-                      sq, false,  p->num_kv_heads, 1, g, may(kDkdvPass)};
+                      sq, false,  p->num_kv_heads, 1, g, may(kDkdvPass), false};
   return 2;
 }
 
@@ -667,6 +670,7 @@ int32_t visible_blocks(const ma_problem_t* p, const int32_t* q_idx,
 struct NoAllocSplit {
   split::Cut cut;
   int32_t row_pieces, split_rows, parts;
+  bool is_short;
 };
 
 NoAllocSplit noalloc_split(const ma_problem_t* p, const int32_t* q_idx,
@@ -676,8 +680,11 @@ NoAllocSplit noalloc_split(const ma_problem_t* p, const int32_t* q_idx,
       static_cast<int32_t>(int64_t{nq} * p->partition_len / kFwdBM);
   for (int32_t qb = 0; qb < nqb; ++qb)
     work[qb] = visible_blocks(p, q_idx, kv_idx, nkv, qb);
-  NoAllocSplit s{split::choose(work, nqb, p->num_q_heads,
-                               fwd_pass(p->head_dim)), 0, 0, 0};
+  NoAllocSplit s{{0, 0}, 0, 0, 0, false};
+  s.is_short = fwd_is_short(int64_t{nqb} * p->num_q_heads,
+                            *std::max_element(work, work + nqb), p->head_dim);
+  if (!s.is_short)
+    s.cut = split::choose(work, nqb, p->num_q_heads, fwd_pass(p->head_dim));
   if (s.cut.c == 0) return s;
   for (int32_t qb = 0; qb < nqb; ++qb) {
     const int32_t n = split::num_pieces(s.cut, qb, work[qb]);
@@ -1009,8 +1016,8 @@ ma_status_t mesh_attn_tile_fwd_noalloc(const ma_problem_t* prob,
     fp.order = order_at(view.a, nullptr);
   } else {
     // The same cut as the call with a workspace of full size.
-    NoAllocSplit sp{{0, 0}, 0, 0, 0};
-    if (parts_of(prob, nq, nkv, kWholeTile) > 0)
+    NoAllocSplit sp{{0, 0}, 0, 0, 0, false};
+    if (items <= fwd_pass(prob->head_dim).max_items)
       sp = noalloc_split(prob, q_idx, nq, kv_idx, nkv);
     const bool split = sp.cut.c > 0;
     PassView v;
@@ -1018,6 +1025,7 @@ ma_status_t mesh_attn_tile_fwd_noalloc(const ma_problem_t* prob,
     v.n_items = v.m * prob->num_q_heads;
     v.n_splits = sp.split_rows;
     v.parts = sp.parts;
+    v.is_short = sp.is_short;
     v.mode = split_mode(v.n_items, split, prob->num_kv_heads % kNumXcd == 0,
                         fwd_pass(prob->head_dim).slots);
     v.off_queue = align_up(static_cast<size_t>(v.m) * sizeof(DevRow));

@@ -54,6 +54,7 @@ struct DevOrder {
                        // from kQueuedMinItems items on
   int32_t m, n_items;  // table entries; times the heads: workgroup items
   int32_t mode, parts, n_splits;
+  int32_t is_short;     // the forward's waves split the keys (fwd_is_short)
   int32_t inline_list;  // the three lists are in the PlanBlob argument
   int32_t off_runs, off_splits;  // at these offsets (rows first)
 };
@@ -123,6 +124,26 @@ hipError_t launch_tile_fwd(const FwdParams& p, const PlanBlob& blob,
 // some 10 KB) and by 5 to 10 us below; this takes 3 to 5 us.
 hipError_t launch_plan_copy(void* dst, const void* src, size_t bytes,
                             hipStream_t stream);
+
+// Whether the forward of a tile of `items` items, the longest of `longest` KV
+// blocks, runs with the keys split over the waves of 32-row workgroups: its
+// 8 * items workgroups (128 KB of LDS each) fit the 256 compute units in one or
+// two rounds, and its waves, which wait for the loads of every block, get few
+// enough of them.  Microseconds a call, this / 256-row workgroups with long
+// items split:
+//   d = 64   8 blocks   16         32         64         128
+//   4 items  8.5/15     7.9/18     9.7/14.5   15.9/17.3  30.9/21.1
+//   32       7.8/15     7.8/22     12.6/22.3  21.5/31.4  37.5/40.0
+//   64       9.9/15.1   12.7/21.9  21.7/26.6  37.7/38.6  78/56
+//   128      18.5/15.6  23.7/26.9  41.6/37.7
+//   d = 128  8          16         32         64
+//   4        7.9/20     11.5/18.3  19.2/19.3  35.9/23.3
+//   32       8.6/20     13.4/26.5  22.2/31.8  37.8/36.2
+//   64       15.2/20.1  25.0/31.1  41.2/38.6
+constexpr bool fwd_is_short(int64_t items, int32_t longest, int head_dim) {
+  return items <= 64 &&
+         longest * (items > 32 ? 2 : 1) <= (head_dim == 64 ? 64 : 32);
+}
 
 struct MergeParams {
   const void* o_parts;

@@ -50,7 +50,8 @@ inline int64_t mask_offset(const ma_problem_t* p, int32_t qp, int64_t q0,
 // One orientation of a tile.  Side A blocks (bm_a rows) own the workgroups,
 // side B blocks (bm_b rows) are walked, `walks` times.  a_is_q: side A is the
 // query side.  `heads` heads own workgroups, `group` of them per KV head.
-// pass: how long items may be split, null to leave them whole.
+// pass: how long items may be split, null to leave them whole; forward: its
+// items may be short ones (fwd_is_short).
 struct Side {
   const ma_problem_t* p;
   const int32_t* a_idx;
@@ -62,6 +63,7 @@ struct Side {
   bool a_is_q;
   int32_t heads, group, walks;
   const split::Pass* pass;
+  bool forward;
 
   int32_t rows() const { return na * static_cast<int32_t>(sa.len / bm_a); }
 };
@@ -82,6 +84,7 @@ struct Built {
   int32_t m = 0, n_runs = 0, n_splits = 0;  // table entries, runs, split rows
   int32_t parts = 0;                        // partials per head
   int32_t mode = 0;
+  bool is_short = false;
 };
 
 // Blocks kb of [0, n) with base + kb * step <= x.
@@ -159,9 +162,14 @@ inline bool build(const Side& s, const Arrays& out, Built* built) {
     out.rows[r].run_b = first;
     out.rows[r].run_e = b.n_runs;
   }
+  b.is_short = s.forward &&
+               fwd_is_short(int64_t{rows} * s.heads,
+                            *std::max_element(out.work, out.work + rows),
+                            s.p->head_dim);
   const split::Cut cut =
-      s.pass ? split::choose(out.work, rows, s.heads, *s.pass)
-             : split::Cut{0, 0};
+      s.pass && !b.is_short
+          ? split::choose(out.work, rows, s.heads, *s.pass)
+          : split::Cut{0, 0};
   for (int32_t r = 0; r < rows; ++r) {
     const int32_t n = split::num_pieces(cut, r, out.work[r]);
     b.m += n;

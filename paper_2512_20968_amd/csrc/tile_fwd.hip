@@ -132,6 +132,41 @@ __device__ __forceinline__ DevOrder order_of(const FwdParams& p) {
   return o;
 }
 
+// Four dims of a row of the result, the lanes of the row together: with
+// `accumulate` (float32) folded into the stored pair with the two-part
+// reducer.  All lanes of the row are in one wave and read the stored LSE before
+// the first of them rewrites it (program order).
+template <int D, bool OUT_F32>
+__device__ __forceinline__ void store_folded(const FwdParams& p, int h,
+                                             int64_t q_row, int col, f32x4 x,
+                                             float lse2) {
+  const int64_t lidx = int64_t{h} * p.rows_q + q_row;
+  const int64_t oidx = (q_row * p.hq + h) * D + col;
+  if constexpr (OUT_F32) {
+    f32x4* dst = reinterpret_cast<f32x4*>(static_cast<float*>(p.o) + oidx);
+    if (p.accumulate) {
+      const float old2 = p.lse[lidx] * 1.4426950408889634f;
+      const f32x4 prev = *dst;
+      const float mx = fmaxf(old2, lse2);
+      const float mu = mx == -INFINITY ? 0.f : mx;
+      const float a = exp2_fast(old2 - mu), b = exp2_fast(lse2 - mu);
+      const float inv = a + b > 0.f ? 1.f / (a + b) : 0.f;
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        x[t] = fmaf(a * inv, prev[t], b * inv * x[t]);
+      lse2 = a + b > 0.f ? mx + __builtin_amdgcn_logf(a + b) : -INFINITY;
+    }
+    *dst = x;
+  } else {
+    bf16x4 val;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) val[t] = static_cast<__bf16>(x[t]);
+    *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(p.o) + oidx) = val;
+  }
+  if (col == 0)
+    p.lse[lidx] = lse2 == -INFINITY ? -INFINITY : lse2 * 0.69314718055994531f;
+}
+
 // Epilogue of one query row per lane pair (halves lh): O = acc / l, LSE =
 // (m + log2 l) * ln 2, or a partial result.
 template <int D, bool OUT_F32>
@@ -749,6 +784,214 @@ __global__ __launch_bounds__(NT, 4) void tile_fwd64_kernel(FwdParams p,
 }
 
 // ---------------------------------------------------------------------------
+// Tiles of a few short items (fwd_is_short): latency is all there is, and a
+// workgroup of 256 rows walks its keys one block after the other on a few
+// compute units.  Here a workgroup takes 32 rows and its waves take every
+// S-th key block each (S = 8 waves at d = 64, 4 at d = 128), with K and V tiles
+// of their own in LDS and no barrier; then they fold their results through
+// LDS in wave order.  8 items of 8 blocks (d = 64, 64 workgroups): 15.3 us
+// as 8 workgroups of 256 rows, 6.0 here.
+// ---------------------------------------------------------------------------
+template <int D>
+struct ShortLayout {
+  static constexpr int S = D == 64 ? 8 : 4;      // waves
+  static constexpr int NT = S * 64;
+  static constexpr int WAVE = 2 * FwdLayout<D>::TILE;  // K and V of one wave
+  static constexpr int SMEM = S * WAVE;
+  // A wave's result after the loop, in the same bytes: [32][D] floats with
+  // rows padded against bank conflicts, then 32 maxima and 32 sums.
+  static constexpr int ROWF = D + 4;
+  static_assert((32 * ROWF + 64) * 4 <= WAVE, "result fits the wave's tiles");
+};
+
+template <int D, bool OUT_F32>
+__global__ __launch_bounds__(ShortLayout<D>::NT) void tile_fwd_short_kernel(
+    FwdParams p, PlanBlob) {
+  using L = FwdLayout<D>;
+  using SL = ShortLayout<D>;
+  extern __shared__ __align__(16) char smem[];
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63;
+  const int li = lane & 31;
+  const int lh = lane >> 5;
+  const DevOrder order = order_of(p);
+  int h;
+  const DevRow item =
+      load_slot(order, blockIdx.x / (BM / 32), p.hq, p.group, &h);
+  const int hk = h / p.group;
+  const int row0 = blockIdx.x % (BM / 32) * 32;  // within the Q block
+  const int64_t q_row0 = int64_t{item.row} * BM + row0;
+
+  bf16x8 qf[D / 16];
+  load_frags<D>(qf, p.q, q_row0 + li, p.hq, h, lh);
+  f32x16 oacc[D / 32];
+#pragma unroll
+  for (int cc = 0; cc < D / 32; ++cc) zero(oacc[cc]);
+  float m = -INFINITY, l = 0.f;
+
+  char* tile = smem + wave * SL::WAVE;
+  Cursor cu;
+  cu.runs = order.runs;
+  cu.r = item.run;
+  cu.off = item.off;
+  cu.left = item.nblk;
+  if (cu.left > 0) cu.run = load_const(cu.runs, cu.r);
+  auto skip = [&](int n) {
+    for (int i = 0; i < n; ++i) cu = next_block(cu);
+  };
+  skip(wave);
+  const uint32_t row_bytes_g = static_cast<uint32_t>(p.hkv) * D * 2;
+  int kra0, vra0;
+  {
+    const int prow = key_perm(li);
+    kra0 = prow * L::ROWB + ((lh ^ L::kswz(prow)) * 16);
+    const int g16 = lane >> 4, s16 = lane & 15;
+    const int vrow = 8 * (g16 >> 1) + (s16 >> 2);
+    const int c16 = 2 * (g16 & 1) + ((s16 & 3) >> 1);
+    vra0 = vrow * L::ROWB + ((c16 ^ L::vswz(vrow)) * 16) + 8 * (s16 & 1);
+  }
+  for (Blk cur = block_at(cu); cur.valid();) {
+    // The tiles' last readers are this wave's own MFMAs, whose operands have
+    // arrived; then its own loads are all it waits for.
+    const int64_t at = (int64_t{cur.idx} * BN * p.hkv + hk) * D;
+    const rsrc_t rk = make_rsrc(p.k + at, BN * row_bytes_g);
+    const rsrc_t rv = make_rsrc(p.v + at, BN * row_bytes_g);
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int j = 0; j < BN / L::RPI; ++j) {
+      const int r = j * L::RPI + lane / L::CPR;
+      buffer_load16_lds(rk, tile + j * L::RPI * L::ROWB,
+                        r * row_bytes_g + ((lane % L::CPR) ^ L::kswz(r)) * 16,
+                        0);
+    }
+#pragma unroll
+    for (int j = 0; j < BN / L::RPI; ++j) {
+      const int r = j * L::RPI + lane / L::CPR;
+      buffer_load16_lds(rv, tile + L::TILE + j * L::RPI * L::ROWB,
+                        r * row_bytes_g + ((lane % L::CPR) ^ L::vswz(r)) * 16,
+                        0);
+    }
+    skip(SL::S);
+    const Blk nxt = block_at(cu);
+    wait_vmem();
+    asm volatile("" ::: "memory");
+    f32x16 sc[2];
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt) {
+      zero(sc[kt]);
+#pragma unroll
+      for (int kk = 0; kk < D / 16; ++kk)
+        sc[kt] = mfma32(*reinterpret_cast<const bf16x8*>(
+                            tile + (kra0 ^ (32 * kk)) + kt * 32 * L::ROWB),
+                        qf[kk], sc[kt]);
+    }
+    if (cur.cls == 1) {
+      const int lim = cur.lim + row0 + li;
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (kt * 32 + acc_row(i, lh) > lim) sc[kt][i] = -INFINITY;
+    }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sc[kt][i]);
+    mx = max_with_other_half(mx) * p.scale_log2;
+    const float m_new = fmaxf(m, mx);
+    const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
+    const float alpha = exp2_fast(m - m_use);
+    l *= alpha;
+#pragma unroll
+    for (int cc = 0; cc < D / 32; ++cc)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) oacc[cc][i] *= alpha;
+    m = m_new;
+    bf16x8 pb[4];
+#pragma unroll
+    for (int ss = 0; ss < 4; ++ss) {
+      float e8[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        e8[e] = exp2_fast(
+            fmaf(sc[ss >> 1][(ss & 1) * 8 + e], p.scale_log2, -m_use));
+        pb[ss][e] = static_cast<__bf16>(e8[e]);
+      }
+      l += ((e8[0] + e8[1]) + (e8[2] + e8[3])) +
+           ((e8[4] + e8[5]) + (e8[6] + e8[7]));
+    }
+#pragma unroll
+    for (int cc = 0; cc < D / 32; ++cc)
+#pragma unroll
+      for (int ss = 0; ss < 4; ++ss) {
+        const char* a0 =
+            tile + L::TILE + (vra0 ^ (64 * cc)) + ss * 16 * L::ROWB;
+        const bf16x8 a =
+            join_bf16(lds_read_tr16(a0), lds_read_tr16(a0 + 4 * L::ROWB));
+        oacc[cc] = mfma32(a, pb[ss], oacc[cc]);
+      }
+    cur = nxt;
+  }
+
+  // Every wave's (O, m, l) of the 32 rows into its own LDS bytes, then the
+  // fold: O = sum_w 2^(m_w - M) O_w / sum_w 2^(m_w - M) l_w.
+  __builtin_amdgcn_s_waitcnt(0xC07F);  // its tile reads have arrived
+  asm volatile("" ::: "memory");
+  float* res = reinterpret_cast<float*>(tile);
+#pragma unroll
+  for (int cc = 0; cc < D / 32; ++cc)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      f32x4 x;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) x[t] = oacc[cc][4 * g + t];
+      *reinterpret_cast<f32x4*>(res + li * SL::ROWF + cc * 32 + g * 8 +
+                                lh * 4) = x;
+    }
+  const float lt = l + __shfl_xor(l, 32);
+  if (lh == 0) {
+    res[32 * SL::ROWF + li] = m;
+    res[32 * SL::ROWF + 32 + li] = lt;
+  }
+  __syncthreads();
+  constexpr int LPR = D / 4;                 // lanes per row, four dims each
+  constexpr int RPP = SL::NT / LPR;          // rows per pass
+  const int col = tid % LPR * 4;
+#pragma unroll
+  for (int pass = 0; pass < 32 / RPP; ++pass) {
+    const int r = pass * RPP + tid / LPR;
+    auto part = [&](int w) {
+      return reinterpret_cast<const float*>(smem + w * SL::WAVE);
+    };
+    float M = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < SL::S; ++w)
+      M = fmaxf(M, part(w)[32 * SL::ROWF + r]);
+    const float mu = M == -INFINITY ? 0.f : M;
+    float sum = 0.f;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < SL::S; ++w) {
+      const float a = exp2_fast(part(w)[32 * SL::ROWF + r] - mu);
+      sum = fmaf(a, part(w)[32 * SL::ROWF + 32 + r], sum);
+      const f32x4 x =
+          *reinterpret_cast<const f32x4*>(part(w) + r * SL::ROWF + col);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) acc[t] = fmaf(a, x[t], acc[t]);
+    }
+    const float inv = sum > 0.f ? 1.f / sum : 0.f;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) acc[t] *= inv;
+    const float lse2 =
+        sum > 0.f ? M + __builtin_amdgcn_logf(sum) : -INFINITY;
+    store_folded<D, OUT_F32>(p, h, q_row0 + r, col, acc, lse2);
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Fold of the partial results of split items (the online-softmax reducer, in
 // piece order): one workgroup per 256 / (D / 4) rows of an item, a lane per
 // four dims of a row, so that loads and stores are 16 bytes and contiguous.
@@ -769,8 +1012,6 @@ __global__ __launch_bounds__(NTC) void fwd_combine_kernel(FwdParams p,
   const int row = (blockIdx.x % GPI) * RPB + threadIdx.x / LPR;
   const int sub = threadIdx.x % LPR;
   const int64_t q_row = int64_t{it.row} * BM + row;
-  const int64_t lidx = int64_t{h} * p.rows_q + q_row;
-  const int64_t oidx = (q_row * p.hq + h) * D + sub * 4;
   float M = -INFINITY, S = 0.f;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
   auto fold = [&](const f32x4& x, float lse) {
@@ -798,31 +1039,12 @@ __global__ __launch_bounds__(NTC) void fwd_combine_kernel(FwdParams p,
     for (int u = 0; u < B; ++u)
       if (k0 + u < it.nparts) fold(x[u], lv[u]);
   }
-  if constexpr (OUT_F32) {
-    if (p.accumulate) {
-      // Every lane of the row reads the stored LSE before lane 0 of the row
-      // rewrites it below (one wave, program order).
-      const float old2 = p.lse[lidx] * 1.4426950408889634f;
-      fold(*reinterpret_cast<const f32x4*>(static_cast<const float*>(p.o) +
-                                           oidx),
-           old2);
-    }
-  }
   const float inv = S > 0.f ? 1.f / S : 0.f;
-  if (sub == 0)
-    p.lse[lidx] = M == -INFINITY
-                      ? -INFINITY
-                      : (M + __builtin_amdgcn_logf(S)) * 0.69314718055994531f;
-  if constexpr (OUT_F32) {
 #pragma unroll
-    for (int t = 0; t < 4; ++t) acc[t] *= inv;
-    *reinterpret_cast<f32x4*>(static_cast<float*>(p.o) + oidx) = acc;
-  } else {
-    bf16x4 val;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) val[t] = static_cast<__bf16>(acc[t] * inv);
-    *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(p.o) + oidx) = val;
-  }
+  for (int t = 0; t < 4; ++t) acc[t] *= inv;
+  store_folded<D, OUT_F32>(
+      p, h, q_row, sub * 4, acc,
+      S > 0.f ? M + __builtin_amdgcn_logf(S) : -INFINITY);
 }
 
 template <int D, bool F32>
@@ -831,6 +1053,15 @@ hipError_t launch(const FwdParams& p, const PlanBlob& blob,
   const size_t smem = FwdLayout<D>::SMEM + 16;  // + the item slot
   const int grid = static_cast<int>(queued_launch_grid(p.order.n_items));
   hipError_t e = hipSuccess;
+  if (p.order.is_short) {
+    using SL = ShortLayout<D>;
+    e = ensure_dynamic_lds<tile_fwd_short_kernel<D, F32>>(SL::SMEM);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((tile_fwd_short_kernel<D, F32>),
+                       dim3(p.order.n_items * (BM / 32)), dim3(SL::NT),
+                       SL::SMEM, stream, p, blob);
+    return hipGetLastError();
+  }
   if constexpr (D == 64) {
     const size_t smem64 = 2 * FwdLayout<D>::SMEM + 16;  // four block buffers
     e = ensure_dynamic_lds<tile_fwd64_kernel<F32>>(smem64);

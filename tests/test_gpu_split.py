@@ -37,8 +37,8 @@ FWD = [
                         kv_idx=list(range(4, 12)), num_q_heads=32,
                         num_kv_heads=4, head_dim=128),
     dataclasses.replace(_T, name="uneven-lanes", q_idx=[1, 7, 3],
-                        kv_idx=[0, 2, 9], num_q_heads=7, num_kv_heads=7,
-                        head_dim=128),
+                        kv_idx=[0, 2, 9, 3, 4, 5, 6, 8, 15], num_q_heads=7,
+                        num_kv_heads=7, head_dim=128),
 ]
 
 
@@ -77,12 +77,58 @@ def test_split_forward(gpu, cfg, out):
     check_fwd(f"{cfg.name} whole", to_np(o1), to_np(lse1), ro, rl)
 
 
-def test_split_chunk_accumulation(gpu):
-    """Chunk tasks of a causal tile, each split: the running (O, LSE) is
-    folded with the partial results."""
-    cfg = dataclasses.replace(_T, partition_len=1536, num_partitions=6,
+# Tiles of a few short items (the waves of a workgroup split the keys): the
+# longest that are, in one round of workgroups and in two, 64 and 16 KV blocks;
+# items of fewer blocks than waves; rows and whole items without a visible key.
+SHORT = [
+    dataclasses.replace(_T, name="short-64", q_idx=[2],
+                        kv_idx=list(range(15, -1, -1)), num_q_heads=32,
+                        num_kv_heads=8),
+    dataclasses.replace(_T, name="short-16", q_idx=[9, 2], kv_idx=[4, 11, 0, 1],
+                        num_q_heads=32, num_kv_heads=4, head_dim=128),
+    dataclasses.replace(_T, name="short-odd", q_idx=[9, 2], kv_idx=[4, 11],
+                        num_q_heads=5, num_kv_heads=5, head_dim=128),
+    dataclasses.replace(_T, name="short-causal", partition_len=512,
+                        q_idx=[1, 0], kv_idx=[1], causal=True, num_q_heads=3,
+                        num_kv_heads=1, outliers=True),
+    dataclasses.replace(_T, name="short-striped", q_idx=[0, 3, 2],
+                        kv_idx=[1, 3], causal=True, layout=1, num_q_heads=4,
+                        num_kv_heads=2, head_dim=128),
+    dataclasses.replace(_T, name="short-unseen", q_idx=[0, 5], kv_idx=[3],
+                        causal=True, num_q_heads=2, num_kv_heads=2),
+]
+
+
+@pytest.mark.parametrize("cfg", SHORT, ids=[c.name for c in SHORT])
+@pytest.mark.parametrize("out", [torch.bfloat16, torch.float32])
+def test_short_forward(gpu, cfg, out):
+    q, k, v, _ = make_qkv(cfg)
+    qd, kd, vd = (t.to(gpu) for t in (q, k, v))
+    prob = cfg.problem()
+    res = []
+    for noalloc in (False, True):
+        o = torch.full(qd.shape, float("nan"), dtype=out, device=gpu)
+        lse = torch.full((cfg.num_q_heads, qd.shape[0]), float("nan"),
+                         device=gpu)
+        fn = (ma.mesh_attn_tile_fwd_noalloc if noalloc
+              else ma.mesh_attn_tile_fwd)
+        fn(prob, cfg.q_idx, cfg.kv_idx, qd, kd, vd, o, lse)
+        torch.cuda.synchronize()
+        res.append((o, lse))
+    assert torch.equal(res[0][0], res[1][0])
+    assert torch.equal(res[0][1], res[1][1])
+    ro, rl = oracle.tile_forward(prob, cfg.q_idx, cfg.kv_idx, to_np(q),
+                                 to_np(k), to_np(v))
+    check_fwd(cfg.name, to_np(res[0][0]), to_np(res[0][1]), ro, rl)
+
+
+@pytest.mark.parametrize("P,d", [(1536, 128), (512, 64), (512, 128)])
+def test_split_chunk_accumulation(gpu, P, d):
+    """Chunk tasks of a causal tile, split (P = 1536) or short: the running
+    (O, LSE) is folded with the partial results."""
+    cfg = dataclasses.replace(_T, partition_len=P, num_partitions=6,
                               q_idx=[4, 1], kv_idx=[1, 0, 4], causal=True,
-                              num_q_heads=2, num_kv_heads=1, head_dim=128)
+                              num_q_heads=2, num_kv_heads=1, head_dim=d)
     kq, kkv = 2, 2
     q, k, v, _ = make_qkv(cfg)
     prob = cfg.problem()

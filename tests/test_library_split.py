@@ -26,7 +26,7 @@ using namespace mesh_attn;
 int main(int argc, char** argv) {
   std::vector<int> a;
   for (int i = 1; i < argc; ++i) a.push_back(atoi(argv[i]));
-  ma_problem_t p{a[2], a[3], a[4], a[5], 64, a[6], a[7], 0.125f};
+  ma_problem_t p{a[2], a[3], a[4], a[5], 128, a[6], a[7], 0.125f};
   const int pass = a[0], kq = a[8], kkv = a[10];
   std::vector<int32_t> q(a.begin() + 13, a.begin() + 13 + a[12]);
   std::vector<int32_t> kv(a.begin() + 14 + a[12], a.end());
@@ -38,10 +38,11 @@ int main(int argc, char** argv) {
   const int nq = static_cast<int>(q.size()), nkv = static_cast<int>(kv.size());
   plan::Side s =
       pass == 1 ? plan::Side{&p, kv.data(), nkv, kBwdBN, skv, q.data(), nq,
-                             kBwdBM, sq, false, p.num_kv_heads, 1, g, ps}
+                             kBwdBM, sq, false, p.num_kv_heads, 1, g, ps,
+                             false}
                 : plan::Side{&p, q.data(), nq, pass ? kBwdBM : kFwdBM, sq,
                              kv.data(), nkv, pass ? kBwdBN : kFwdBN, skv, true,
-                             p.num_q_heads, g, 1, ps};
+                             p.num_q_heads, g, 1, ps, pass == 0};
   if (!a[1]) s.pass = nullptr;
   const int rows = s.rows(), most = rows + ps->max_parts();
   std::vector<DevRow> table(most);
@@ -114,7 +115,7 @@ TILES = [
     # name, tile, forward split expected (None: either)
     ("one round, equal", _tile(64, 1024, [0], R[16:32], 4, 1), True),
     ("one round, causal", _tile(8, 1024, [2, 3], R[:4], 8, 2, 1), True),
-    ("one item", _tile(9, 256, [3], [0, 1, 2, 7], 1, 1), True),
+    ("one head", _tile(9, 1024, [3], [0, 1, 2, 7], 1, 1), True),
     ("short items", _tile(4, 256, [0, 1], [0, 1], 4, 4, 1), False),
     ("unseen keys and rows",
      _tile(16, 256, [0, 9, 3], [4, 0, 11, 2, 1], 4, 4, 1), None),
@@ -163,7 +164,7 @@ def test_work_list_covers_the_canonical_one(program, name, t, want, may_split,
     assert parts * heads <= bound <= max_parts
 
     # Element offsets of every visible block pair, from the oracle's positions.
-    bm, bn = ma.mesh_attn_block_shape(64, int(pass_ > 0))
+    bm, bn = ma.mesh_attn_block_shape(128, int(pass_ > 0))
     cq, ckv = t["P"] // t["kq"][0], t["P"] // t["kkv"][0]
 
     def positions(idx, chunk, c):
