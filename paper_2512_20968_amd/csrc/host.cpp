@@ -448,9 +448,9 @@ int sides_of(int pass, const ma_problem_t* p, const int32_t* q_idx, int32_t nq,
     return 1;
   }
   out[0] = plan::Side{p,   q_idx, nq,   kBwdBM, sq, kv_idx, nkv, kBwdBN,
-                      skv, true,  p->num_q_heads, g, 1, may(kDqPass), false};
+                      skv, true,  p->num_q_heads, g, 1, may(dq_pass(p->head_dim)), false};
   out[1] = plan::Side{p,  kv_idx, nkv,  kBwdBN, skv, q_idx, nq, kBwdBM,
-                      sq, false,  p->num_kv_heads, 1, g, may(kDkdvPass), false};
+                      sq, false,  p->num_kv_heads, 1, g, may(dkdv_pass(p->head_dim)), false};
   return 2;
 }
 
@@ -602,8 +602,8 @@ BwdParts bwd_parts(const ma_problem_t* p, int32_t nq, int32_t nkv,
         any_chunk ? std::min<int64_t>(items, ps.max_items) : items, blocks, ps);
   };
   const int32_t g = p->num_q_heads / p->num_kv_heads;
-  BwdParts b{parts(kv_items, nqb * g, kDkdvPass),
-             parts(q_items, nkb, kDqPass), 0, 0, 0};
+  BwdParts b{parts(kv_items, nqb * g, dkdv_pass(p->head_dim)),
+             parts(q_items, nkb, dq_pass(p->head_dim)), 0, 0, 0};
   const size_t tile = size_t{128} * p->head_dim * 4;
   static_assert(kBwdBM == 128 && kBwdBN == 128, "rows of a partial result");
   b.kv_bytes = align_up(b.kv * 2 * tile);

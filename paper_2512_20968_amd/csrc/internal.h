@@ -189,10 +189,21 @@ struct BwdParams {
 };
 
 // The backward passes as the cut of long items sees them; a block is 128 x 128.
-// dK/dV: one workgroup per compute unit, 3.8 us per block with the chip full;
-// dQ: two per compute unit, 5.5 us per block each.
-constexpr split::Pass kDkdvPass{256, 2048, 3, 2, 1, 40};
-constexpr split::Pass kDqPass{512, 4096, 2, 2, 1, 120};
+// d = 128: dK/dV one workgroup per compute unit, 3.8 us per block with the chip
+// full; dQ two, 5.5 us per block each.  d = 64: three workgroups of either per
+// compute unit, 6.1 and 4.6 us per block each; the two passes share a launch
+// and get half of its 768 places each (a 4K-token tile of 12 heads takes 66 us
+// so, 72 with 768 places each, 78 with 512 and 256).
+constexpr split::Pass kDkdvPass128{256, 2048, 3, 2, 1, 40};
+constexpr split::Pass kDkdvPass64{384, 2048, 2, 2, 1, 100};
+constexpr split::Pass kDqPass128{512, 4096, 2, 2, 1, 120};
+constexpr split::Pass kDqPass64{384, 4096, 2, 2, 1, 200};
+constexpr const split::Pass& dkdv_pass(int head_dim) {
+  return head_dim == 128 ? kDkdvPass128 : kDkdvPass64;
+}
+constexpr const split::Pass& dq_pass(int head_dim) {
+  return head_dim == 128 ? kDqPass128 : kDqPass64;
+}
 
 hipError_t launch_tile_bwd(const BwdParams& p, const PlanBlob& blob,
                            int head_dim, hipStream_t stream);

@@ -2,7 +2,8 @@
 // Algorithm 3, summed over the tile.  Deterministic: every output element is
 // owned by exactly one thread, no atomics.
 //
-// Three launches on the caller's stream:
+// Three launches on the caller's stream (d = 64: 2 and 3 in one; and one more
+// where items were split, to sum their partial gradients):
 //  1. prep:   D_i = <dO_i, O_i> and LSE_i * log2(e) for every (row, query
 //     head), float32 (a row without a visible key gets +inf, so that its
 //     probabilities exp2(s S - LSE) are 0).
@@ -12,7 +13,7 @@
 //     64-row stages, and keeps dK, dV in registers.  The dV role computes
 //     S = Q K^T,  P = exp(s S - LSE),  dV += P^T dO  and leaves P in LDS; the
 //     dK role, one stage behind, computes  dP = dO V^T,  dS = P (dP - D),
-//     dK += s dS^T Q.
+//     dK += s dS^T Q.  (d = 64: four waves that each do both, see 2b.)
 //  3. dQ:     one workgroup per (Q block of 128 rows, query head), 4 waves x
 //     32 rows (two workgroups per CU), walking the Q-major runs of KV blocks
 //     in 64-key stages:
@@ -32,6 +33,8 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <algorithm>
 
 #include "internal.h"
 #include "tile_common.h"
@@ -219,6 +222,51 @@ struct DkdvLayout {
 
 constexpr int NT_KV = 512;  // dK/dV: eight waves
 
+// One gradient of a wave's 32 keys: dV (ROLE 0) or dK (ROLE 1, scaled).
+// Accumulator register i of chunk c holds key row 8*(i/4) + 4*lh + i%4 of the
+// wave's keys, dim 32*c + li.
+// With accumulate, every old value is read before the first store, so the
+// loads are issued back to back instead of one read-modify-write at a time.
+template <int D, int ROLE>
+__device__ __forceinline__ void write_keys(const BwdParams& p,
+                                           const DevRow& pc, int hk, int kw,
+                                           int li, int lh,
+                                           const f32x16 (&acc)[D / 32]) {
+  const int kvblk = pc.row;
+  float* out = ROLE == 0 ? p.dv : p.dk;
+  const float sc_out = ROLE == 0 ? 1.f : p.scale;
+  if (pc.part >= 0) {
+    const int64_t slot = int64_t{hk} * p.kvorder.parts + pc.part;
+    float* po = p.kvparts + (slot * 2 + ROLE) * BK * D;
+#pragma unroll
+    for (int c = 0; c < D / 32; ++c)
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        po[(kw * 32 + 8 * (i >> 2) + 4 * lh + (i & 3)) * D + c * 32 + li] =
+            acc[c][i] * sc_out;
+    return;
+  }
+  auto index = [&](int c, int i) {
+    const int64_t row =
+        int64_t{kvblk} * BK + kw * 32 + 8 * (i >> 2) + 4 * lh + (i & 3);
+    return (row * p.hkv + hk) * D + c * 32 + li;
+  };
+  f32x16 prev[D / 32];
+#pragma unroll
+  for (int c = 0; c < D / 32; ++c) zero(prev[c]);
+  if (p.accumulate) {
+#pragma unroll
+    for (int c = 0; c < D / 32; ++c)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) prev[c][i] = out[index(c, i)];
+  }
+#pragma unroll
+  for (int c = 0; c < D / 32; ++c)
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      out[index(c, i)] = fmaf(acc[c][i], sc_out, prev[c][i]);
+}
+
 // Eight waves in two roles over the same 128 keys (wave w: keys 32*(w%4) ..
 // +32).  Waves 0-3 (dV role) compute S = Q K^T, P = exp(s S - LSE) and
 // dV += P^T dO for stage t, and leave P (bf16) in LDS; waves 4-7 (dK role)
@@ -237,9 +285,8 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem,
   const int lh = lane >> 5;
   const int kw = wave & 3;
   const int k_in_blk = kw * 32 + li;
-  const int kvblk = pc.row;
   const DevRun* runs = p.kvorder.runs;
-  const int64_t kv_row = int64_t{kvblk} * BK + k_in_blk;
+  const int64_t kv_row = int64_t{pc.row} * BK + k_in_blk;
 
   // dV role: K fragments (B operand of S); dK role: V fragments (of dP).
   bf16x8 frag[D / 16];
@@ -420,42 +467,7 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem,
     }
   }
 
-  // Accumulator register i of chunk c: key row 8*(i/4) + 4*lh + i%4 of the
-  // wave's 32 keys, dim 32*c + li.
-  // With accumulate, every old value is read before the first store, so the
-  // loads are issued back to back instead of one read-modify-write at a time.
-  float* out = ROLE == 0 ? p.dv : p.dk;
-  const float sc_out = ROLE == 0 ? 1.f : p.scale;
-  if (pc.part >= 0) {
-    const int64_t slot = int64_t{hk} * p.kvorder.parts + pc.part;
-    float* po = p.kvparts + (slot * 2 + ROLE) * BK * D;
-#pragma unroll
-    for (int c = 0; c < D / 32; ++c)
-#pragma unroll
-      for (int i = 0; i < 16; ++i)
-        po[(kw * 32 + 8 * (i >> 2) + 4 * lh + (i & 3)) * D + c * 32 + li] =
-            acc[c][i] * sc_out;
-    return;
-  }
-  auto index = [&](int c, int i) {
-    const int64_t row =
-        int64_t{kvblk} * BK + kw * 32 + 8 * (i >> 2) + 4 * lh + (i & 3);
-    return (row * p.hkv + hk) * D + c * 32 + li;
-  };
-  f32x16 prev[D / 32];
-#pragma unroll
-  for (int c = 0; c < D / 32; ++c) zero(prev[c]);
-  if (p.accumulate) {
-#pragma unroll
-    for (int c = 0; c < D / 32; ++c)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) prev[c][i] = out[index(c, i)];
-  }
-#pragma unroll
-  for (int c = 0; c < D / 32; ++c)
-#pragma unroll
-    for (int i = 0; i < 16; ++i)
-      out[index(c, i)] = fmaf(acc[c][i], sc_out, prev[c][i]);
+  write_keys<D, ROLE>(p, pc, hk, kw, li, lh, acc);
 }
 
 template <int D>
@@ -466,7 +478,8 @@ __global__ __launch_bounds__(NT_KV, 1) void bwd_dkdv_kernel(BwdParams p) {
   const int lane = tid & 63;
   const DevOrder& order = p.kvorder;
   const int slot = queued_slot(order.n_items, order.queue,
-                               reinterpret_cast<int*>(smem + DkdvLayout<D>::SMEM));
+                               reinterpret_cast<int*>(smem + DkdvLayout<D>::SMEM),
+                               blockIdx.x);
   if (slot < 0) return;
   // The whole item (its runs once per query head of the group), or a piece.
   int hk;
@@ -475,6 +488,166 @@ __global__ __launch_bounds__(NT_KV, 1) void bwd_dkdv_kernel(BwdParams p) {
     dkdv_role<D, 0>(p, smem, pc, hk, wave, lane);
   else
     dkdv_role<D, 1>(p, smem, pc, hk, wave, lane);
+}
+
+// ---------------------------------------------------------------------------
+// 2b. dK / dV, head dim 64
+//
+// At d = 64 one wave holds all four operands of its 32 keys -- K and V
+// fragments, dK and dV accumulators, 96 registers -- beside the scores, so no
+// roles and no P through LDS: four waves of 32 keys, Q and dO stages double
+// buffered (34 KB), three workgroups per compute unit.  8192 queries x 16384
+// keys x 32 heads: 2760 us with two roles of waves (two per SIMD, bound by
+// the dK role's chain of dP, dS and dK), 2060-2190 here.
+// ---------------------------------------------------------------------------
+template <int D>
+struct FusedLayout {
+  static constexpr int TILE = StageTile<D>::BYTES;
+  static constexpr int STAGE = 2 * TILE + 2 * SUB * 4;  // Q, dO, lse2, delta
+  static constexpr int SMEM = 2 * STAGE;
+};
+
+template <int D>
+__device__ __forceinline__ void dkdv_fused(const BwdParams& p, char* smem,
+                                           int block) {
+  using L = FusedLayout<D>;
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63;
+  const int li = lane & 31;
+  const int lh = lane >> 5;
+  const DevOrder& order = p.kvorder;
+  const int slot = queued_slot(order.n_items, order.queue,
+                               reinterpret_cast<int*>(smem + L::SMEM), block);
+  if (slot < 0) return;
+  // The whole item (its runs once per query head of the group), or a piece.
+  int hk;
+  const DevRow pc = load_slot(order, slot, p.hkv, 1, &hk);
+  const int k_in_blk = wave * 32 + li;
+  const int64_t kv_row = int64_t{pc.row} * BK + k_in_blk;
+
+  bf16x8 kf[D / 16], vf[D / 16];
+  load_frags<D>(kf, p.k, kv_row, p.hkv, hk, lh);
+  load_frags<D>(vf, p.v, kv_row, p.hkv, hk, lh);
+  f32x16 acc_v[D / 32], acc_k[D / 32];
+#pragma unroll
+  for (int c = 0; c < D / 32; ++c) {
+    zero(acc_v[c]);
+    zero(acc_k[c]);
+  }
+
+  if (pc.nblk > 0) {
+    TileAddr<D> ta;
+    ta.init(lane, wave, 0);
+    // Stage cursor over (query head of the group, run, block in run, half).
+    struct Cur {
+      int g, r, off, s;
+      DevRun run;
+    };
+    auto advance = [&](Cur c) {
+      if (++c.s == 2) {
+        c.s = 0;
+        if (++c.off == c.run.nblk) {
+          c.off = 0;
+          if (++c.r == pc.run_e) {
+            c.r = pc.run_b;
+            ++c.g;
+          }
+          c.run = load_const(order.runs, c.r);
+        }
+      }
+      return c;
+    };
+    auto issue = [&](const Cur& c, int buf) {
+      char* base = smem + buf * L::STAGE;
+      const int h = hk * p.group + c.g;
+      const int64_t row0 = int64_t{c.run.blk0 + c.off} * BQ + c.s * SUB;
+      load_stage_tile<D>(p.q, row0, p.hq, h, base, wave, lane);
+      load_stage_tile<D>(p.d_o, row0, p.hq, h, base + L::TILE, wave, lane);
+      float* f = reinterpret_cast<float*>(base + 2 * L::TILE);
+      const int64_t at = int64_t{h} * p.rows_q + row0;
+      if (wave == 0) load_stage_floats(p.lse2 + at, f, lane);
+      if (wave == 1) load_stage_floats(p.delta + at, f + SUB, lane);
+    };
+
+    Cur cur{pc.walk, pc.run, pc.off, 0, load_const(order.runs, pc.run)};
+    issue(cur, 0);
+#pragma unroll
+    for (int kk = 0; kk < D / 16; ++kk) {
+      wait_for(kf[kk]);
+      wait_for(vf[kk]);
+    }
+    wait_vmem();
+    __syncthreads();
+    int buf = 0;
+    for (int left = 2 * pc.nblk;;) {
+      --left;
+      const Cur nxt = advance(cur);
+      if (left > 0) issue(nxt, buf ^ 1);
+      const char* sq = smem + buf * L::STAGE;
+      const char* sdo = sq + L::TILE;
+      const float* slse = reinterpret_cast<const float*>(sq + 2 * L::TILE);
+      const float* sdlt = slse + SUB;
+#pragma unroll
+      for (int qt = 0; qt < 2; ++qt) {
+        // S = Q K^T and dP = dO V^T: lane li owns key k_in_blk, register i
+        // owns query 32*qt + acc_row(i, lh).
+        f32x16 x, y;
+        zero(x);
+        zero(y);
+#pragma unroll
+        for (int kk = 0; kk < D / 16; ++kk) {
+          x = mfma32(read_row_op<D>(sq, ta.row, qt, kk), kf[kk], x);
+          y = mfma32(read_row_op<D>(sdo, ta.row, qt, kk), vf[kk], y);
+        }
+        if (cur.run.cls == 1) {
+          // key k of the block is hidden from query q of the run iff
+          // k - q > delta + (offset of this stage in the run).
+          const int lim =
+              k_in_blk - cur.run.delta - cur.off * BQ - cur.s * SUB;
+#pragma unroll
+          for (int i = 0; i < 16; ++i)
+            if (qt * 32 + acc_row(i, lh) < lim) x[i] = -INFINITY;
+        }
+        bf16x8 pf[2], ds[2];
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh) {
+          const int q0 = qt * 32 + hh * 16 + lh * 8;
+#pragma unroll
+          for (int q4 = 0; q4 < 2; ++q4) {
+            const f32x4 ls =
+                *reinterpret_cast<const f32x4*>(slse + q0 + 4 * q4);
+            const f32x4 dl =
+                *reinterpret_cast<const f32x4*>(sdlt + q0 + 4 * q4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const int i = hh * 8 + q4 * 4 + e;
+              const float pv = exp2_fast(fmaf(x[i], p.scale_log2, -ls[e]));
+              pf[hh][q4 * 4 + e] = static_cast<__bf16>(pv);
+              ds[hh][q4 * 4 + e] = static_cast<__bf16>(pv * (y[i] - dl[e]));
+            }
+          }
+        }
+        // dV += P^T dO, dK += dS^T Q (scaled at the end).
+#pragma unroll
+        for (int c = 0; c < D / 32; ++c)
+#pragma unroll
+          for (int hh = 0; hh < 2; ++hh) {
+            acc_v[c] = mfma32(pf[hh], read_tr_op<D>(sdo, ta, c, 2 * qt + hh),
+                              acc_v[c]);
+            acc_k[c] = mfma32(ds[hh], read_tr_op<D>(sq, ta, c, 2 * qt + hh),
+                              acc_k[c]);
+          }
+      }
+      if (left == 0) break;
+      wait_vmem();
+      lds_barrier();  // stage buf^1 landed; every wave is done with buf
+      buf ^= 1;
+      cur = nxt;
+    }
+  }
+  write_keys<D, 0>(p, pc, hk, wave, li, lh, acc_v);
+  write_keys<D, 1>(p, pc, hk, wave, li, lh, acc_k);
 }
 
 // ---------------------------------------------------------------------------
@@ -488,8 +661,8 @@ struct DqLayout {
 };
 
 template <int D>
-__global__ __launch_bounds__(NT, 1) void bwd_dq_kernel(BwdParams p) {
-  extern __shared__ __align__(16) char smem[];
+__device__ __forceinline__ void dq_item(const BwdParams& p, char* smem,
+                                        int block) {
   using L = DqLayout<D>;
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -499,7 +672,7 @@ __global__ __launch_bounds__(NT, 1) void bwd_dq_kernel(BwdParams p) {
 
   const DevOrder& order = p.qorder;
   const int slot = queued_slot(order.n_items, order.queue,
-                               reinterpret_cast<int*>(smem + L::SMEM));
+                               reinterpret_cast<int*>(smem + L::SMEM), block);
   if (slot < 0) return;
   // The whole item, or a piece of it.
   int h;
@@ -672,6 +845,27 @@ __global__ __launch_bounds__(NT, 1) void bwd_dq_kernel(BwdParams p) {
     }
 }
 
+template <int D>
+__global__ __launch_bounds__(NT, 1) void bwd_dq_kernel(BwdParams p) {
+  extern __shared__ __align__(16) char smem[];
+  dq_item<D>(p, smem, blockIdx.x);
+}
+
+// Head dim 64: both passes in one launch, the dK/dV workgroups (the longer
+// ones) first.  They have the same shape (four waves, 168 registers, 34 and 32
+// KB of LDS), so dQ items fill the compute units that run out of dK/dV items
+// and only one start and one end of a launch is paid.
+template <int D>
+__global__ __launch_bounds__(NT, 3) void bwd_both_kernel(BwdParams p,
+                                                         int kv_wgs) {
+  extern __shared__ __align__(16) char smem[];
+  const int block = blockIdx.x;
+  if (block < kv_wgs)
+    dkdv_fused<D>(p, smem, block);
+  else
+    dq_item<D>(p, smem, block - kv_wgs);
+}
+
 // ---------------------------------------------------------------------------
 // Sum of the partial gradients of split items, in piece order (a fixed order,
 // so the result stays deterministic).  A workgroup sums RPB rows of one
@@ -726,14 +920,6 @@ __global__ __launch_bounds__(NT) void bwd_sum_kernel(BwdParams p) {
 template <int D>
 hipError_t launch(const BwdParams& p, const PlanBlob& blob,
                   hipStream_t stream) {
-  // + one int for the item slot of a queued workgroup
-  const size_t smem_kv = DkdvLayout<D>::SMEM + 16;
-  const size_t smem_q = DqLayout<D>::SMEM + 16;
-  {
-    hipError_t e = ensure_dynamic_lds<bwd_dkdv_kernel<D>>(smem_kv);
-    if (e == hipSuccess) e = ensure_dynamic_lds<bwd_dq_kernel<D>>(smem_q);
-    if (e != hipSuccess) return e;
-  }
   const int64_t prep_threads = p.rows_q * p.hq * (D / 8);
   const int plan_wgs = (p.plan_bytes / 16 + NT - 1) / NT;
   const int prep_grid =
@@ -742,16 +928,27 @@ hipError_t launch(const BwdParams& p, const PlanBlob& blob,
                      p, blob);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(
-      bwd_dkdv_kernel<D>,
-      dim3(static_cast<int>(queued_launch_grid(p.kvorder.n_items))),
-      dim3(NT_KV), smem_kv, stream, p);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(
-      bwd_dq_kernel<D>,
-      dim3(static_cast<int>(queued_launch_grid(p.qorder.n_items))), dim3(NT),
-      smem_q, stream, p);
+  const int grid_kv = static_cast<int>(queued_launch_grid(p.kvorder.n_items));
+  const int grid_q = static_cast<int>(queued_launch_grid(p.qorder.n_items));
+  // LDS: + one int for the item slot of a queued workgroup.
+  if constexpr (D == 64) {
+    const size_t smem = std::max(FusedLayout<D>::SMEM, DqLayout<D>::SMEM) + 16;
+    const int kv_wgs = (grid_kv + kNumXcd - 1) / kNumXcd * kNumXcd;
+    hipLaunchKernelGGL(bwd_both_kernel<D>, dim3(kv_wgs + grid_q), dim3(NT),
+                       smem, stream, p, kv_wgs);
+  } else {
+    const size_t smem_kv = DkdvLayout<D>::SMEM + 16;
+    const size_t smem_q = DqLayout<D>::SMEM + 16;
+    e = ensure_dynamic_lds<bwd_dkdv_kernel<D>>(smem_kv);
+    if (e == hipSuccess) e = ensure_dynamic_lds<bwd_dq_kernel<D>>(smem_q);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(bwd_dkdv_kernel<D>, dim3(grid_kv), dim3(NT_KV), smem_kv,
+                       stream, p);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(bwd_dq_kernel<D>, dim3(grid_q), dim3(NT), smem_q,
+                       stream, p);
+  }
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int sums = (2 * p.kvorder.n_splits * p.hkv +

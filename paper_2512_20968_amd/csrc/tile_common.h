@@ -34,14 +34,17 @@ constexpr int kTileRows = 64;  // rows of a staged tile
 // -1 if every lane is taken.  A plain read of a lane's counter skips a taken
 // lane without an atomic.  s_slot is one int of LDS; every thread of the
 // workgroup must call this (it ends at a barrier when it takes the queue).
+// `block` is the workgroup's index in this order's part of the launch, which
+// starts at a multiple of 8 workgroups.
 __device__ __forceinline__ int queued_slot(int n_items, int32_t* queue,
-                                           int* s_slot) {
+                                           int* s_slot, int block) {
   constexpr int kLanes = kNumXcd;
   const int n_static = static_cast<int>(queued_static_slots(n_items));
-  const int slot = static_cast<int>(blockIdx.x);
+  const int slot = block;
   if (slot < n_static) return slot;
+  if (n_static == n_items) return -1;  // padding of the launch
   if (threadIdx.x == 0) {
-    const int x = static_cast<int>(blockIdx.x % kLanes);
+    const int x = block % kLanes;
     const int j0 = n_static / kLanes;  // positions taken statically
     int got = -1;
     for (int t = 0; t < kLanes && got < 0; ++t) {

@@ -288,7 +288,7 @@ __global__ __launch_bounds__(NT, 1) void tile_fwd_kernel(FwdParams p,
   // Item, or piece of one (order slot; see queued_static_slots).
   const DevOrder order = order_of(p);
   const int slot = queued_slot(order.n_items, order.queue,
-                               reinterpret_cast<int*>(smem + L::SMEM));
+                               reinterpret_cast<int*>(smem + L::SMEM), blockIdx.x);
   if (slot < 0) return;
   int h;
   const DevRow item = load_slot(order, slot, p.hq, p.group, &h);
@@ -637,7 +637,7 @@ __global__ __launch_bounds__(NT, 4) void tile_fwd64_kernel(FwdParams p,
 
   const DevOrder order = order_of(p);
   const int slot = queued_slot(order.n_items, order.queue,
-                               reinterpret_cast<int*>(smem + 2 * L::SMEM));
+                               reinterpret_cast<int*>(smem + 2 * L::SMEM), blockIdx.x);
   if (slot < 0) return;
   int h;
   const DevRow item = load_slot(order, slot, p.hq, p.group, &h);

@@ -33,7 +33,7 @@ int main(int argc, char** argv) {
   const plan::Slice sq{p.partition_len / kq, a[9] * (p.partition_len / kq)},
       skv{p.partition_len / kkv, a[11] * (p.partition_len / kkv)};
   const split::Pass* ps = &(pass == 0 ? kFwdPass128
-                            : pass == 1 ? kDkdvPass : kDqPass);
+                            : pass == 1 ? kDkdvPass128 : kDqPass128);
   const int g = p.num_q_heads / p.num_kv_heads;
   const int nq = static_cast<int>(q.size()), nkv = static_cast<int>(kv.size());
   plan::Side s =
