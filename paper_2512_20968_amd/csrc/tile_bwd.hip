@@ -2,27 +2,26 @@
 // Algorithm 3, summed over the tile.  Deterministic: every output element is
 // owned by exactly one thread, no atomics.
 //
-// Three launches on the caller's stream (d = 64: 2 and 3 in one; and one more
-// where items were split, to sum their partial gradients):
+// Two launches on the caller's stream, and a third where items were split, to
+// sum their partial gradients:
 //  1. prep:   D_i = <dO_i, O_i> and LSE_i * log2(e) for every (row, query
 //     head), float32 (a row without a visible key gets +inf, so that its
-//     probabilities exp2(s S - LSE) are 0).
-//  2. dK/dV:  one workgroup per (KV block of 128 keys, KV head), eight waves
-//     in two roles over four 32-key groups.  It walks the KV block's runs of
-//     Q blocks (KV-major work list) for every query head of the GQA group, in
-//     64-row stages, and keeps dK, dV in registers.  The dV role computes
-//     S = Q K^T,  P = exp(s S - LSE),  dV += P^T dO  and leaves P in LDS; the
-//     dK role, one stage behind, computes  dP = dO V^T,  dS = P (dP - D),
-//     dK += s dS^T Q.  (d = 64: four waves that each do both, see 2b.)
-//  3. dQ:     one workgroup per (Q block of 128 rows, query head), 4 waves x
-//     32 rows (two workgroups per CU), walking the Q-major runs of KV blocks
-//     in 64-key stages:
+//     probabilities exp2(s S - LSE) are 0); it also copies the work lists to
+//     the workspace.
+//  2. dK/dV:  one workgroup per (KV block of 128 keys, KV head), four waves of
+//     32 keys.  It walks the KV block's runs of Q blocks (KV-major work list)
+//     for every query head of the GQA group, in 64-row stages, and keeps dK,
+//     dV in registers:
+//     S = Q K^T,  P = exp(s S - LSE),  dP = dO V^T,  dS = P (dP - D),
+//     dV += P^T dO,  dK += s dS^T Q.
+//  3. dQ, in the same launch:  one workgroup per (Q block of 128 rows, query
+//     head), four waves of 32 rows, walking the Q-major runs of KV blocks in
+//     64-key stages:
 //     S^T = K Q^T,  dP^T = V dO^T,  dS^T = P^T (dP^T - D),  dQ^T += s K^T dS^T.
 //
 // The stage tiles (Q and dO, or K and V: 64 rows x d) stream from HBM
-// straight into LDS (buffer loads with the LDS-destination form), one barrier
-// per stage; dQ keeps two stages, dK/dV three (the dK role reads the stage
-// before the one the dV role reads).  Each tile is stored once, row-major, and
+// straight into LDS (buffer loads with the LDS-destination form), two stages
+// deep with one barrier per stage.  Each tile is stored once, row-major, and
 // read two ways: as rows (the A operand of the score MFMAs, 16-byte reads) and
 // transposed (the B operand of dV / dK, the A operand of dQ) through the
 // gfx950 LDS transpose read ds_read_b64_tr_b16.  One XOR swizzle of the
@@ -170,12 +169,24 @@ __device__ __forceinline__ void load_stage_tile(const uint16_t* base,
   const rsrc_t r = make_rsrc(base + (row0 * heads + head) * D,
                              static_cast<uint32_t>(SUB) * row_bytes_g);
   const int lrow = lane / T::CPR, lchunk = lane % T::CPR;
+  if constexpr (D == 128) {
+    // swz(tr + lrow) = 4 (lrow & 3) + (tr / 4 & 3): one base, its chunk bits
+    // XORed per load.
+    const uint32_t base_off = lrow * row_bytes_g + (lchunk ^ (4 * lrow)) * 16;
 #pragma unroll
-  for (int j = 0; j < RPW / T::RPI; ++j) {
-    const int tr = wg * RPW + j * T::RPI;  // first row of this load
-    const uint32_t voff =
-        lrow * row_bytes_g + ((lchunk ^ T::swz(tr + lrow)) * 16);
-    buffer_load16_lds(r, tile + tr * T::ROWB, voff, tr * row_bytes_g);
+    for (int j = 0; j < RPW / T::RPI; ++j) {
+      const int tr = wg * RPW + j * T::RPI;  // first row of this load
+      buffer_load16_lds(r, tile + tr * T::ROWB,
+                        base_off ^ (16u * ((tr >> 2) & 3)), tr * row_bytes_g);
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < RPW / T::RPI; ++j) {
+      const int tr = wg * RPW + j * T::RPI;  // first row of this load
+      const uint32_t voff =
+          lrow * row_bytes_g + ((lchunk ^ T::swz(tr + lrow)) * 16);
+      buffer_load16_lds(r, tile + tr * T::ROWB, voff, tr * row_bytes_g);
+    }
   }
 }
 
@@ -209,19 +220,6 @@ __device__ __forceinline__ bf16x8 read_tr_op(const char* tile,
 // ---------------------------------------------------------------------------
 // 2. dK / dV
 // ---------------------------------------------------------------------------
-template <int D>
-struct DkdvLayout {
-  static constexpr int TILE = StageTile<D>::BYTES;
-  static constexpr int STAGE = 2 * TILE + 2 * SUB * 4;  // Q, dO, lse2, delta
-  static constexpr int NSTAGE = 3;
-  // P of one stage, bf16, in the dV waves' register layout: [key wave 4]
-  // [query tile 2][half 2][lane 64] x 16 bytes.
-  static constexpr int PBUF = 4 * 2 * 2 * 64 * 16;
-  static constexpr int SMEM = NSTAGE * STAGE + 2 * PBUF;
-};
-
-constexpr int NT_KV = 512;  // dK/dV: eight waves
-
 // One gradient of a wave's 32 keys: dV (ROLE 0) or dK (ROLE 1, scaled).
 // Accumulator register i of chunk c holds key row 8*(i/4) + 4*lh + i%4 of the
 // wave's keys, dim 32*c + li.
@@ -267,250 +265,59 @@ __device__ __forceinline__ void write_keys(const BwdParams& p,
       out[index(c, i)] = fmaf(acc[c][i], sc_out, prev[c][i]);
 }
 
-// Eight waves in two roles over the same 128 keys (wave w: keys 32*(w%4) ..
-// +32).  Waves 0-3 (dV role) compute S = Q K^T, P = exp(s S - LSE) and
-// dV += P^T dO for stage t, and leave P (bf16) in LDS; waves 4-7 (dK role)
-// follow one stage behind: dP = dO V^T, dS = P (dP - D) with the P of stage
-// t-1 from LDS, dK += dS^T Q.  Four products per (key block, query stage)
-// as in the algorithm, split evenly between the roles, and each wave needs
-// one accumulator and its operand fragments, so it fits 256 registers and
-// two waves share each SIMD.  Stage tiles are kept three deep (the dK role
-// reads stage t-1 while the dV role reads t and loads t+1).
-template <int D, int ROLE>
-__device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem,
-                                          const DevRow& pc, int hk, int wave,
-                                          int lane) {
-  using L = DkdvLayout<D>;
-  const int li = lane & 31;
-  const int lh = lane >> 5;
-  const int kw = wave & 3;
-  const int k_in_blk = kw * 32 + li;
-  const DevRun* runs = p.kvorder.runs;
-  const int64_t kv_row = int64_t{pc.row} * BK + k_in_blk;
+// Operand reads by LDS byte address: the stage's base is part of the address
+// register, so that no XORed copies of it stay live over the loop.
+typedef float f32x8 __attribute__((ext_vector_type(8)));
 
-  // dV role: K fragments (B operand of S); dK role: V fragments (of dP).
-  bf16x8 frag[D / 16];
-  load_frags<D>(frag, ROLE == 0 ? p.k : p.v, kv_row, p.hkv, hk, lh);
+__device__ __forceinline__ bf16x8 lds_frag(uint32_t a) {
+  typedef __attribute__((address_space(3))) const bf16x8 T;
+  return *(T*)a;
+}
+__device__ __forceinline__ f32x4 lds_f4(uint32_t a) {
+  typedef __attribute__((address_space(3))) const f32x4 T;
+  return *(T*)a;
+}
+__device__ __forceinline__ bf16x8 lds_tr(uint32_t a0, uint32_t a1, int imm) {
+  typedef __attribute__((address_space(3))) s16x4 T;
+  return join_bf16(__builtin_amdgcn_ds_read_tr16_b64_v4i16((T*)(a0 + imm)),
+                   __builtin_amdgcn_ds_read_tr16_b64_v4i16((T*)(a1 + imm)));
+}
 
-  f32x16 acc[D / 32];
+// Order of a block of N MFMAs with R LDS operand reads each: the reads of
+// AHEAD MFMAs in flight ahead of the MFMA that uses them.
+template <int N, int R, int AHEAD>
+__device__ __forceinline__ void pipeline_reads() {
+  __builtin_amdgcn_sched_group_barrier(0x100, R * AHEAD, 0);
 #pragma unroll
-  for (int cc = 0; cc < D / 32; ++cc) zero(acc[cc]);
-
-  if (pc.nblk > 0) {
-    TileAddr<D> ta;
-    ta.init(lane, wave, 0);
-    bf16x8* pbuf = reinterpret_cast<bf16x8*>(smem + L::NSTAGE * L::STAGE);
-    // Stage cursor over (query head of the group, run, block in run, half);
-    // the callers count the stages.
-    struct Cur {
-      int g, r, off, s;
-      DevRun run;
-    };
-    auto advance = [&](Cur c) {
-      if (++c.s == 2) {
-        c.s = 0;
-        if (++c.off == c.run.nblk) {
-          c.off = 0;
-          if (++c.r == pc.run_e) {
-            c.r = pc.run_b;
-            ++c.g;
-          }
-          c.run = load_const(runs, c.r);
-        }
-      }
-      return c;
-    };
-    auto issue = [&](const Cur& c, int buf) {
-      char* base = smem + buf * L::STAGE;
-      const int h = hk * p.group + c.g;
-      const int64_t row0 = int64_t{c.run.blk0 + c.off} * BQ + c.s * SUB;
-      // Only the dV waves load: a wave that issues direct-to-LDS loads is
-      // held up for a few hundred cycles per stage, and the dK role is the
-      // longer of the two (its products read P from LDS after the dV role
-      // wrote it), so the loads go where there is slack (measured: dK/dV
-      // 4-5 % faster than eight loading waves).
-      if constexpr (ROLE == 0) {
-        load_stage_tile<D, 4>(p.q, row0, p.hq, h, base, kw, lane);
-        load_stage_tile<D, 4>(p.d_o, row0, p.hq, h, base + L::TILE, kw, lane);
-        float* f = reinterpret_cast<float*>(base + 2 * L::TILE);
-        if (kw == 0) load_stage_floats(p.lse2 + int64_t{h} * p.rows_q + row0,
-                                       f, lane);
-        if (kw == 1) load_stage_floats(p.delta + int64_t{h} * p.rows_q + row0,
-                                       f + SUB, lane);
-      }
-    };
-
-    const int nstage = 2 * pc.nblk;
-    // Iterations t = 0 .. nstage: loads of stage t+1; the dV role computes
-    // stage t (t < nstage), the dK role stage t-1 (t >= 1).  Every iteration
-    // but the last ends with a barrier, the same count in both roles.  Stage
-    // j lives in buffer j % 3 (its previous occupant, stage j-3, was last
-    // read by the dK role in iteration j-2) and its P in P buffer j % 2.
-    Cur lc{pc.walk, pc.run, pc.off, 0,
-           load_const(runs, pc.run)};  // next load
-    Cur cc_ = lc;  // stage this wave computes next
-    issue(lc, 0);
-    lc = advance(lc);
-#pragma unroll
-    for (int kk = 0; kk < D / 16; ++kk) wait_for(frag[kk]);
-    wait_vmem();
-    __syncthreads();
-    int lbuf = 1;   // buffer of the stage loaded next
-    int cbuf = 0;   // buffer of the stage computed next
-    int pb_i = 0;   // P buffer of that stage
-    for (int t = 0; t <= nstage; ++t) {
-      if (t + 1 < nstage) {
-        issue(lc, lbuf);
-        lc = advance(lc);
-        lbuf = lbuf == L::NSTAGE - 1 ? 0 : lbuf + 1;
-      }
-      const bool work = ROLE == 0 ? t < nstage : t >= 1;
-      if (work) {
-        const char* base = smem + cbuf * L::STAGE;
-        const char* sq = base;
-        const char* sdo = base + L::TILE;
-        const float* slse =
-            reinterpret_cast<const float*>(base + 2 * L::TILE);
-        const float* sdlt = slse + SUB;
-        const int lim =
-            k_in_blk - cc_.run.delta - cc_.off * BQ - cc_.s * SUB;
-        bf16x8* pst = pbuf + pb_i * (L::PBUF / 16) + kw * 256;
-#pragma unroll
-        for (int qt = 0; qt < 2; ++qt) {
-          __builtin_amdgcn_sched_barrier(0);
-          // dV role: S = Q K^T; dK role: dP = dO V^T.  Lane li owns key
-          // k_in_blk, register i owns query 32*qt + acc_row(i, lh).
-          f32x16 x;
-          zero(x);
-          const char* at = ROLE == 0 ? sq : sdo;
-#pragma unroll
-          for (int kk = 0; kk < D / 16; ++kk)
-            x = mfma32(read_row_op<D>(at, ta.row, qt, kk), frag[kk], x);
-          {
-            constexpr int NM = D / 16;
-            __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
-#pragma unroll
-            for (int i = 0; i < NM - 3; ++i) {
-              __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-              __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            }
-            __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);
-          }
-          bf16x8 op[2];  // P (dV role) or dS (dK role), k-contiguous
-          if constexpr (ROLE == 0) {
-            if (cc_.run.cls == 1) {
-              // key k of the block is hidden from query q of the run iff
-              // k - q > delta + (offset of this stage in the run).
-#pragma unroll
-              for (int i = 0; i < 16; ++i)
-                if (qt * 32 + acc_row(i, lh) < lim) x[i] = -INFINITY;
-            }
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh) {
-              const int q0 = qt * 32 + hh * 16 + lh * 8;
-              const f32x4 l0 = *reinterpret_cast<const f32x4*>(slse + q0);
-              const f32x4 l1 = *reinterpret_cast<const f32x4*>(slse + q0 + 4);
-#pragma unroll
-              for (int e = 0; e < 8; ++e) {
-                const float lq = e < 4 ? l0[e] : l1[e - 4];
-                op[hh][e] = static_cast<__bf16>(
-                    exp2_fast(fmaf(x[hh * 8 + e], p.scale_log2, -lq)));
-              }
-              pst[(qt * 2 + hh) * 64 + lane] = op[hh];
-            }
-          } else {
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh) {
-              const int q0 = qt * 32 + hh * 16 + lh * 8;
-              const f32x4 d0 = *reinterpret_cast<const f32x4*>(sdlt + q0);
-              const f32x4 d1 = *reinterpret_cast<const f32x4*>(sdlt + q0 + 4);
-              const bf16x8 pv = pst[(qt * 2 + hh) * 64 + lane];
-#pragma unroll
-              for (int e = 0; e < 8; ++e) {
-                const float dq = e < 4 ? d0[e] : d1[e - 4];
-                op[hh][e] = static_cast<__bf16>(static_cast<float>(pv[e]) *
-                                                (x[hh * 8 + e] - dq));
-              }
-            }
-          }
-          // dV += P^T dO or dK += dS^T Q (scale at the end); the B operand
-          // is read transposed from the dO or Q row tile.
-          __builtin_amdgcn_sched_barrier(0);
-          const char* bt = ROLE == 0 ? sdo : sq;
-#pragma unroll
-          for (int c = 0; c < D / 32; ++c)
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh)
-              acc[c] = mfma32(op[hh], read_tr_op<D>(bt, ta, c, 2 * qt + hh),
-                              acc[c]);
-          {
-            constexpr int NM = D / 16;  // two transpose reads per MFMA
-            __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
-#pragma unroll
-            for (int i = 0; i < NM - 3; ++i) {
-              __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-              __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-            }
-            __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);
-          }
-        }
-      }
-      if (work) {
-        cc_ = advance(cc_);
-        cbuf = cbuf == L::NSTAGE - 1 ? 0 : cbuf + 1;
-        pb_i ^= 1;
-      }
-      if (t < nstage) {
-        wait_vmem();
-        lds_barrier();
-      }
-    }
+  for (int i = 0; i < N - AHEAD; ++i) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, R, 0);
   }
-
-  write_keys<D, ROLE>(p, pc, hk, kw, li, lh, acc);
+  __builtin_amdgcn_sched_group_barrier(0x008, AHEAD, 0);
 }
 
+// A wave holds everything of its 32 keys: K and V fragments and dK and dV
+// accumulators, 192 registers at d = 128, 96 at d = 64, beside the scores.  At
+// d = 128 that fits 256 registers (two workgroups per compute unit, 67 KB of
+// LDS each) only because the addresses take five, S and dP use one tile of
+// registers after the other and P is unpacked again for dS instead of kept in
+// float32; d = 64 has room for both and fits 168 (three workgroups).  Before, eight waves in two roles
+// passed P through LDS, one role a stage behind the other (two waves per SIMD).
+// 8192 queries x 16384 keys x 32 heads, whole backward: d = 128 6730 us with
+// the roles, 6533 without, 6450 with the operand reads two or three MFMAs ahead;
+// d = 64 4073, 3574 and 3545.
 template <int D>
-__global__ __launch_bounds__(NT_KV, 1) void bwd_dkdv_kernel(BwdParams p) {
-  extern __shared__ __align__(16) char smem[];
-  const int tid = threadIdx.x;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lane = tid & 63;
-  const DevOrder& order = p.kvorder;
-  const int slot = queued_slot(order.n_items, order.queue,
-                               reinterpret_cast<int*>(smem + DkdvLayout<D>::SMEM),
-                               blockIdx.x);
-  if (slot < 0) return;
-  // The whole item (its runs once per query head of the group), or a piece.
-  int hk;
-  const DevRow pc = load_slot(order, slot, p.hkv, 1, &hk);
-  if (wave < 4)
-    dkdv_role<D, 0>(p, smem, pc, hk, wave, lane);
-  else
-    dkdv_role<D, 1>(p, smem, pc, hk, wave, lane);
-}
-
-// ---------------------------------------------------------------------------
-// 2b. dK / dV, head dim 64
-//
-// At d = 64 one wave holds all four operands of its 32 keys -- K and V
-// fragments, dK and dV accumulators, 96 registers -- beside the scores, so no
-// roles and no P through LDS: four waves of 32 keys, Q and dO stages double
-// buffered (34 KB), three workgroups per compute unit.  8192 queries x 16384
-// keys x 32 heads: 2760 us with two roles of waves (two per SIMD, bound by
-// the dK role's chain of dP, dS and dK), 2060-2190 here.
-// ---------------------------------------------------------------------------
-template <int D>
-struct FusedLayout {
+struct DkdvLayout {
   static constexpr int TILE = StageTile<D>::BYTES;
   static constexpr int STAGE = 2 * TILE + 2 * SUB * 4;  // Q, dO, lse2, delta
   static constexpr int SMEM = 2 * STAGE;
 };
 
 template <int D>
-__device__ __forceinline__ void dkdv_fused(const BwdParams& p, char* smem,
+__device__ __forceinline__ void dkdv_item(const BwdParams& p, char* smem,
                                            int block) {
-  using L = FusedLayout<D>;
+  using L = DkdvLayout<D>;
+  constexpr int ROWB = StageTile<D>::ROWB;
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63;
@@ -580,68 +387,109 @@ __device__ __forceinline__ void dkdv_fused(const BwdParams& p, char* smem,
     wait_vmem();
     __syncthreads();
     int buf = 0;
+    typedef __attribute__((address_space(3))) char lds_char;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)smem;
+    uint32_t ra = lds0 + ta.row, t0 = lds0 + ta.tr0, t1 = lds0 + ta.tr1;
+    uint32_t fa = lds0 + 2 * L::TILE + lh * 32;
     for (int left = 2 * pc.nblk;;) {
       --left;
       const Cur nxt = advance(cur);
       if (left > 0) issue(nxt, buf ^ 1);
-      const char* sq = smem + buf * L::STAGE;
-      const char* sdo = sq + L::TILE;
-      const float* slse = reinterpret_cast<const float*>(sq + 2 * L::TILE);
-      const float* sdlt = slse + SUB;
 #pragma unroll
       for (int qt = 0; qt < 2; ++qt) {
         // S = Q K^T and dP = dO V^T: lane li owns key k_in_blk, register i
-        // owns query 32*qt + acc_row(i, lh).
-        f32x16 x, y;
-        zero(x);
-        zero(y);
+        // owns query 32*qt + acc_row(i, lh).  P = exp2(s S - LSE),
+        // dS = P (dP - D).
+        auto scores = [&](f32x16& x, const bf16x8 (&f)[D / 16], int tile) {
+          zero(x);
 #pragma unroll
-        for (int kk = 0; kk < D / 16; ++kk) {
-          x = mfma32(read_row_op<D>(sq, ta.row, qt, kk), kf[kk], x);
-          y = mfma32(read_row_op<D>(sdo, ta.row, qt, kk), vf[kk], y);
-        }
-        if (cur.run.cls == 1) {
+          for (int kk = 0; kk < D / 16; ++kk)
+            x = mfma32(lds_frag((ra ^ (32 * kk)) + tile + qt * 32 * ROWB),
+                       f[kk], x);
+        };
+        auto mask = [&](f32x16& x) {
+          if (cur.run.cls != 1) return;
           // key k of the block is hidden from query q of the run iff
-          // k - q > delta + (offset of this stage in the run).
-          const int lim =
-              k_in_blk - cur.run.delta - cur.off * BQ - cur.s * SUB;
+          // k - q > delta + (offset of this stage in the run); the lane half's
+          // share of the query index is on the limit's side.
+          const int lim = k_in_blk - 8 * lh -
+                          __builtin_amdgcn_readfirstlane(
+                              cur.run.delta + cur.off * BQ + cur.s * SUB);
 #pragma unroll
           for (int i = 0; i < 16; ++i)
-            if (qt * 32 + acc_row(i, lh) < lim) x[i] = -INFINITY;
-        }
+            if (qt * 32 + acc_row(i, 0) < lim) x[i] = -INFINITY;
+        };
+        // LSE (j = 0) or D (j = 1) of queries 8*hh + 0..7 of the lane half.
+        auto row_floats = [&](int j, int hh) {
+          const uint32_t at = fa + 4 * (j * SUB + qt * 32 + hh * 16);
+          const f32x4 lo = lds_f4(at), hi = lds_f4(at + 16);
+          return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        };
+        auto probs = [&](const f32x16& x, int hh) {
+          const f32x8 lse = row_floats(0, hh);
+          f32x8 e8;
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            e8[e] = exp2_fast(fmaf(x[hh * 8 + e], p.scale_log2, -lse[e]));
+          return e8;
+        };
         bf16x8 pf[2], ds[2];
+        auto make_ds = [&](f32x8 e8, const f32x16& y, int hh) {
+          const f32x8 dlt = row_floats(1, hh);
 #pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-          const int q0 = qt * 32 + hh * 16 + lh * 8;
+          for (int e = 0; e < 8; ++e) e8[e] *= y[hh * 8 + e] - dlt[e];
+          ds[hh] = __builtin_convertvector(e8, bf16x8);
+        };
+        if constexpr (D == 64) {
+          // Room for both score tiles: dS from P in float32.
+          f32x16 x, y;
+          scores(x, kf, 0);
+          scores(y, vf, L::TILE);
+          mask(x);
 #pragma unroll
-          for (int q4 = 0; q4 < 2; ++q4) {
-            const f32x4 ls =
-                *reinterpret_cast<const f32x4*>(slse + q0 + 4 * q4);
-            const f32x4 dl =
-                *reinterpret_cast<const f32x4*>(sdlt + q0 + 4 * q4);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const int i = hh * 8 + q4 * 4 + e;
-              const float pv = exp2_fast(fmaf(x[i], p.scale_log2, -ls[e]));
-              pf[hh][q4 * 4 + e] = static_cast<__bf16>(pv);
-              ds[hh][q4 * 4 + e] = static_cast<__bf16>(pv * (y[i] - dl[e]));
-            }
+          for (int hh = 0; hh < 2; ++hh) {
+            const f32x8 e8 = probs(x, hh);
+            pf[hh] = __builtin_convertvector(e8, bf16x8);
+            make_ds(e8, y, hh);
           }
+        } else {
+          f32x16 x;
+          scores(x, kf, 0);
+          pipeline_reads<D / 16, 1, 3>();
+          mask(x);
+#pragma unroll
+          for (int hh = 0; hh < 2; ++hh) {
+            pf[hh] = __builtin_convertvector(probs(x, hh), bf16x8);
+            asm("" : "+v"(pf[hh]));  // unpack below instead of rounding again
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          scores(x, vf, L::TILE);
+          pipeline_reads<D / 16, 1, 3>();
+#pragma unroll
+          for (int hh = 0; hh < 2; ++hh)
+            make_ds(__builtin_convertvector(pf[hh], f32x8), x, hh);
+          __builtin_amdgcn_sched_barrier(0);
         }
         // dV += P^T dO, dK += dS^T Q (scaled at the end).
 #pragma unroll
         for (int c = 0; c < D / 32; ++c)
 #pragma unroll
           for (int hh = 0; hh < 2; ++hh) {
-            acc_v[c] = mfma32(pf[hh], read_tr_op<D>(sdo, ta, c, 2 * qt + hh),
-                              acc_v[c]);
-            acc_k[c] = mfma32(ds[hh], read_tr_op<D>(sq, ta, c, 2 * qt + hh),
-                              acc_k[c]);
+            const uint32_t a0 = t0 ^ (64 * c), a1 = t1 ^ (64 * c);
+            const int at = (2 * qt + hh) * 16 * ROWB;
+            acc_v[c] = mfma32(pf[hh], lds_tr(a0, a1, L::TILE + at), acc_v[c]);
+            acc_k[c] = mfma32(ds[hh], lds_tr(a0, a1, at), acc_k[c]);
           }
+        if constexpr (D == 128) pipeline_reads<D / 8, 2, 2>();
       }
       if (left == 0) break;
       wait_vmem();
       lds_barrier();  // stage buf^1 landed; every wave is done with buf
+      const int d = buf ? -L::STAGE : L::STAGE;
+      ra += d;
+      t0 += d;
+      t1 += d;
+      fa += d;
       buf ^= 1;
       cur = nxt;
     }
@@ -845,23 +693,20 @@ __device__ __forceinline__ void dq_item(const BwdParams& p, char* smem,
     }
 }
 
+// Both passes in one launch, the dK/dV workgroups (the longer ones) first.
+// They have the same shape (four waves; 256 registers and 67 and 64 KB of LDS at
+// d = 128, 168 and 34 and 32 KB at d = 64), so dQ items fill the compute units
+// that run out of dK/dV items and only one start and one end of a launch is
+// paid: 72 -> 66 us for a 4K-token backward with d = 64, 930 -> 882 us for the
+// four chunk tasks of a striped tile with d = 128.
 template <int D>
-__global__ __launch_bounds__(NT, 1) void bwd_dq_kernel(BwdParams p) {
-  extern __shared__ __align__(16) char smem[];
-  dq_item<D>(p, smem, blockIdx.x);
-}
-
-// Head dim 64: both passes in one launch, the dK/dV workgroups (the longer
-// ones) first.  They have the same shape (four waves, 168 registers, 34 and 32
-// KB of LDS), so dQ items fill the compute units that run out of dK/dV items
-// and only one start and one end of a launch is paid.
-template <int D>
-__global__ __launch_bounds__(NT, 3) void bwd_both_kernel(BwdParams p,
-                                                         int kv_wgs) {
-  extern __shared__ __align__(16) char smem[];
+__global__ __launch_bounds__(NT, D == 64 ? 3 : 2) void bwd_kernel(BwdParams p,
+                                                                    int kv_wgs) {
+  // Aligned so that XORs of an address's chunk bits do not reach its base.
+  extern __shared__ __align__(256) char smem[];
   const int block = blockIdx.x;
   if (block < kv_wgs)
-    dkdv_fused<D>(p, smem, block);
+    dkdv_item<D>(p, smem, block);
   else
     dq_item<D>(p, smem, block - kv_wgs);
 }
@@ -931,24 +776,12 @@ hipError_t launch(const BwdParams& p, const PlanBlob& blob,
   const int grid_kv = static_cast<int>(queued_launch_grid(p.kvorder.n_items));
   const int grid_q = static_cast<int>(queued_launch_grid(p.qorder.n_items));
   // LDS: + one int for the item slot of a queued workgroup.
-  if constexpr (D == 64) {
-    const size_t smem = std::max(FusedLayout<D>::SMEM, DqLayout<D>::SMEM) + 16;
-    const int kv_wgs = (grid_kv + kNumXcd - 1) / kNumXcd * kNumXcd;
-    hipLaunchKernelGGL(bwd_both_kernel<D>, dim3(kv_wgs + grid_q), dim3(NT),
-                       smem, stream, p, kv_wgs);
-  } else {
-    const size_t smem_kv = DkdvLayout<D>::SMEM + 16;
-    const size_t smem_q = DqLayout<D>::SMEM + 16;
-    e = ensure_dynamic_lds<bwd_dkdv_kernel<D>>(smem_kv);
-    if (e == hipSuccess) e = ensure_dynamic_lds<bwd_dq_kernel<D>>(smem_q);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(bwd_dkdv_kernel<D>, dim3(grid_kv), dim3(NT_KV), smem_kv,
-                       stream, p);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(bwd_dq_kernel<D>, dim3(grid_q), dim3(NT), smem_q,
-                       stream, p);
-  }
+  const size_t smem = std::max(DkdvLayout<D>::SMEM, DqLayout<D>::SMEM) + 16;
+  e = ensure_dynamic_lds<bwd_kernel<D>>(smem);
+  if (e != hipSuccess) return e;
+  const int kv_wgs = (grid_kv + kNumXcd - 1) / kNumXcd * kNumXcd;
+  hipLaunchKernelGGL(bwd_kernel<D>, dim3(kv_wgs + grid_q), dim3(NT), smem,
+                     stream, p, kv_wgs);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int sums = (2 * p.kvorder.n_splits * p.hkv +

@@ -82,9 +82,12 @@ __device__ __forceinline__ DevRow load_slot(const DevOrder& o, int slot,
                                             int heads, int group, int* head) {
   const SlotPlace at = place_slot(o.mode, slot, o.m, heads, group);
   DevRow e = load_const(o.rows, at.probe);
-  int entry;
-  place_in_class(o.mode, at, e.before, e.same, heads, group, &entry, head);
+  int entry, h;
+  place_in_class(o.mode, at, e.before, e.same, heads, group, &entry, &h);
   if (entry != at.probe) e = load_const(o.rows, entry);
+  // Uniform, but computed by divisions in the vector unit: kept scalar, or
+  // every buffer descriptor formed from it would be read lane by lane.
+  *head = __builtin_amdgcn_readfirstlane(h);
   return e;
 }
 
