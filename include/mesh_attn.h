@@ -260,7 +260,7 @@ ma_status_t mesh_attn_chunk_fwd(const ma_problem_t* prob, const int32_t* q_idx,
                                 float* lse, int32_t accumulate, void* ws,
                                 size_t ws_bytes, hipStream_t stream);
 
-/* Device workspace bytes mesh_attn_chunk_bwd needs (any chunk of the tile). */
+/* Device workspace bytes mesh_attn_chunk_bwd uses (any chunk of the tile). */
 size_t mesh_attn_chunk_bwd_workspace_size(const ma_problem_t* prob,
                                           int32_t nq, int32_t nkv);
 
@@ -342,7 +342,10 @@ ma_status_t mesh_attn_lse_merge(int32_t k_parts, int64_t rows, int32_t heads,
  * Backward (Algorithm 3, the per-pair loop, summed over the tile).
  * ------------------------------------------------------------------------- */
 
-/* Device workspace bytes mesh_attn_tile_bwd needs for this tile. */
+/* Device workspace bytes mesh_attn_tile_bwd uses for this tile: the work lists,
+ * two floats per row and query head and, for tiles of few work items, room
+ * for partial gradients of split items (at most 135 MB).  A workspace without
+ * that room is accepted, as in the forward. */
 size_t mesh_attn_bwd_workspace_size(const ma_problem_t* prob, int32_t nq,
                                     int32_t nkv);
 

@@ -297,7 +297,9 @@ ma_status_t take_buffer(size_t bytes, PinnedBuf** out) {
   }
   auto* b = new PinnedBuf;
   b->cap = std::max(bytes, kAlign);
-  hipError_t e = hipHostMalloc(&b->host, b->cap, hipHostMallocDefault);
+  // Read by kernels, on whichever device a call runs.
+  hipError_t e = hipHostMalloc(&b->host, b->cap,
+                               hipHostMallocPortable | hipHostMallocMapped);
   if (e != hipSuccess) {
     delete b;
     return hip_fail(e, "hipHostMalloc(work list)");

@@ -39,6 +39,12 @@ FWD = [
     dataclasses.replace(_T, name="uneven-lanes", q_idx=[1, 7, 3],
                         kv_idx=[0, 2, 9, 3, 4, 5, 6, 8, 15], num_q_heads=7,
                         num_kv_heads=7, head_dim=128),
+    # A list too long for the kernel arguments (copied to the workspace, or
+    # built on the device by the allocation-free call).
+    dataclasses.replace(_T, name="long-list", num_partitions=64,
+                        q_idx=list(range(63, 3, -1)),
+                        kv_idx=list(range(0, 60, 5)), causal=True, layout=1,
+                        num_q_heads=1, num_kv_heads=1),
 ]
 
 
@@ -75,6 +81,41 @@ def test_split_forward(gpu, cfg, out):
                                  to_np(k), to_np(v))
     check_fwd(f"{cfg.name} split", to_np(o), to_np(lse), ro, rl)
     check_fwd(f"{cfg.name} whole", to_np(o1), to_np(lse1), ro, rl)
+
+
+def test_long_list_noalloc_in_a_captured_graph(gpu):
+    """The allocation-free forward whose list is built on the device, split and
+    whole, captured and replayed three times with an eager call of the other
+    tile (which rewrites the scratch arrays) before each replay."""
+    split = next(c for c in FWD if c.name == "long-list")
+    whole = dataclasses.replace(split, kv_idx=[60, 3], name="whole-list",
+                                num_q_heads=5)
+    calls = []
+    for cfg in (split, whole):
+        q, k, v, _ = make_qkv(cfg)
+        qd, kd, vd = (t.to(gpu) for t in (q, k, v))
+        o = torch.empty_like(qd)
+        lse = torch.empty((cfg.num_q_heads, qd.shape[0]), device=gpu)
+
+        def call(cfg=cfg, qd=qd, kd=kd, vd=vd, o=o, lse=lse):
+            ma.mesh_attn_tile_fwd_noalloc(cfg.problem(), cfg.q_idx,
+                                          cfg.kv_idx, qd, kd, vd, o, lse)
+        call()
+        torch.cuda.synchronize()
+        calls.append((call, o, lse, o.clone(), lse.clone()))
+    for i in (0, 1):
+        call, o, lse, ref_o, ref_l = calls[i]
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            call()
+        for rep in range(3):
+            o.fill_(float("nan"))
+            lse.fill_(float("nan"))
+            calls[1 - i][0]()
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(o, ref_o) and torch.equal(lse, ref_l), (i, rep)
 
 
 # Tiles of a few short items (the waves of a workgroup split the keys): the
