@@ -34,10 +34,12 @@ resident in HBM (all bf16, head_dim 128):
                    compute units busy: the same work per compute unit at
                    different chip load, which separates the kernel's
                    efficiency in clock cycles from the clock the chip holds.
+                   The workspace leaves no room for partial results, so that
+                   no item is split over idle compute units.
   bwd_items64 .. bwd_items256  (not in the default step) the backward on
-                   64, 128 or 256 dK/dV items of equal length (a quarter,
-                   half or all of the compute units for the dK/dV kernel),
-                   for the same comparison.
+                   64, 128 or 256 dK/dV items of equal length, as the library
+                   runs it: items split where that pays, dQ items in the same
+                   launch.
 
 `value` is the headline tile's forward TFLOP/s: algorithmic FLOPs
 (4 * d * Hq * visible (query, key) pairs) divided by the forward call's mean
@@ -270,7 +272,9 @@ def main():
             ma, WORKLOADS["mesh1m-causal-outlier"], dev)
     for name in ITEM_LEGS:
         if name in legs:
-            tiles[name] = Tile(ma, WORKLOADS[f"items-{name[9:]}"], dev)
+            tiles[name] = t = Tile(ma, WORKLOADS[f"items-{name[9:]}"], dev)
+            # Room for the work list only (partials take megabytes).
+            t.ws = t.ws[:256 * 1024]
     for name in BWD_ITEM_LEGS:
         if name in legs:
             t = Tile(ma, WORKLOADS[f"bwd-items-{name[9:]}"], dev,

@@ -59,8 +59,9 @@ struct Slice<true> {
 //
 // LPI lanes per (row, head) item and items indexed in 32 bits, where head_dim
 // and the sizes allow it (else LPI 0, head_dim / 8 at run time, in 64 bits):
-// with 64-bit divisions by run-time values and a batch of 4, a fold of 3 float32 partials of 1535 x 21 x 64 (33 MB) spent as long on
-// addresses as on its one round trip to memory (8.8 us a kernel, 7.3 now).
+// with 64-bit divisions by run-time values and a batch of 4, a fold of 3
+// float32 partials of 1535 x 21 x 64 (33 MB) spent as long on addresses as on
+// its one round trip to memory (8.8 us a kernel, 7.3 now).
 template <bool IN_F32, bool OUT_F32, int B, int LPI, typename Index>
 __global__ __launch_bounds__(NT) void lse_merge_kernel(MergeParams p) {
   constexpr float kLog2e = 1.4426950408889634f;
