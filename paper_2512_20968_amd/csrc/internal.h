@@ -60,8 +60,13 @@ struct DevOrder {
 };
 
 // A small work list travels in the kernel's arguments instead of the
-// workspace: no upload, and no pinned copy to keep until one is done.
-constexpr int kInlinePlan = 3072;
+// workspace: no upload, and no pinned copy to keep until one is done.  Kernel
+// arguments stay within 4 KB; 512 bytes are left for the other ones.  A list
+// that has to be copied costs a copy kernel and an event: 64 items of 1024
+// blocks (16 rows in 4 pieces each, 3.1 KB) 483 us a call with the copy, 475
+// in the arguments; calls with shorter lists the same within 0.6 % when the
+// arguments grow from 3 KB.
+constexpr int kInlinePlan = 3584;
 struct PlanBlob {
   alignas(16) char bytes[kInlinePlan];
 };
@@ -187,6 +192,9 @@ struct BwdParams {
   float* kvparts;
   float* qparts;
 };
+static_assert(sizeof(FwdParams) + sizeof(PlanBlob) <= 4096 &&
+                  sizeof(BwdParams) + sizeof(PlanBlob) <= 4096,
+              "kernel arguments");
 
 // The backward passes as the cut of long items sees them; a block is 128 x 128.
 // d = 128: dK/dV one workgroup per compute unit, 3.8 us per block with the chip
