@@ -308,6 +308,8 @@ ma_status_t take_buffer(size_t bytes, PinnedBuf** out) {
   return MA_OK;
 }
 
+// What a plan depends on: head_dim too, through the cut (the passes of
+// internal.h) and fwd_is_short.
 std::string plan_key(int pass, const ma_problem_t* p, const int32_t* q_idx,
                      int32_t nq, const int32_t* kv_idx, int32_t nkv,
                      const ma_chunk_t& ch) {
@@ -321,6 +323,7 @@ std::string plan_key(int pass, const ma_problem_t* p, const int32_t* q_idx,
   put(&p->partition_len, sizeof(int32_t));
   put(&p->num_q_heads, sizeof(int32_t));
   put(&p->num_kv_heads, sizeof(int32_t));
+  put(&p->head_dim, sizeof(int32_t));
   put(&p->causal, sizeof(int32_t));
   put(&p->layout, sizeof(int32_t));
   put(&nq, sizeof nq);
@@ -433,6 +436,14 @@ size_t split_bound(int64_t parts, size_t part_bytes) {
 }
 
 constexpr ma_chunk_t kWholeTile{0, 1, 0, 1};
+
+// Partial results of a plan against the slots that the call has room for.
+ma_status_t check_parts(const PassView& v, int32_t heads, int64_t slots) {
+  if (int64_t{v.parts} * heads <= slots) return MA_OK;
+  return fail(MA_ERR_WORKSPACE_TOO_SMALL,
+              "work list of %d partial results for each of %d heads, room for "
+              "%lld", v.parts, heads, static_cast<long long>(slots));
+}
 
 // The sides of a call: the forward's Q-major one, or the backward's Q-major
 // (dQ) and KV-major (dK/dV) ones.  Returns their number.
@@ -742,6 +753,9 @@ ma_status_t fwd_impl(const ma_problem_t* prob, const int32_t* q_idx,
   return with_plan(
       0, prob, q_idx, nq, kv_idx, nkv, ch, may_split, stream, &blob,
       [&](const PlanView& plan) {
+        const int64_t slots = may_split ? parts_of(prob, nq, nkv, ch) : 0;
+        const ma_status_t room = check_parts(plan.a, fp.hq, slots);
+        if (room != MA_OK) return room;
         hipError_t e = hipSuccess;
         if (plan.src) {
           e = launch_plan_copy(wsb, plan.src, plan.bytes, stream);
@@ -750,7 +764,7 @@ ma_status_t fwd_impl(const ma_problem_t* prob, const int32_t* q_idx,
         fp.order = order_at(plan.a, plan.src ? wsb : nullptr);
         fp.part_lse = reinterpret_cast<float*>(
             wsb + (plan.src ? align_up(plan.bytes) : 0));
-        fp.part_o = fp.part_lse + parts_of(prob, nq, nkv, ch) * kFwdBM;
+        fp.part_o = fp.part_lse + slots * kFwdBM;
         e = launch_tile_fwd(fp, blob, prob->head_dim, o_f32, stream);
         if (e != hipSuccess) return hip_fail(e, "tile_fwd launch");
         return ok();
@@ -786,6 +800,7 @@ ma_status_t bwd_impl(const ma_problem_t* prob, const int32_t* q_idx,
     return fail(MA_ERR_WORKSPACE_TOO_SMALL, "workspace %zu bytes < %zu",
                 ws_bytes, need);
   const BwdParts parts = bwd_parts(prob, nq, nkv, ch, false);
+  const bool may_split = ws_bytes >= need + parts.bytes;
   char* wsb = static_cast<char*>(ws);
   BwdParams bp{};
   bp.q = static_cast<const uint16_t*>(q);
@@ -807,8 +822,13 @@ ma_status_t bwd_impl(const ma_problem_t* prob, const int32_t* q_idx,
   bp.accumulate = accumulate;
   PlanBlob blob;
   return with_plan(
-      1, prob, q_idx, nq, kv_idx, nkv, ch, ws_bytes >= need + parts.bytes,
-      stream, &blob, [&](const PlanView& plan) {
+      1, prob, q_idx, nq, kv_idx, nkv, ch, may_split, stream, &blob,
+      [&](const PlanView& plan) {
+        ma_status_t room =
+            check_parts(plan.a, bp.hq, may_split ? parts.q : 0);
+        if (room == MA_OK)
+          room = check_parts(plan.b, bp.hkv, may_split ? parts.kv : 0);
+        if (room != MA_OK) return room;
         const size_t row_bytes =
             align_up(static_cast<size_t>(nq) * prob->partition_len *
                      prob->num_q_heads * 4);

@@ -13,7 +13,8 @@ import oracle
 import paper_2512_20968_amd as ma
 from mesh_inputs import WORKLOADS, make_grad, make_qkv
 
-from helpers import check_fwd, check_grad, log, to_np
+from helpers import (check_fwd, check_grad, log, oracle_backward_rows,
+                     to_np)
 
 pytestmark = pytest.mark.gpu
 
@@ -116,6 +117,44 @@ def test_long_list_noalloc_in_a_captured_graph(gpu):
             graph.replay()
             torch.cuda.synchronize()
             assert torch.equal(o, ref_o) and torch.equal(lse, ref_l), (i, rep)
+
+
+@pytest.mark.parametrize("first", [64, 128])
+def test_long_lists_that_differ_in_head_dim_only(gpu, first):
+    """One tile at both head dims, whose cuts differ, through the cache of long
+    lists: each gets the bits of its allocation-free forward (which has no
+    cache), and the backward the oracle's gradients."""
+    base = dataclasses.replace(
+        _T, num_partitions=8, partition_len=4096, q_idx=[0, 1, 2, 3, 4],
+        kv_idx=[0, 1] if first == 64 else [1, 0], num_q_heads=4,
+        num_kv_heads=4, grad_seed=73)
+    for d in (first, 192 - first):
+        cfg = dataclasses.replace(base, head_dim=d)
+        prob = cfg.problem()
+        q, k, v, _ = make_qkv(cfg)
+        do = make_grad(cfg)
+        qd, kd, vd, dod = (t.to(gpu) for t in (q, k, v, do))
+        o, o2 = (torch.empty_like(qd) for _ in range(2))
+        lse, lse2 = (torch.empty((4, qd.shape[0]), device=gpu)
+                     for _ in range(2))
+        log(f"d = {d}: forward, allocation-free forward, backward")
+        ma.mesh_attn_tile_fwd(prob, cfg.q_idx, cfg.kv_idx, qd, kd, vd, o, lse)
+        ma.mesh_attn_tile_fwd_noalloc(prob, cfg.q_idx, cfg.kv_idx, qd, kd, vd,
+                                      o2, lse2)
+        torch.cuda.synchronize()
+        assert torch.equal(o, o2) and torch.equal(lse, lse2)
+        dq, dk, dv = (torch.full(t.shape, float("nan"), device=gpu)
+                      for t in (qd, kd, vd))
+        ma.mesh_attn_tile_bwd(prob, cfg.q_idx, cfg.kv_idx, qd, kd, vd, o, dod,
+                              lse, dq, dk, dv)
+        torch.cuda.synchronize()
+        q_rows, kv_rows = [0, 4095, 9000, 20479], [0, 4095, 4096, 8191]
+        rq, rk, rv, _ = oracle_backward_rows(
+            prob, cfg.q_idx, cfg.kv_idx, q, k, v, do, [3], q_rows, kv_rows)
+        for name, g, rows, r in (("dq", dq, q_rows, rq), ("dk", dk, kv_rows, rk),
+                                 ("dv", dv, kv_rows, rv)):
+            assert torch.isfinite(g).all()
+            check_grad(f"d = {d} {name}", to_np(g[rows][:, [3]]), r)
 
 
 # Tiles of a few short items (the waves of a workgroup split the keys): the

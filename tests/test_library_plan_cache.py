@@ -1,0 +1,149 @@
+"""The cache of long work lists on the CPU: the library's host code linked with
+a stand-in for the GPU (stub_runtime.cpp) whose stream runs when the test says
+so and whose launches check every range that the kernels write."""
+
+import ctypes
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+import paper_2512_20968_amd as ma
+from paper_2512_20968_amd import _binding
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HERE = os.path.join(ROOT, "tests")
+
+
+@pytest.fixture(scope="module")
+def library(tmp_path_factory):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("g++ not available")
+    out = tmp_path_factory.mktemp("host") / "libhost.so"
+    csrc = os.path.join(ROOT, "paper_2512_20968_amd", "csrc")
+    subprocess.run(
+        [gxx, "-std=c++17", "-O1", "-Wall", "-shared", "-fPIC",
+         "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROOT, "include"), "-I",
+         csrc, "-I", "/opt/rocm/include", os.path.join(csrc, "host.cpp"),
+         os.path.join(HERE, "stub_runtime.cpp"), "-o", str(out),
+         "-Wl,-Bsymbolic"], check=True)
+    return out
+
+
+class Host:
+    """One copy of the library, with a cache of its own."""
+
+    FAKE = [ctypes.c_void_p(0x10000 * (i + 1)) for i in range(10)]
+
+    def __init__(self, path):
+        lib = ctypes.CDLL(str(path))
+        for name in ("tile_fwd", "tile_bwd", "chunk_fwd", "chunk_bwd",
+                     "fwd_workspace_size", "bwd_workspace_size",
+                     "chunk_fwd_workspace_size", "chunk_bwd_workspace_size",
+                     "tile_fwd_noalloc", "last_error"):
+            fn = getattr(lib, "mesh_attn_" + name)
+            fn.restype, fn.argtypes = _binding._SIGNATURES["mesh_attn_" + name]
+        lib.stub_workspace.argtypes = [ctypes.c_void_p, ctypes.c_size_t]
+        lib.stub_run.argtypes = [ctypes.c_int64]
+        lib.stub_pending.restype = ctypes.c_int64
+        self.lib = lib
+        self.ws = np.empty(0, np.uint8)
+
+    def workspace(self, nbytes):
+        if self.ws.size < nbytes + 256:
+            self.ws = np.empty(nbytes + 256, np.uint8)
+        at = (self.ws.ctypes.data + 255) // 256 * 256
+        self.lib.stub_workspace(at, nbytes)
+        return at
+
+    @staticmethod
+    def _list(idx):
+        return (ctypes.c_int32 * len(idx))(*idx), len(idx)
+
+    def call(self, pass_, prob, q_idx, kv_idx, ws_bytes=None, chunk=None,
+             check=True):
+        """Runs a forward (0) or backward (1); returns the status."""
+        pr = ma.Problem.make(prob)
+        q, nq = self._list(q_idx)
+        kv, nkv = self._list(kv_idx)
+        kind = "chunk_" if chunk else ""
+        name = kind + ("bwd" if pass_ else "fwd")
+        if ws_bytes is None:
+            ws_bytes = getattr(self.lib, f"mesh_attn_{name}_workspace_size")(
+                ctypes.byref(pr), nq, nkv)
+        ws = self.workspace(ws_bytes)
+        head = [ctypes.byref(pr), q, nq, kv, nkv]
+        f = self.FAKE
+        if chunk:
+            head.append(ctypes.byref(_binding.Chunk(*chunk)))
+        if pass_:
+            args = f[:9] + [0, ws, ws_bytes, None]
+        elif chunk:
+            args = f[:5] + [0, ws, ws_bytes, None]
+        else:
+            args = f[:4] + [0, f[4], ws, ws_bytes, None]
+        fn = getattr(self.lib,
+                     "mesh_attn_" + (name if chunk else "tile_" + name))
+        st = fn(*head, *args)
+        if check:
+            assert st == 0, self.lib.mesh_attn_last_error()
+        return st
+
+    def last(self):
+        out = (ctypes.c_int32 * 14)()
+        self.lib.stub_last(out)
+        return tuple(out[:7]), tuple(out[7:])
+
+    def counts(self):
+        out = (ctypes.c_int32 * 4)()
+        self.lib.stub_counts(out)
+        return dict(zip(("out_of_range", "stale", "pinned", "launches"), out))
+
+    def finish(self):
+        self.lib.stub_run(self.lib.stub_pending())
+
+
+@pytest.fixture
+def host(library, tmp_path):
+    # A copy per test: its own globals, so an empty cache.
+    return Host(shutil.copy(library, tmp_path / "libhost.so"))
+
+
+@pytest.fixture
+def other(library, tmp_path):
+    return Host(shutil.copy(library, tmp_path / "libother.so"))
+
+
+def _prob(n, P, hq, hkv, d, causal=0, layout=0):
+    return dict(num_partitions=n, partition_len=P, num_q_heads=hq,
+                num_kv_heads=hkv, head_dim=d, causal=causal, layout=layout,
+                softmax_scale=0.125)
+
+
+# Lists too long for the kernel arguments, of few items, long enough to be
+# split; the numbers of pieces and partials of the two head dims differ.
+SPLIT_LONG = [
+    (0, _prob(8, 4096, 4, 4, 64), [0, 1, 2, 3, 4], [0, 1]),
+    (0, _prob(64, 1024, 2, 1, 64, 1, 1), list(range(63, 23, -1)),
+     list(range(0, 60, 5))),
+    (1, _prob(8, 4096, 2, 2, 64), [0, 1, 2, 3], [0, 1]),
+    (1, _prob(8, 2048, 8, 2, 64, 1), [3, 1, 5], [2, 3, 0, 1]),
+]
+
+
+@pytest.mark.parametrize("first", [64, 128])
+@pytest.mark.parametrize("pass_,prob,q,kv", SPLIT_LONG)
+def test_tiles_that_differ_in_head_dim_have_plans_of_their_own(
+        host, other, pass_, prob, q, kv, first):
+    second = 192 - first
+    host.call(pass_, dict(prob, head_dim=first), q, kv)
+    assert not any(o[0] for o in host.last())  # not in the kernel arguments
+    assert any(o[5] > 0 for o in host.last())  # split
+    host.call(pass_, dict(prob, head_dim=second), q, kv)
+    other.call(pass_, dict(prob, head_dim=second), q, kv)
+    # What the second head dim gets does not depend on the first call.
+    assert host.last() == other.last()
+    assert host.counts()["out_of_range"] == 0
