@@ -180,10 +180,12 @@ __device__ __forceinline__ void write_rows(const FwdParams& p,
   const float inv = lt > 0.f ? 1.f / lt : 0.f;
   const float lse2 = lt > 0.f ? m + __builtin_amdgcn_logf(lt) : -INFINITY;
   if (item.part >= 0) {
-    // A partial result: O normalised, float32, and the LSE in log2 units.
+    // A partial result: O normalised, float32, and the LSE in log2 units.  A
+    // sum that is not a number stays so until the fold, whose result is then
+    // the whole item's (O NaN, LSE -inf).
     const int64_t prow =
         int64_t{h * order.parts + item.part} * BM + q_in_blk;
-    if (lh == 0) p.part_lse[prow] = lse2;
+    if (lh == 0) p.part_lse[prow] = lt == lt ? lse2 : lt;
 #pragma unroll
     for (int cc = 0; cc < D / 32; ++cc)
 #pragma unroll

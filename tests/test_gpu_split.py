@@ -84,6 +84,38 @@ def test_split_forward(gpu, cfg, out):
     check_fwd(f"{cfg.name} whole", to_np(o1), to_np(lse1), ro, rl)
 
 
+@pytest.mark.parametrize("cfg", FWD[:3], ids=[c.name for c in FWD[:3]])
+def test_split_forward_of_a_nan_key(gpu, cfg):
+    """A key that is not a number: rows that see it get NaN in O and -inf in
+    LSE, split or whole, and the others what they get without it."""
+    q, k, v, _ = make_qkv(cfg)
+    row = 3 * cfg.partition_len + 77
+    k[row] = float("nan")
+    qd, kd, vd = (t.to(gpu) for t in (q, k, v))
+    prob = cfg.problem()
+    need = ma.mesh_attn_fwd_workspace_size(prob, cfg.nq, cfg.nkv)
+    qpos = oracle.problem_positions(prob, cfg.q_idx)
+    kpos = oracle.problem_positions(prob, cfg.kv_idx)
+    hit = torch.from_numpy(qpos >= (kpos[row] if cfg.causal else 0)).to(gpu)
+    assert hit.any()
+    for nbytes in (need, need - 256):
+        o = torch.empty_like(qd)
+        lse = torch.empty((cfg.num_q_heads, qd.shape[0]), device=gpu)
+        ws = torch.empty(nbytes, dtype=torch.uint8, device=gpu)
+        ma.mesh_attn_tile_fwd(prob, cfg.q_idx, cfg.kv_idx, qd, kd, vd, o, lse,
+                              ws=ws)
+        torch.cuda.synchronize()
+        assert torch.isnan(o[hit]).all() and torch.isfinite(o[~hit]).all()
+        assert torch.isneginf(lse[:, hit]).all(), nbytes
+        if not hit.all():
+            k2 = torch.where(torch.isnan(kd), 0.0, kd)
+            o2, lse2 = torch.empty_like(o), torch.empty_like(lse)
+            ma.mesh_attn_tile_fwd(prob, cfg.q_idx, cfg.kv_idx, qd, k2, vd, o2,
+                                  lse2, ws=ws)
+            assert torch.equal(o[~hit], o2[~hit])
+            assert torch.equal(lse[:, ~hit], lse2[:, ~hit])
+
+
 def test_long_list_noalloc_in_a_captured_graph(gpu):
     """The allocation-free forward whose list is built on the device, split and
     whole, captured and replayed three times with an eager call of the other
