@@ -132,10 +132,25 @@ __device__ __forceinline__ DevOrder order_of(const FwdParams& p) {
   return o;
 }
 
+// Weights of the two-part online-softmax reducer (running accumulation: the
+// stored pair and this call's): lse = M + log2(2^(old - M) + 2^(new - M)) with
+// M the larger, O = w_old O_old + w_new O_new with w = 2^(lse_part - lse).
+// Neither part sees a key: the stored O stays.  log2 units.
+struct FoldWeights {
+  float w_old, w_new, lse2;
+};
+__device__ __forceinline__ FoldWeights fold_weights(float old2, float new2) {
+  const float mx = fmaxf(old2, new2);
+  if (mx == -INFINITY) return {1.f, 0.f, new2};
+  const float a = exp2_fast(old2 - mx), b = exp2_fast(new2 - mx);
+  const float sum = a + b;
+  return {a / sum, b / sum, mx + __builtin_amdgcn_logf(sum)};
+}
+
 // Four dims of a row of the result, the lanes of the row together: with
-// `accumulate` (float32) folded into the stored pair with the two-part
-// reducer.  All lanes of the row are in one wave and read the stored LSE before
-// the first of them rewrites it (program order).
+// `accumulate` (float32) folded into the stored pair.  All lanes of the row are
+// in one wave and read the stored LSE before the first of them rewrites it
+// (program order).
 template <int D, bool OUT_F32>
 __device__ __forceinline__ void store_folded(const FwdParams& p, int h,
                                              int64_t q_row, int col, f32x4 x,
@@ -145,16 +160,12 @@ __device__ __forceinline__ void store_folded(const FwdParams& p, int h,
   if constexpr (OUT_F32) {
     f32x4* dst = reinterpret_cast<f32x4*>(static_cast<float*>(p.o) + oidx);
     if (p.accumulate) {
-      const float old2 = p.lse[lidx] * 1.4426950408889634f;
+      const FoldWeights w = fold_weights(p.lse[lidx] * 1.4426950408889634f,
+                                         lse2);
       const f32x4 prev = *dst;
-      const float mx = fmaxf(old2, lse2);
-      const float mu = mx == -INFINITY ? 0.f : mx;
-      const float a = exp2_fast(old2 - mu), b = exp2_fast(lse2 - mu);
-      const float inv = a + b > 0.f ? 1.f / (a + b) : 0.f;
 #pragma unroll
-      for (int t = 0; t < 4; ++t)
-        x[t] = fmaf(a * inv, prev[t], b * inv * x[t]);
-      lse2 = a + b > 0.f ? mx + __builtin_amdgcn_logf(a + b) : -INFINITY;
+      for (int t = 0; t < 4; ++t) x[t] = fmaf(w.w_old, prev[t], w.w_new * x[t]);
+      lse2 = w.lse2;
     }
     *dst = x;
   } else {
@@ -199,35 +210,20 @@ __device__ __forceinline__ void write_rows(const FwdParams& p,
     return;
   }
   const int64_t lidx = int64_t{h} * p.rows_q + q_row;
-  // Running accumulation (float32 partials only): fold (O, LSE) of this
-  // call into the stored pair with the two-part online-softmax reducer,
-  // lse = M + ln(e^(lse_old - M) + e^(lse_new - M)) with M the larger, and
-  // O = w_old O_old + w_new O_new with w = e^(lse_part - lse).  Both lane
-  // halves of a row read the stored LSE before the first half rewrites it
-  // (same wave, program order).
-  float w_old = 0.f, w_new = 1.f, lse_out = lse2;  // log2 units
+  // Running accumulation (float32 partials only): both lane halves of a row
+  // read the stored LSE before the first half rewrites it (same wave, program
+  // order).
+  FoldWeights w{0.f, 1.f, lse2};
   if constexpr (OUT_F32) {
-    if (p.accumulate) {
-      const float old2 = p.lse[lidx] * 1.4426950408889634f;
-      const float mx = fmaxf(old2, lse2);
-      if (mx == -INFINITY) {
-        w_old = 1.f;  // neither part sees a key: keep the stored O = 0
-        w_new = 0.f;
-      } else {
-        const float a = exp2_fast(old2 - mx), b = exp2_fast(lse2 - mx);
-        const float sum = a + b;
-        lse_out = mx + __builtin_amdgcn_logf(sum);
-        w_old = a / sum;
-        w_new = b / sum;
-      }
-    }
+    if (p.accumulate)
+      w = fold_weights(p.lse[lidx] * 1.4426950408889634f, lse2);
   }
   if (lh == 0)
     p.lse[lidx] =
-        lse_out == -INFINITY ? -INFINITY : lse_out * 0.69314718055994531f;
+        w.lse2 == -INFINITY ? -INFINITY : w.lse2 * 0.69314718055994531f;
   // O^T accumulator: register 4g+t of chunk cc holds dim 32cc + 8g + 4lh + t.
   const int64_t obase = (q_row * p.hq + h) * D;
-  const float sc_new = inv * w_new;
+  const float sc_new = inv * w.w_new;
   // Accumulating: every stored value is read before the first store, so the
   // loads are issued back to back.
   f32x4 prev[OUT_F32 ? D / 32 : 1][4];
@@ -258,7 +254,7 @@ __device__ __forceinline__ void write_rows(const FwdParams& p,
         f32x4* dst = reinterpret_cast<f32x4*>(static_cast<float*>(p.o) + obase +
                                               dim);
 #pragma unroll
-        for (int t = 0; t < 4; ++t) x[t] = fmaf(w_old, prev[cc][g][t], x[t]);
+        for (int t = 0; t < 4; ++t) x[t] = fmaf(w.w_old, prev[cc][g][t], x[t]);
         *dst = x;
       } else {
         bf16x4 val;

@@ -274,6 +274,36 @@ def test_split_chunk_accumulation(gpu, P, d):
                   rl[:, rows])
 
 
+@pytest.mark.parametrize("P,d", [(1536, 128), (512, 64), (512, 128)])
+def test_accumulation_into_special_values(gpu, P, d):
+    """Accumulating chunk tasks, split or short: a row that sees no key of the
+    chunk keeps its O, also where its stored LSE is -inf; a row whose stored
+    LSE is NaN ends with NaN."""
+    cfg = dataclasses.replace(_T, partition_len=P, num_partitions=6,
+                              q_idx=[4, 0], kv_idx=[1, 3], causal=True,
+                              num_q_heads=2, num_kv_heads=1, head_dim=d)
+    q, k, v, _ = make_qkv(cfg)
+    qd, kd, vd = (t.to(gpu) for t in (q, k, v))
+    prob = cfg.problem()
+    o = torch.full(qd.shape, 2.0, device=gpu)
+    lse = torch.full((2, 2 * P), -float("inf"), device=gpu)
+    lse[0, 5] = lse[1, P - 1] = float("nan")  # rows that see keys
+    ma.mesh_attn_chunk_fwd(prob, cfg.q_idx, cfg.kv_idx, (0, 1, 0, 1), qd, kd,
+                           vd, o, lse, accumulate=1)
+    torch.cuda.synchronize()
+    assert (o[P:] == 2.0).all() and torch.isneginf(lse[:, P:]).all()
+    bad = torch.zeros((2, 2 * P), dtype=torch.bool, device=gpu)
+    bad[0, 5] = bad[1, P - 1] = True
+    assert torch.equal(torch.isnan(lse), bad)
+    assert torch.equal(torch.isnan(o).all(-1), bad.T)
+    ro, rl = oracle.tile_forward(prob, cfg.q_idx, cfg.kv_idx, to_np(q),
+                                 to_np(k), to_np(v))
+    good = ~bad[0].cpu().numpy() & ~bad[1].cpu().numpy()
+    good[P:] = False
+    check_fwd(f"d = {d}", to_np(o)[good], to_np(lse)[:, good], ro[good],
+              rl[:, good])
+
+
 # Backward: both passes split in one round; GQA whose pieces cross the walks
 # over the group's heads; causal with rows and keys that see nothing; only the
 # dK/dV side split (many query heads on one KV head); KV heads a multiple of
