@@ -743,8 +743,12 @@ __global__ __launch_bounds__(NT) void bwd_sum_kernel(BwdParams p) {
   const int heads = kv ? p.hkv : p.hq;
   float* out = (kv ? (role ? p.dk : p.dv) : p.dq) +
                ((int64_t{it.row} * 128 + row) * heads + head) * D + col;
+  // The stored value joins last, in one addition as with whole items: it may be
+  // much larger than the partials, which must not be rounded to its last bit one
+  // by one.
+  f32x4 stored = {0.f, 0.f, 0.f, 0.f};
+  if (p.accumulate) stored = *reinterpret_cast<const f32x4*>(out);
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  if (p.accumulate) acc = *reinterpret_cast<const f32x4*>(out);
   constexpr int B = 4;  // partials in flight
   for (int k0 = 0; k0 < it.nparts; k0 += B) {
     f32x4 x[B];
@@ -759,6 +763,8 @@ __global__ __launch_bounds__(NT) void bwd_sum_kernel(BwdParams p) {
 #pragma unroll
         for (int t = 0; t < 4; ++t) acc[t] += x[u][t];
   }
+#pragma unroll
+  for (int t = 0; t < 4; ++t) acc[t] += stored[t];
   *reinterpret_cast<f32x4*>(out) = acc;
 }
 

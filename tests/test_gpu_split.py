@@ -358,3 +358,36 @@ def test_split_backward(gpu, cfg, accumulate):
     for name, s, w, r in zip(("dq", "dk", "dv"), split, whole, refs):
         check_grad(f"{cfg.name} {name} split", to_np(s), r)
         check_grad(f"{cfg.name} {name} whole", to_np(w), r)
+
+
+_ADD = [BWD[0], BWD[2], BWD[3]]
+
+
+@pytest.mark.parametrize("cfg", _ADD, ids=[c.name for c in _ADD])
+def test_split_backward_accumulates_in_one_addition(gpu, cfg):
+    """accumulate = 1 adds the sum of the partial gradients in one addition:
+    exactly the stored value plus what accumulate = 0 gives, also where the
+    stored value is much larger.  Whole items too, where scaling dK and dQ in
+    the same rounding changes nothing (a scale that is a power of two)."""
+    cfg = dataclasses.replace(cfg, grad_seed=74)
+    q, k, v, _ = make_qkv(cfg)
+    prob = cfg.problem()
+    qd, kd, vd, dod = (t.to(gpu) for t in (q, k, v, make_grad(cfg)))
+    o = torch.empty_like(qd)
+    lse = torch.empty((cfg.num_q_heads, qd.shape[0]), device=gpu)
+    ma.mesh_attn_tile_fwd(prob, cfg.q_idx, cfg.kv_idx, qd, kd, vd, o, lse)
+    need = ma.mesh_attn_bwd_workspace_size(prob, cfg.nq, cfg.nkv)
+    always = (0, 1, 2) if cfg.head_dim == 64 else (2,)
+    for nbytes, exact in ((need, (0, 1, 2) if cfg.name == "both-sides"
+                           else always), (need - 256, always)):
+        res = []
+        for accumulate in (0, 1):
+            g = [torch.full(t.shape, 1000.0 * accumulate, device=gpu)
+                 for t in (qd, kd, vd)]
+            ws = torch.empty(nbytes, dtype=torch.uint8, device=gpu)
+            ma.mesh_attn_tile_bwd(prob, cfg.q_idx, cfg.kv_idx, qd, kd, vd, o,
+                                  dod, lse, *g, accumulate=accumulate, ws=ws)
+            torch.cuda.synchronize()
+            res.append(g)
+        for i in exact:
+            assert torch.equal(res[1][i], 1000.0 + res[0][i]), (nbytes, i)
