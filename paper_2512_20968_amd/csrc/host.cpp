@@ -220,7 +220,8 @@ ma_status_t export_runs(const std::vector<int32_t>& ptr,
 // while the library is in use: every upload records an event on the caller's
 // stream, an evicted plan's buffer joins a spare list, and a spare buffer is
 // reused for a new plan only once all events recorded after copies from it
-// have completed (hipEventQuery, which does not wait).  No call synchronizes.
+// have completed (hipEventQuery, which does not wait) and no call is between
+// finding its plan and recording its event.  No call synchronizes.
 // ---------------------------------------------------------------------------
 
 constexpr size_t kAlign = 256;
@@ -244,6 +245,7 @@ struct PinnedBuf {
   void* host = nullptr;
   size_t cap = 0;
   std::vector<PendingEvent> pending;  // recorded after copies from this buffer
+  int in_use = 0;  // calls that have yet to record theirs
 };
 
 struct Plan {
@@ -287,7 +289,7 @@ ma_status_t take_buffer(size_t bytes, PinnedBuf** out) {
   size_t best = g_spare.size();
   for (size_t i = 0; i < g_spare.size(); ++i) {
     PinnedBuf* b = g_spare[i];
-    if (b->cap < bytes || !retire_completed(b)) continue;
+    if (b->cap < bytes || b->in_use > 0 || !retire_completed(b)) continue;
     if (best == g_spare.size() || b->cap < g_spare[best]->cap) best = i;
   }
   if (best != g_spare.size()) {
@@ -467,9 +469,8 @@ int sides_of(int pass, const ma_problem_t* p, const int32_t* q_idx, int32_t nq,
   return 2;
 }
 
-// Builds the plan of a call: into `blob` if it is short, else (or from the
-// cache) into a pinned buffer, *buf.  Called with the cache locked for the
-// second part.
+// The cached plan of a call, built into a pinned buffer if it is not there.
+// Called with the cache locked.
 ma_status_t cached_plan(const std::string& key, const plan::Side* sides, int n,
                         Plan** out) {
   auto it = g_plans.find(key);
@@ -516,9 +517,10 @@ ma_status_t cached_plan(const std::string& key, const plan::Side* sides, int n,
 }
 
 // Runs `launch(view)`, which enqueues the work of a call on `stream`, with the
-// call's plan in `blob` or in a pinned buffer.  With a pinned one the cache
-// stays locked until the event behind that work is recorded, so that no other
-// thread can recycle the buffer in between.
+// call's plan in `blob` or in a pinned buffer.  A pinned one is marked in use
+// until the event behind that work is recorded, so that no other thread can
+// recycle it in between; the cache is not locked meanwhile (a launch may wait
+// for room in its queue).
 template <class F>
 ma_status_t with_plan(int pass, const ma_problem_t* p, const int32_t* q_idx,
                       int32_t nq, const int32_t* kv_idx, int32_t nkv,
@@ -531,36 +533,42 @@ ma_status_t with_plan(int pass, const ma_problem_t* p, const int32_t* q_idx,
   if (inline_plan(sides, n, blob, &view)) return launch(view);
   const std::string key =
       plan_key(pass * 2 + may_split, p, q_idx, nq, kv_idx, nkv, ch);
-  std::lock_guard<std::mutex> lock(g_plan_mu);
-  Plan* plan = nullptr;
-  ma_status_t st = cached_plan(key, sides, n, &plan);
-  if (st != MA_OK) return st;
-  retire_completed(plan->buf);  // keeps the list as short as the copies in flight
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
-  std::vector<hipEvent_t>& pool = g_free_events[dev];
-  hipEvent_t ev;
-  if (!pool.empty()) {
-    ev = pool.back();
-    pool.pop_back();
-  } else {
-    e = hipEventCreateWithFlags(&ev, hipEventDisableTiming |
-                                          hipEventDisableSystemFence);
-    if (e != hipSuccess) return hip_fail(e, "hipEventCreateWithFlags");
+  PinnedBuf* buf = nullptr;
+  PendingEvent pe{nullptr, 0};
+  {
+    std::lock_guard<std::mutex> lock(g_plan_mu);
+    Plan* plan = nullptr;
+    const ma_status_t st = cached_plan(key, sides, n, &plan);
+    if (st != MA_OK) return st;
+    buf = plan->buf;
+    retire_completed(buf);  // keeps the list as short as the copies in flight
+    hipError_t e = hipGetDevice(&pe.dev);
+    if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
+    std::vector<hipEvent_t>& pool = g_free_events[pe.dev];
+    if (!pool.empty()) {
+      pe.ev = pool.back();
+      pool.pop_back();
+    } else {
+      e = hipEventCreateWithFlags(&pe.ev, hipEventDisableTiming |
+                                              hipEventDisableSystemFence);
+      if (e != hipSuccess) return hip_fail(e, "hipEventCreateWithFlags");
+    }
+    view.bytes = plan->bytes;
+    view.a = plan->a;
+    view.b = plan->b;
+    view.src = buf->host;
+    ++buf->in_use;
   }
-  view.bytes = plan->bytes;
-  view.a = plan->a;
-  view.b = plan->b;
-  view.src = plan->buf->host;
-  st = launch(view);
+  const ma_status_t st = launch(view);
   // Also after a failed launch: the copy may have been enqueued before it.
-  e = hipEventRecord(ev, stream);
+  const hipError_t e = hipEventRecord(pe.ev, stream);
+  std::lock_guard<std::mutex> lock(g_plan_mu);
   if (e != hipSuccess) {
-    pool.push_back(ev);
+    g_free_events[pe.dev].push_back(pe.ev);
     return st != MA_OK ? st : hip_fail(e, "hipEventRecord(work list)");
   }
-  plan->buf->pending.push_back(PendingEvent{ev, dev});
+  buf->pending.push_back(pe);
+  --buf->in_use;
   return st;
 }
 

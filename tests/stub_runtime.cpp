@@ -1,13 +1,14 @@
 // A stand-in for the GPU under the library's host code, for CPU tests: linked
-// with csrc/host.cpp instead of the HIP runtime and the kernels.  One stream
-// whose work (copies of work lists, events) runs only when the test says so,
-// so that the lifetime of the pinned work lists can be checked; a launch
-// checks that everything its kernels write in the workspace lies inside it.
+// with csrc/host.cpp instead of the HIP runtime and the kernels.  The work of a
+// stream (copies of work lists, events) runs only when the test says so, so
+// that the lifetime of the pinned work lists can be checked; a launch checks
+// that everything its kernels write in the workspace lies inside it.
 
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <deque>
+#include <map>
 #include <mutex>
 #include <vector>
 
@@ -29,20 +30,21 @@ struct Op {
   std::vector<char> want;  // the source when the copy was enqueued
 };
 
-std::deque<Op> ops;
+std::map<hipStream_t, std::deque<Op>> ops;
 char *ws = nullptr, *ws_end = nullptr;
 int32_t out_of_range = 0, stale = 0, pinned = 0, launches = 0;
 int32_t fail_launch = 0, fail_event = 0;
 int32_t last[2][7];
 void (*hook)() = nullptr;
 
-void enqueue_copy(void* dst, const void* src, size_t bytes) {
+void enqueue_copy(void* dst, const void* src, size_t bytes,
+                  hipStream_t stream) {
   Op o;
   o.dst = static_cast<char*>(dst);
   o.src = static_cast<const char*>(src);
   o.want.assign(o.src, o.src + bytes);
   if (o.dst < ws || o.dst + bytes > ws_end) ++out_of_range;
-  ops.push_back(std::move(o));
+  ops[stream].push_back(std::move(o));
 }
 
 void inside(const void* at, size_t bytes, const void* end) {
@@ -70,6 +72,7 @@ hipError_t launched() {
 extern "C" {
 
 const char* hipGetErrorString(hipError_t) { return "stub error"; }
+hipError_t hipGetLastError() { return hipSuccess; }
 hipError_t hipGetDevice(int* d) {
   *d = 0;
   return hipSuccess;
@@ -84,7 +87,7 @@ hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
   *e = reinterpret_cast<hipEvent_t>(new Event);
   return hipSuccess;
 }
-hipError_t hipEventRecord(hipEvent_t e, hipStream_t) {
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t stream) {
   std::lock_guard<std::recursive_mutex> lock(mu);
   if (fail_event > 0) {
     --fail_event;
@@ -93,7 +96,7 @@ hipError_t hipEventRecord(hipEvent_t e, hipStream_t) {
   Op o;
   o.ev = reinterpret_cast<Event*>(e);
   ++o.ev->recorded;
-  ops.push_back(std::move(o));
+  ops[stream].push_back(std::move(o));
   return hipSuccess;
 }
 hipError_t hipEventQuery(hipEvent_t e) {
@@ -106,23 +109,18 @@ void stub_workspace(char* p, size_t bytes) {
   ws = p;
   ws_end = p + bytes;
 }
-// Runs the first n pending operations of the stream.
-void stub_run(int64_t n) {
+// Runs the pending operations of the stream.
+void stub_run(hipStream_t stream) {
   std::lock_guard<std::recursive_mutex> lock(mu);
-  for (; n > 0 && !ops.empty(); --n) {
-    Op& o = ops.front();
+  for (; !ops[stream].empty(); ops[stream].pop_front()) {
+    Op& o = ops[stream].front();
     if (o.ev) {
       ++o.ev->done;
     } else {
       if (std::memcmp(o.src, o.want.data(), o.want.size()) != 0) ++stale;
       std::memcpy(o.dst, o.src, o.want.size());
     }
-    ops.pop_front();
   }
-}
-int64_t stub_pending() {
-  std::lock_guard<std::recursive_mutex> lock(mu);
-  return static_cast<int64_t>(ops.size());
 }
 void stub_fail(int32_t n_launches, int32_t n_events) {
   fail_launch = n_launches;
@@ -146,9 +144,9 @@ void stub_last(int32_t out[2][7]) { std::memcpy(out, last, sizeof last); }
 namespace mesh_attn {
 
 hipError_t launch_plan_copy(void* dst, const void* src, size_t bytes,
-                            hipStream_t) {
+                            hipStream_t stream) {
   std::lock_guard<std::recursive_mutex> lock(mu);
-  enqueue_copy(dst, src, bytes);
+  enqueue_copy(dst, src, bytes, stream);
   return hipSuccess;
 }
 
@@ -169,11 +167,12 @@ hipError_t launch_tile_fwd(const FwdParams& p, const PlanBlob&, int head_dim,
 }
 
 hipError_t launch_tile_bwd(const BwdParams& p, const PlanBlob&, int head_dim,
-                           hipStream_t) {
+                           hipStream_t stream) {
   std::lock_guard<std::recursive_mutex> lock(mu);
   note(0, p.qorder);
   note(1, p.kvorder);
-  if (p.plan_src) enqueue_copy(p.plan_dst, p.plan_src, p.plan_bytes);
+  if (p.plan_src)
+    enqueue_copy(p.plan_dst, p.plan_src, p.plan_bytes, stream);
   inside(p.plan_dst, p.plan_bytes, p.delta);
   inside(p.delta, p.rows_q * p.hq * 4, p.lse2);
   const size_t tile = size_t{128} * head_dim * 4;

@@ -6,6 +6,7 @@ import ctypes
 import os
 import shutil
 import subprocess
+import threading
 
 import numpy as np
 import pytest
@@ -47,8 +48,7 @@ class Host:
             fn = getattr(lib, "mesh_attn_" + name)
             fn.restype, fn.argtypes = _binding._SIGNATURES["mesh_attn_" + name]
         lib.stub_workspace.argtypes = [ctypes.c_void_p, ctypes.c_size_t]
-        lib.stub_run.argtypes = [ctypes.c_int64]
-        lib.stub_pending.restype = ctypes.c_int64
+        lib.stub_run.argtypes = [ctypes.c_void_p]
         self.lib = lib
         self.ws = np.empty(0, np.uint8)
 
@@ -64,7 +64,7 @@ class Host:
         return (ctypes.c_int32 * len(idx))(*idx), len(idx)
 
     def call(self, pass_, prob, q_idx, kv_idx, ws_bytes=None, chunk=None,
-             check=True):
+             stream=None, check=True):
         """Runs a forward (0) or backward (1); returns the status."""
         pr = ma.Problem.make(prob)
         q, nq = self._list(q_idx)
@@ -80,11 +80,11 @@ class Host:
         if chunk:
             head.append(ctypes.byref(_binding.Chunk(*chunk)))
         if pass_:
-            args = f[:9] + [0, ws, ws_bytes, None]
+            args = f[:9] + [0, ws, ws_bytes, stream]
         elif chunk:
-            args = f[:5] + [0, ws, ws_bytes, None]
+            args = f[:5] + [0, ws, ws_bytes, stream]
         else:
-            args = f[:4] + [0, f[4], ws, ws_bytes, None]
+            args = f[:4] + [0, f[4], ws, ws_bytes, stream]
         fn = getattr(self.lib,
                      "mesh_attn_" + (name if chunk else "tile_" + name))
         st = fn(*head, *args)
@@ -102,8 +102,9 @@ class Host:
         self.lib.stub_counts(out)
         return dict(zip(("out_of_range", "stale", "pinned", "launches"), out))
 
-    def finish(self):
-        self.lib.stub_run(self.lib.stub_pending())
+    def run(self, *streams):
+        for s in streams:
+            self.lib.stub_run(s)
 
 
 @pytest.fixture
@@ -147,3 +148,43 @@ def test_tiles_that_differ_in_head_dim_have_plans_of_their_own(
     # What the second head dim gets does not depend on the first call.
     assert host.last() == other.last()
     assert host.counts()["out_of_range"] == 0
+
+
+# A tile whose list is too long for the kernel arguments: 128 Q blocks.
+LONG = _prob(2048, 256, 1, 1, 64)
+
+
+def _long_tile(i):
+    return LONG, list(range(128)), [i]
+
+
+def test_a_launch_does_not_hold_up_other_threads(host):
+    """While one call is inside its launch (a full queue may hold it there),
+    another thread's call with a long list gets through."""
+    host.workspace(1 << 20)
+    done = []
+
+    def other_call():
+        host.call(0, *_long_tile(1), ws_bytes=1 << 20, stream=2)
+        done.append(True)
+
+    @ctypes.CFUNCTYPE(None)
+    def inside_the_launch():
+        th = threading.Thread(target=other_call, daemon=True)
+        th.start()
+        th.join(20)
+
+    host.lib.stub_hook(inside_the_launch)
+    host.call(0, *_long_tile(0), ws_bytes=1 << 20, stream=1)
+    assert done == [True]
+    host.run(1, 2)
+    assert host.counts() == dict(out_of_range=0, stale=0, pinned=2, launches=2)
+
+
+def test_a_failed_launch_is_reported(host):
+    host.lib.stub_fail(1, 0)
+    assert host.call(0, *_long_tile(0), check=False) == _binding.MA_ERR_HIP
+    assert b"launch" in host.lib.mesh_attn_last_error()
+    host.call(0, *_long_tile(0))
+    host.run(None)
+    assert host.counts()["stale"] == 0
