@@ -245,7 +245,7 @@ struct PinnedBuf {
   void* host = nullptr;
   size_t cap = 0;
   std::vector<PendingEvent> pending;  // recorded after copies from this buffer
-  int in_use = 0;  // calls that have yet to record theirs
+  int in_use = 0;  // calls that have yet to record theirs, or could not
 };
 
 struct Plan {
@@ -564,8 +564,11 @@ ma_status_t with_plan(int pass, const ma_problem_t* p, const int32_t* q_idx,
   const hipError_t e = hipEventRecord(pe.ev, stream);
   std::lock_guard<std::mutex> lock(g_plan_mu);
   if (e != hipSuccess) {
+    // The work is on its way, so the call has not failed; but nothing will
+    // tell when the list has been read: the buffer stays in use for good.
+    (void)hipGetLastError();  // or the next launch would report it
     g_free_events[pe.dev].push_back(pe.ev);
-    return st != MA_OK ? st : hip_fail(e, "hipEventRecord(work list)");
+    return st;
   }
   buf->pending.push_back(pe);
   --buf->in_use;

@@ -181,6 +181,20 @@ def test_a_launch_does_not_hold_up_other_threads(host):
     assert host.counts() == dict(out_of_range=0, stale=0, pinned=2, launches=2)
 
 
+@pytest.mark.parametrize("pass_", [0, 1])
+def test_a_failed_event_after_the_launch_is_not_a_failed_call(host, pass_):
+    host.lib.stub_fail(0, 1)
+    host.call(pass_, *_long_tile(0), stream=1)
+    assert host.counts()["launches"] == 1
+    # Nothing says when that call has read its list, so it keeps its buffer,
+    # also after the list has been evicted.
+    for i in range(1, 1100):
+        host.call(pass_, *_long_tile(i), stream=2)
+        host.run(2)
+    host.run(1)
+    assert host.counts()["stale"] == 0
+
+
 def test_a_failed_launch_is_reported(host):
     host.lib.stub_fail(1, 0)
     assert host.call(0, *_long_tile(0), check=False) == _binding.MA_ERR_HIP
