@@ -62,7 +62,9 @@ typedef enum {
   MA_OK = 0,
   MA_ERR_INVALID_ARG = 1,         /* bad size, index, flag or pointer */
   MA_ERR_UNSUPPORTED = 2,         /* valid request the library does not serve */
-  MA_ERR_WORKSPACE_TOO_SMALL = 3, /* ws_bytes below the *_workspace_size() */
+  MA_ERR_WORKSPACE_TOO_SMALL = 3, /* ws_bytes below what the call cannot do
+                                     without: its work lists and, in the
+                                     backward, two floats per row and head */
   MA_ERR_HIP = 4,                 /* HIP runtime error, text in last_error */
   MA_ERR_CAPACITY = 5             /* caller-provided output array too small */
 } ma_status_t;
@@ -157,9 +159,11 @@ ma_status_t mesh_attn_worklist_kv_major(const ma_problem_t* prob,
  * with the online-softmax reducer inside the kernel).
  * ------------------------------------------------------------------------- */
 
-/* Device workspace bytes mesh_attn_tile_fwd uses for this tile: the work list
- * and, for tiles of few work items, room for partial results of items that are
- * split over several workgroups (at most 68 MB). */
+/* Device workspace bytes for mesh_attn_tile_fwd of this tile: the work list and
+ * room for partial results of items that are split over several workgroups (at
+ * most 68 MB).  Never less for more partitions: a workspace of this size also
+ * serves, with the same results as one of its own, every tile of the same
+ * problem with no more partitions in either list, and their chunk tasks. */
 size_t mesh_attn_fwd_workspace_size(const ma_problem_t* prob, int32_t nq,
                                     int32_t nkv);
 
@@ -169,10 +173,10 @@ size_t mesh_attn_fwd_workspace_size(const ma_problem_t* prob, int32_t nq,
  *           float32 (MA_FP32, a partial to be merged exactly later).
  *   lse     [Hq][nq*P] float32 device; -inf for a row that sees no key, whose
  *           O row is then 0.
- *   ws      device workspace of ws_bytes >= mesh_attn_fwd_workspace_size().
- *           One sized for another tile that holds this one's work list but
- *           not its partial results is accepted: no item is split then, which
- *           is slower and rounds differently.
+ *   ws      device workspace; mesh_attn_fwd_workspace_size() bytes always do.
+ *           Fewer are accepted if they hold this tile's work list: without
+ *           room for its partial results no item is split, which is slower
+ *           and rounds differently.
  * O = sum_j exp(x_j - LSE) v_j with x_j = s <q, k_j> over the visible keys;
  * LSE = ln sum_j exp(x_j).  bf16 MFMA products, float32 accumulation and
  * softmax. */
@@ -232,7 +236,7 @@ typedef struct {
                             rows (see mesh_attn_block_shape, pass 0)         */
 } ma_chunk_t;
 
-/* Device workspace bytes mesh_attn_chunk_fwd uses (any chunk of the tile). */
+/* Device workspace bytes for mesh_attn_chunk_fwd (any chunk of the tile). */
 size_t mesh_attn_chunk_fwd_workspace_size(const ma_problem_t* prob,
                                           int32_t nq, int32_t nkv);
 
@@ -260,7 +264,7 @@ ma_status_t mesh_attn_chunk_fwd(const ma_problem_t* prob, const int32_t* q_idx,
                                 float* lse, int32_t accumulate, void* ws,
                                 size_t ws_bytes, hipStream_t stream);
 
-/* Device workspace bytes mesh_attn_chunk_bwd uses (any chunk of the tile). */
+/* Device workspace bytes for mesh_attn_chunk_bwd (any chunk of the tile). */
 size_t mesh_attn_chunk_bwd_workspace_size(const ma_problem_t* prob,
                                           int32_t nq, int32_t nkv);
 
@@ -342,10 +346,10 @@ ma_status_t mesh_attn_lse_merge(int32_t k_parts, int64_t rows, int32_t heads,
  * Backward (Algorithm 3, the per-pair loop, summed over the tile).
  * ------------------------------------------------------------------------- */
 
-/* Device workspace bytes mesh_attn_tile_bwd uses for this tile: the work lists,
- * two floats per row and query head and, for tiles of few work items, room
- * for partial gradients of split items (at most 135 MB).  A workspace without
- * that room is accepted, as in the forward. */
+/* Device workspace bytes for mesh_attn_tile_bwd of this tile: the work lists,
+ * two floats per row and query head and room for partial gradients of split
+ * items (at most 135 MB).  It serves smaller tiles too, and one without room
+ * for partial gradients is accepted, as in the forward. */
 size_t mesh_attn_bwd_workspace_size(const ma_problem_t* prob, int32_t nq,
                                     int32_t nkv);
 

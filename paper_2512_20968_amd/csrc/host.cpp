@@ -584,16 +584,18 @@ size_t fwd_part_bytes(const ma_problem_t* p) {
   return static_cast<size_t>(kFwdBM) * (p->head_dim + 1) * 4;
 }
 
-// What splitting the forward's items adds to fwd_ws_bound.  any_chunk: enough
-// for every chunk pair of the tile, which has fewer items of fewer blocks.
+// What splitting the forward's items adds to fwd_ws_bound: for this chunk pair
+// alone, or (smaller_too) also for every tile of fewer partitions and every
+// chunk pair of them.  Those have no more blocks, but may be split where this
+// one has too many items.
 size_t fwd_split_bytes(const ma_problem_t* p, int32_t nq, int32_t nkv,
-                       const ma_chunk_t& ch, bool any_chunk) {
+                       const ma_chunk_t& ch, bool smaller_too) {
   const int64_t P = p->partition_len;
   const int64_t items = nq * (P / ch.num_q_chunks / kFwdBM) * p->num_q_heads;
   const int64_t blocks = nkv * (P / ch.num_kv_chunks / kFwdBN);
   const split::Pass& ps = fwd_pass(p->head_dim);
   const int64_t counted =
-      any_chunk ? std::min<int64_t>(items, ps.max_items) : items;
+      smaller_too ? std::min<int64_t>(items, ps.max_items) : items;
   const int64_t parts = split::parts_bound(counted, blocks, ps);
   return split_bound(parts, fwd_part_bytes(p));
 }
@@ -607,7 +609,7 @@ size_t bwd_ws_bound(const ma_problem_t* p, int32_t nq, int32_t nkv) {
 }
 
 // Partial slots of the split backward passes, and what splitting adds to
-// bwd_ws_bound (any_chunk as in fwd_split_bytes).
+// bwd_ws_bound (smaller_too as in fwd_split_bytes).
 struct BwdParts {
   int64_t kv, q;
   size_t kv_bytes, q_bytes;  // of the partial results
@@ -615,7 +617,7 @@ struct BwdParts {
 };
 
 BwdParts bwd_parts(const ma_problem_t* p, int32_t nq, int32_t nkv,
-                   const ma_chunk_t& ch, bool any_chunk) {
+                   const ma_chunk_t& ch, bool smaller_too) {
   const int64_t P = p->partition_len;
   const int64_t nqb = nq * (P / ch.num_q_chunks / kBwdBM);
   const int64_t nkb = nkv * (P / ch.num_kv_chunks / kBwdBN);
@@ -623,7 +625,8 @@ BwdParts bwd_parts(const ma_problem_t* p, int32_t nq, int32_t nkv,
   const int64_t q_items = nqb * p->num_q_heads;
   auto parts = [&](int64_t items, int64_t blocks, const split::Pass& ps) {
     return split::parts_bound(
-        any_chunk ? std::min<int64_t>(items, ps.max_items) : items, blocks, ps);
+        smaller_too ? std::min<int64_t>(items, ps.max_items) : items, blocks,
+        ps);
   };
   const int32_t g = p->num_q_heads / p->num_kv_heads;
   BwdParts b{parts(kv_items, nqb * g, dkdv_pass(p->head_dim)),
@@ -743,8 +746,8 @@ ma_status_t fwd_impl(const ma_problem_t* prob, const int32_t* q_idx,
   if (ws_bytes < need)
     return fail(MA_ERR_WORKSPACE_TOO_SMALL, "workspace %zu bytes < %zu",
                 ws_bytes, need);
-  // A workspace without room for partial results (one sized for another,
-  // larger tile) serves the call with whole items.
+  // A workspace without room for partial results serves the call with whole
+  // items.
   const bool may_split =
       ws_bytes >= need + fwd_split_bytes(prob, nq, nkv, ch, false);
   char* wsb = static_cast<char*>(ws);
@@ -944,14 +947,14 @@ size_t mesh_attn_fwd_workspace_size(const ma_problem_t* prob, int32_t nq,
                                     int32_t nkv) {
   if (check_problem(prob) != MA_OK || nq < 1 || nkv < 1) return 0;
   return fwd_ws_bound(prob, nq, nkv) +
-         fwd_split_bytes(prob, nq, nkv, kWholeTile, false);
+         fwd_split_bytes(prob, nq, nkv, kWholeTile, true);
 }
 
 size_t mesh_attn_bwd_workspace_size(const ma_problem_t* prob, int32_t nq,
                                     int32_t nkv) {
   if (check_problem(prob) != MA_OK || nq < 1 || nkv < 1) return 0;
   return bwd_ws_bound(prob, nq, nkv) +
-         bwd_parts(prob, nq, nkv, kWholeTile, false).bytes;
+         bwd_parts(prob, nq, nkv, kWholeTile, true).bytes;
 }
 
 ma_status_t mesh_attn_tile_fwd(const ma_problem_t* prob, const int32_t* q_idx,
@@ -968,9 +971,7 @@ ma_status_t mesh_attn_tile_fwd(const ma_problem_t* prob, const int32_t* q_idx,
 size_t mesh_attn_chunk_fwd_workspace_size(const ma_problem_t* prob,
                                           int32_t nq, int32_t nkv) {
   // A chunk's work list is never longer than the whole tile's.
-  if (check_problem(prob) != MA_OK || nq < 1 || nkv < 1) return 0;
-  return fwd_ws_bound(prob, nq, nkv) +
-         fwd_split_bytes(prob, nq, nkv, kWholeTile, true);
+  return mesh_attn_fwd_workspace_size(prob, nq, nkv);
 }
 
 ma_status_t mesh_attn_chunk_fwd(const ma_problem_t* prob, const int32_t* q_idx,
@@ -1142,9 +1143,7 @@ ma_status_t mesh_attn_tile_bwd(const ma_problem_t* prob, const int32_t* q_idx,
 size_t mesh_attn_chunk_bwd_workspace_size(const ma_problem_t* prob,
                                           int32_t nq, int32_t nkv) {
   // A chunk's work lists and row buffers never exceed the whole tile's.
-  if (check_problem(prob) != MA_OK || nq < 1 || nkv < 1) return 0;
-  return bwd_ws_bound(prob, nq, nkv) +
-         bwd_parts(prob, nq, nkv, kWholeTile, true).bytes;
+  return mesh_attn_bwd_workspace_size(prob, nq, nkv);
 }
 
 ma_status_t mesh_attn_chunk_bwd(const ma_problem_t* prob, const int32_t* q_idx,

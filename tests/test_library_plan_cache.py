@@ -202,3 +202,41 @@ def test_a_failed_launch_is_reported(host):
     host.call(0, *_long_tile(0))
     host.run(None)
     assert host.counts()["stale"] == 0
+
+
+# Heads, head dim, and the partitions of a large and of a small tile: the large
+# one has too many items to split any.
+SMALLER = [(4, 1, 128, (40, 16), (1, 16)), (8, 8, 64, (20, 20), (2, 20)),
+           (5, 5, 128, (40, 8), (2, 8))]
+
+
+@pytest.mark.parametrize("pass_", [0, 1])
+@pytest.mark.parametrize("hq,hkv,d,large,small", SMALLER)
+def test_a_workspace_serves_every_smaller_tile(host, other, pass_, hq, hkv, d,
+                                               large, small):
+    """A workspace sized for a tile is as good for one of fewer partitions, and
+    for every chunk task of either, as one of its own."""
+    prob = _prob(40, 4096, hq, hkv, d)
+    size = getattr(ma, f"mesh_attn_{'bwd' if pass_ else 'fwd'}_workspace_size")
+    need = size(prob, *large)
+    assert need >= size(prob, *small)
+    q, kv = list(range(small[0])), list(range(20, 20 + small[1]))
+    for chunk in (None, (0, 1, 1, 2), (1, 2, 0, 4)):
+        host.call(pass_, prob, q, kv, ws_bytes=need, chunk=chunk)
+        other.call(pass_, prob, q, kv, chunk=chunk)
+        assert host.last() == other.last()
+        if chunk is None:
+            assert any(o[5] > 0 for o in host.last())  # split
+    assert host.counts()["out_of_range"] == 0
+
+
+def test_workspace_sizes_grow_with_the_tile():
+    for name in ("fwd", "bwd", "chunk_fwd", "chunk_bwd"):
+        size = getattr(ma, f"mesh_attn_{name}_workspace_size")
+        for P, hq, hkv, d in ((256, 21, 7, 64), (1024, 1, 1, 128),
+                              (4096, 32, 8, 128), (4096, 64, 64, 64)):
+            prob = _prob(64, P, hq, hkv, d)
+            got = np.array([[size(prob, nq, nkv) for nkv in range(1, 40)]
+                            for nq in range(1, 40)])
+            assert (np.diff(got, axis=0) >= 0).all()
+            assert (np.diff(got, axis=1) >= 0).all()
