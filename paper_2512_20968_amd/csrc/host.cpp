@@ -411,6 +411,31 @@ bool inline_plan(const plan::Side* sides, int n, PlanBlob* blob,
   return true;
 }
 
+// Whether the lists are likely too long for a PlanBlob, from sizes alone: an
+// entry per row, or where items may be split about as many as fill the chip in
+// one round, and the runs.  Such calls look in the cache before they build
+// anything (a lookup takes 0.2 us, building a list up to its overflow 2 to 41
+// us); a wrong guess costs that time and no more.
+bool likely_long(const plan::Side* sides, int n) {
+  int64_t bytes = 0;
+  for (int i = 0; i < n; ++i) {
+    const plan::Side& s = sides[i];
+    const int64_t rows = s.rows(), items = rows * s.heads;
+    const int64_t longest = s.nb * (s.sb.len / s.bm_b) * s.walks;
+    int64_t entries = rows;
+    if (s.pass && items <= s.pass->max_items &&
+        longest > 2 * s.pass->min_piece &&
+        !(s.forward &&
+          fwd_is_short(items, static_cast<int32_t>(longest), s.p->head_dim)))
+      entries = std::max<int64_t>(rows, s.pass->slots / s.heads);
+    const int64_t runs = !s.p->causal                          ? 1
+                         : s.p->layout == MA_LAYOUT_CONTIGUOUS ? 2
+                                                               : 2 * s.nb;
+    bytes += entries * sizeof(DevRow) + rows * runs * sizeof(DevRun);
+  }
+  return bytes > kInlinePlan;
+}
+
 // Upper bound of one side's packed bytes from sizes alone (at most two
 // non-empty runs per (block, list entry): along a partition visibility only
 // drops, FULL blocks first, then PARTIAL, then EMPTY).
@@ -530,13 +555,19 @@ ma_status_t with_plan(int pass, const ma_problem_t* p, const int32_t* q_idx,
   const int n =
       sides_of(pass, p, q_idx, nq, kv_idx, nkv, ch, may_split, sides);
   PlanView view;
-  if (inline_plan(sides, n, blob, &view)) return launch(view);
+  const bool cache_first = likely_long(sides, n);
+  if (!cache_first && inline_plan(sides, n, blob, &view)) return launch(view);
   const std::string key =
       plan_key(pass * 2 + may_split, p, q_idx, nq, kv_idx, nkv, ch);
   PinnedBuf* buf = nullptr;
   PendingEvent pe{nullptr, 0};
   {
-    std::lock_guard<std::mutex> lock(g_plan_mu);
+    std::unique_lock<std::mutex> lock(g_plan_mu);
+    if (cache_first && g_plans.find(key) == g_plans.end()) {
+      lock.unlock();
+      if (inline_plan(sides, n, blob, &view)) return launch(view);
+      lock.lock();
+    }
     Plan* plan = nullptr;
     const ma_status_t st = cached_plan(key, sides, n, &plan);
     if (st != MA_OK) return st;

@@ -7,6 +7,7 @@ import os
 import shutil
 import subprocess
 import threading
+import time
 
 import numpy as np
 import pytest
@@ -50,12 +51,12 @@ class Host:
         lib.stub_workspace.argtypes = [ctypes.c_void_p, ctypes.c_size_t]
         lib.stub_run.argtypes = [ctypes.c_void_p]
         self.lib = lib
-        self.ws = np.empty(0, np.uint8)
+        self.bufs = [np.empty(0, np.uint8)]  # pending copies may use old ones
 
     def workspace(self, nbytes):
-        if self.ws.size < nbytes + 256:
-            self.ws = np.empty(nbytes + 256, np.uint8)
-        at = (self.ws.ctypes.data + 255) // 256 * 256
+        if self.bufs[-1].size < nbytes + 256:
+            self.bufs.append(np.empty(nbytes + 256, np.uint8))
+        at = (self.bufs[-1].ctypes.data + 255) // 256 * 256
         self.lib.stub_workspace(at, nbytes)
         return at
 
@@ -240,3 +241,26 @@ def test_workspace_sizes_grow_with_the_tile():
                             for nq in range(1, 40)])
             assert (np.diff(got, axis=0) >= 0).all()
             assert (np.diff(got, axis=1) >= 0).all()
+
+
+def test_a_cached_list_is_not_built_again(host):
+    """A call whose list is in the cache finds it there without building it
+    (choosing the cut of this tile takes tens of microseconds), so it takes
+    about as long as the smallest call: the fastest of many, by the clock of
+    this process's CPU time."""
+    tiny = (0, _prob(4, 256, 4, 4, 64), [0, 1], [0, 1])
+    long = (0, _prob(64, 4096, 1, 1, 128, 1), list(range(50, 55)),
+            list(range(40)))
+
+    def fastest(args):
+        host.call(*args)  # builds the list
+        best = float("inf")
+        for _ in range(400):
+            t = time.process_time_ns()
+            host.call(*args, ws_bytes=1 << 28)
+            best = min(best, time.process_time_ns() - t)
+            host.run(None)
+        return best
+
+    # 40 more indexes to pass, a lookup, a copy and an event.
+    assert fastest(long) < 2.5 * fastest(tiny)
