@@ -174,12 +174,14 @@ def _check(fn, status):
 
 def _idx(lst):
     lst = list(lst)
-    try:
-        ints = array.array("i", lst)  # refuses what does not fit 32 bits
-        if lst:
+    # Python's own integers the fast way; all else by NumPy's conversion rules
+    # (which refuse elements in device memory: reading those would wait for it).
+    if lst and type(lst[0]) is int:
+        try:
+            ints = array.array("i", lst)  # refuses what does not fit 32 bits
             return ints, (ctypes.c_int32 * len(lst)).from_buffer(ints), len(lst)
-    except TypeError:  # not integers: NumPy's conversion rules
-        pass
+        except TypeError:
+            pass
     arr = np.ascontiguousarray(np.asarray(lst, dtype=np.int32))
     return arr, arr.ctypes.data_as(_I32P), int(arr.size)
 

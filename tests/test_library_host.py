@@ -284,3 +284,24 @@ def test_concurrent_host_calls_and_thread_local_errors():
     for th in threads:
         th.join()
     assert not failures, failures
+
+
+def test_index_lists_are_converted_by_numpys_rules():
+    """Whatever NumPy makes 32-bit integers of is an index list, and what it
+    refuses is refused: elements in device memory (as those of a GPU tensor,
+    which convert themselves to an integer by waiting for the device) too."""
+    class OnDevice:
+        def __index__(self):
+            return 1
+
+        def __array__(self, *args, **kwargs):
+            raise TypeError("can't convert device tensor to numpy")
+
+    for lst in ([OnDevice(), OnDevice()], [None], [2 ** 31], [float("nan")]):
+        with pytest.raises((TypeError, OverflowError, ValueError)):
+            ma._binding._idx(lst)
+    for lst in ([3, 1], (3, 1), np.array([3, 1]), [np.int64(3), 1], [3.0, 1],
+                [3, True], (i for i in (3, 1)), ["3", "1"]):
+        _, ptr, n = ma._binding._idx(lst)
+        assert n == 2 and [ptr[0], ptr[1]] == [3, 1]
+    assert ma._binding._idx([])[2] == 0
