@@ -21,19 +21,20 @@ _MAIN = r"""
 #include <vector>
 #include "plan.h"
 using namespace mesh_attn;
-// argv: pass (0 forward, 1 dK/dV, 2 dQ) split n P hq hkv causal layout
-//       k_q i k_kv j nq q... nkv kv...
+// argv: head_dim pass (0 forward, 1 dK/dV, 2 dQ) split n P hq hkv causal
+//       layout k_q i k_kv j nq q... nkv kv...
 int main(int argc, char** argv) {
   std::vector<int> a;
-  for (int i = 1; i < argc; ++i) a.push_back(atoi(argv[i]));
-  ma_problem_t p{a[2], a[3], a[4], a[5], 128, a[6], a[7], 0.125f};
+  for (int i = 2; i < argc; ++i) a.push_back(atoi(argv[i]));
+  const int d = atoi(argv[1]);
+  ma_problem_t p{a[2], a[3], a[4], a[5], d, a[6], a[7], 0.125f};
   const int pass = a[0], kq = a[8], kkv = a[10];
   std::vector<int32_t> q(a.begin() + 13, a.begin() + 13 + a[12]);
   std::vector<int32_t> kv(a.begin() + 14 + a[12], a.end());
   const plan::Slice sq{p.partition_len / kq, a[9] * (p.partition_len / kq)},
       skv{p.partition_len / kkv, a[11] * (p.partition_len / kkv)};
-  const split::Pass* ps = &(pass == 0 ? kFwdPass128
-                            : pass == 1 ? kDkdvPass128 : kDqPass128);
+  const split::Pass* ps =
+      &(pass == 0 ? fwd_pass(d) : pass == 1 ? dkdv_pass(d) : dq_pass(d));
   const int g = p.num_q_heads / p.num_kv_heads;
   const int nq = static_cast<int>(q.size()), nkv = static_cast<int>(kv.size());
   plan::Side s =
@@ -54,11 +55,11 @@ int main(int argc, char** argv) {
                          ps->max_parts(), work.data()};
   plan::Built b;
   if (!plan::build(s, arr, &b)) return 1;
-  int64_t longest = 0;
-  for (int32_t w : work) longest = w > longest ? w : longest;
   printf("built %d %d %d %d\n", b.m, b.n_splits, b.parts, b.mode);
+  // The slots that a workspace reserves: from the sizes, all blocks visible.
   printf("bound %d %lld\n", ps->max_parts(), static_cast<long long>(
-         split::parts_bound(int64_t{rows} * s.heads, longest, *ps)));
+         split::parts_bound(int64_t{rows} * s.heads,
+                            s.nb * (s.sb.len / s.bm_b) * s.walks, *ps)));
   for (int i = 0; i < b.n_runs; ++i)
     printf("run %d %d %d %d\n", runs[i].blk0, runs[i].nblk, runs[i].cls,
            runs[i].delta);
@@ -112,7 +113,7 @@ def _tile(n, P, q, kv, hq, hkv, causal=0, layout=0, kq=(1, 0), kkv=(1, 0)):
 
 R = list(range(32))
 TILES = [
-    # name, tile, forward split expected (None: either)
+    # name, tile, forward at head dim 128 split (None: either)
     ("one round, equal", _tile(64, 1024, [0], R[16:32], 4, 1), True),
     ("one round, causal", _tile(8, 1024, [2, 3], R[:4], 8, 2, 1), True),
     ("one head", _tile(9, 1024, [3], [0, 1, 2, 7], 1, 1), True),
@@ -137,13 +138,14 @@ TILES = [
 ]
 
 
+@pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("pass_", [0, 1, 2])
 @pytest.mark.parametrize("may_split", [0, 1])
 @pytest.mark.parametrize("name,t,want", TILES, ids=[t[0] for t in TILES])
 def test_work_list_covers_the_canonical_one(program, name, t, want, may_split,
-                                            pass_):
+                                            pass_, d):
     out = subprocess.run(
-        [program, *map(str, (pass_, may_split, t["n"], t["P"], t["hq"],
+        [program, *map(str, (d, pass_, may_split, t["n"], t["P"], t["hq"],
                              t["hkv"], t["causal"], t["layout"], *t["kq"],
                              *t["kkv"], len(t["q"]), *t["q"], len(t["kv"]),
                              *t["kv"]))],
@@ -159,12 +161,12 @@ def test_work_list_covers_the_canonical_one(program, name, t, want, may_split,
     walks = t["hq"] // t["hkv"] if kv_major else 1
     if not may_split:
         assert n_splits == 0
-    elif want is not None and pass_ == 0:
+    elif want is not None and pass_ == 0 and d == 128:
         assert (n_splits > 0) == want
     assert parts * heads <= bound <= max_parts
 
     # Element offsets of every visible block pair, from the oracle's positions.
-    bm, bn = ma.mesh_attn_block_shape(128, int(pass_ > 0))
+    bm, bn = ma.mesh_attn_block_shape(d, int(pass_ > 0))
     cq, ckv = t["P"] // t["kq"][0], t["P"] // t["kkv"][0]
 
     def positions(idx, chunk, c):
