@@ -32,6 +32,43 @@ def queued_tail_config():
         num_q_heads=21, num_kv_heads=7, head_dim=64, causal=True, seed=63)
 
 
+def plan_cache_tiles():
+    """1100 distinct tiles of one problem, more than the library's cache of
+    work lists holds (1024): 100 Q partitions (100 forward Q blocks, 200 of the
+    backward) against an ordered pair of KV partitions, one head.  Their lists
+    are too long for the kernel arguments in both passes, and differ in the
+    class and mask offset of the block pairs."""
+    import dataclasses
+    import itertools
+    from mesh_inputs import WORKLOADS
+    cfg = dataclasses.replace(WORKLOADS["tiny-nc"], name="plan-cache",
+                              num_partitions=104, partition_len=256,
+                              q_idx=list(range(100)), kv_idx=[0, 1],
+                              num_q_heads=1, num_kv_heads=1, head_dim=64,
+                              causal=True, seed=51, grad_seed=52)
+    pairs = list(itertools.permutations(range(104), 2))
+    rng = np.random.default_rng(3)
+    return cfg, [list(pairs[i]) for i in rng.permutation(len(pairs))[:1100]]
+
+
+def concurrency_tiles():
+    """Two tiles for each of four threads.  Every thread's second one has lists
+    too long for the kernel arguments in both passes, as have the backward lists
+    of the first ones of threads 0 and 2."""
+    import dataclasses
+    from mesh_inputs import WORKLOADS
+    base = dataclasses.replace(WORKLOADS["tiny-nc"], num_partitions=6,
+                               causal=True)
+    lists = [([5, 2], [0, 2, 4, 5]), ([3, 2, 5, 0], [3, 1]),
+             ([4, 0, 1], [1, 4]), ([2, 5, 1, 4], [5, 0]),
+             ([1, 2], [0, 1, 2, 3, 4, 5]), ([0, 3, 4, 5], [3, 0]),
+             ([4], [4, 2, 0]), ([5, 1, 3, 2], [1, 5, 3])]
+    return [dataclasses.replace(base, q_idx=q, kv_idx=kv, seed=70 + i,
+                                grad_seed=90 + i, layout=i % 2,
+                                partition_len=4096 if i % 2 else 1024)
+            for i, (q, kv) in enumerate(lists)]
+
+
 def log(msg):
     print(f"[{time.strftime('%H:%M:%S')}] {msg}", file=sys.stderr, flush=True)
 

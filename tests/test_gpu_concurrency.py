@@ -3,34 +3,22 @@
 ctypes releases the GIL, so the library's host code (validation, the plan
 cache and its pinned upload buffers and events) runs in parallel in four
 threads while their kernels overlap on the GPU.  Each thread alternates
-between two tiles of its own (so the shared plan cache keeps changing) and
-two of them also run the backward; every result must equal the
-single-threaded result of the same call bit for bit (both passes are
-deterministic)."""
+between two tiles of its own, one whose work list travels in the kernel
+arguments and one whose list is in the shared cache, and two of them also run
+the backward; every result must equal the single-threaded result of the same
+call bit for bit (both passes are deterministic)."""
 
-import dataclasses
 import threading
 
 import pytest
 import torch
 
 import paper_2512_20968_amd as ma
-from mesh_inputs import WORKLOADS, make_grad, make_qkv
+from mesh_inputs import make_grad, make_qkv
 
-from helpers import log
+from helpers import concurrency_tiles, log
 
 pytestmark = pytest.mark.gpu
-
-
-def _tiles():
-    base = dataclasses.replace(WORKLOADS["tiny-nc"], num_partitions=6,
-                               partition_len=1024, causal=True)
-    lists = [([5, 2], [0, 2, 4, 5]), ([3], [3, 1]), ([4, 0, 1], [1, 4]),
-             ([2, 5], [5]), ([1], [0, 1, 2, 3, 4, 5]), ([0, 3], [3, 0]),
-             ([4], [4, 2, 0]), ([5, 1], [1, 5, 3])]
-    return [dataclasses.replace(base, q_idx=q, kv_idx=kv, seed=70 + i,
-                                grad_seed=90 + i, layout=i % 2)
-            for i, (q, kv) in enumerate(lists)]
 
 
 class _Case:
@@ -70,7 +58,7 @@ class _Case:
 
 
 def test_threads_on_separate_streams_match_serial_results(gpu):
-    tiles = _tiles()
+    tiles = concurrency_tiles()
     # Thread t owns tiles 2t and 2t+1; threads 0 and 2 also run the backward.
     cases = [[_Case(tiles[2 * t + j], gpu, with_bwd=(t % 2 == 0))
               for j in range(2)] for t in range(4)]

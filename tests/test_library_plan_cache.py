@@ -15,6 +15,8 @@ import pytest
 import paper_2512_20968_amd as ma
 from paper_2512_20968_amd import _binding
 
+from helpers import concurrency_tiles, plan_cache_tiles
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HERE = os.path.join(ROOT, "tests")
 
@@ -157,6 +159,62 @@ LONG = _prob(2048, 256, 1, 1, 64)
 
 def _long_tile(i):
     return LONG, list(range(128)), [i]
+
+
+def test_evicted_lists_keep_their_buffers_until_they_have_been_read(host):
+    """More tiles than the cache holds, on two streams: no buffer is handed out
+    again while a copy from it is pending, and all are once none is."""
+    for i in range(1100):
+        host.call(i % 2, *_long_tile(i), stream=1 + i % 3 // 2)
+    assert host.counts()["pinned"] == 1100  # none could be recycled
+    # Stream 1 goes on: of the 76 lists evicted so far (the first ones), those
+    # that it has read give their buffers to the next tiles of their pass.
+    host.run(1)
+    for i in range(1100, 1140):
+        host.call(i % 2, *_long_tile(i), stream=1)
+    assert host.counts()["pinned"] == 1100
+    for i in range(1140, 1400):
+        host.call(i % 2, *_long_tile(i), stream=1)
+        host.run(1)
+    before = host.counts()["pinned"]
+    assert before < 1250
+    host.run(2)
+    for i in range(1400, 2000):
+        host.call(i % 2, *_long_tile(i), stream=1 + i % 2)
+        host.run(1, 2)
+    assert host.counts() == dict(out_of_range=0, stale=0, pinned=before,
+                                 launches=2000)
+
+
+def test_a_list_seen_again_is_the_same(host, other):
+    host.call(0, *_long_tile(0))
+    first = host.last()
+    for i in range(1, 1100):
+        host.call(0, *_long_tile(i))
+        host.run(None)
+    pinned = host.counts()["pinned"]
+    host.call(0, *_long_tile(0))  # evicted since, built again
+    assert host.last() == first and host.counts()["pinned"] == pinned
+    host.call(0, *_long_tile(0))
+    host.run(None)
+    assert host.last() == first and host.counts()["stale"] == 0
+
+
+def test_the_gpu_tests_of_the_cache_use_it(host):
+    cfg, kv_lists = plan_cache_tiles()
+    assert len({tuple(kv) for kv in kv_lists}) == 1100
+    for pass_ in (0, 1):
+        for kv in kv_lists[::50]:
+            host.call(pass_, cfg.problem(), cfg.q_idx, kv)
+            assert not any(o[0] for o in host.last())
+    used = {}
+    for i, c in enumerate(concurrency_tiles()):
+        for pass_ in (0, 1):
+            pinned = host.counts()["pinned"]
+            host.call(pass_, c.problem(), c.q_idx, c.kv_idx)
+            used[i, pass_] = host.counts()["pinned"] > pinned
+    assert all(used[i, 0] == (i % 2 == 1) for i in range(8))
+    assert all(used[i, 1] for i in (0, 1, 4, 5))
 
 
 def test_a_launch_does_not_hold_up_other_threads(host):
