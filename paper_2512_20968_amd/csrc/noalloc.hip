@@ -121,18 +121,37 @@ __device__ int row_runs(const PlanBuildParams& p, int qb, F emit) {
   return work;
 }
 
+// Exclusive scan of one value per thread of the workgroup (Hillis-Steele).
+__device__ int scan_before(int* s_scan, int v) {
+  const int t = threadIdx.x;
+  s_scan[t] = v;
+  __syncthreads();
+  for (int off = 1; off < kBuildThreads; off <<= 1) {
+    const int add = t >= off ? s_scan[t - off] : 0;
+    __syncthreads();
+    s_scan[t] += add;
+    __syncthreads();
+  }
+  return s_scan[t] - v;
+}
+
 __global__ __launch_bounds__(kBuildThreads) void fwd_plan_build_kernel(
     PlanBuildParams p) {
   __shared__ int s_work[kNoAllocMaxQBlocks];
   __shared__ int s_run[kNoAllocMaxQBlocks];     // first run of each Q block
-  // Split tiles: blocks and Q block of each piece (before ranking), first piece
-  // and first partial (or -1) of each Q block.  Whole items: piece i is Q
-  // block i.
+  // Split tiles: blocks, Q block and index of each piece (before ranking), first
+  // piece and first partial (or -1) of each Q block.  Whole items: piece i is Q
+  // block i.  The indexes lie behind the work of the (at most kSplitMaxRows) Q
+  // blocks of a split tile.
   __shared__ int s_len[kSplitMaxPieces];
   __shared__ uint16_t s_row[kSplitMaxPieces];
   __shared__ uint16_t s_pre[kSplitMaxRows];
   __shared__ int16_t s_part[kSplitMaxRows];
   __shared__ int s_scan[kBuildThreads];
+  uint16_t* s_idx = reinterpret_cast<uint16_t*>(s_work + kSplitMaxRows);
+  static_assert(kSplitMaxPieces * 2 <=
+                    (kNoAllocMaxQBlocks - kSplitMaxRows) * 4,
+                "room for the piece indexes");
   const int t = threadIdx.x;
   const bool cut = p.cut.c > 0;
   // Thread t owns a contiguous segment of Q blocks for the run list.
@@ -142,44 +161,42 @@ __global__ __launch_bounds__(kBuildThreads) void fwd_plan_build_kernel(
   int cnt = 0;
   for (int qb = lo; qb < hi; ++qb)
     s_work[qb] = row_runs(p, qb, [&](const DevRun&) { ++cnt; });
-  s_scan[t] = cnt;
-  __syncthreads();
-  // Inclusive scan of the segment counts (Hillis-Steele).
-  for (int off = 1; off < kBuildThreads; off <<= 1) {
-    const int add = t >= off ? s_scan[t - off] : 0;
-    __syncthreads();
-    s_scan[t] += add;
-    __syncthreads();
-  }
-  int at = s_scan[t] - cnt;
+  int at = scan_before(s_scan, cnt);
+  const int n_runs = s_scan[kBuildThreads - 1];
   for (int qb = lo; qb < hi; ++qb) {
     s_run[qb] = at;
     row_runs(p, qb, [&](const DevRun& r) { p.runs[at++] = r; });
   }
-  const int n_runs = s_scan[kBuildThreads - 1];
   if (cut) {
-    // A split tile has few Q blocks per head: one thread walks them.
-    if (t == 0) {
-      int pre = 0, parts = 0, splits = 0;
-      for (int qb = 0; qb < p.nqb; ++qb) {
-        const int n = split::num_pieces(p.cut, qb, s_work[qb]);
-        s_pre[qb] = static_cast<uint16_t>(pre);
-        s_part[qb] = static_cast<int16_t>(n > 1 ? parts : -1);
-        if (n > 1) {
-          p.splits[splits++] = DevSplit{qb, parts, n};
-          parts += n;
-        }
-        pre += n;
-      }
+    // Pieces and split rows of the Q blocks before each, in one scan (at most
+    // kSplitMaxPieces and kSplitMaxRows); the partials follow, as a row that is
+    // not split is one piece and no partial.
+    __syncthreads();  // the last reads of the first scan
+    constexpr int kBits = 12;
+    static_assert(kSplitMaxPieces < 1 << kBits && kSplitMaxRows < 1 << kBits,
+                  "two counts in one value");
+    int sum = 0;
+    for (int qb = lo; qb < hi; ++qb) {
+      const int n = split::num_pieces(p.cut, qb, s_work[qb]);
+      sum += n + ((n > 1) << kBits);
     }
-    __syncthreads();
-    for (int qb = t; qb < p.nqb; qb += kBuildThreads) {
+    int before = scan_before(s_scan, sum);
+    for (int qb = lo; qb < hi; ++qb) {
       const int w = s_work[qb], n = split::num_pieces(p.cut, qb, w);
+      const int pre = before & ((1 << kBits) - 1), splits = before >> kBits;
+      const int part = pre - (qb - splits);
+      s_pre[qb] = static_cast<uint16_t>(pre);
+      s_part[qb] = static_cast<int16_t>(n > 1 ? part : -1);
+      if (n > 1) p.splits[splits] = DevSplit{qb, part, n};
+      int begin = 0;
       for (int j = 0; j < n; ++j) {
-        s_row[s_pre[qb] + j] = static_cast<uint16_t>(qb);
-        s_len[s_pre[qb] + j] =
-            split::piece_begin(w, n, j + 1) - split::piece_begin(w, n, j);
+        const int end = split::piece_begin(w, n, j + 1);
+        s_row[pre + j] = static_cast<uint16_t>(qb);
+        s_idx[pre + j] = static_cast<uint16_t>(j);
+        s_len[pre + j] = end - begin;
+        begin = end;
       }
+      before += n + ((n > 1) << kBits);
     }
   }
   __syncthreads();  // and the runs, read back below
@@ -187,16 +204,23 @@ __global__ __launch_bounds__(kBuildThreads) void fwd_plan_build_kernel(
   const int* len_of = cut ? s_len : s_work;
   const bool by_len = p.mode != kModeOneRound;
   for (int i = t; i < p.m; i += kBuildThreads) {
-    const int qb = cut ? s_row[i] : i, idx = cut ? i - s_pre[qb] : 0;
+    const int qb = cut ? s_row[i] : i, idx = cut ? s_idx[i] : 0;
     const int len = len_of[i];
     int before = 0, same = 0, same_before = 0;
-    for (int i2 = 0; i2 < p.m; ++i2) {
-      const int k2 = by_len ? -len_of[i2] : i2 - s_pre[s_row[i2]];
-      const int k = by_len ? -len : idx;
-      before += k2 < k;
-      same += k2 == k;
-      same_before += (k2 == k) & (i2 < i);
-    }
+    auto count = [&](auto key) {
+      const int k = key(i);
+#pragma unroll 8
+      for (int i2 = 0; i2 < p.m; ++i2) {
+        const int k2 = key(i2);
+        before += k2 < k;
+        same += k2 == k;
+        same_before += (k2 == k) & (i2 < i);
+      }
+    };
+    if (by_len)
+      count([&](int x) { return -len_of[x]; });
+    else
+      count([&](int x) { return int{s_idx[x]}; });
     const int run_b = s_run[qb], run_e = qb + 1 < p.nqb ? s_run[qb + 1] : n_runs;
     int run = run_b, off = 0;
     if (idx > 0) {
