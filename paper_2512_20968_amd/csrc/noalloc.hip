@@ -121,18 +121,27 @@ __device__ int row_runs(const PlanBuildParams& p, int qb, F emit) {
   return work;
 }
 
-// Exclusive scan of one value per thread of the workgroup (Hillis-Steele).
-__device__ int scan_before(int* s_scan, int v) {
-  const int t = threadIdx.x;
-  s_scan[t] = v;
-  __syncthreads();
-  for (int off = 1; off < kBuildThreads; off <<= 1) {
-    const int add = t >= off ? s_scan[t - off] : 0;
-    __syncthreads();
-    s_scan[t] += add;
-    __syncthreads();
+// Exclusive scan of one value per thread of the workgroup, and the total: in
+// each wave, then over the waves' sums.
+__device__ int scan_before(int* s_wave, int v, int* total) {
+  constexpr int kWaves = kBuildThreads / 64;
+  const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
+  int x = v;
+  for (int off = 1; off < 64; off <<= 1) {
+    const int y = __shfl_up(x, off);
+    if (lane >= off) x += y;
   }
-  return s_scan[t] - v;
+  __syncthreads();  // the reads of a scan before this one
+  if (lane == 63) s_wave[wave] = x;
+  __syncthreads();
+  int base = 0, sum = 0;
+#pragma unroll
+  for (int i = 0; i < kWaves; ++i) {
+    base += i < wave ? s_wave[i] : 0;
+    sum += s_wave[i];
+  }
+  *total = sum;
+  return base + x - v;
 }
 
 __global__ __launch_bounds__(kBuildThreads) void fwd_plan_build_kernel(
@@ -147,7 +156,7 @@ __global__ __launch_bounds__(kBuildThreads) void fwd_plan_build_kernel(
   __shared__ uint16_t s_row[kSplitMaxPieces];
   __shared__ uint16_t s_pre[kSplitMaxRows];
   __shared__ int16_t s_part[kSplitMaxRows];
-  __shared__ int s_scan[kBuildThreads];
+  __shared__ int s_wave[kBuildThreads / 64];
   uint16_t* s_idx = reinterpret_cast<uint16_t*>(s_work + kSplitMaxRows);
   static_assert(kSplitMaxPieces * 2 <=
                     (kNoAllocMaxQBlocks - kSplitMaxRows) * 4,
@@ -161,8 +170,8 @@ __global__ __launch_bounds__(kBuildThreads) void fwd_plan_build_kernel(
   int cnt = 0;
   for (int qb = lo; qb < hi; ++qb)
     s_work[qb] = row_runs(p, qb, [&](const DevRun&) { ++cnt; });
-  int at = scan_before(s_scan, cnt);
-  const int n_runs = s_scan[kBuildThreads - 1];
+  int n_runs = 0;
+  int at = scan_before(s_wave, cnt, &n_runs);
   for (int qb = lo; qb < hi; ++qb) {
     s_run[qb] = at;
     row_runs(p, qb, [&](const DevRun& r) { p.runs[at++] = r; });
@@ -171,7 +180,6 @@ __global__ __launch_bounds__(kBuildThreads) void fwd_plan_build_kernel(
     // Pieces and split rows of the Q blocks before each, in one scan (at most
     // kSplitMaxPieces and kSplitMaxRows); the partials follow, as a row that is
     // not split is one piece and no partial.
-    __syncthreads();  // the last reads of the first scan
     constexpr int kBits = 12;
     static_assert(kSplitMaxPieces < 1 << kBits && kSplitMaxRows < 1 << kBits,
                   "two counts in one value");
@@ -180,7 +188,8 @@ __global__ __launch_bounds__(kBuildThreads) void fwd_plan_build_kernel(
       const int n = split::num_pieces(p.cut, qb, s_work[qb]);
       sum += n + ((n > 1) << kBits);
     }
-    int before = scan_before(s_scan, sum);
+    int all = 0;
+    int before = scan_before(s_wave, sum, &all);
     for (int qb = lo; qb < hi; ++qb) {
       const int w = s_work[qb], n = split::num_pieces(p.cut, qb, w);
       const int pre = before & ((1 << kBits) - 1), splits = before >> kBits;

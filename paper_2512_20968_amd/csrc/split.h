@@ -44,10 +44,11 @@ __host__ __device__ inline int32_t num_pieces(const Cut& s, int32_t row,
   return s.c > 0 && row >= s.whole && w > s.c ? (w + s.c - 1) / s.c : 1;
 }
 
-// First block of piece j of n.
+// First block of piece j of n: w * j / n, without 64-bit division (j and n are at
+// most a few thousand).
 __host__ __device__ inline int32_t piece_begin(int32_t w, int32_t n,
                                                int32_t j) {
-  return static_cast<int32_t>(int64_t{w} * j / n);
+  return w / n * j + w % n * j / n;
 }
 
 // Partial results a tile may need, from its sizes alone: `items` items of at
