@@ -92,9 +92,18 @@ struct FwdParams {
 // compute unit (its eight waves of 256 registers fill the SIMDs); items of 4
 // and 64 KV blocks measured 14.3 and 100.8 us (1.44 us per block and six
 // blocks of overhead); folding 256 partials of 256 x 128 takes 7-9 us, and
-// writing them about as long.  d = 64: two workgroups per compute unit.
+// writing them about as long.  d = 64: two workgroups per compute unit, 2.37 us
+// per block each; a whole item with a compute unit to itself takes 46, 80 and
+// 152 us for 32, 64 and 128 blocks, half of that rate, while a cut in two then
+// fills the unit and gains nothing.  Its price is set a little above (the
+// estimates of cuts are, too), where it tells the cuts that measured slower from
+// those that measured faster, microseconds whole / cut:
+//   192 items of  32 blocks  45.8/52.7 (whole)   112 of  32  43.3/35.2 (cut)
+//   192 of        64         79.9/89.6 (whole)   168 of  64  79.7/68.0 (cut)
+//   256 of        64         89.1/96.4 (whole)   128 of  64  79.8/55.1 (cut)
+//   192 of       128        151.8/156  (whole)   256 of 256   325/313  (cut)
 constexpr split::Pass kFwdPass128{256, 2048, 6, 4, 2, 20};
-constexpr split::Pass kFwdPass64{512, 2048, 4, 4, 2, 60};
+constexpr split::Pass kFwdPass64{512, 2048, 4, 4, 2, 60, 57, 7};
 constexpr const split::Pass& fwd_pass(int head_dim) {
   return head_dim == 128 ? kFwdPass128 : kFwdPass64;
 }

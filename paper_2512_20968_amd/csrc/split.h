@@ -29,6 +29,9 @@ struct Pass {
                       // items of at most two such pieces stay whole
   int32_t fold;       // launch of the kernel that folds the partials
   int32_t fold_rate;  // partials written and read back per block
+  // Where two workgroups share a compute unit, whole items that have one each
+  // run faster than their slots say: alone blocks per 100 and alone_overhead.
+  int32_t alone = 0, alone_overhead = 0;
   // Most partial results a pass holds.
   __host__ __device__ constexpr int32_t max_parts() const { return 2 * slots; }
 };
@@ -108,7 +111,12 @@ inline Cut choose(const int32_t* w, int32_t n, int32_t heads,
   }
   if (items > ps.max_items || longest <= 2 * ps.min_piece)
     return {0, 0};
-  const int64_t whole_time = estimate(w, n, heads, {0, 0}, ps).time;
+  int64_t whole_time = estimate(w, n, heads, {0, 0}, ps).time;
+  if (ps.alone > 0 && 2 * items <= ps.slots) {
+    const int64_t alone =
+        (int64_t{longest} * ps.alone + 99) / 100 + ps.alone_overhead;
+    if (alone < whole_time) whole_time = alone;
+  }
   Cut best{0, 0};
   int64_t best_time = whole_time * 19 / 20;
   auto consider = [&](const Cut& s) {

@@ -322,3 +322,15 @@ def test_a_cached_list_is_not_built_again(host):
 
     # 40 more indexes to pass, a lookup, a copy and an event.
     assert fastest(long) < 2.5 * fastest(tiny)
+
+
+@pytest.mark.parametrize("nq,nkv,P,heads,split", [
+    (3, 1, 4096, 4, False), (4, 1, 4096, 4, False), (3, 1, 2048, 8, False),
+    (3, 2, 4096, 4, False), (3, 4, 1024, 14, True), (2, 2, 2048, 8, True),
+    (2, 2, 1024, 14, True), (4, 4, 4096, 4, True)])
+def test_items_with_a_compute_unit_each(host, nq, nkv, P, heads, split):
+    """Head dim 64, at most 256 items: they are cut where that measured faster
+    than leaving them whole."""
+    host.call(0, _prob(8, P, heads, heads, 64), list(range(nq)),
+              list(range(nkv)))
+    assert (host.last()[0][5] > 0) == split
