@@ -738,7 +738,7 @@ NoAllocSplit noalloc_split(const ma_problem_t* p, const int32_t* q_idx,
       static_cast<int32_t>(int64_t{nq} * p->partition_len / kFwdBM);
   for (int32_t qb = 0; qb < nqb; ++qb)
     work[qb] = visible_blocks(p, q_idx, kv_idx, nkv, qb);
-  NoAllocSplit s{{0, 0}, 0, 0, 0, false};
+  NoAllocSplit s{{}, 0, 0, 0, false};
   s.is_short = fwd_is_short(int64_t{nqb} * p->num_q_heads,
                             *std::max_element(work, work + nqb), p->head_dim);
   if (!s.is_short)
@@ -1081,7 +1081,7 @@ ma_status_t mesh_attn_tile_fwd_noalloc(const ma_problem_t* prob,
     fp.order = order_at(view.a, nullptr);
   } else {
     // The same cut as the call with a workspace of full size.
-    NoAllocSplit sp{{0, 0}, 0, 0, 0, false};
+    NoAllocSplit sp{{}, 0, 0, 0, false};
     if (items <= fwd_pass(prob->head_dim).max_items)
       sp = noalloc_split(prob, q_idx, nq, kv_idx, nkv);
     const bool split = sp.cut.c > 0;
@@ -1092,7 +1092,7 @@ ma_status_t mesh_attn_tile_fwd_noalloc(const ma_problem_t* prob,
     v.parts = sp.parts;
     v.is_short = sp.is_short;
     v.mode = split_mode(v.n_items, split, prob->num_kv_heads % kNumXcd == 0,
-                        fwd_pass(prob->head_dim).slots);
+                        sp.cut.slots);
     v.off_queue = align_up(static_cast<size_t>(v.m) * sizeof(DevRow));
     v.off_splits = v.off_queue + kAlign;
     v.off_runs = v.off_splits + align_up(sp.split_rows * sizeof(DevSplit));

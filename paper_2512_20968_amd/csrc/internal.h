@@ -206,14 +206,25 @@ static_assert(sizeof(FwdParams) + sizeof(PlanBlob) <= 4096 &&
               "kernel arguments");
 
 // The backward passes as the cut of long items sees them; a block is 128 x 128.
-// d = 128: dK/dV one workgroup per compute unit, 3.8 us per block with the chip
-// full; dQ two, 5.5 us per block each.  d = 64: three workgroups of either per
-// compute unit, 6.1 and 4.6 us per block each; the two passes share a launch
-// and get half of its 768 places each (a 4K-token tile of 12 heads takes 66 us
-// so, 72 with 768 places each, 78 with 512 and 256).
+// The two passes share a launch.  d = 128: two workgroups of either per compute
+// unit, dK/dV first.  The numbers are fitted to whole launches, not the
+// residency: cuts for 256 places of dK/dV and 512 of dQ were as good as or better
+// than 512/512, 384/384 and 512/256 on a grid of 187 tiles (geometric mean 2 to
+// 4 % slower with those).  But dQ items that are left whole for 512 places (they
+// fill one round, or nearly whole rounds) have only one place per compute unit
+// beside a dK/dV item: looked at again for 256 places, the 14 tiles of the grid
+// that are then cut take 5 to 19 % less, microseconds before / now:
+//   256 dK/dV items of 384 blocks, 384 dQ of 256   2630/2323 (2526 as launches
+//   256 of  48, 384 of  32                          347/316   (343) of their own)
+//   512 of 672, 1344 of 256                        8865/8159  (8552)
+// d = 64: three workgroups of either per compute unit, 6.1 and 4.6 us per block
+// each; each pass gets half of the 768 places (fitted on one 4K-token tile of 12
+// heads: 66 us so, 72 with 768 places each, 78 with 512 and 256).
 constexpr split::Pass kDkdvPass128{256, 2048, 3, 2, 1, 40};
 constexpr split::Pass kDkdvPass64{384, 2048, 2, 2, 1, 100};
-constexpr split::Pass kDqPass128{512, 4096, 2, 2, 1, 120};
+constexpr split::Pass kDqBesideDkdv128{256, 4096, 2, 4, 2, 60};
+constexpr split::Pass kDqPass128{512, 4096, 2, 2, 1, 120, 0, 0,
+                                 &kDqBesideDkdv128};
 constexpr split::Pass kDqPass64{384, 4096, 2, 2, 1, 200};
 constexpr const split::Pass& dkdv_pass(int head_dim) {
   return head_dim == 128 ? kDkdvPass128 : kDkdvPass64;

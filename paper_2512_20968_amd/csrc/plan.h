@@ -169,7 +169,7 @@ inline bool build(const Side& s, const Arrays& out, Built* built) {
   const split::Cut cut =
       s.pass && !b.is_short
           ? split::choose(out.work, rows, s.heads, *s.pass)
-          : split::Cut{0, 0};
+          : split::Cut{};
   for (int32_t r = 0; r < rows; ++r) {
     const int32_t n = split::num_pieces(cut, r, out.work[r]);
     b.m += n;
@@ -206,8 +206,7 @@ inline bool build(const Side& s, const Arrays& out, Built* built) {
   // Rank order: longest first, or in one round of a split tile by piece index
   // (`before` holds it until the ranks are known).
   b.mode = split_mode(int64_t{b.m} * s.heads, cut.c > 0,
-                      s.heads / s.group % kNumXcd == 0,
-                      s.pass ? s.pass->slots : 0);
+                      s.heads / s.group % kNumXcd == 0, cut.slots);
   const bool by_len = b.mode != kModeOneRound;
   auto key = [&](const DevRow& x) { return by_len ? -x.nblk : x.before; };
   std::sort(out.rows, out.rows + b.m, [&](const DevRow& x, const DevRow& y) {

@@ -32,14 +32,17 @@ struct Pass {
   // Where two workgroups share a compute unit, whole items that have one each
   // run faster than their slots say: alone blocks per 100 and alone_overhead.
   int32_t alone = 0, alone_overhead = 0;
+  // The pass with fewer slots, where it shares its launch with another one: a
+  // tile that is left whole for all of its slots is looked at again for these.
+  const Pass* beside = nullptr;
   // Most partial results a pass holds.
   __host__ __device__ constexpr int32_t max_parts() const { return 2 * slots; }
 };
 
 // Rows [0, whole) of every head stay whole, the others are cut into pieces of
-// at most c blocks; c = 0: nothing is cut.
+// at most c blocks, for a round of `slots` workgroups; c = 0: nothing is cut.
 struct Cut {
-  int32_t c, whole;
+  int32_t c = 0, whole = 0, slots = 0;
 };
 
 __host__ __device__ inline int32_t num_pieces(const Cut& s, int32_t row,
@@ -97,11 +100,11 @@ inline Estimate estimate(const int32_t* w, int32_t n, int32_t heads,
   return {t + (parts > 0 ? ps.fold + parts / ps.fold_rate : 0), parts};
 }
 
-// The cut of a tile, {0, 0} to leave every item whole: the best estimate over
-// the pieces of the longest item, and for equal items also whole rounds with
-// only the rows of the last, partly filled round cut.  A cut has to be
-// estimated 5 % faster than whole items.
-inline Cut choose(const int32_t* w, int32_t n, int32_t heads,
+// The cut of a tile for ps.slots, Cut{} to leave every item whole: the best
+// estimate over the pieces of the longest item, and for equal items also whole
+// rounds with only the rows of the last, partly filled round cut.  A cut has to
+// be estimated 5 % faster than whole items.
+inline Cut choose_alone(const int32_t* w, int32_t n, int32_t heads,
                   const Pass& ps) {
   const int64_t items = int64_t{n} * heads;
   int32_t longest = 0, shortest = INT32_MAX;
@@ -110,14 +113,14 @@ inline Cut choose(const int32_t* w, int32_t n, int32_t heads,
     if (w[i] < shortest) shortest = w[i];
   }
   if (items > ps.max_items || longest <= 2 * ps.min_piece)
-    return {0, 0};
-  int64_t whole_time = estimate(w, n, heads, {0, 0}, ps).time;
+    return {};
+  int64_t whole_time = estimate(w, n, heads, Cut{}, ps).time;
   if (ps.alone > 0 && 2 * items <= ps.slots) {
     const int64_t alone =
         (int64_t{longest} * ps.alone + 99) / 100 + ps.alone_overhead;
     if (alone < whole_time) whole_time = alone;
   }
-  Cut best{0, 0};
+  Cut best;
   int64_t best_time = whole_time * 19 / 20;
   auto consider = [&](const Cut& s) {
     const Estimate e = estimate(w, n, heads, s, ps);
@@ -133,7 +136,7 @@ inline Cut choose(const int32_t* w, int32_t n, int32_t heads,
     if (c < ps.min_piece) break;
     if (c == last) continue;
     last = c;
-    if (!consider({c, 0})) break;
+    if (!consider({c, 0, ps.slots})) break;
   }
   if (longest == shortest && items > ps.slots) {
     const int32_t rounds = static_cast<int32_t>(items / ps.slots);
@@ -143,10 +146,17 @@ inline Cut choose(const int32_t* w, int32_t n, int32_t heads,
       const int64_t k =
           (int64_t{rounds + 1} * ps.slots - int64_t{whole} * heads) / rest;
       const int32_t c = static_cast<int32_t>((longest + k - 1) / k);
-      if (k > 1 && c >= ps.min_piece) consider({c, whole});
+      if (k > 1 && c >= ps.min_piece) consider({c, whole, ps.slots});
     }
   }
   return best;
+}
+
+inline Cut choose(const int32_t* w, int32_t n, int32_t heads,
+                  const Pass& ps) {
+  const Cut best = choose_alone(w, n, heads, ps);
+  return best.c == 0 && ps.beside ? choose_alone(w, n, heads, *ps.beside)
+                                  : best;
 }
 
 }  // namespace split

@@ -334,3 +334,15 @@ def test_items_with_a_compute_unit_each(host, nq, nkv, P, heads, split):
     host.call(0, _prob(8, P, heads, heads, 64), list(range(nq)),
               list(range(nkv)))
     assert (host.last()[0][5] > 0) == split
+
+
+@pytest.mark.parametrize("nq,nkv,P,hq,hkv,split", [
+    (3, 8, 4096, 4, 1, True), (3, 2, 2048, 8, 8, True),
+    (3, 4, 4096, 14, 2, True), (4, 4, 4096, 8, 8, False),
+    (1, 4, 4096, 16, 16, False)])
+def test_dq_items_beside_dkdv_items(host, nq, nkv, P, hq, hkv, split):
+    """Head dim 128, equal items, dK/dV items whole: dQ items that fill whole
+    rounds of their places stay whole, others are cut."""
+    host.call(1, _prob(8, P, hq, hkv, 128), list(range(nq)), list(range(nkv)))
+    dq, dkdv = host.last()
+    assert dkdv[5] == 0 and (dq[5] > 0) == split

@@ -135,6 +135,8 @@ TILES = [
      _tile(6, 2048, [5, 0, 2], [1, 3, 0, 2], 8, 8, 1, 1, (4, 3), (2, 0)),
      None),
     ("many heads on one", _tile(4, 512, [3, 0], [1], 11, 1, 1, 1), None),
+    ("dQ cut for the places beside dK/dV",
+     _tile(8, 2048, [0, 1, 2], [0, 1], 8, 8), None),
 ]
 
 
