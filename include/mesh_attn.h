@@ -198,15 +198,17 @@ ma_status_t mesh_attn_tile_fwd(const ma_problem_t* prob, const int32_t* q_idx,
  * workspace: a short work list is built on the host's stack and passed by
  * value as a kernel argument; a longer one is built on the device (from the
  * index lists, passed the same way) into a scratch array of
- * MA_NOALLOC_SCRATCH_BYTES that the library holds on every GPU it runs on
- * until the process ends, beside one of 68 MB for the partial results of split
- * items.  The call allocates nothing (no hipMalloc, no
+ * MA_NOALLOC_SCRATCH_BYTES that the library holds on every GPU that has run
+ * this call until the process ends, beside one of 68 MB for the partial results
+ * of split items.  The call allocates nothing (no hipMalloc, no
  * pinned host memory, no host heap), copies nothing from the host and never
  * synchronizes.
- * Limits: nq, nkv <= MA_NOALLOC_MAX_LIST; nq * P / 256 <= MA_NOALLOC_MAX_QBLOCKS;
- * the tile's work list (mesh_attn_fwd_workspace_size bytes) must fit the
- * scratch array.  Larger tiles return MA_ERR_UNSUPPORTED with the sizes in
- * mesh_attn_last_error(), before anything is launched.
+ * Limits: nq, nkv <= MA_NOALLOC_MAX_LIST; B = nq * P / 256 Q blocks <=
+ * MA_NOALLOC_MAX_QBLOCKS; and 4 (B + 1) + 32 B nkv + 8 (B Hq + 8) bytes, each
+ * term rounded up to 256, plus 256, <= MA_NOALLOC_SCRATCH_BYTES (independent of
+ * the workspace sizes above, which hold partial results too).  Larger tiles
+ * return MA_ERR_UNSUPPORTED with the sizes in mesh_attn_last_error(), before
+ * anything is launched.
  * Every call on one GPU shares that GPU's scratch arrays (each call rewrites
  * them before reading them): calls on one stream are ordered, but calls that
  * overlap on one GPU (different streams without ordering between them) race

@@ -445,8 +445,11 @@ size_t side_bound(int64_t n_blocks, int64_t n_list) {
          align_up(kNumXcd * 4);
 }
 
-// The list size that the allocation-free forward is limited by: 4 bytes per Q
-// block, 8 per item and two runs per Q block and KV partition.
+// What the allocation-free forward is limited by: 4 bytes per Q block, 8 per item
+// and two runs per Q block and KV partition.  An upper bound of no list that is
+// built today (its runs are the largest part of the device-built one, whose
+// table lies beside the scratch array); kept as the public limit, so that every
+// tile that was served is.
 size_t noalloc_list_bytes(int64_t n_blocks, int64_t n_list, int64_t heads) {
   return align_up((n_blocks + 1) * 4) +
          align_up(n_blocks * n_list * 2 * sizeof(DevRun)) +
@@ -1047,8 +1050,9 @@ ma_status_t mesh_attn_tile_fwd_noalloc(const ma_problem_t* prob,
   const size_t need = noalloc_list_bytes(nqb, nkv, prob->num_q_heads);
   if (nqb > kNoAllocMaxQBlocks || need > kNoAllocScratchBytes)
     return fail(MA_ERR_UNSUPPORTED,
-                "noalloc forward: the tile's work list (%lld Q blocks, %zu "
-                "bytes) exceeds the scratch maximum (%d Q blocks, %zu bytes)",
+                "noalloc forward: the tile (%lld Q blocks, %zu bytes of the "
+                "limit's formula) exceeds the scratch maximum (%d Q blocks, "
+                "%zu bytes)",
                 static_cast<long long>(nqb), need, kNoAllocMaxQBlocks,
                 kNoAllocScratchBytes);
   const int64_t items = nqb * prob->num_q_heads;

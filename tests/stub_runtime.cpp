@@ -159,6 +159,10 @@ hipError_t launch_tile_fwd(const FwdParams& p, const PlanBlob&, int head_dim,
   std::lock_guard<std::recursive_mutex> lock(mu);
   note(0, p.order);
   const size_t parts = size_t{1} * p.order.parts * p.hq;
+  const DevSplit* splits_end = p.order.splits + p.order.n_splits;
+  if (!p.order.inline_list && p.order.runs >= (const void*)p.order.splits &&
+      p.order.runs < (const void*)splits_end)
+    ++out_of_range;
   if (parts > 0) {
     inside(p.part_lse, parts * kFwdBM * 4, p.part_o);
     inside(p.part_o, parts * kFwdBM * head_dim * 4, ws_end);
@@ -188,8 +192,11 @@ hipError_t launch_lse_merge(const MergeParams&, bool, bool, hipStream_t) {
   return launched();
 }
 
+namespace {
+std::vector<char> lists(kNoAllocScratchBytes + kNoAllocTableBytes);
+}
+
 hipError_t noalloc_scratch(void** ptr, void** parts) {
-  static std::vector<char> lists(kNoAllocScratchBytes + kNoAllocTableBytes);
   static std::vector<char> partials(kNoAllocPartBytes);
   *ptr = lists.data();
   *parts = partials.data();
@@ -197,7 +204,20 @@ hipError_t noalloc_scratch(void** ptr, void** parts) {
   return hipSuccess;
 }
 
-hipError_t launch_fwd_plan_build(const PlanBuildParams&, hipStream_t) {
+// The lists in order, none into the next, the runs (at most two per Q block and
+// KV partition) up to the array's end.
+hipError_t launch_fwd_plan_build(const PlanBuildParams& p, hipStream_t) {
+  const void* at[] = {p.rows, p.queue, p.splits, p.runs};
+  const size_t bytes[] = {p.m * sizeof(DevRow), kNumXcd * 4,
+                          0,  // their number: launch_tile_fwd
+                          size_t{2} * p.nqb * p.nkv * sizeof(DevRun)};
+  const char* end = lists.data();
+  for (int i = 0; i < 4; ++i) {
+    const char* begin = static_cast<const char*>(at[i]);
+    if (begin < end) ++out_of_range;
+    end = begin + bytes[i];
+  }
+  if (end > lists.data() + lists.size()) ++out_of_range;
   return launched();
 }
 

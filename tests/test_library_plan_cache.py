@@ -64,7 +64,7 @@ class Host:
 
     @staticmethod
     def _list(idx):
-        return (ctypes.c_int32 * len(idx))(*idx), len(idx)
+        return [(ctypes.c_int32 * len(idx))(*idx), len(idx)]
 
     def call(self, pass_, prob, q_idx, kv_idx, ws_bytes=None, chunk=None,
              stream=None, check=True):
@@ -94,6 +94,13 @@ class Host:
         if check:
             assert st == 0, self.lib.mesh_attn_last_error()
         return st
+
+    def call_noalloc(self, prob, q_idx, kv_idx):
+        pr = ma.Problem.make(prob)
+        f = self.FAKE
+        return self.lib.mesh_attn_tile_fwd_noalloc(
+            ctypes.byref(pr), *self._list(q_idx), *self._list(kv_idx), *f[:4],
+            0, f[4], None)
 
     def last(self):
         out = (ctypes.c_int32 * 14)()
@@ -346,3 +353,30 @@ def test_dq_items_beside_dkdv_items(host, nq, nkv, P, hq, hkv, split):
     host.call(1, _prob(8, P, hq, hkv, 128), list(range(nq)), list(range(nkv)))
     dq, dkdv = host.last()
     assert dkdv[5] == 0 and (dq[5] > 0) == split
+
+
+def test_noalloc_limit_is_the_headers_formula(host):
+    """The allocation-free forward serves the tiles within its documented limit
+    and no other, and their lists lie inside the scratch array."""
+    def up(x):
+        return (x + 255) // 256 * 256
+
+    def fits(P, hq, nq, nkv):
+        blocks = nq * P // 256
+        return (blocks <= 4096 and
+                up(4 * (blocks + 1)) + up(32 * blocks * nkv) +
+                up(8 * (blocks * hq + 8)) + 256 <= 8 << 20)
+
+    served = 0
+    for P, hq, d in ((256, 1, 64), (4096, 32, 128), (1024, 7, 64),
+                     (2048, 64, 128), (1024, 1, 64)):
+        for nq in (1, 100, 128, 200, 255, 256):
+            for nkv in (1, 30, 31, 62, 63, 64, 128, 255, 256):
+                st = host.call_noalloc(_prob(512, P, hq, 1, d, 1), range(nq),
+                                       range(nkv))
+                ok = fits(P, hq, nq, nkv)
+                served += ok
+                assert st == (0 if ok else _binding.MA_ERR_UNSUPPORTED)
+                assert ok or b"scratch" in host.lib.mesh_attn_last_error()
+    assert 100 < served < 250
+    assert host.counts()["out_of_range"] == 0
