@@ -55,7 +55,10 @@ struct Slice<true> {
 // together (all loads issued before any is used), so a lane waits for one
 // round trip to memory per batch.  The host picks the smallest B that covers
 // k_parts (at most 16 for bf16 partials, 8 for float32); slots past k_parts
-// load the last partial again.
+// load the last partial again.  Batches of 3, 6 and 12 beside the powers of two,
+// 4096 x 32 x 128, microseconds with the next power of two / so: bf16 partials 3
+// 25.8/24.5, 5 38.3/35.4, 6 42.2/40.4, 9 66.9/59.7, 12 79.6/73.6; float32 3
+// 58.8/51.7, 5 95.3/82.0, 6 100.2/87.1.
 //
 // LPI lanes per (row, head) item and items indexed in 32 bits, where head_dim
 // and the sizes allow it (else LPI 0, head_dim / 8 at run time, in 64 bits):

@@ -126,11 +126,10 @@ struct StageTile {
 template <int D>
 struct TileAddr {
   using T = StageTile<D>;
-  uint32_t load;   // load j: lane's global offset within the rows of load j
   int row;         // row reads: row perm(li) (+32 t), chunk 2kk + lh
   int tr0, tr1;    // transpose reads, first and second half (+4 rows)
 
-  __device__ void init(int lane, int wg, uint32_t row_bytes_g) {
+  __device__ void init(int lane) {
     const int li = lane & 31, lh = lane >> 5;
     {
       const int r = mfma_row_perm(li);
@@ -148,8 +147,6 @@ struct TileAddr {
       const int r1 = r0 + 4;
       tr1 = r1 * T::ROWB + ((c16 ^ T::swz(r1)) * 16) + 8 * (s16 & 1);
     }
-    (void)wg;
-    (void)row_bytes_g;
   }
 };
 
@@ -345,7 +342,7 @@ __device__ __forceinline__ void dkdv_item(const BwdParams& p, char* smem,
 
   if (pc.nblk > 0) {
     TileAddr<D> ta;
-    ta.init(lane, wave, 0);
+    ta.init(lane);
     // Stage cursor over (query head of the group, run, block in run, half).
     struct Cur {
       int g, r, off, s;
@@ -542,7 +539,7 @@ __device__ __forceinline__ void dq_item(const BwdParams& p, char* smem,
 
   if (pc.nblk > 0) {
     TileAddr<D> ta;
-    ta.init(lane, wave, 0);
+    ta.init(lane);
     struct Cur {
       int r, off, s, left;  // left: stages from this one on
       DevRun run;

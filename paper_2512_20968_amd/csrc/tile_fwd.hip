@@ -269,7 +269,8 @@ __device__ __forceinline__ void write_rows(const FwdParams& p,
 // Head dim 128 (head dim 64 below).
 template <int D, bool OUT_F32>
 __global__ __launch_bounds__(NT, 1) void tile_fwd_kernel(FwdParams p,
-                                                             PlanBlob) {
+                                                         PlanBlob) {
+  static_assert(D == 128, "head dim 64 has a kernel of its own");
   using L = FwdLayout<D>;
   extern __shared__ __align__(16) char smem[];
 
@@ -614,7 +615,8 @@ __global__ __launch_bounds__(NT, 1) void tile_fwd_kernel(FwdParams p,
 // them exponentials), so the vector unit bounds it.  The two ping-pong groups
 // of d = 128 leave it idle whenever a wave waits on its own dependent
 // instructions; four waves per SIMD do so less, and a wave of 32 rows fits 128
-// registers at d = 64.  So two workgroups of eight waves share a compute unit,
+// registers at d = 64 (with 8 spilled, 36 bytes, all outside the key loop).  So
+// two workgroups of eight waves share a compute unit,
 // every wave loading its eighth of the K and V tiles of the next two blocks
 // (64 KB per workgroup) before it computes two, one barrier per two blocks.
 // 16384 rows x 32768 keys x 32 heads: 5141 us (856 TFLOP/s) with the ping-pong
@@ -1048,7 +1050,6 @@ __global__ __launch_bounds__(NTC) void fwd_combine_kernel(FwdParams p,
 template <int D, bool F32>
 hipError_t launch(const FwdParams& p, const PlanBlob& blob,
                   hipStream_t stream) {
-  const size_t smem = FwdLayout<D>::SMEM + 16;  // + the item slot
   const int grid = static_cast<int>(queued_launch_grid(p.order.n_items));
   hipError_t e = hipSuccess;
   if (p.order.is_short) {
@@ -1060,18 +1061,17 @@ hipError_t launch(const FwdParams& p, const PlanBlob& blob,
                        SL::SMEM, stream, p, blob);
     return hipGetLastError();
   }
-  if constexpr (D == 64) {
-    const size_t smem64 = 2 * FwdLayout<D>::SMEM + 16;  // four block buffers
-    e = ensure_dynamic_lds<tile_fwd64_kernel<F32>>(smem64);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(tile_fwd64_kernel<F32>, dim3(grid), dim3(NT), smem64,
-                       stream, p, blob);
-  } else {
-    e = ensure_dynamic_lds<tile_fwd_kernel<D, F32>>(smem);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((tile_fwd_kernel<D, F32>), dim3(grid), dim3(NT), smem,
-                       stream, p, blob);
-  }
+  // + the item slot; head dim 64 keeps four blocks in LDS, 128 two.
+  const size_t smem = (D == 64 ? 2 : 1) * FwdLayout<D>::SMEM + 16;
+  constexpr auto kernel = [] {
+    if constexpr (D == 64)
+      return tile_fwd64_kernel<F32>;
+    else
+      return tile_fwd_kernel<D, F32>;
+  }();
+  e = ensure_dynamic_lds<kernel>(smem);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(NT), smem, stream, p, blob);
   e = hipGetLastError();
   if (e != hipSuccess || p.order.n_splits == 0) return e;
   constexpr int GPI = BM / (NTC / (D / 4));
