@@ -51,6 +51,31 @@ def plan_cache_tiles():
     return cfg, [list(pairs[i]) for i in rng.permutation(len(pairs))[:1100]]
 
 
+def device_list_tiles():
+    """Forward tiles whose lists are too long for the kernel arguments and whose
+    items are split, so that the allocation-free forward builds pieces on the
+    device: in one round, in the plain order and by KV head, at both head dims,
+    and with more Q blocks than the building workgroup has threads (only the
+    last rows cut)."""
+    import dataclasses
+    from mesh_inputs import WORKLOADS
+    out = []
+    for n, P, q, kv, hq, hkv, d, causal, layout in (
+            (64, 256, range(63, 3, -1), range(0, 60, 5), 1, 1, 64, True, 1),
+            (64, 256, range(63, 3, -1), range(0, 60, 5), 1, 1, 128, True, 1),
+            (16, 1024, range(2, 14), range(14), 8, 8, 64, True, 1),
+            (16, 4096, range(8, 14), range(8), 3, 3, 128, False, 0),
+            (40, 512, range(5, 38), range(0, 33, 2), 8, 8, 64, True, 0),
+            (70, 256, range(70), range(70), 3, 1, 128, True, 0),
+            (256, 1280, range(220), range(230, 235), 1, 1, 128, False, 0)):
+        out.append(dataclasses.replace(
+            WORKLOADS["tiny-nc"], num_partitions=n, partition_len=P,
+            q_idx=list(q), kv_idx=list(kv), num_q_heads=hq, num_kv_heads=hkv,
+            head_dim=d, causal=causal, layout=layout, seed=81,
+            name=f"{len(q)}x{P}-{hq}-{d}"))
+    return out
+
+
 def concurrency_tiles():
     """Two tiles for each of four threads.  Every thread's second one has lists
     too long for the kernel arguments in both passes, as have the backward lists

@@ -13,8 +13,8 @@ import oracle
 import paper_2512_20968_amd as ma
 from mesh_inputs import WORKLOADS, make_grad, make_qkv
 
-from helpers import (check_fwd, check_grad, log, oracle_backward_rows,
-                     to_np)
+from helpers import (check_fwd, check_grad, device_list_tiles, log,
+                     oracle_backward_rows, to_np)
 
 pytestmark = pytest.mark.gpu
 
@@ -149,6 +149,30 @@ def test_long_list_noalloc_in_a_captured_graph(gpu):
             graph.replay()
             torch.cuda.synchronize()
             assert torch.equal(o, ref_o) and torch.equal(lse, ref_l), (i, rep)
+
+
+@pytest.mark.parametrize("cfg", device_list_tiles(), ids=lambda c: c.name)
+def test_device_built_lists_of_split_tiles(gpu, cfg):
+    """The list that the allocation-free forward builds on the device against
+    the host's: the same bits in every row, and the oracle's on some."""
+    q, k, v, _ = make_qkv(cfg)
+    qd, kd, vd = (t.to(gpu) for t in (q, k, v))
+    prob = cfg.problem()
+    res = []
+    for fn in (ma.mesh_attn_tile_fwd, ma.mesh_attn_tile_fwd_noalloc):
+        o = torch.full(qd.shape, float("nan"), device=gpu)
+        lse = torch.full((cfg.num_q_heads, qd.shape[0]), float("nan"),
+                         device=gpu)
+        fn(prob, cfg.q_idx, cfg.kv_idx, qd, kd, vd, o, lse)
+        torch.cuda.synchronize()
+        res.append((o, lse))
+    assert torch.equal(res[0][0], res[1][0])
+    assert torch.equal(res[0][1], res[1][1])
+    rows = list(range(0, qd.shape[0], qd.shape[0] // 61)) + [qd.shape[0] - 1]
+    ro, rl = oracle.tile_forward(prob, cfg.q_idx, cfg.kv_idx, to_np(q),
+                                 to_np(k), to_np(v), rows=rows, heads=[0])
+    check_fwd(cfg.name, to_np(res[1][0][rows][:, :1]),
+              to_np(res[1][1][:1, rows]), ro, rl)
 
 
 @pytest.mark.parametrize("first", [64, 128])

@@ -15,7 +15,7 @@ import pytest
 import paper_2512_20968_amd as ma
 from paper_2512_20968_amd import _binding
 
-from helpers import concurrency_tiles, plan_cache_tiles
+from helpers import concurrency_tiles, device_list_tiles, plan_cache_tiles
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HERE = os.path.join(ROOT, "tests")
@@ -380,3 +380,62 @@ def test_noalloc_limit_is_the_headers_formula(host):
                 assert ok or b"scratch" in host.lib.mesh_attn_last_error()
     assert 100 < served < 250
     assert host.counts()["out_of_range"] == 0
+
+
+def _random_call(rng):
+    P = 256 * int(rng.choice([1, 2, 3, 4, 5, 8, 12, 16, 32]))
+    n = int(rng.integers(1, 40))
+    nq, nkv = (int(min(n, rng.integers(1, 18))) for _ in range(2))
+    hkv, g = int(rng.choice([1, 2, 3, 4, 7, 8, 16])), int(rng.choice([1, 2, 3, 8]))
+    prob = _prob(n, P, hkv * g, hkv, int(rng.choice([64, 128])),
+                 int(rng.integers(2)), int(rng.integers(2)))
+    q, kv = ([int(x) for x in rng.permutation(n)[:k]] for k in (nq, nkv))
+    chunk = None
+    if rng.random() < 0.3:
+        kq = int(rng.choice([x for x in (1, 2, 3, 4) if P % (256 * x) == 0]))
+        kk = int(rng.choice([x for x in (1, 2, 4, 6) if P % (128 * x) == 0]))
+        chunk = (int(rng.integers(kq)), kq, int(rng.integers(kk)), kk)
+    return prob, q, kv, chunk
+
+
+def test_the_gpu_test_of_device_built_lists_covers_the_slot_orders(host):
+    modes = set()
+    for c in device_list_tiles():
+        assert host.call_noalloc(c.problem(), c.q_idx, c.kv_idx) == 0
+        inline, _, _, mode, parts, splits, _ = host.last()[0]
+        assert not inline and parts > 0 and splits > 0
+        modes.add((mode, c.head_dim))
+    assert {(0, 128), (1, 64), (2, 64), (2, 128)} <= modes
+    assert c.nq * c.partition_len // 256 > 1024
+
+
+def test_random_calls_stay_inside_their_workspace(host):
+    """Forward, backward, chunk tasks and the allocation-free forward of random
+    tiles, in workspaces of their own size, sized for a larger tile, and without
+    room for all partial results: every range that a launch writes lies inside,
+    and the allocation-free forward cuts as a workspace of full size does."""
+    rng = np.random.default_rng(17)
+    split = 0
+    for _ in range(400):
+        prob, q, kv, chunk = _random_call(rng)
+        for pass_ in (0, 1):
+            size = getattr(ma, f"mesh_attn_{'bwd' if pass_ else 'fwd'}"
+                           "_workspace_size")
+            own = size(prob, len(q), len(kv))
+            for ws in (own, size(prob, len(q) + 3, len(kv) + 2),
+                       int(own * rng.random())):
+                st = host.call(pass_, prob, q, kv, ws_bytes=ws, chunk=chunk,
+                               check=False)
+                small = _binding.MA_ERR_WORKSPACE_TOO_SMALL
+                assert st == 0 or (st == small and ws < own), (prob, q, kv, ws)
+                host.run(None)
+            if pass_ == 0 and chunk is None:
+                host.call(0, prob, q, kv)
+                want = host.last()[0][1:]  # inline or not
+                host.run(None)
+                if host.call_noalloc(prob, q, kv) == 0:
+                    assert host.last()[0][1:] == want, (prob, q, kv)
+                split += want[4] > 0
+        assert host.counts()["out_of_range"] == 0, (prob, q, kv, chunk)
+        assert host.counts()["stale"] == 0
+    assert split > 40
